@@ -48,8 +48,4 @@ hipError_t launch_source_dot(Grid3 g, double dx, double dy, double dz, const uin
                              double sigma, const float* sacc, const ClassParams* cp_dev,
                              double dt, double* partial, int nblk, hipStream_t st);
 
-hipError_t launch_source_dot_fields(Grid3 g, const uint8_t* lab, const double* u, int n_tines,
-                                    const float* sacc, const ClassParams* cp_dev, double dt,
-                                    double* partial, int nblk, hipStream_t st);
-
 }  // namespace rfa

@@ -514,36 +514,6 @@ __global__ __launch_bounds__(256) void k_source_dot(const uint8_t* lab, const Ch
   if (threadIdx.x == 0) partial[(size_t)t * gridDim.x + blockIdx.x] = acc;
 }
 
-// The same sums from stored per-tine densities u[t][n] (same traversal and
-// order, so identical results).
-__global__ __launch_bounds__(256) void k_source_dot_fields(const uint8_t* lab, const double* u,
-                                                           const float* sacc,
-                                                           const ClassParams* cp, double dt,
-                                                           size_t n, double* partial) {
-  __shared__ double sh[4];
-  const int t = blockIdx.y;
-  const double* ut = u + (size_t)t * n;
-  double acc = 0.0;
-  for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-       p += (size_t)gridDim.x * blockDim.x) {
-    const unsigned v = lab[p];
-    if (v & kHeld) continue;
-    const double sv = (double)sacc[p] * dt / cp->rc[class_of(v)];
-    if (sv == 0.0) continue;
-    acc += ut[p] * sv;
-  }
-  acc = block_sum_256(acc, sh);
-  if (threadIdx.x == 0) partial[(size_t)t * gridDim.x + blockIdx.x] = acc;
-}
-
-hipError_t launch_source_dot_fields(Grid3 g, const uint8_t* lab, const double* u, int n_tines,
-                                    const float* sacc, const ClassParams* cp_dev, double dt,
-                                    double* partial, int nblk, hipStream_t st) {
-  hipLaunchKernelGGL(k_source_dot_fields, dim3(nblk, n_tines), dim3(256), 0, st, lab, u, sacc,
-                     cp_dev, dt, g.n(), partial);
-  return hipGetLastError();
-}
-
 hipError_t launch_source_dot(Grid3 g, double dx, double dy, double dz, const uint8_t* lab,
                              const Chord* chords, const int* tine_first, int n_tines,
                              double sigma, const float* sacc, const ClassParams* cp_dev,

@@ -103,11 +103,14 @@ struct rfa_grid_s {
   Chord* chords_dev = nullptr;     // chords of the rasterised needle
   int* first_dev = nullptr;        // first chord of each tine (+ end)
   std::vector<double> tine_sums;   // integral of each tine's unnormalised density, m
-  double* tine_u = nullptr;        // [n_tines][n] unnormalised densities (if kept)
-  size_t tine_u_cap = 0;           // doubles allocated at tine_u
-  bool fields_ok = false;          // tine_u holds the current needle's densities
-  double* scale_dev = nullptr;     // [scale_cap] power / integral per tine
-  size_t scale_cap = 0;
+  // unnormalised densities of the tines (if kept), their capacity in
+  // (tine, voxel) pairs, and whether they are the current needle's
+  SourceFields fields{};
+  size_t fields_cap = 0;
+  bool fields_ok = false;
+  double* tine_dev = nullptr;      // [3][n_tines] power, integral, power / integral
+  size_t tine_cap = 0;             // tines allocated at tine_dev (and first_dev)
+  size_t chords_cap = 0;           // chords allocated at chords_dev
 
   // perfusion-correction B-spline (m^3 control points), if set
   int bs_m = 0;
@@ -162,6 +165,14 @@ struct rfa_grid_s {
 
 namespace {
 
+void free_fields(rfa_grid g) {
+  SourceFields& f = g->fields;
+  for (void* p : {(void*)f.u, (void*)f.active, (void*)f.list, (void*)f.count, (void*)f.partial})
+    if (p) (void)hipFree(p);
+  f = SourceFields{};
+  g->fields_cap = 0;
+}
+
 void free_all(rfa_grid g) {
   auto f = [](void* p) {
     if (p) (void)hipFree(p);
@@ -185,8 +196,8 @@ void free_all(rfa_grid g) {
   f(g->bad);
   f(g->chords_dev);
   f(g->first_dev);
-  f(g->tine_u);
-  f(g->scale_dev);
+  free_fields(g);
+  f(g->tine_dev);
   f(g->bs_ctrl);
   f(g->bs_vfirst);
   f(g->ckpt);
@@ -294,6 +305,28 @@ rfa_status compute_dt_max(rfa_grid g) {
   return RFA_OK;
 }
 
+// Room for nt tines' densities and their scratch; false (fields empty)
+// without memory for them.
+bool ensure_fields(rfa_grid g, int nt) {
+  const size_t nu = (size_t)nt * g->g.n();
+  if (g->fields_cap >= nu) return true;
+  free_fields(g);
+  const size_t pairs = (size_t)nt * source_tiles(g->g);
+  SourceFields& f = g->fields;
+  const bool ok = hipMalloc((void**)&f.u, nu * sizeof(double)) == hipSuccess &&
+                  hipMalloc((void**)&f.active, pairs) == hipSuccess &&
+                  hipMalloc((void**)&f.list, pairs * sizeof(int2)) == hipSuccess &&
+                  hipMalloc((void**)&f.partial, pairs * sizeof(double)) == hipSuccess &&
+                  hipMalloc((void**)&f.count, sizeof(unsigned)) == hipSuccess;
+  (void)hipGetLastError();
+  if (!ok) {
+    free_fields(g);
+    return false;
+  }
+  g->fields_cap = nu;
+  return true;
+}
+
 // Rasterise the stored needle into q64 (zero if none) and invalidate s.
 rfa_status rasterise(rfa_grid g) {
   g->src_dt = -1.0;
@@ -329,96 +362,76 @@ rfa_status rasterise(rfa_grid g) {
     }
   }
   first[nt] = (int)chords.size();
-  Chord* d_chords = nullptr;
-  int* d_first = nullptr;
-  double* d_sums = nullptr;
-  double* d_partial = nullptr;
+  // device copies of the chords (also read by the adjoint's dL/dP), tine
+  // ranges and powers; grown, kept with the grid
   rfa_status s;
-  if ((s = dmalloc(&d_chords, chords.size())) != RFA_OK) return s;
-  if ((s = dmalloc(&d_first, first.size())) != RFA_OK) { (void)hipFree(d_chords); return s; }
-  if ((s = dmalloc(&d_sums, 2 * (size_t)nt)) != RFA_OK) {
-    (void)hipFree(d_chords); (void)hipFree(d_first); return s;
+  if (g->chords_cap < chords.size()) {
+    Chord* c = nullptr;
+    if ((s = dmalloc(&c, chords.size())) != RFA_OK) return s;
+    if (g->chords_dev) (void)hipFree(g->chords_dev);
+    g->chords_dev = c;
+    g->chords_cap = chords.size();
   }
-  if ((s = dmalloc(&d_partial, (size_t)nt * 1024)) != RFA_OK) {
-    (void)hipFree(d_chords); (void)hipFree(d_first); (void)hipFree(d_sums); return s;
+  if (g->tine_cap < (size_t)nt) {
+    int* f = nullptr;
+    double* d = nullptr;
+    if ((s = dmalloc(&f, first.size())) != RFA_OK) return s;
+    if ((s = dmalloc(&d, 3 * (size_t)nt)) != RFA_OK) { (void)hipFree(f); return s; }
+    if (g->first_dev) (void)hipFree(g->first_dev);
+    if (g->tine_dev) (void)hipFree(g->tine_dev);
+    g->first_dev = f;
+    g->tine_dev = d;
+    g->tine_cap = nt;
   }
-  auto cleanup = [&]() {
-    (void)hipFree(d_chords);
-    (void)hipFree(d_first);
-    (void)hipFree(d_sums);
-    (void)hipFree(d_partial);
-  };
-  std::vector<double> sums(nt), scale(nt);
-  hipError_t e = hipSuccess;
-  int nblk = 0;
+  double* d_power = g->tine_dev;
+  double* d_sums = g->tine_dev + nt;
+  double* d_weight = g->tine_dev + 2 * nt;
   // Keep the per-tine densities when they fit the budget: new tine powers
   // then only recombine them, and dL/dP reads them instead of recomputing.
   const size_t nu = (size_t)nt * g->g.n();
-  bool keep = nu * sizeof(double) <= kFieldBudget;
-  if (keep && g->tine_u_cap < nu) {
-    if (g->tine_u) (void)hipFree(g->tine_u);
-    g->tine_u = nullptr;
-    g->tine_u_cap = 0;
-    if (hipMalloc((void**)&g->tine_u, nu * sizeof(double)) == hipSuccess)
-      g->tine_u_cap = nu;
-    else
-      keep = false;  // fall back to recomputing the densities
-    (void)hipGetLastError();
-  }
-  g->fields_ok = false;
+  const bool keep = nu * sizeof(double) <= kFieldBudget && ensure_fields(g, nt);
+  double* d_partial = nullptr;
+  if (!keep && (s = dmalloc(&d_partial, (size_t)nt * 1024)) != RFA_OK) return s;
+  std::vector<double> sums(nt), scale(nt);
+  hipError_t e = hipSuccess;
+  int nblk = 0;
   do {
-    if ((e = hipMemcpyAsync(d_chords, chords.data(), chords.size() * sizeof(Chord),
+    if ((e = hipMemcpyAsync(g->chords_dev, chords.data(), chords.size() * sizeof(Chord),
                             hipMemcpyHostToDevice, g->st)) != hipSuccess) break;
-    if ((e = hipMemcpyAsync(d_first, first.data(), first.size() * sizeof(int),
+    if ((e = hipMemcpyAsync(g->first_dev, first.data(), first.size() * sizeof(int),
                             hipMemcpyHostToDevice, g->st)) != hipSuccess) break;
-    if (keep) {
-      if ((e = launch_source_fields(g->g, g->dx, g->dy, g->dz, g->lab, d_chords, d_first, nt,
-                                    g->sigma, g->tine_u, g->st)) != hipSuccess) break;
-      if ((e = launch_field_sums(g->g, g->dx, g->dy, g->dz, g->lab, g->tine_u, nt, d_partial,
-                                 d_sums, g->st)) != hipSuccess) break;
-    } else if ((e = launch_source_sums(g->g, g->dx, g->dy, g->dz, g->lab, d_chords, d_first,
-                                       nt, g->sigma, d_partial, &nblk, d_sums, g->st)) !=
-               hipSuccess) {
-      break;
-    }
+    if ((e = hipMemcpyAsync(d_power, g->power.data(), nt * sizeof(double),
+                            hipMemcpyHostToDevice, g->st)) != hipSuccess) break;
+    e = keep ? launch_source_fields(g->g, g->dx, g->dy, g->dz, g->lab, g->chords_dev,
+                                    g->first_dev, nt, g->sigma, d_power, g->fields, d_sums,
+                                    d_weight, g->st)
+             : launch_source_sums(g->g, g->dx, g->dy, g->dz, g->lab, g->chords_dev,
+                                  g->first_dev, nt, g->sigma, d_partial, &nblk, d_sums, g->st);
+    if (e != hipSuccess) break;
     if ((e = hipMemcpyAsync(sums.data(), d_sums, nt * sizeof(double), hipMemcpyDeviceToHost,
                             g->st)) != hipSuccess) break;
-    if ((e = hipStreamSynchronize(g->st)) != hipSuccess) break;
+    e = hipStreamSynchronize(g->st);
   } while (false);
-  if (e != hipSuccess) {
-    cleanup();
+  if (d_partial) (void)hipFree(d_partial);
+  if (e != hipSuccess)
     return fail(RFA_ERR_HIP, "source rasterisation failed: %s", hipGetErrorString(e));
-  }
   for (int t = 0; t < nt; ++t) {
-    if (!(sums[t] > 0.0)) {
-      cleanup();
-      return fail(RFA_ERR_ARG, "tine %d has no weight on free voxels", t);
-    }
+    if (!(sums[t] > 0.0)) return fail(RFA_ERR_ARG, "tine %d has no weight on free voxels", t);
     scale[t] = g->power[t] / sums[t];
   }
-  do {
-    if ((e = hipMemcpyAsync(d_sums + nt, scale.data(), nt * sizeof(double),
-                            hipMemcpyHostToDevice, g->st)) != hipSuccess) break;
-    if (keep)
-      e = launch_source_combine(g->g, g->lab, g->tine_u, nt, d_sums + nt, g->q64, g->st);
-    else
-      e = launch_source_write(g->g, g->dx, g->dy, g->dz, g->lab, d_chords, d_first, nt,
-                              g->sigma, d_sums + nt, g->q64, g->st);
-    if (e != hipSuccess) break;
-    if ((e = hipStreamSynchronize(g->st)) != hipSuccess) break;
-  } while (false);
-  if (e != hipSuccess) {
-    cleanup();
-    return fail(RFA_ERR_HIP, "source write failed: %s", hipGetErrorString(e));
+  if (keep) {
+    e = launch_source_combine(g->g, g->lab, g->fields, nt, d_weight, g->q64, g->st);
+  } else {
+    e = hipMemcpyAsync(d_weight, scale.data(), nt * sizeof(double), hipMemcpyHostToDevice,
+                       g->st);
+    if (e == hipSuccess)
+      e = launch_source_write(g->g, g->dx, g->dy, g->dz, g->lab, g->chords_dev, g->first_dev, nt,
+                              g->sigma, d_weight, g->q64, g->st);
+    if (e == hipSuccess) e = hipStreamSynchronize(g->st);
   }
+  if (e != hipSuccess)
+    return fail(RFA_ERR_HIP, "source write failed: %s", hipGetErrorString(e));
   g->fields_ok = keep;
-  // keep the chord list and tine integrals for the adjoint's dL/dP
-  (void)hipFree(d_sums);
-  (void)hipFree(d_partial);
-  if (g->chords_dev) (void)hipFree(g->chords_dev);
-  if (g->first_dev) (void)hipFree(g->first_dev);
-  g->chords_dev = d_chords;
-  g->first_dev = d_first;
   g->tine_sums = sums;
   double tot = 0.0;
   for (double p : g->power) tot += p;
@@ -1505,17 +1518,10 @@ rfa_status rfa_set_tine_powers(rfa_grid g, const double* power) {
     // recombine the kept per-tine densities with the new powers
     std::vector<double> scale(nt);
     for (size_t t = 0; t < nt; ++t) scale[t] = power[t] / g->tine_sums[t];
-    rfa_status s;
-    if (g->scale_cap < nt) {
-      if (g->scale_dev) (void)hipFree(g->scale_dev);
-      g->scale_dev = nullptr;
-      g->scale_cap = 0;
-      if ((s = dmalloc(&g->scale_dev, nt)) != RFA_OK) return s;
-      g->scale_cap = nt;
-    }
-    HIP_TRY(hipMemcpyAsync(g->scale_dev, scale.data(), nt * sizeof(double),
-                           hipMemcpyHostToDevice, g->st));
-    HIP_TRY(launch_source_combine(g->g, g->lab, g->tine_u, (int)nt, g->scale_dev, g->q64, g->st));
+    double* d_weight = g->tine_dev + 2 * nt;
+    HIP_TRY(hipMemcpyAsync(d_weight, scale.data(), nt * sizeof(double), hipMemcpyHostToDevice,
+                           g->st));
+    HIP_TRY(launch_source_combine(g->g, g->lab, g->fields, (int)nt, d_weight, g->q64, g->st));
     HIP_TRY(hipStreamSynchronize(g->st));
     g->power.assign(power, power + nt);
     g->src_dt = -1.0;
@@ -1795,7 +1801,7 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
     if ((s = dmalloc(&part, (size_t)nt * kBlk)) != RFA_OK) return s;
     std::vector<double> host((size_t)nt * kBlk);
     hipError_t e = g->fields_ok
-                       ? launch_source_dot_fields(g->g, g->lab, g->tine_u, nt, sacc, g->cp_dev,
+                       ? launch_source_dot_fields(g->g, g->lab, g->fields, nt, sacc, g->cp_dev,
                                                   g->adj_dt, part, kBlk, g->st)
                        : launch_source_dot(g->g, g->dx, g->dy, g->dz, g->lab, g->chords_dev,
                                            g->first_dev, nt, g->sigma, sacc, g->cp_dev,

@@ -108,16 +108,30 @@ hipError_t launch_source_write(Grid3 g, double dx, double dy, double dz, const u
                                const Chord* chords, const int* tine_first, int n_tines,
                                double sigma, const double* scale, double* q,
                                hipStream_t st);
-// Stored per-tine densities u[t][n] (0 on held voxels), their integrals
-// (same order as launch_source_sums) and q = sum_t scale[t] u_t.
+// Kept per-tine densities: u[t][n] on the source tiles (4 x 4 x 16 voxels)
+// that the tine's chords reach, active[t][tile] = 1 there; elsewhere the
+// density is zero and u is not written.
+constexpr int kSrcTx = 4, kSrcTy = 4, kSrcTz = 16;
+int source_tiles(Grid3 g);
+struct SourceFields {
+  double* u;          // [n_tines][n], 0 on held voxels of active tiles
+  uint8_t* active;    // [n_tines][tiles]
+  int2* list;         // scratch [n_tines * tiles]: active (tile, tine)
+  unsigned* count;    // scratch: length of list
+  double* partial;    // scratch [n_tines * tiles]
+};
+// The densities, their integrals sums[t] and weight[t] = power[t] / sums[t].
 hipError_t launch_source_fields(Grid3 g, double dx, double dy, double dz, const uint8_t* lab,
                                 const Chord* chords, const int* tine_first, int n_tines,
-                                double sigma, double* u, hipStream_t st);
-hipError_t launch_field_sums(Grid3 g, double dx, double dy, double dz, const uint8_t* lab,
-                             const double* u, int n_tines, double* partial, double* sums,
-                             hipStream_t st);
-hipError_t launch_source_combine(Grid3 g, const uint8_t* lab, const double* u, int n_tines,
+                                double sigma, const double* power, const SourceFields& f,
+                                double* sums, double* weight, hipStream_t st);
+// q = sum_t scale[t] u_t.
+hipError_t launch_source_combine(Grid3 g, const uint8_t* lab, const SourceFields& f, int n_tines,
                                  const double* scale, double* q, hipStream_t st);
+// partial[t * nblk + b]: per-block sums of u_t(p) sacc_p dt / (rho c)_p.
+hipError_t launch_source_dot_fields(Grid3 g, const uint8_t* lab, const SourceFields& f,
+                                    int n_tines, const float* sacc, const ClassParams* cp_dev,
+                                    double dt, double* partial, int nblk, hipStream_t st);
 // s = dt q / (rho c) on free voxels, 0 on held voxels; the labels' source
 // flag (kSource) set exactly where s != 0.
 hipError_t launch_source_increment(Grid3 g, uint8_t* lab, const double* q,

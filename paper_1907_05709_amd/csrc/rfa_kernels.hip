@@ -441,80 +441,263 @@ hipError_t launch_source_sums(Grid3 g, double dx, double dy, double dz, const ui
   return hipGetLastError();
 }
 
-// u[t][p] = g_t(p), the unnormalised density of tine t, on free voxels and
-// 0 on held ones (kept so that new tine powers only recombine the fields).
-__global__ void k_source_fields(const uint8_t* lab, const Chord* chords, const int* tine_first,
-                                int n_tines, double sigma, double* u, int nx, int ny, int nz,
-                                double dx, double dy, double dz) {
+// Kept per-tine densities.  A chord's density is exactly zero beyond the
+// 9 sigma cut of chord_density(), so nearly all of a grid lies outside every
+// tine's reach (umbrella of 9 x 64 chords at 192^3: 5 % of the tile-tine
+// pairs are active).  The grid is cut into source tiles of 4 x 4 x 16 voxels
+// (128-byte runs of a density image; one voxel per thread of a work-group);
+// k_source_cull finds the pairs (tile, tine) that some chord reaches and
+// lists them, k_source_fields evaluates only those, each against only the
+// chords that reach its tile, and the readers skip the pairs whose active
+// byte is 0 (their densities are zero and not written).  Testing every
+// chord at every voxel took 5.59 ms at 192^3, all of it FP64 arithmetic on
+// pairs out of reach; a pair per work-group rather than a tile keeps the
+// serial chord sums at the tip, where all tines meet, short.
+namespace {
+
+struct SourceTile {
+  int i0, j0, k0;  // first voxel
+};
+
+__device__ __forceinline__ SourceTile source_tile(int tile, int ny, int nz) {
+  const int ty = (ny + kSrcTy - 1) / kSrcTy, tz = (nz + kSrcTz - 1) / kSrcTz;
+  const int c = tile % tz, r = tile / tz;
+  return SourceTile{(r / ty) * kSrcTx, (r % ty) * kSrcTy, c * kSrcTz};
+}
+
+// Voxel of this thread in the tile; false outside the grid.
+__device__ __forceinline__ bool tile_voxel(const SourceTile& t, int nx, int ny, int nz, int& i,
+                                           int& j, int& k, size_t& p) {
+  const int tid = threadIdx.x;
+  k = t.k0 + tid % kSrcTz;
+  j = t.j0 + (tid / kSrcTz) % kSrcTy;
+  i = t.i0 + tid / (kSrcTz * kSrcTy);
+  p = vidx(i, j, k, ny, nz);
+  return i < nx && j < ny && k < nz;
+}
+
+// Centre of a tile's box of voxel centres and its half diagonal, widened by
+// far more than the rounding of the tests.
+struct TileBall {
+  double x, y, z, r;
+};
+
+__device__ __forceinline__ TileBall tile_ball(const SourceTile& t, int nx, int ny, int nz,
+                                              double dx, double dy, double dz) {
+  TileBall b;
+  b.x = (2.0 * t.i0 + (kSrcTx - 1) - (nx - 1)) * dx / 2.0;
+  b.y = (2.0 * t.j0 + (kSrcTy - 1) - (ny - 1)) * dy / 2.0;
+  b.z = (2.0 * t.k0 + (kSrcTz - 1) - (nz - 1)) * dz / 2.0;
+  const double hx = 0.5 * (kSrcTx - 1) * dx, hy = 0.5 * (kSrcTy - 1) * dy,
+               hz = 0.5 * (kSrcTz - 1) * dz;
+  b.r = sqrt(hx * hx + hy * hy + hz * hz) * (1.0 + 1e-6) +
+        1e-9 * (fabs(b.x) + fabs(b.y) + fabs(b.z));
+  return b;
+}
+
+// Whether the chord's density can be nonzero in the ball: the distance from
+// its line and the offset along it both change by at most the distance moved.
+__device__ __forceinline__ bool chord_reaches(const Chord& c, const TileBall& b, double sigma) {
+  const double rx = b.x - c.mx, ry = b.y - c.my, rz = b.z - c.mz;
+  const double s = rx * c.ux + ry * c.uy + rz * c.uz;
+  const double dp2 = fmax(rx * rx + ry * ry + rz * rz - s * s, 0.0);
+  const double slack = 1e-6 * (fabs(rx) + fabs(ry) + fabs(rz));  // cancellation in dp2
+  const double reach = 9.0 * sigma + b.r + slack;
+  return dp2 <= reach * reach && fabs(s) <= c.half + reach;
+}
+
+}  // namespace
+
+int source_tiles(Grid3 g) {
+  return ((g.nx + kSrcTx - 1) / kSrcTx) * ((g.ny + kSrcTy - 1) / kSrcTy) *
+         ((g.nz + kSrcTz - 1) / kSrcTz);
+}
+
+// One thread per tile, grid.y = tine: active[t][tile], the list of active
+// pairs (in no fixed order: each pair's results have their own place) and
+// zero partial sums for the others.
+__global__ __launch_bounds__(256) void k_source_cull(const Chord* chords, const int* tine_first,
+                                                     double sigma, int nx, int ny, int nz,
+                                                     double dx, double dy, double dz,
+                                                     int n_tiles, uint8_t* active, int2* list,
+                                                     unsigned* count, double* partial) {
+  const int t = blockIdx.y;
+  const int tile = blockIdx.x * 256 + threadIdx.x;
+  bool on = false;
+  if (tile < n_tiles) {
+    const TileBall b = tile_ball(source_tile(tile, ny, nz), nx, ny, nz, dx, dy, dz);
+    const int c1 = tine_first[t + 1];
+    for (int c = tine_first[t]; c < c1 && !on; ++c) on = chord_reaches(chords[c], b, sigma);
+    active[(size_t)t * n_tiles + tile] = on ? 1 : 0;
+    if (!on) partial[(size_t)t * n_tiles + tile] = 0.0;
+  }
+  const unsigned long long m = __ballot(on);
+  if (m == 0ull) return;
+  const int lane = threadIdx.x & 63;
+  unsigned base = 0;
+  if (lane == 0) base = atomicAdd(count, (unsigned)__popcll(m));
+  base = __shfl(base, 0, 64);
+  if (on) list[base + __popcll(m & ((1ull << lane) - 1ull))] = make_int2(tile, t);
+}
+
+// u[t][p] = g_t(p), the unnormalised density of tine t, on the tiles of the
+// listed pairs (0 on held voxels), and each pair's sum.  The chords that
+// reach the tile are gathered in LDS in their order, so a voxel's sum has
+// the terms of k_source_write in the same order, less exact zeros.
+__global__ __launch_bounds__(256) void k_source_fields(const uint8_t* lab, const Chord* chords,
+                                                       const int* tine_first, double sigma,
+                                                       double* u, int nx, int ny, int nz,
+                                                       double dx, double dy, double dz,
+                                                       int n_tiles, const int2* list,
+                                                       const unsigned* count, double* partial) {
+  __shared__ Chord near[256];
+  __shared__ int n_near[4];
+  __shared__ double sh[kRedThreads / 64];
   const size_t n = (size_t)nx * ny * nz;
-  for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-       p += (size_t)gridDim.x * blockDim.x) {
-    if (lab[p] & kHeld) {
-      for (int t = 0; t < n_tines; ++t) u[(size_t)t * n + p] = 0.0;
-      continue;
-    }
-    const int k = (int)(p % nz);
-    const int j = (int)((p / nz) % ny);
-    const int i = (int)(p / ((size_t)nz * ny));
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const unsigned pairs = *count;
+  for (unsigned e = blockIdx.x; e < pairs; e += gridDim.x) {
+    const int2 pr = list[e];
+    const SourceTile tl = source_tile(pr.x, ny, nz);
+    const TileBall ball = tile_ball(tl, nx, ny, nz, dx, dy, dz);
+    int i, j, k;
+    size_t p;
+    const bool inside = tile_voxel(tl, nx, ny, nz, i, j, k, p);
+    const bool free = inside && !(lab[inside ? p : 0] & kHeld);
     const double x = (2.0 * i - (nx - 1)) * dx / 2.0;
     const double y = (2.0 * j - (ny - 1)) * dy / 2.0;
     const double z = (2.0 * k - (nz - 1)) * dz / 2.0;
-    for (int t = 0; t < n_tines; ++t)
-      u[(size_t)t * n + p] = tine_density(chords, tine_first[t], tine_first[t + 1], x, y, z, sigma);
+    const int c1 = tine_first[pr.y + 1];
+    double g = 0.0;
+    for (int c0 = tine_first[pr.y]; c0 < c1; c0 += 256) {
+      const int c = c0 + (int)threadIdx.x;
+      const bool on = c < c1 && chord_reaches(chords[c], ball, sigma);
+      const unsigned long long m = __ballot(on);
+      if (lane == 0) n_near[w] = __popcll(m);
+      __syncthreads();
+      int at = 0, total = 0;
+      for (int v = 0; v < 4; ++v) {
+        if (v < w) at += n_near[v];
+        total += n_near[v];
+      }
+      if (on) near[at + __popcll(m & ((1ull << lane) - 1ull))] = chords[c];
+      __syncthreads();
+      if (free)
+        for (int v = 0; v < total; ++v) g += chord_density(near[v], x, y, z, sigma);
+      __syncthreads();  // near and n_near are refilled
+    }
+    if (inside) u[(size_t)pr.y * n + p] = g;
+    const double sum = block_sum_d(g, sh);
+    if (threadIdx.x == 0) partial[(size_t)pr.y * n_tiles + pr.x] = sum;
   }
 }
 
-// Per-tine integrals from stored fields: the traversal and summation order
-// of k_source_sums, so the results are identical.
-__global__ __launch_bounds__(kRedThreads) void k_field_sums(const uint8_t* lab, const double* u,
-                                                            size_t n, double* partial) {
-  __shared__ double sh[kRedThreads / 64];
-  const int t = blockIdx.y;
-  const double* ut = u + (size_t)t * n;
-  double acc = 0.0;
-  for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-       p += (size_t)gridDim.x * blockDim.x) {
-    if (lab[p] & kHeld) continue;
-    acc += ut[p];
+// sums[t] = scale * the tine's pair sums in fixed order, weight[t] = power[t] / sums[t].
+__global__ __launch_bounds__(1024) void k_tine_sums(const double* partial, int n_tiles,
+                                                    double scale, const double* power,
+                                                    double* sums, double* weight) {
+  __shared__ double sh[16];
+  const double* row = partial + (size_t)blockIdx.x * n_tiles;
+  double v = 0.0;
+  int e = threadIdx.x;
+  constexpr int kU = 8;  // loads in flight per thread
+  for (; e + (kU - 1) * 1024 < n_tiles; e += kU * 1024) {
+    double q[kU];
+#pragma unroll
+    for (int k = 0; k < kU; ++k) q[k] = row[e + k * 1024];
+#pragma unroll
+    for (int k = 0; k < kU; ++k) v += q[k];
   }
-  acc = block_sum_d(acc, sh);
-  if (threadIdx.x == 0) partial[(size_t)t * gridDim.x + blockIdx.x] = acc;
+  for (; e < n_tiles; e += 1024) v += row[e];
+  v = wave_sum_d(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < 16; ++w) t += sh[w];
+    t *= scale;
+    sums[blockIdx.x] = t;
+    weight[blockIdx.x] = power[blockIdx.x] / t;
+  }
 }
 
-// q[p] = sum_t scale[t] u_t(p) on free voxels, in the order of k_source_write.
-__global__ void k_source_combine(const uint8_t* lab, const double* u, int n_tines,
-                                 const double* scale, double* q, size_t n) {
-  for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-       p += (size_t)gridDim.x * blockDim.x) {
+// q[p] = sum_t scale[t] u_t(p) on free voxels, in the order of
+// k_source_write; one work-group per tile, inactive pairs not read.
+__global__ __launch_bounds__(256) void k_source_combine(const uint8_t* lab, const double* u,
+                                                        const uint8_t* active, int n_tiles,
+                                                        int n_tines, const double* scale,
+                                                        double* q, int nx, int ny, int nz) {
+  const size_t n = (size_t)nx * ny * nz;
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    int i, j, k;
+    size_t p;
+    if (!tile_voxel(source_tile(tile, ny, nz), nx, ny, nz, i, j, k, p)) continue;
     double v = 0.0;
     if (!(lab[p] & kHeld))
-      for (int t = 0; t < n_tines; ++t) v += scale[t] * u[(size_t)t * n + p];
+      for (int t = 0; t < n_tines; ++t)
+        if (active[(size_t)t * n_tiles + tile]) v += scale[t] * u[(size_t)t * n + p];
     q[p] = v;
   }
 }
 
 hipError_t launch_source_fields(Grid3 g, double dx, double dy, double dz, const uint8_t* lab,
                                 const Chord* chords, const int* tine_first, int n_tines,
-                                double sigma, double* u, hipStream_t st) {
-  hipLaunchKernelGGL(k_source_fields, dim3(4096), dim3(256), 0, st, lab, chords, tine_first,
-                     n_tines, sigma, u, g.nx, g.ny, g.nz, dx, dy, dz);
+                                double sigma, const double* power, const SourceFields& f,
+                                double* sums, double* weight, hipStream_t st) {
+  const int tiles = source_tiles(g);
+  hipError_t e = hipMemsetAsync(f.count, 0, sizeof(unsigned), st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_source_cull, dim3((tiles + 255) / 256, n_tines), dim3(256), 0, st, chords,
+                     tine_first, sigma, g.nx, g.ny, g.nz, dx, dy, dz, tiles, f.active, f.list,
+                     f.count, f.partial);
+  const long long pairs = (long long)tiles * n_tines;
+  hipLaunchKernelGGL(k_source_fields, dim3((unsigned)std::min<long long>(pairs, 8192)),
+                     dim3(256), 0, st, lab, chords, tine_first, sigma, f.u, g.nx, g.ny, g.nz, dx,
+                     dy, dz, tiles, f.list, f.count, f.partial);
+  hipLaunchKernelGGL(k_tine_sums, dim3(n_tines), dim3(1024), 0, st, f.partial, tiles,
+                     dx * dy * dz, power, sums, weight);
   return hipGetLastError();
 }
 
-hipError_t launch_field_sums(Grid3 g, double dx, double dy, double dz, const uint8_t* lab,
-                             const double* u, int n_tines, double* partial, double* sums,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(k_field_sums, dim3(kRedBlocks, n_tines), dim3(kRedThreads), 0, st, lab, u,
-                     g.n(), partial);
-  hipLaunchKernelGGL(k_sum_rows, dim3(n_tines), dim3(kRedThreads), 0, st, partial, kRedBlocks,
-                     dx * dy * dz, sums);
-  return hipGetLastError();
-}
-
-hipError_t launch_source_combine(Grid3 g, const uint8_t* lab, const double* u, int n_tines,
+hipError_t launch_source_combine(Grid3 g, const uint8_t* lab, const SourceFields& f, int n_tines,
                                  const double* scale, double* q, hipStream_t st) {
-  hipLaunchKernelGGL(k_source_combine, dim3(4096), dim3(256), 0, st, lab, u, n_tines, scale, q,
-                     g.n());
+  const int tiles = source_tiles(g);
+  hipLaunchKernelGGL(k_source_combine, dim3(std::min(tiles, 16384)), dim3(256), 0, st, lab, f.u,
+                     f.active, tiles, n_tines, scale, q, g.nx, g.ny, g.nz);
+  return hipGetLastError();
+}
+
+// Per-tine sums sum_p u_t(p) v_p with v_p = sacc_p dt / (rho c)_p on free
+// voxels (grid.y = tine), over the tine's active tiles; partial[t][block].
+__global__ __launch_bounds__(256) void k_source_dot_fields(const uint8_t* lab, const double* u,
+                                                           const uint8_t* active, int n_tiles,
+                                                           const float* sacc,
+                                                           const ClassParams* cp, double dt,
+                                                           int nx, int ny, int nz,
+                                                           double* partial) {
+  __shared__ double sh[kRedThreads / 64];
+  const int t = blockIdx.y;
+  const double* ut = u + (size_t)t * nx * ny * nz;
+  double acc = 0.0;
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    if (!active[(size_t)t * n_tiles + tile]) continue;
+    int i, j, k;
+    size_t p;
+    if (!tile_voxel(source_tile(tile, ny, nz), nx, ny, nz, i, j, k, p)) continue;
+    const unsigned v = lab[p];
+    if (v & kHeld) continue;
+    const double sv = (double)sacc[p] * dt / cp->rc[class_of(v)];
+    if (sv != 0.0) acc += ut[p] * sv;
+  }
+  acc = block_sum_d(acc, sh);
+  if (threadIdx.x == 0) partial[(size_t)t * gridDim.x + blockIdx.x] = acc;
+}
+
+hipError_t launch_source_dot_fields(Grid3 g, const uint8_t* lab, const SourceFields& f,
+                                    int n_tines, const float* sacc, const ClassParams* cp_dev,
+                                    double dt, double* partial, int nblk, hipStream_t st) {
+  hipLaunchKernelGGL(k_source_dot_fields, dim3(nblk, n_tines), dim3(256), 0, st, lab, f.u,
+                     f.active, source_tiles(g), sacc, cp_dev, dt, g.nx, g.ny, g.nz, partial);
   return hipGetLastError();
 }
 

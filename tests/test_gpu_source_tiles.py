@@ -1,0 +1,59 @@
+"""The RF source on its tiles against the oracle's source: sizes around the
+tiles' edges, a tine of more chords than one gathering pass takes, more
+tines than a wave has lanes, and new powers on the kept densities."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_1907_05709_amd import rfa
+from paper_1907_05709_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(shape, spacing, n_tines, n_points, seed):
+    rng = np.random.default_rng(seed)
+    labels = W._with_boundary(np.full(shape, W.LABEL_LIVER, dtype=np.uint8))
+    tissue = W.standard_tissue()[:2]
+    tissue[1] = dataclasses.replace(tissue[1], h=0.0)
+    half = np.array([(n - 1) * d / 2 for n, d in zip(shape, spacing)])
+    pts = rng.uniform(-0.9 * half, 0.9 * half, size=(n_tines * n_points, 3))
+    needle = W.Needle(np.arange(n_tines + 1, dtype=np.int32) * n_points, pts,
+                      rng.uniform(1.0, 20.0, size=n_tines), 0.7 * min(spacing))
+    return W.Case("tiles", shape, spacing, labels, tissue, needle, 0.01, 1, seed)
+
+
+@pytest.mark.parametrize("shape, spacing, n_tines, n_points", [
+    ((3, 3, 3), (1e-3, 1e-3, 1e-3), 1, 2),
+    ((4, 4, 16), (1e-3, 1e-3, 1e-3), 1, 2),
+    ((5, 9, 17), (1e-3, 0.5e-3, 2e-3), 3, 4),
+    ((40, 7, 70), (1e-3, 1e-3, 1e-3), 2, 300),
+    ((33, 30, 31), (0.8e-3, 1e-3, 1.2e-3), 70, 3),
+])
+def test_source_matches_oracle(shape, spacing, n_tines, n_points):
+    case = _case(shape, spacing, n_tines, n_points, 11 + n_tines)
+    g = rfa.Grid(case.shape, case.spacing)
+    g.load_case(case)
+    free = np.zeros(shape, bool)
+    free[1:-1, 1:-1, 1:-1] = True
+    rc = W.RHO_LIVER * W.C_LIVER
+
+    def check(powers):
+        # one step from uniform 37 degC without perfusion adds dt q / (rho c),
+        # held in float32 (2^-24 relative), added to a zero excess
+        ref = O.source(dataclasses.replace(
+            case, needle=dataclasses.replace(case.needle, power=powers))) * case.dt / rc
+        g.reset_state()
+        g.step(1, case.dt)
+        got = g.temperature() - 37.0
+        tol = 2.0 ** -23 * np.abs(ref) + 1e-12 * ref.max() + 1e-14
+        assert np.all(np.abs(got - ref)[free] <= tol[free])
+        assert np.all(got[~free] == 0.0)
+
+    check(case.needle.power)
+    p2 = case.needle.power[::-1].copy()
+    g.set_tine_powers(p2)
+    check(p2)
+    g.close()
