@@ -20,7 +20,8 @@ CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "librfa.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 SOURCES = ["rfa_api.hip", "rfa_kernels.hip", "rfa_step.hip", "rfa_tiled.hip", "rfa_tiled2.hip",
-           "rfa_wide.hip",
+           "rfa_wide.hip", "rfa_pair.hip", "rfa_pair_16x2.hip", "rfa_pair_8x2.hip",
+           "rfa_pair_8x1.hip", "rfa_pair_4x1.hip",
            "rfa_adjoint.hip", "rfa_warp.hip"]
 ARCH = "gfx950"
 

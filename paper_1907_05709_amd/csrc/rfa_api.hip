@@ -86,6 +86,7 @@ struct rfa_grid_s {
   float* lo[2] = {nullptr, nullptr};
   int cur = 0;
   float* om = nullptr;
+  float* om_alt = nullptr;  // second damage image (damage-coupled grids on pair plans)
   float* src = nullptr;
   double* q64 = nullptr;
   float* perf = nullptr;  // null = no perfusion multiplier
@@ -147,6 +148,11 @@ struct rfa_grid_s {
   bool energy_valid = false;
 
   StepPlan plan{};
+  // wave codes of the pair plan's shape (waves, voxels per lane), made from
+  // the current labels and classes
+  uint8_t* codes = nullptr;
+  size_t codes_cap = 0;
+  int codes_waves = 0, codes_v = 0;  // 0: none
 
   // step-kernel timing
   std::vector<hipEvent_t> events;
@@ -184,6 +190,8 @@ void free_all(rfa_grid g) {
   f(g->lo[0]);
   f(g->lo[1]);
   f(g->om);
+  f(g->om_alt);
+  f(g->codes);
   f(g->src);
   f(g->q64);
   f(g->perf);
@@ -278,6 +286,10 @@ StepConst step_const(rfa_grid g, double dt) {
   K.cap = (float)g->opt.omega_cap;
   K.thr = (float)(g->opt.t_death - 37.0);
   K.decay2 = g->perf_decay ? (float)M_LOG2E : 0.0f;
+  // |exponent| = c2 |theta| / (T_aK + theta) below 2^-29, where 2^x rounds
+  // to 1 whatever its sign
+  const double c2 = c * M_LOG2E;
+  K.cold = (float)(c2 > 0.0 ? std::min(1.0, std::ldexp(0.5 * kTBodyK / c2, -29)) : 1.0);
   return K;
 }
 
@@ -457,6 +469,28 @@ rfa_status ensure_side_stream(rfa_grid g) {
   return RFA_OK;
 }
 
+// The wave codes a pair plan's launches read, and the second damage image
+// that damage-coupled grids need there.
+rfa_status ensure_pair(rfa_grid g, const StepPlan& p) {
+  if (!p.pv) return RFA_OK;
+  rfa_status s;
+  if (g->perf_decay && !g->om_alt && (s = dmalloc(&g->om_alt, g->g.n())) != RFA_OK) return s;
+  if (g->codes_waves == p.ty && g->codes_v == p.pv) return RFA_OK;
+  const PairShape sh = pair_shape(g->g, p.ty, p.pv, p.xc);  // codes do not depend on xc
+  const size_t need = pair_code_bytes(g->g, sh);
+  if (g->codes_cap < need) {
+    if (g->codes) (void)hipFree(g->codes);
+    g->codes_cap = 0;
+    g->codes_waves = 0;
+    if ((s = dmalloc(&g->codes, need)) != RFA_OK) return s;
+    g->codes_cap = need;
+  }
+  HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp_dev, g->codes, g->st));
+  g->codes_waves = p.ty;
+  g->codes_v = p.pv;
+  return RFA_OK;
+}
+
 // Per-dt coefficient tables and source increment of grid g.
 rfa_status prepare_dt(rfa_grid g, double dt) {
   if (dt != g->tab_dt) {
@@ -483,13 +517,18 @@ rfa_status ensure_events(rfa_grid g, int count);
 // not touched).
 rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
                        float* traj = nullptr, int* traj_t = nullptr) {
-  StepState ss{g->hi, g->lo, &g->cur, g->lab, g->src, g->om, g->perf, g->tab_dev,
+  StepState ss{g->hi, g->lo, &g->cur, g->lab, g->src, &g->om, g->perf, g->tab_dev,
                g->n_classes};
-  // one step per launch for the kept trajectory, and with damage-coupled
-  // perfusion: the two-step kernel reads the damage integral of its halo
+  // the 2.5-D two-step kernel takes neither the kept trajectory nor
+  // damage-coupled perfusion (it reads the damage integral of its halo
   // voxels while the neighbouring work-groups overwrite it, harmless while
-  // the damage integral feeds no temperature
-  const StepPlan plan = (traj || g->perf_decay) ? plan_one(g->plan) : g->plan;
+  // the damage integral feeds no temperature)
+  const bool single = g->plan.depth == 2 && !g->plan.pv && (traj || g->perf_decay);
+  const StepPlan plan = single ? plan_one(g->plan) : g->plan;
+  if (n_steps >= plan.depth)  // fewer steps run on the one-step plan
+    if (rfa_status sp = ensure_pair(g, plan); sp != RFA_OK) return sp;
+  ss.codes = g->codes;
+  ss.om_alt = g->perf_decay ? &g->om_alt : nullptr;
   if (traj) {
     ss.traj = traj;
     ss.traj_t = traj_t;
@@ -803,6 +842,7 @@ rfa_status rfa_set_tissue(rfa_grid g, const uint8_t* labels, const rfa_tissue* t
   g->cp_dev = ncp;
   g->cp = cp;
   g->n_classes = n_classes;
+  g->codes_waves = 0;
   std::memcpy(g->table, table, n_classes * sizeof(rfa_tissue));
   g->has_tissue = true;
   g->cur = 0;
@@ -1314,10 +1354,10 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   if ((s = dmalloc(&om2, n)) != RFA_OK) return s;
   if ((s = dmalloc(&lab2, n)) != RFA_OK) { (void)hipFree(om2); return s; }
   if ((s = ensure_events(g, 2)) != RFA_OK) { (void)hipFree(om2); (void)hipFree(lab2); return s; }
-  StepPlan cand[64];
-  const int nc = plan_candidates(g->g, g->opt.depth == 1 ? 1 : kMaxDepth, cand, 64);
+  StepPlan cand[128];
+  const int nc = plan_candidates(g->g, g->opt.depth == 1 ? 1 : kMaxDepth, cand, 128);
   const StepConst K = step_const(g, dt);
-  StepBuffers b;
+  StepBuffers b{};
   b.hi_in = g->hi[g->cur];
   b.lo_in = g->lo[g->cur];
   b.hi_out = g->hi[1 - g->cur];
@@ -1325,6 +1365,7 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   b.lab = lab2;
   b.src = g->src;
   b.omega = om2;
+  b.omega_out = om2;  // timing only: the scratch damage is not read back
   b.perf = g->perf;
   b.tab = g->tab_dev;
   b.n_classes = g->n_classes;
@@ -1337,6 +1378,8 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   for (int c = 0; c < nc && e == hipSuccess; ++c) {
     if ((e = hipMemcpyAsync(om2, g->om, n * sizeof(float), hipMemcpyDeviceToDevice, g->st))) break;
     if ((e = hipMemcpyAsync(lab2, g->lab, n, hipMemcpyDeviceToDevice, g->st))) break;
+    if ((s = ensure_pair(g, cand[c])) != RFA_OK) break;
+    b.codes = g->codes;
     if ((e = launch_plan(g->g, cand[c], b, K, g->st))) break;  // warm-up
     if ((e = hipEventRecord(g->events[0], g->st))) break;
     for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch_plan(g->g, cand[c], b, K, g->st);
@@ -1355,6 +1398,7 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   (void)hipFree(om2);
   (void)hipFree(lab2);
   if (e != hipSuccess) return fail(RFA_ERR_HIP, "tune failed: %s", hipGetErrorString(e));
+  if (s != RFA_OK) return s;
   g->plan = best;
   g_tuned.push_back({key, best});
   return RFA_OK;
@@ -1747,6 +1791,9 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
   // adjoint reads.
   if (every > 0) {
     if ((s = ensure_side_stream(g)) != RFA_OK) return s;
+    const StepPlan one = plan_one(g->plan);
+    const StepPlan re = g->plan.pv ? g->plan : one;
+    if ((s = ensure_pair(g, re)) != RFA_OK) return s;
     hipEvent_t start = g->side_ev[0];
     hipEvent_t ready[2] = {g->side_ev[1], g->side_ev[2]};
     hipEvent_t read[2] = {g->side_ev[3], g->side_ev[4]};
@@ -1769,20 +1816,24 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
       HIP_TRY(hipMemcpyAsync(traj, c, n * sizeof(float), hipMemcpyDeviceToDevice, g->side));
       HIP_TRY(
           hipMemcpyAsync(lopp[0], c + n, n * sizeof(float), hipMemcpyDeviceToDevice, g->side));
-      for (int t = 0; t < k; ++t) {
-        StepBuffers b;
+      for (int t = 0, i = 0; t < k; ++i) {
+        const StepPlan& p = t + re.depth <= k ? re : one;
+        StepBuffers b{};
         b.hi_in = traj + (size_t)t * n;
-        b.lo_in = lopp[t & 1];
-        b.hi_out = traj + (size_t)(t + 1) * n;
-        b.lo_out = lopp[(t + 1) & 1];
+        b.lo_in = lopp[i & 1];
+        b.hi_out = traj + (size_t)(t + p.depth) * n;
+        b.lo_out = lopp[(i + 1) & 1];
         b.lab = g->lab_scratch;
         b.src = g->src;
         b.omega = om_s;
+        b.omega_out = om_s;
         b.perf = g->perf;
         b.tab = g->tab_dev;
         b.partials = nullptr;
         b.n_classes = g->n_classes;
-        HIP_TRY(launch_plan_temperature(g->g, plan_one(g->plan), b, K, g->side));
+        b.codes = g->codes;
+        HIP_TRY(launch_plan_temperature(g->g, p, b, traj + (size_t)(t + 1) * n, K, g->side));
+        t += p.depth;
       }
       HIP_TRY(hipEventRecord(ready[half], g->side));
       HIP_TRY(hipStreamWaitEvent(g->st, ready[half], 0));

@@ -58,6 +58,7 @@ struct StepConst {
   float cap;     // Omega cap
   float thr;     // t_death - 37
   float decay2;  // log2(e) with damage-coupled perfusion, else 0
+  float cold;    // |theta| below which the damage exponent rounds to 2^0 = 1
 };
 
 // Per-thread diagnostic partials of one step.
@@ -86,17 +87,99 @@ __device__ __forceinline__ float ff_diff(float hn, float ln, float hi, float lo)
   return (hn - hi) + (ln - lo);
 }
 
-// One voxel of one step.  No output of a held voxel depends on its
-// neighbours' values, which may be arbitrary (even NaN: the tiled kernels
-// leave halo cells outside the grid unwritten), so those values only ever
-// reach results through selects on the held flag.
-// cf points at the LDS copy of Tables::cf (3 x 256 float2), cls at Tables::cls.
-//
+// The update of one voxel's temperature before any selection: new pair
+// (h2, l2), conduction and perfusion terms and their sum inc, from the six
+// neighbour differences d (x-, x+, y-, y+, z-, z+), their coefficients
+// k = C(l, l_nb) and the class entry c.
+__device__ __forceinline__ void thermal_update(float hi, float lo, const float2 (&k)[6],
+                                               const float4& c, const float (&d)[6], float s,
+                                               float pf, float& h2, float& l2, float& cond,
+                                               float& perf, float& inc) {
+  // Six face terms C(l, l_nb) d_nb, one fused chain per part of the
+  // float-float coefficient (the lo chain carries the coefficients'
+  // rounding, which is the same over a whole region).
+  float ch = k[0].x * d[0], cl = k[0].y * d[0];
+#pragma unroll
+  for (int f = 1; f < 6; ++f) {
+    ch = __builtin_fmaf(k[f].x, d[f], ch);
+    cl = __builtin_fmaf(k[f].y, d[f], cl);
+  }
+  cond = ch + cl;
+  const float bh = c.x * pf, bl = c.y * pf;
+  perf = __builtin_fmaf(bh, hi, __builtin_fmaf(bl, hi, bh * lo));
+  inc = (cond - perf) + (c.z + s);
+  // float-float accumulation: (hi, lo) + inc, renormalised
+  const float t = lo + inc;
+  const float s1 = hi + t;
+  const float v = s1 - hi;
+  const float e = (hi - (s1 - v)) + (t - v);
+  h2 = s1 + e;
+  l2 = e - (h2 - s1);
+}
+
+// Whether a free voxel's increment counts as cooling.
+__device__ __forceinline__ bool cools(float hi, float inc) {
+  return inc < -__builtin_fmaf(kCoolRel, fabsf(hi), kCoolAbs);
+}
+
+// The temperature part of one voxel's step.  No output of a held voxel
+// depends on the differences, which may be arbitrary (even NaN: the tiled
+// kernels leave halo cells outside the grid unwritten), so they only ever
+// reach results through selects on held.  count: the voxel's sums go into
+// acc (kDiag).
+template <bool kDiag = true>
+__device__ __forceinline__ void voxel_thermal(float hi, float lo, bool held,
+                                              const float2 (&k)[6], const float4& c,
+                                              const float (&d)[6], float s, float pf, float& nh,
+                                              float& nl, Partial& acc, bool count) {
+  float h2, l2, cond, perf, inc;
+  thermal_update(hi, lo, k, c, d, s, pf, h2, l2, cond, perf, inc);
+  nh = held ? hi : h2;
+  nl = held ? lo : l2;
+  if constexpr (kDiag) {
+    acc.mono += (count && cools(hi, inc)) ? 1u : 0u;
+    acc.perf = count ? __builtin_fmaf(c.w, perf, acc.perf) : acc.perf;
+    acc.bnd = count ? __builtin_fmaf(c.w, cond, acc.bnd) : acc.bnd;
+  }
+}
+
+// Arrhenius increment dt rate at the step's input temperature.
+__device__ __forceinline__ float damage_increment(float hi, const StepConst& K) {
+  float x = K.c2 * hi * __builtin_amdgcn_rcpf(K.tak + hi);
+  x = fminf(x, K.clamp2);
+  return K.dtka * __builtin_amdgcn_exp2f(x);
+}
+
 // The damage update has two forms with the same bits: branch-free (the
 // default, one basic block per plane, fewer live registers in the kernels
 // with one or two voxels per lane) and a select that lets the compiler
 // branch around the transcendentals off tissue (kSelectDamage, fewer live
 // registers where each lane carries four voxels).
+template <bool kSelectDamage>
+__device__ __forceinline__ float damage_add(float om, float rate, bool tissue,
+                                            const StepConst& K) {
+  if constexpr (kSelectDamage) return tissue ? fminf(om + rate, K.cap) : om;
+  // off tissue: om + rate * 0 = om and fminf(om, inf) = om (om >= +0)
+  return fminf(__builtin_fmaf(rate, tissue ? 1.0f : 0.0f, om),
+               tissue ? K.cap : __builtin_huge_valf());
+}
+
+__device__ __forceinline__ unsigned latch(unsigned lab, float nh, float nl, const StepConst& K) {
+  const bool reached = (nh > K.thr) | ((nh == K.thr) & (nl >= 0.0f));
+  return ((lab & kTissue) && reached) ? (lab | kLatch) : lab;
+}
+
+// C(l, l_nb) from an LDS copy cf of Tables::cf (3 x 256 float2), addressed in
+// bytes: row of the own class (16 entries of 8 bytes), entry of the
+// neighbour's class (its masked label byte).
+__device__ __forceinline__ float2 table_entry(const float2* __restrict__ cf, int axis,
+                                              unsigned lab, unsigned nb) {
+  const char* t = reinterpret_cast<const char*>(cf + axis * kMaxClasses * kMaxClasses);
+  return *reinterpret_cast<const float2*>(t + (((lab & kClassMask) << 4) | (nb & kClassMask)));
+}
+
+// One voxel of one step from its neighbours' values and class bytes.  cf
+// points at the LDS copy of Tables::cf, cls at Tables::cls.
 //
 // field: pf comes from a perfusion field (kernels with a field; a constant
 // after inlining).  Only those kernels apply the damage coupling: the host
@@ -114,65 +197,17 @@ __device__ __forceinline__ void voxel_step(
     const float4* __restrict__ cls, const StepConst& K,
     float& nh, float& nl, unsigned& nlab, Partial& acc, bool field = false) {
   if (field) pf *= __builtin_amdgcn_exp2f(-om * K.decay2);
-  // C(l, l_nb) addressed in bytes: row of the own class (16 entries of 8
-  // bytes), entry of the neighbour's class (its masked label byte)
-  const unsigned row = (lab & kClassMask) << 4;
-  auto entry = [&](int axis, unsigned nb) {
-    const char* t = reinterpret_cast<const char*>(cf + axis * kMaxClasses * kMaxClasses);
-    return *reinterpret_cast<const float2*>(t + (row | (nb & kClassMask)));
-  };
-  const float2 kxm = entry(0, bxm), kxp = entry(0, bxp);
-  const float2 kym = entry(1, bym), kyp = entry(1, byp);
-  const float2 kzm = entry(2, bzm), kzp = entry(2, bzp);
-  const float dxm = ff_diff(hxm, lxm, hi, lo), dxp = ff_diff(hxp, lxp, hi, lo);
-  const float dym = ff_diff(hym, lym, hi, lo), dyp = ff_diff(hyp, lyp, hi, lo);
-  const float dzm = ff_diff(hzm, lzm, hi, lo), dzp = ff_diff(hzp, lzp, hi, lo);
-  // Six face terms C(l, l_nb) d_nb, one fused chain per part of the
-  // float-float coefficient (the lo chain carries the coefficients'
-  // rounding, which is the same over a whole region).
-  float ch = kxm.x * dxm, cl = kxm.y * dxm;
-  ch = __builtin_fmaf(kxp.x, dxp, ch);
-  cl = __builtin_fmaf(kxp.y, dxp, cl);
-  ch = __builtin_fmaf(kym.x, dym, ch);
-  cl = __builtin_fmaf(kym.y, dym, cl);
-  ch = __builtin_fmaf(kyp.x, dyp, ch);
-  cl = __builtin_fmaf(kyp.y, dyp, cl);
-  ch = __builtin_fmaf(kzm.x, dzm, ch);
-  cl = __builtin_fmaf(kzm.y, dzm, cl);
-  ch = __builtin_fmaf(kzp.x, dzp, ch);
-  cl = __builtin_fmaf(kzp.y, dzp, cl);
-  const float cond = ch + cl;
+  const float2 k[6] = {table_entry(cf, 0, lab, bxm), table_entry(cf, 0, lab, bxp),
+                       table_entry(cf, 1, lab, bym), table_entry(cf, 1, lab, byp),
+                       table_entry(cf, 2, lab, bzm), table_entry(cf, 2, lab, bzp)};
+  const float d[6] = {ff_diff(hxm, lxm, hi, lo), ff_diff(hxp, lxp, hi, lo),
+                      ff_diff(hym, lym, hi, lo), ff_diff(hyp, lyp, hi, lo),
+                      ff_diff(hzm, lzm, hi, lo), ff_diff(hzp, lzp, hi, lo)};
   const float4 c = cls[class_of(lab)];
-  const float bh = c.x * pf, bl = c.y * pf;
-  const float perf = __builtin_fmaf(bh, hi, __builtin_fmaf(bl, hi, bh * lo));
-  const float inc = (cond - perf) + (c.z + s);
-  // float-float accumulation: (hi, lo) + inc, renormalised
-  const float t = lo + inc;
-  const float s1 = hi + t;
-  const float v = s1 - hi;
-  const float e = (hi - (s1 - v)) + (t - v);
-  const float h2 = s1 + e;
-  const float l2 = e - (h2 - s1);
   const bool held = (lab & kHeld) != 0u;
-  nh = held ? hi : h2;
-  nl = held ? lo : l2;
-  // Arrhenius increment evaluated at the step's input temperature.
-  float x = K.c2 * hi * __builtin_amdgcn_rcpf(K.tak + hi);
-  x = fminf(x, K.clamp2);
-  const float rate = K.dtka * __builtin_amdgcn_exp2f(x);
-  const bool tissue = (lab & kTissue) != 0u;
-  if constexpr (kSelectDamage) {
-    om = tissue ? fminf(om + rate, K.cap) : om;
-  } else {
-    // off tissue: om + rate * 0 = om and fminf(om, inf) = om (om >= +0)
-    om = fminf(__builtin_fmaf(rate, tissue ? 1.0f : 0.0f, om),
-               tissue ? K.cap : __builtin_huge_valf());
-  }
-  const bool reached = (nh > K.thr) | ((nh == K.thr) & (nl >= 0.0f));
-  nlab = (tissue && reached) ? (lab | kLatch) : lab;
-  acc.mono += (!held && inc < -__builtin_fmaf(kCoolRel, fabsf(hi), kCoolAbs)) ? 1u : 0u;
-  acc.perf = held ? acc.perf : __builtin_fmaf(c.w, perf, acc.perf);
-  acc.bnd = held ? acc.bnd : __builtin_fmaf(c.w, cond, acc.bnd);
+  voxel_thermal(hi, lo, held, k, c, d, s, pf, nh, nl, acc, !held);
+  om = damage_add<kSelectDamage>(om, damage_increment(hi, K), (lab & kTissue) != 0u, K);
+  nlab = latch(lab, nh, nl, K);
 }
 
 // Wave sums through DPP lane moves instead of LDS permutes: lanes ^ 1 and

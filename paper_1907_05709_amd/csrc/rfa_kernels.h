@@ -64,6 +64,8 @@ struct StepBuffers {
   const Tables* tab;
   float* partials;       // [nwg * 3] for this step, may be null
   int n_classes;         // classes in use (table rows staged into LDS)
+  float* omega_out;      // two-step kernel: new damage integral (may be omega)
+  const uint8_t* codes;  // two-step kernel: wave codes of its shape
 };
 
 // ---- stepping ------------------------------------------------------------

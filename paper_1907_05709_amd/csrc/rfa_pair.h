@@ -1,0 +1,60 @@
+// rfa_pair.h -- launcher of the two-step kernel (internal).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "rfa_kernels.h"
+#include "rfa_tiled.h"
+
+namespace rfa {
+
+// Footprint of a work-group of the two-step kernel: waves * 64 * v
+// consecutive voxels of a (y, z) plane, of which it owns seg (the plane's
+// segments are seg voxels apart) and nz on either side are its halo.
+struct PairShape {
+  int waves = 0;   // wavefronts per work-group
+  int v = 0;       // voxels per lane
+  int xc = 0;      // x planes per work-group
+  int seg = 0;     // owned voxels per segment
+  int segs = 0;    // segments per plane
+  int chunks = 0;  // chunks along x
+  int nwg = 0;     // work-groups per launch
+};
+
+// Wave code: class in bits 0-3, which of the wave's voxels are tissue in bits
+// 4-5; kPairIrregular if its coefficients differ from voxel to voxel.
+constexpr unsigned kPairIrregular = 255u;
+constexpr unsigned kPairTissueFree = 0x10u;  // the free voxels
+constexpr unsigned kPairTissueAll = 0x20u;   // every voxel inside the plane
+
+// What a launch moves besides the state of StepBuffers.
+enum PairMode {
+  kPairFull = 0,  // both steps' damage and latches
+  kPairKeep = 1,  // the same, and the hi image between the steps is kept
+  kPairTemp = 2   // temperature only, the hi image between the steps kept
+};
+
+// Whether the kernel exists for this work-group and grid.
+bool pair_fits(Grid3 g, int waves, int v, int xc);
+PairShape pair_shape(Grid3 g, int waves, int v, int xc);
+// Bytes of a shape's wave codes, and the kernel that fills them (after every
+// change of the labels or the class table).
+size_t pair_code_bytes(Grid3 g, const PairShape& s);
+hipError_t launch_pair_codes(Grid3 g, const PairShape& s, const uint8_t* lab,
+                             const ClassParams* cp_dev, uint8_t* codes, hipStream_t st);
+// Two steps.  b.codes: the shape's wave codes; hi_mid: the image between the
+// steps (kPairKeep, kPairTemp).
+hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b,
+                            const StepConst& K, PairMode mode, float* hi_mid, int store,
+                            hipStream_t st);
+
+// The kinds of work-group (waves x voxels per lane), for launch_step_pair().
+#define RFA_PAIR_LAUNCH(name)                                                             \
+  hipError_t name(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K, \
+                  PairMode mode, float* hi_mid, int store, hipStream_t st)
+RFA_PAIR_LAUNCH(launch_pair_16x2);
+RFA_PAIR_LAUNCH(launch_pair_8x2);
+RFA_PAIR_LAUNCH(launch_pair_8x1);
+RFA_PAIR_LAUNCH(launch_pair_4x1);
+
+}  // namespace rfa

@@ -1,0 +1,115 @@
+// rfa_pair.hip -- shapes, wave codes and launches of the two-step kernel
+// (rfa_pair_kernel.h; each work-group size is compiled by its own source).
+#include "rfa_pair.h"
+
+namespace rfa {
+
+// Wave codes: for plane x, segment and wave of the footprint, the class that
+// all its free voxels share if every neighbour has that class's
+// conductivity (0 without free voxels) and which of its voxels are tissue;
+// kPairIrregular if neither holds.  The face coefficients of such a wave are all
+// C(c, c): the harmonic mean of equal conductivities over the own class's
+// heat capacity.
+__global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, const ClassParams* cp,
+                                                    int nx, int ny, int nz, int nt, int v, int seg,
+                                                    int segs, size_t n_codes, uint8_t* codes) {
+  const int lane = threadIdx.x & 63;
+  const int nw = nt / 64, np = ny * nz;
+  const size_t id = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (id >= n_codes) return;
+  const int wave = (int)(id % nw);
+  const int sg = (int)((id / nw) % segs);
+  const size_t plane = (id / nw / segs) * (size_t)np;
+  unsigned code = 0u;
+  bool found = false, regular = true;
+  bool none = true, only_free = true, all = true;  // which voxels are tissue
+  for (int j = 0; j < v; ++j) {
+    // the kernel's mapping: odd j runs through the waves in reverse
+    const int f = sg * seg - nz + j * nt + ((j & 1) ? nw - 1 - wave : wave) * 64 + lane;
+    const bool valid = f >= 0 && f < np;
+    bool free = false, ok = true, tissue = false;
+    unsigned c = 0u;
+    if (valid) {
+      const uint8_t* p = lab + plane + f;
+      tissue = (p[0] & kTissue) != 0u;
+      if (!(p[0] & kHeld)) {  // free voxels are never on the outer layer
+        free = true;
+        c = class_of(p[0]);
+        const double k = cp->k[c];
+        ok = cp->k[class_of(p[-1])] == k && cp->k[class_of(p[1])] == k &&
+             cp->k[class_of(p[-nz])] == k && cp->k[class_of(p[nz])] == k &&
+             cp->k[class_of(p[-(ptrdiff_t)np])] == k && cp->k[class_of(p[np])] == k;
+      }
+    }
+    none = none && __ballot(tissue) == 0ull;
+    only_free = only_free && __ballot(tissue != free) == 0ull;
+    all = all && __ballot(valid && !tissue) == 0ull;
+    const unsigned long long m = __ballot(free);
+    if (m == 0ull) continue;
+    if (!found) code = (unsigned)__builtin_amdgcn_readlane((int)c, __ffsll(m) - 1);
+    found = true;
+    regular = regular && __ballot(free && (!ok || c != code)) == 0ull;
+  }
+  regular = regular && (none || only_free || all);
+  code |= none ? 0u : (only_free ? kPairTissueFree : kPairTissueAll);
+  if (lane == 0) codes[id] = (uint8_t)(regular ? code : kPairIrregular);
+}
+
+namespace {
+
+// Work-groups built: {waves, voxels per lane, largest nz}.
+struct PairKind {
+  int waves, v, max_nz;
+};
+constexpr PairKind kPairKinds[] = {{16, 2, 256}, {8, 2, 128}, {8, 1, 128}, {4, 1, 96}};
+
+}  // namespace
+
+bool pair_fits(Grid3 g, int waves, int v, int xc) {
+  for (const PairKind& k : kPairKinds)
+    if (k.waves == waves && k.v == v)
+      return g.nz <= k.max_nz && 2 * g.nz <= 64 * waves && 64 * waves * v - 2 * g.nz >= 64 &&
+             (double)(xc + 6) * g.ny * g.nz * 4.0 < 2147483647.0;
+  return false;
+}
+
+PairShape pair_shape(Grid3 g, int waves, int v, int xc) {
+  PairShape s;
+  s.waves = waves;
+  s.v = v;
+  s.xc = xc;
+  const int np = g.ny * g.nz;
+  const int most = (64 * waves * v - 2 * g.nz) / 32 * 32;
+  s.segs = (np + most - 1) / most;
+  s.seg = ((np + s.segs - 1) / s.segs + 31) / 32 * 32;
+  s.segs = (np + s.seg - 1) / s.seg;
+  s.chunks = (g.nx + xc - 1) / xc;
+  s.nwg = s.segs * s.chunks;
+  return s;
+}
+
+size_t pair_code_bytes(Grid3 g, const PairShape& s) {
+  return (size_t)g.nx * s.segs * s.waves;
+}
+
+hipError_t launch_pair_codes(Grid3 g, const PairShape& s, const uint8_t* lab,
+                             const ClassParams* cp_dev, uint8_t* codes, hipStream_t st) {
+  const size_t n = pair_code_bytes(g, s);
+  hipLaunchKernelGGL(k_pair_codes, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, lab, cp_dev,
+                     g.nx, g.ny, g.nz, 64 * s.waves, s.v, s.seg, s.segs, n, codes);
+  return hipGetLastError();
+}
+
+hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b,
+                            const StepConst& K, PairMode mode, float* hi_mid, int store,
+                            hipStream_t st) {
+  if (!pair_fits(g, s.waves, s.v, s.xc) || !b.codes || (mode != kPairFull && !hi_mid))
+    return hipErrorInvalidValue;
+  if (s.waves == 16 && s.v == 2) return launch_pair_16x2(s, g, b, K, mode, hi_mid, store, st);
+  if (s.waves == 8 && s.v == 2) return launch_pair_8x2(s, g, b, K, mode, hi_mid, store, st);
+  if (s.waves == 8 && s.v == 1) return launch_pair_8x1(s, g, b, K, mode, hi_mid, store, st);
+  if (s.waves == 4 && s.v == 1) return launch_pair_4x1(s, g, b, K, mode, hi_mid, store, st);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace rfa

@@ -1,0 +1,10 @@
+// rfa_pair_8x2.hip -- two-step kernel, 8 waves of 2 voxels per lane, nz <= 128.
+#include "rfa_pair_kernel.h"
+
+namespace rfa {
+
+RFA_PAIR_LAUNCH(launch_pair_8x2) {
+  return launch_store<512, 2, 128>(s, g, b, K, mode, hi_mid, store, st);
+}
+
+}  // namespace rfa

@@ -1,0 +1,535 @@
+// rfa_pair_kernel.h -- two time steps per pass over memory (temporal blocking).
+//
+// A work-group owns a flat segment of a (y, z) plane (seg consecutive voxels;
+// whole rows need no z halo and no lanes are lost to rows that are not a
+// multiple of 64) and marches it along x.  Its footprint is the segment and
+// the nz voxels before and after it: the first step is computed on the
+// footprint, the second on the segment, one plane behind:
+//   iteration x: barrier; loads of plane x + 2 issued;
+//                first step of plane x (x neighbours from registers), its
+//                result and input plane x + 1 (own voxels and nz halo voxels
+//                on either side) go to the LDS buffers last read before
+//                the barrier;
+//                second step of plane x - 1 (its x + 1 neighbour is the plane
+//                just computed), stored.
+// One barrier per plane for two steps; every pass issues the same memory
+// instructions (stores that must not happen get an out-of-range offset), so
+// the compiler's wait counts stay exact.
+//
+// Arithmetic.  Each step is voxel_thermal() / damage_increment() of
+// rfa_device.h with the operands of the one-step kernels, so the states are
+// bitwise theirs.  Two things cost fewer instructions:
+//  * the difference to the x + 1 neighbour is the next plane's difference to
+//    x - 1, negated (exact), so it is formed once;
+//  * most waves lie in one tissue: where all free voxels of a wave's plane
+//    have one class and every neighbour that class's conductivity (its wave
+//    code, made once per tissue by k_pair_codes), the coefficients are
+//    scalars: no neighbour class bytes, no table reads.  Where such a wave
+//    is also cold (|theta| below K.cold everywhere, so that the damage
+//    exponent rounds to 2^0), the transcendentals are skipped.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "rfa_pair.h"
+#include "rfa_tile_common.h"
+
+namespace rfa {
+
+namespace {
+
+using namespace tile;
+
+constexpr int kPairRing = 4;  // register sets: planes x - 1 .. x + 2
+
+template <int NT, int V, int MAXNZ>
+struct PairSmem {
+  static constexpr int P = NT * V;            // footprint
+  static constexpr int CELLS = P + 2 * MAXNZ;
+  float2 cf[3 * kMaxClasses * kMaxClasses];
+  float4 cls[kMaxClasses];
+  float2 in[2][CELLS];    // input planes: footprint q at nz + q
+  float2 mid[2][CELLS];   // first-step planes, footprint q at nz + q (halo cells unused)
+  uint8_t lab[kPairRing][CELLS];
+  float red[3 * NT / 64];
+};
+
+template <int V>
+struct PairPlane {
+  float h[V], l[V], om[V], s[V], pf[V];
+  unsigned b[V];
+  float hh, hl;  // halo element
+  unsigned hb;
+  unsigned code;
+};
+
+// Coefficients of one class, read through the scalar cache (uniform class
+// and constant memory: the tables are written before the launch).
+struct ClassCoef {
+  float2 k[3];
+  float4 c;
+};
+typedef const __attribute__((address_space(4))) float ConstF;
+
+__device__ __forceinline__ ClassCoef class_coef(const Tables* tab, unsigned c) {
+  ConstF* t = (ConstF*)(uintptr_t)tab;
+  ClassCoef r;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    ConstF* k = t + 2 * (a * kMaxClasses * kMaxClasses + c * (kMaxClasses + 1));
+    r.k[a] = make_float2(k[0], k[1]);
+  }
+  ConstF* q = t + offsetof(Tables, cls) / 4 + 4 * c;
+  r.c = make_float4(q[0], q[1], q[2], q[3]);
+  return r;
+}
+
+// min(v, m) for a wave-uniform bound m, without the canonicalisation
+// fminf() adds to each operand; v_min_f32 has fminf's NaN rule.
+__device__ __forceinline__ float min_uniform(float v, float m) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "s"(m), "v"(v));
+  return r;
+}
+
+__device__ __forceinline__ bool lane_of(unsigned long long m) {
+  return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+
+}  // namespace
+
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE>
+__global__ __launch_bounds__(NT, 4) void k_step_pair(
+    StepBuffers b, StepConst K, float* hi_mid, int nx, int ny, int nz, int xc, int seg, int segs,
+    int nwg) {
+  using S = PairSmem<NT, V, MAXNZ>;
+  constexpr bool TEMP = MODE == kPairTemp;
+  constexpr bool KEEP = MODE != kPairFull;
+  constexpr int P = S::P;
+  constexpr int NW = NT / 64;
+  __shared__ S sm;
+  const int wg = remap_xcd(blockIdx.x, nwg);
+  const int sg = wg % segs;
+  const int x0 = (wg / segs) * xc;
+  const int x1 = min(x0 + xc, nx);
+  const int xb = max(x0 - 2, 0);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int np = ny * nz;
+  const unsigned psz = (unsigned)np;
+  const int f0 = sg * seg;
+
+  __amdgpu_buffer_rsrc_t r_hi, r_lo, r_lab, r_src, r_om, r_omo, r_pf, r_hio, r_loo, r_mid, r_code;
+  {
+    const size_t off = (size_t)xb * psz;
+    const size_t rest = (size_t)(nx - xb) * psz;
+    r_hi = make_rsrc(b.hi_in + off, rest * 4);
+    r_lo = make_rsrc(b.lo_in + off, rest * 4);
+    r_lab = make_rsrc(b.lab + off, rest);
+    r_src = make_rsrc(b.src + off, rest * 4);
+    r_om = make_rsrc(b.omega + off, rest * 4);
+    r_omo = PERF ? make_rsrc(b.omega_out + off, rest * 4) : r_om;
+    r_pf = PERF ? make_rsrc(b.perf + off, rest * 4) : r_src;
+    r_hio = make_rsrc(b.hi_out + off, rest * 4);
+    r_loo = make_rsrc(b.lo_out + off, rest * 4);
+    r_mid = KEEP ? make_rsrc(hi_mid + off, rest * 4) : r_hio;
+    r_code = make_rsrc(b.codes + (size_t)xb * segs * NW, (size_t)(nx - xb) * segs * NW);
+  }
+
+  // Own voxels: column in the plane (0, a held corner, outside the grid),
+  // store offsets (out of range unless owned)
+  unsigned col[V], own4[V], own1[V], omc[V];
+  int cell[V];  // LDS cell
+  bool owned[V];
+  unsigned long long ownm[V];  // lanes whose voxel is owned
+  bool wave_owns = false, wave_valid = false;
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    // odd v: waves in reverse order, so that the waves at the footprint's two
+    // ends, which hold only halo voxels, are the same ones and skip the
+    // second step
+    const int q = v * NT + ((v & 1) ? (NT - 64 - (tid & ~63)) + (tid & 63) : tid);
+    const int f = f0 - nz + q;
+    const bool valid = f >= 0 && f < np;
+    cell[v] = nz + q;
+    owned[v] = valid && q >= nz && q < nz + seg;
+    ownm[v] = __ballot(owned[v]);
+    col[v] = valid ? (unsigned)f : 0u;
+    own4[v] = owned[v] ? (unsigned)f * 4u : kOob;
+    own1[v] = owned[v] ? (unsigned)f : kOob;
+    // the damage integral enters the temperature only through the coupling;
+    // without a field it is read on owned voxels alone
+    omc[v] = (PERF ? valid : owned[v]) ? (unsigned)f * 4u : kOob;
+    wave_owns = wave_owns || owned[v];
+    wave_valid = wave_valid || valid;
+  }
+  const bool do_mid = __ballot(wave_valid) != 0ull;  // uniform
+  const bool do_out = __ballot(wave_owns) != 0ull;   // uniform
+
+  // Halo element: the nz voxels before and after the footprint.  Elements
+  // outside the plane stand next to held voxels only: any finite value.
+  const bool has_halo = tid < 2 * nz;
+  int hcell = 0;
+  unsigned hoff = kOob;
+  if (has_halo) {
+    const int f = tid < nz ? f0 - 2 * nz + tid : f0 - 2 * nz + P + tid;
+    hcell = tid < nz ? tid : P + tid;
+    if (f >= 0 && f < np) hoff = (unsigned)f;
+  }
+  const unsigned hoff4 = hoff == kOob ? kOob : hoff * 4u;
+
+  auto plane_of = [&](int x) { return min(max(x, 0), nx - 1) - xb; };  // uniform
+  auto load = [&](int x, PairPlane<V>& q) {
+    const int so1 = plane_of(x) * (int)psz, so4 = so1 * 4;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      q.b[v] = ld_u8(r_lab, col[v], so1);
+      q.h[v] = ld_f32(r_hi, col[v] * 4u, so4);
+      q.l[v] = ld_f32(r_lo, col[v] * 4u, so4);
+    }
+    q.code = ld_u8(r_code, 0u, (plane_of(x) * segs + sg) * NW + wave);
+    q.hh = ld_f32(r_hi, hoff4, so4);
+    q.hl = ld_f32(r_lo, hoff4, so4);
+    q.hb = ld_u8(r_lab, hoff, so1);
+  };
+  // what only the own step of plane x needs: source increments on flagged
+  // voxels (its class bytes are there), damage integral, perfusion factor
+  auto load_s = [&](int x, PairPlane<V>& q) {
+    const int so4 = plane_of(x) * (int)psz * 4;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      q.s[v] = ld_f32(r_src, (q.b[v] & kSource) ? col[v] * 4u : kOob, so4);
+      q.om[v] = TEMP ? 0.0f : ld_f32(r_om, omc[v], so4);
+      if constexpr (PERF) q.pf[v] = ld_f32(r_pf, col[v] * 4u, so4);
+    }
+  };
+
+  PairPlane<V> ring[kPairRing];
+  const int xs = x0 - 1;  // first plane of the first step
+  float din[V], dmid[V];  // difference to the x + 1 neighbour of the plane before
+  {
+    float ph[V], pl[V];
+    const int so4 = plane_of(xs - 1) * (int)psz * 4;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      ph[v] = ld_f32(r_hi, col[v] * 4u, so4);
+      pl[v] = ld_f32(r_lo, col[v] * 4u, so4);
+      sm.lab[3][cell[v]] = (uint8_t)ld_u8(r_lab, col[v], so4 / 4);  // plane xs - 1
+    }
+    load(xs, ring[0]);
+    load(xs + 1, ring[1]);
+    stage_tables(sm.cf, sm.cls, b.tab, b.n_classes, NT);
+    load_s(xs, ring[0]);
+#pragma unroll
+    for (int v = 0; v < V; ++v) din[v] = ff_diff(ring[0].h[v], ring[0].l[v], ph[v], pl[v]);
+  }
+  // first-step results of the plane before: temperature, damage, class byte
+  float mh[V], ml[V], mom[V];
+  unsigned mb[V];
+  unsigned long long mheld[V];  // held lanes of that plane
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    mh[v] = ml[v] = mom[v] = dmid[v] = 0.0f;
+    mb[v] = 0u;
+    mheld[v] = 0ull;
+  }
+#pragma unroll
+  for (int v = 0; v < V; ++v) ring[3].s[v] = 0.0f, ring[3].pf[v] = 1.0f;
+  ring[3].code = 0u;
+
+  Partial acc{0.0f, 0.0f, 0u};
+  unsigned mono = 0u;  // cooling voxels of the wave (scalar)
+  // halo cells of the first-step planes are never written: they enter only
+  // lanes whose results are dropped, but must be finite
+  for (int c = tid; c < 2 * nz; c += NT) {
+    const int e = c < nz ? c : P + c;
+    sm.mid[0][e] = sm.mid[1][e] = make_float2(0.0f, 0.0f);
+  }
+
+  // One step of this lane's V voxels.  t: plane in LDS, h/l/b/om: own
+  // values, dn: difference to x + 1, dp: difference of x - 1 to the plane
+  // (both from registers), tl / tp: class bytes of the plane and of x - 1 in
+  // LDS, bn: of x + 1,
+  // heldm: lanes whose voxel is held, cntm: lanes whose sums count (free ones).
+  auto step = [&](const float2* t, const uint8_t* tl, const uint8_t* tp, unsigned code,
+                  const float (&h)[V],
+                  const float (&l)[V], const unsigned (&lb)[V], float (&om)[V],
+                  const float (&s)[V], const float (&pf)[V], const float (&dn)[V],
+                  const float (&dp)[V], const unsigned (&bn)[V],
+                  const unsigned long long (&heldm)[V], const unsigned long long (&cntm)[V], float (&nh)[V], float (&nl)[V],
+                  unsigned (&nb)[V]) {
+    float f[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      f[v] = 1.0f;
+      if constexpr (PERF) f[v] = pf[v] * __builtin_amdgcn_exp2f(-om[v] * K.decay2);
+    }
+    if (code != kPairIrregular) {
+      const ClassCoef coef = class_coef(b.tab, code & (kMaxClasses - 1));
+      const float2 k[6] = {coef.k[0], coef.k[0], coef.k[1], coef.k[1], coef.k[2], coef.k[2]};
+      bool warm = false, hot = false, falls = false;
+      float incs[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const int c = cell[v];
+        const float2 ym = t[c - nz], yp = t[c + nz], zm = t[c - 1], zp = t[c + 1];
+        const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h[v], l[v]),
+                            ff_diff(yp.x, yp.y, h[v], l[v]), ff_diff(zm.x, zm.y, h[v], l[v]),
+                            ff_diff(zp.x, zp.y, h[v], l[v])};
+        float h2, l2, cond, perf, inc;
+        thermal_update(h[v], l[v], k, coef.c, d, s[v], f[v], h2, l2, cond, perf, inc);
+        const bool held = lane_of(heldm[v]);
+        nh[v] = held ? h[v] : h2;
+        nl[v] = held ? l[v] : l2;
+        if constexpr (DIAG) {
+          // lanes that do not count add 0 times a finite term
+          const float w = lane_of(cntm[v]) ? coef.c.w : 0.0f;
+          acc.perf = __builtin_fmaf(w, perf, acc.perf);
+          acc.bnd = __builtin_fmaf(w, cond, acc.bnd);
+          incs[v] = inc;
+          falls = falls || inc < 0.0f;
+        }
+        warm = warm || !(fabsf(h[v]) < K.cold);
+        hot = hot || nh[v] >= K.thr;
+        nb[v] = lb[v];
+      }
+      if (DIAG && __ballot(falls) != 0ull) {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+          mono += __popcll(__ballot(cools(h[v], incs[v])) & cntm[v]);
+      }
+      if constexpr (!TEMP) {
+        float rate[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) rate[v] = K.dtka;
+        if (__ballot(warm) != 0ull) {
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            const float x = K.c2 * h[v] * __builtin_amdgcn_rcpf(K.tak + h[v]);
+            rate[v] = K.dtka * __builtin_amdgcn_exp2f(min_uniform(x, K.clamp2));
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const unsigned long long tism =
+              (code & kPairTissueAll) ? ~0ull : ((code & kPairTissueFree) ? ~heldm[v] : 0ull);
+          om[v] = lane_of(tism) ? min_uniform(om[v] + rate[v], K.cap) : om[v];
+        }
+        if (__ballot(hot) != 0ull) {
+#pragma unroll
+          for (int v = 0; v < V; ++v) nb[v] = latch(lb[v], nh[v], nl[v], K);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const int c = cell[v];
+        const float2 ym = t[c - nz], yp = t[c + nz], zm = t[c - 1], zp = t[c + 1];
+        const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h[v], l[v]),
+                            ff_diff(yp.x, yp.y, h[v], l[v]), ff_diff(zm.x, zm.y, h[v], l[v]),
+                            ff_diff(zp.x, zp.y, h[v], l[v])};
+        const float2 k[6] = {table_entry(sm.cf, 0, lb[v], tp[c]),
+                             table_entry(sm.cf, 0, lb[v], bn[v]),
+                             table_entry(sm.cf, 1, lb[v], tl[c - nz]),
+                             table_entry(sm.cf, 1, lb[v], tl[c + nz]),
+                             table_entry(sm.cf, 2, lb[v], tl[c - 1]),
+                             table_entry(sm.cf, 2, lb[v], tl[c + 1])};
+        voxel_thermal<DIAG>(h[v], l[v], lane_of(heldm[v]), k, sm.cls[class_of(lb[v])], d, s[v],
+                            f[v], nh[v], nl[v], acc, lane_of(cntm[v]));
+        nb[v] = lb[v];
+        if constexpr (!TEMP) {
+          om[v] = damage_add<true>(om[v], damage_increment(h[v], K), (lb[v] & kTissue) != 0u, K);
+          nb[v] = latch(lb[v], nh[v], nl[v], K);
+        }
+      }
+    }
+  };
+
+  // input plane q (of ring slot SL) to LDS
+  auto publish = [&](auto SL_, const PairPlane<V>& q) {
+    constexpr int SL = decltype(SL_)::value;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      sm.in[SL & 1][cell[v]] = make_float2(q.h[v], q.l[v]);
+      sm.lab[SL][cell[v]] = (uint8_t)q.b[v];
+    }
+    if (has_halo) {
+      sm.in[SL & 1][hcell] = make_float2(q.hh, q.hl);
+      sm.lab[SL][hcell] = (uint8_t)q.hb;
+    }
+  };
+
+  auto iterate = [&](auto SL_, int x) {
+    constexpr int SL = decltype(SL_)::value;   // plane x
+    constexpr int SP = (SL + 3) % kPairRing;   // plane x - 1
+    constexpr int SN = (SL + 1) % kPairRing;   // plane x + 1
+    constexpr int SA = (SL + 2) % kPairRing;   // receives plane x + 2; in LDS still plane x - 2
+    constexpr int BUF = SL & 1;
+    PairPlane<V>& C = ring[SL];
+    PairPlane<V>& N = ring[SN];
+    const PairPlane<V>& B = ring[SP];
+    __syncthreads();
+    load(x + 2, ring[SA]);
+    const unsigned code = __builtin_amdgcn_readfirstlane(C.code);
+    const unsigned pcode = __builtin_amdgcn_readfirstlane(B.code);
+    // first step of plane x
+    float nh[V], nl[V], nom[V], dn[V];
+    unsigned nb[V];
+    unsigned long long held[V], cnt[V];
+    const bool in_chunk = x >= x0 && x < x1;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      dn[v] = ff_diff(N.h[v], N.l[v], C.h[v], C.l[v]);
+      nom[v] = C.om[v];
+      held[v] = __ballot((C.b[v] & kHeld) != 0u);
+      cnt[v] = in_chunk ? ownm[v] & ~held[v] : 0ull;
+      nh[v] = C.h[v];
+      nl[v] = C.l[v];
+      nb[v] = C.b[v];
+    }
+    if (do_mid)
+      step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C.h, C.l, C.b, nom, C.s, C.pf, dn, din, N.b,
+           held, cnt, nh, nl, nb);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      din[v] = dn[v];
+      sm.mid[BUF][cell[v]] = make_float2(nh[v], nl[v]);
+    }
+    publish(std::integral_constant<int, SN>{}, N);
+    load_s(x + 1, N);
+    if constexpr (KEEP) {
+      const int so = plane_of(x) * (int)psz * 4;
+#pragma unroll
+      for (int v = 0; v < V; ++v) st_f32<AUX>(nh[v], r_mid, in_chunk ? own4[v] : kOob, so);
+    }
+    // second step of plane x - 1
+    {
+      float oh[V], ol[V], oom[V], dm[V];
+      unsigned ob[V], lb1[V];
+      const bool out = x > x0;  // uniform: plane x - 1 is in the chunk
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        dm[v] = ff_diff(nh[v], nl[v], mh[v], ml[v]);
+        oom[v] = mom[v];
+        oh[v] = mh[v];
+        ol[v] = ml[v];
+        ob[v] = mb[v];
+        cnt[v] = ownm[v] & ~mheld[v];
+        lb1[v] = kOob;
+      }
+      if (do_out && out) {
+        step(sm.mid[BUF ^ 1], sm.lab[SP], sm.lab[SA], pcode, mh, ml, mb, oom, B.s, B.pf, dm, dmid,
+             C.b, mheld, cnt, oh, ol, ob);
+        if constexpr (!TEMP) {
+          // class bytes are stored where a latch flipped in either step
+          bool latched = false;
+#pragma unroll
+          for (int v = 0; v < V; ++v) latched = latched || (ob[v] & kLatch);
+          if (__ballot(latched) != 0ull) {
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+              lb1[v] = ob[v] != sm.lab[SP][cell[v]] ? own1[v] : kOob;
+          }
+        }
+      }
+      const int so = plane_of(x - 1) * (int)psz;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const unsigned v4 = out ? own4[v] : kOob;
+        st_f32<AUX>(oh[v], r_hio, v4, so * 4);
+        st_f32<AUX>(ol[v], r_loo, v4, so * 4);
+        if constexpr (!TEMP) {
+          st_f32<AUX>(oom[v], r_omo, v4, so * 4);
+          st_u8<AUX>(ob[v], r_lab, lb1[v], so);
+        }
+        dmid[v] = dm[v];
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      mh[v] = nh[v];
+      ml[v] = nl[v];
+      mom[v] = nom[v];
+      mb[v] = nb[v];
+      mheld[v] = held[v];
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  static_assert(kPairRing == 4, "unrolled for a ring of four planes");
+  publish(I0{}, ring[0]);
+  for (int x = xs;; x += kPairRing) {
+    iterate(I0{}, x);
+    if (x + 1 > x1) break;
+    iterate(I1{}, x + 1);
+    if (x + 2 > x1) break;
+    iterate(I2{}, x + 2);
+    if (x + 3 > x1) break;
+    iterate(I3{}, x + 3);
+    if (x + 4 > x1) break;
+  }
+  if (DIAG && (tid & 63) == 0) acc.mono += mono;
+  if constexpr (DIAG) write_partials(acc, sm.red, NW, b.partials + (size_t)wg * 3);
+}
+
+
+namespace {
+
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX>
+hipError_t launch_mode(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K,
+                       PairMode mode, float* hi_mid, hipStream_t st) {
+  const dim3 grid(s.nwg), block(NT);
+  switch (mode) {
+    case kPairFull:
+      hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, DIAG, AUX, kPairFull>), grid, block, 0,
+                         st, b, K, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
+      break;
+    case kPairKeep:
+      if constexpr (!DIAG)
+        hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, false, AUX, kPairKeep>), grid, block,
+                           0, st, b, K, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
+      else
+        return hipErrorInvalidValue;
+      break;
+    case kPairTemp:
+      if constexpr (!DIAG)
+        hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, false, AUX, kPairTemp>), grid, block,
+                           0, st, b, K, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
+      else
+        return hipErrorInvalidValue;
+      break;
+  }
+  return hipGetLastError();
+}
+
+template <int NT, int V, int MAXNZ, int AUX>
+hipError_t launch_kind(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K,
+                       PairMode mode, float* hi_mid, hipStream_t st) {
+  if (b.perf)
+    return b.partials
+               ? launch_mode<NT, V, MAXNZ, true, true, AUX>(s, g, b, K, mode, hi_mid, st)
+               : launch_mode<NT, V, MAXNZ, true, false, AUX>(s, g, b, K, mode, hi_mid, st);
+  return b.partials ? launch_mode<NT, V, MAXNZ, false, true, AUX>(s, g, b, K, mode, hi_mid, st)
+                    : launch_mode<NT, V, MAXNZ, false, false, AUX>(s, g, b, K, mode, hi_mid, st);
+}
+
+template <int NT, int V, int MAXNZ>
+hipError_t launch_store(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K,
+                        PairMode mode, float* hi_mid, int store, hipStream_t st) {
+  switch (store) {
+    case kPolicyThrough:
+      return launch_kind<NT, V, MAXNZ, kStoreThrough>(s, g, b, K, mode, hi_mid, st);
+    case kPolicyStream:
+      return launch_kind<NT, V, MAXNZ, kStoreStream>(s, g, b, K, mode, hi_mid, st);
+    default:
+      return launch_kind<NT, V, MAXNZ, kStoreBack>(s, g, b, K, mode, hi_mid, st);
+  }
+}
+
+}  // namespace
+
+}  // namespace rfa

@@ -6,6 +6,7 @@
 
 #include "../../include/rfa.h"
 #include "rfa_kernels.h"
+#include "rfa_pair.h"
 #include "rfa_tiled.h"
 
 namespace rfa {
@@ -21,6 +22,8 @@ struct StepPlan {
   int xc = 1;      // x planes per work-group (tiled)
   int nwg = 0;     // work-groups per launch (stride of the partials)
   int zv = 1;      // consecutive z voxels per lane (tiled, one step per launch)
+  int pv = 0;      // depth 2: voxels per lane of the pair kernel (its work-groups
+                   // have ty waves), 0 for the 2.5-D two-step kernel
   int store = 0;   // StorePolicy of the step launches
   // one-step plan for step counts not divisible by depth (equal to the
   // plan itself when depth == 1)
@@ -31,6 +34,7 @@ StepPlan plan_naive(Grid3 g);
 StepPlan plan_tiled(Grid3 g, int ty, int xc);
 StepPlan plan_tiled2(Grid3 g, int ty, int xc);
 StepPlan plan_wide(Grid3 g, int zv, int ty, int xc);
+StepPlan plan_pair(Grid3 g, int waves, int v, int xc);
 // The one-step plan that accompanies a plan.
 StepPlan plan_one(const StepPlan& p);
 // Heuristic plan from the options (kernel, depth, tile_y, tile_x, z_vec,
@@ -48,26 +52,32 @@ struct StepState {
   int* cur;         // index of the current image
   uint8_t* lab;
   const float* src;
-  float* om;
+  float** om;
   const float* perf;
   const Tables* tab;
   int n_classes;
-  // Trajectory mode (traj not null, one-step plans only): the hi image of
+  // Trajectory mode (traj not null; one-step and pair plans): the hi image of
   // step *traj_t is read from traj[*traj_t] and written to traj[*traj_t + 1]
   // (images of traj_n voxels); lo keeps ping-ponging in lo[2].
   float* traj = nullptr;
   int* traj_t = nullptr;
   size_t traj_n = 0;
+  const uint8_t* codes = nullptr;  // wave codes of a pair plan's shape
+  // second damage image (damage-coupled grids on a pair plan, whose launches
+  // read the damage integral of neighbouring work-groups' voxels): a launch
+  // reads *om and writes *om_alt, then the two are swapped
+  float** om_alt = nullptr;
 };
 
 // One launch of the plan (plan.depth steps) from b's input to its output image.
 hipError_t launch_plan(Grid3 g, const StepPlan& plan, const StepBuffers& b, const StepConst& K,
                        hipStream_t st);
-// One step of a one-step plan where only the temperature must come out
-// right (no damage-coupled perfusion): the wide kernel then skips the damage
-// integral and the class bytes; other plans run their full step.
+// One launch where only the temperature must come out right (no
+// damage-coupled perfusion): the wide and pair kernels then skip the damage
+// integral and the class bytes; other plans run their full step.  Pair plans
+// also write the hi image between their two steps to hi_mid.
 hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuffers& b,
-                                   const StepConst& K, hipStream_t st);
+                                   float* hi_mid, const StepConst& K, hipStream_t st);
 
 // Advance n_steps: n_steps / depth launches of the plan, then the rest with
 // its one-step plan.  partials (nullable) has room for `slots` launches and

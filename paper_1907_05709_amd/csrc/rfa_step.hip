@@ -94,6 +94,18 @@ StepPlan plan_tiled2(Grid3 g, int ty, int xc) {
   return with_one(with_store(p, g), plan_default(g, kStepTiled, 1, 0, 0, 0));
 }
 
+StepPlan plan_pair(Grid3 g, int waves, int v, int xc) {
+  const PairShape s = pair_shape(g, waves, v, xc);
+  StepPlan p;
+  p.kind = kStepTiled;
+  p.depth = 2;
+  p.ty = waves;
+  p.xc = xc;
+  p.nwg = s.nwg;
+  p.pv = v;
+  return with_one(with_store(p, g), plan_default(g, kStepTiled, 1, 0, 0, 0));
+}
+
 StepPlan plan_one(const StepPlan& p) {
   StepPlan o = p;
   o.kind = p.one_kind;
@@ -102,12 +114,60 @@ StepPlan plan_one(const StepPlan& p) {
   o.xc = p.one_xc;
   o.nwg = p.one_nwg;
   o.zv = p.one_zv;
+  o.pv = 0;
   return o;
 }
 
 namespace {
+
+// Two-step plan with the least estimated time, waves / v / tile_x as asked
+// (0: any); false if no work-group fits the grid.
+//
+// A launch costs about 5 us plus, per round of resident work-groups, xc + 2
+// plane iterations (the first step runs on one plane more at either end of
+// a chunk).  An iteration's time grows with the work-groups m that share a
+// compute unit, a + b m; a and b fitted to 100-step runs of 11 grids from
+// 32^3 to 256^3, every kind and 16 chunk lengths (the fit holds to 10 %
+// where it decides).  It picks e.g. 4 waves x 1 voxel at 32^3 (3.4 us a step;
+// one-step kernel 6.0), 8 x 1 at 64^3 (5.0; 6.4), 8 x 2 at 128^3 (12.8;
+// 13.3), 16 x 2 at 160^3 (19.4; 33.7) and 256^3 (68; 80).
+bool best_pair(Grid3 g, int waves, int v, int tile_x, StepPlan* out) {
+  struct Kind {
+    int waves, v, per_cu;  // per_cu: work-groups a compute unit holds
+    double a, b;           // us per iteration
+  };
+  constexpr Kind kinds[] = {{16, 2, 1, 1.0, 1.8},
+                            {8, 2, 2, 1.0, 0.8},
+                            {8, 1, 2, 0.5, 0.45},
+                            {4, 1, 5, 0.35, 0.28}};
+  constexpr int kCu = 256;
+  double best = 1e300;
+  for (const Kind& k : kinds) {
+    if ((waves && waves != k.waves) || (v && v != k.v)) continue;
+    const int lo = tile_x ? std::min(tile_x, g.nx) : 1;
+    const int hi = tile_x ? lo : std::min(g.nx, 64);
+    for (int xc = lo; xc <= hi; ++xc) {
+      if (!pair_fits(g, k.waves, k.v, xc)) continue;
+      const int nwg = pair_shape(g, k.waves, k.v, xc).nwg;
+      const int slots = kCu * k.per_cu, rest = nwg % slots;
+      double us = 5.0 + (nwg / slots) * (xc + 2) * (k.a + k.b * k.per_cu);
+      if (rest) us += (xc + 2) * (k.a + k.b * ((rest + kCu - 1) / kCu));
+      if (us < best) {
+        best = us;
+        *out = plan_pair(g, k.waves, k.v, xc);
+      }
+    }
+  }
+  return best < 1e300;
+}
+
 StepPlan default_shape(Grid3 g, int kernel, int depth, int tile_y, int tile_x, int zv) {
   if (kernel == kStepNaive || !tiled_fits(g, 4)) return plan_naive(g);
+  // two steps per launch wherever a work-group holds the rows (nz <= 256),
+  // unless the options ask for one step or for a shape of its kernels
+  StepPlan pair;
+  if (depth == 2 && best_pair(g, tile_y, 0, tile_x, &pair)) return pair;
+  if (depth == 0 && !tile_y && !tile_x && !zv && best_pair(g, 0, 0, 0, &pair)) return pair;
   // automatic: four z voxels per lane once a tile row spans 256 voxels, two
   // (with 8-row tiles) from 96
   if (zv == 0 && depth != 2 && g.nz >= 256 && g.nz % 4 == 0) zv = 4;
@@ -165,6 +225,18 @@ int plan_candidates(Grid3 g, int max_depth, StepPlan* out, int max_out) {
         out[n++] = plan_wide(g, zv, ty, std::min(xc, g.nx));
       }
   if (max_depth < 2) return n;
+  for (int waves : {16, 8, 4})
+    for (int v : {2, 1})
+      for (int xc : {2, 4, 6, 8, 12, 20, 43}) {
+        if (n >= max_out) return n;
+        if (xc <= g.nx && pair_fits(g, waves, v, xc)) out[n++] = plan_pair(g, waves, v, xc);
+      }
+  StepPlan pair;
+  if (n < max_out && best_pair(g, 0, 0, 0, &pair)) {
+    out[n++] = pair;
+    return n;
+  }
+  // grids without a pair plan: the 2.5-D two-step kernel
   const int tys2[] = {8, 16};
   const int xcs2[] = {6, 14, 30, 62};  // 2 mod 4: no pass outside the chunk
   for (int ty : tys2)
@@ -181,12 +253,18 @@ int plan_max_wg(Grid3 g) {
   const int tys[] = {4, 8, 16};
   for (int ty : tys) m = std::max(m, tiled_shape(g, ty, 1).nwg);
   m = std::max(m, tiled2_shape(g, 8, 1).nwg);
+  for (int waves : {4, 8, 16})
+    for (int v : {1, 2})
+      if (pair_fits(g, waves, v, 1)) m = std::max(m, pair_shape(g, waves, v, 1).nwg);
   return m;
 }
 
 hipError_t launch_plan(Grid3 g, const StepPlan& plan, const StepBuffers& b, const StepConst& K,
                        hipStream_t st) {
   if (plan.kind == kStepNaive) return launch_step_naive(g, b, K, st);
+  if (plan.pv)
+    return launch_step_pair(pair_shape(g, plan.ty, plan.pv, plan.xc), g, b, K, kPairFull, nullptr,
+                            plan.store, st);
   if (plan.depth == 2)
     return launch_step_tiled2(tiled2_shape(g, plan.ty, plan.xc), g, b, K, plan.store, st);
   if (plan.zv > 1)
@@ -196,7 +274,10 @@ hipError_t launch_plan(Grid3 g, const StepPlan& plan, const StepBuffers& b, cons
 }
 
 hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuffers& b,
-                                   const StepConst& K, hipStream_t st) {
+                                   float* hi_mid, const StepConst& K, hipStream_t st) {
+  if (plan.pv)
+    return launch_step_pair(pair_shape(g, plan.ty, plan.pv, plan.xc), g, b, K, kPairTemp, hi_mid,
+                            plan.store, st);
   if (plan.kind != kStepNaive && plan.depth == 1 && plan.zv > 1)
     return launch_step_wide_temperature(plan.zv, wide_shape(g, plan.zv, plan.ty, plan.xc), g, b,
                                         K, plan.store, st);
@@ -206,46 +287,57 @@ hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuff
 rfa_status run_steps(Grid3 g, const StepPlan& plan, StepState& s, const StepConst& K,
                      int n_steps, float* partials, int slots, double* dacc, hipEvent_t* events,
                      int period, int* n_timed, int* n_launches, hipStream_t st) {
-  if (s.traj && plan.depth != 1) return RFA_ERR_ARG;
-  auto buffers = [&]() {
-    StepBuffers b;
+  if (s.traj && plan.depth != 1 && !plan.pv) return RFA_ERR_ARG;
+  // one launch of p with the current images, which it then swaps
+  auto launch = [&](const StepPlan& p, float* part) -> hipError_t {
+    StepBuffers b{};
     b.hi_in = s.hi[*s.cur];
     b.lo_in = s.lo[*s.cur];
     b.hi_out = s.hi[1 - *s.cur];
     b.lo_out = s.lo[1 - *s.cur];
+    float* mid = nullptr;
     if (s.traj) {
       float* h = s.traj + (size_t)*s.traj_t * s.traj_n;
+      mid = h + s.traj_n;
       b.hi_in = h;
-      b.hi_out = h + s.traj_n;
+      b.hi_out = h + p.depth * s.traj_n;
     }
     b.lab = s.lab;
     b.src = s.src;
-    b.omega = s.om;
+    b.omega = *s.om;
+    const bool swap_om = p.pv && s.om_alt;
+    b.omega_out = swap_om ? *s.om_alt : *s.om;
     b.perf = s.perf;
     b.tab = s.tab;
     b.n_classes = s.n_classes;
-    b.partials = nullptr;
-    return b;
+    b.codes = s.codes;
+    b.partials = part;
+    const hipError_t e =
+        p.pv && s.traj ? launch_step_pair(pair_shape(g, p.ty, p.pv, p.xc), g, b, K, kPairKeep, mid,
+                                          p.store, st)
+                       : launch_plan(g, p, b, K, st);
+    if (e != hipSuccess) return e;
+    if (s.traj) *s.traj_t += p.depth;
+    *s.cur = 1 - *s.cur;
+    if (swap_om) std::swap(*s.om, *s.om_alt);
+    return hipSuccess;
   };
   const int n_main = n_steps / plan.depth;
   const int n_rest = n_steps - n_main * plan.depth;
   int pending = 0;
   int timed = 0;
   for (int n = 0; n < n_main; ++n) {
-    StepBuffers b = buffers();
-    b.partials = partials ? partials + (size_t)pending * plan.nwg * 3 : nullptr;
     // Blocks of `period` consecutive launches are bracketed by one event pair
     // (the diagnostic reductions fall between blocks, never inside one).
     const bool open = events && (n % period) == 0;
     const bool close = events && ((n % period) == period - 1 || n == n_main - 1);
     if (open && hipEventRecord(events[2 * timed], st) != hipSuccess) return RFA_ERR_HIP;
-    if (launch_plan(g, plan, b, K, st) != hipSuccess) return RFA_ERR_HIP;
-    if (s.traj) ++*s.traj_t;
+    if (launch(plan, partials ? partials + (size_t)pending * plan.nwg * 3 : nullptr) != hipSuccess)
+      return RFA_ERR_HIP;
     if (close) {
       if (hipEventRecord(events[2 * timed + 1], st) != hipSuccess) return RFA_ERR_HIP;
       ++timed;
     }
-    *s.cur = 1 - *s.cur;
     if (partials && ++pending == slots) {
       if (launch_reduce_partials(partials, pending, plan.nwg, dacc, st) != hipSuccess)
         return RFA_ERR_HIP;
@@ -257,10 +349,7 @@ rfa_status run_steps(Grid3 g, const StepPlan& plan, StepState& s, const StepCons
       return RFA_ERR_HIP;
   const StepPlan one = plan_one(plan);
   for (int r = 0; r < n_rest; ++r) {
-    StepBuffers b = buffers();
-    b.partials = partials;
-    if (launch_plan(g, one, b, K, st) != hipSuccess) return RFA_ERR_HIP;
-    *s.cur = 1 - *s.cur;
+    if (launch(one, partials) != hipSuccess) return RFA_ERR_HIP;
     if (partials && launch_reduce_partials(partials, 1, one.nwg, dacc, st) != hipSuccess)
       return RFA_ERR_HIP;
   }

@@ -1,0 +1,103 @@
+"""The two-step kernel of the automatic plans against the one-thread-per-voxel
+reference, bit for bit: every work-group kind at the edges of its segments
+and chunks, tissue in regions (waves with scalar coefficients) and at random
+(table look-ups), every form of perfusion, diagnostics on and off, odd step
+counts, and its trajectory forms inside the checkpointed adjoint."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_1907_05709_amd import rfa
+from paper_1907_05709_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(kind, shape, seed):
+    if kind == "random":
+        return W.random_tissue_case(seed, shape=shape, n_classes=5, n_tines=2)
+    rng = np.random.default_rng(seed)
+    sp = (1e-3, 0.9e-3, 1.1e-3)
+    labels, _ = W.tissue_labels(rng, shape, sp, (0.0, 0.0, 0.0), 3e-3, 2)
+    tissue = W.standard_tissue()
+    needle = W.straight_needle([0.0, 0.0, 2e-3], [0.2, 0.1, 1.0], 4e-3, 25.0, 1e-3)
+    if kind == "tissue_everywhere":  # held voxels that are tissue, metabolic heat
+        labels = np.ones_like(labels)
+        tissue[1] = dataclasses.replace(tissue[1], q_met=1e4)
+    if kind == "held_tissue":        # a hot held block of a tissue class inside
+        tissue.append(W.Tissue(0.52, 1060.0, 3600.0, 0.0, 0.0, 70.0, fixed=1, tissue=1))
+        c = [n // 2 for n in shape]
+        labels[c[0] - 1:c[0] + 1, c[1] - 1:c[1] + 1, c[2] - 1:c[2] + 1] = 4
+    return W.Case(kind, shape, sp, labels, tissue, needle, 0.04, 0, seed)
+
+
+def _perfusion(g, form, shape):
+    if form == "field":
+        g.set_perfusion(np.random.default_rng(3).uniform(0.5, 2.0, shape).astype(np.float32))
+    if form == "coupled":
+        g.set_perfusion_decay(True)
+
+
+# automatic plans: 4 waves (32^3, thin), 8 x 1 (64-row planes), 8 x 2 (128),
+# 16 x 2 (long rows); explicit ones: chunks of one plane, of the whole grid
+@pytest.mark.parametrize("shape, kind, form, kw", [
+    ((32, 32, 32), "regions", "class", {}),
+    ((7, 12, 96), "random", "field", {}),
+    ((60, 50, 70), "regions", "coupled", {}),
+    ((60, 51, 64), "held_tissue", "class", {}),
+    ((61, 64, 97), "tissue_everywhere", "class", {}),
+    ((40, 128, 128), "regions", "field", {}),
+    ((24, 70, 256), "regions", "coupled", {}),
+    ((13, 21, 255), "random", "class", {}),
+    ((5, 6, 7), "random", "class", {}),
+    ((9, 40, 60), "regions", "class", dict(depth=2, tile_y=8, tile_x=1)),
+    ((21, 40, 200), "held_tissue", "field", dict(depth=2, tile_y=16, tile_x=64)),
+])
+def test_pair_kernel_bitwise_equals_reference(shape, kind, form, kw):
+    case = _case(kind, shape, 5)
+    grids = [rfa.Grid(case.shape, case.spacing, kernel=1), rfa.Grid(case.shape, case.spacing, **kw)]
+    for g in grids:
+        g.load_case(case)
+        _perfusion(g, form, shape)
+    assert grids[1].plan()["depth"] == 2
+    dt = 0.9 * min(case.dt, grids[0].dt_max())
+    for n, diag in ((1, True), (2, True), (7, False), (60, True)):
+        d = [g.step(n, dt, diag=diag) for g in grids]
+        for a, b in zip(grids[0].raw_state(), grids[1].raw_state()):
+            assert np.array_equal(a, b), n
+        (m1, o1, _), (m2, o2, _) = (g.damage() for g in grids)
+        assert np.array_equal(m1, m2) and np.array_equal(o1, o2), n
+        if diag:
+            assert d[0]["mono_violations"] == d[1]["mono_violations"]
+            scale = sum(abs(d[0][k]) for k in ("injected_J", "perfusion_J", "boundary_J"))
+            for k in ("perfusion_J", "boundary_J"):
+                # FP32 sums of up to 2^20 terms in another order
+                assert abs(d[0][k] - d[1][k]) <= 1e-6 * scale, k
+    if kind != "random":
+        assert m1.max() > 0
+    for g in grids:
+        g.close()
+
+
+@pytest.mark.parametrize("shape, every, steps", [((24, 30, 33), 5, 23), ((20, 40, 150), 8, 24),
+                                                 ((20, 40, 150), 0, 9)])
+def test_adjoint_over_pair_steps_equals_reference(shape, every, steps):
+    """Kept trajectories, checkpoints and recomputed segments (odd and even
+    lengths) of the two-step kernel give the reference kernels' gradients."""
+    case = _case("regions", shape, 9)
+    out = []
+    for kw in (dict(kernel=1), {}):
+        g = rfa.Grid(case.shape, case.spacing, **kw)
+        g.load_case(case)
+        g.set_perfusion_bspline(np.linspace(-0.3, 0.3, 125, dtype=np.float32).reshape(5, 5, 5))
+        g.forward_checkpointed(steps, 0.04, every)
+        w = np.random.default_rng(4).uniform(0.5, 1.0, shape).astype(np.float32)
+        out.append((g.temperature(), g.omega()) + g.adjoint(w, 1, 5, want_dperf=True))
+        again = g.adjoint(w, 1, 5, want_dperf=True)
+        for a, b in zip(out[-1][2:], again):
+            assert np.array_equal(a, b)
+        g.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    assert np.abs(out[0][2]).max() > 0
