@@ -106,11 +106,13 @@ typedef struct {
   void* stream;       /* hipStream_t for all device work (NULL)            */
   int inputs_on_device; /* bulk voxel arrays are device pointers (0)        */
   int depth;          /* steps per kernel launch: 1, or 2 = temporal
-                         blocking (tiled kernel, tile_y 8 or 16; two steps
-                         per pass over memory, bitwise equal to two single
-                         steps; odd step counts end with a single step;
-                         one step per launch while damage-coupled perfusion
-                         is on); 0 = automatic (0)                           */
+                         blocking (tiled kernel, tile_y 8 or 16 wavefronts
+                         per work-group; two steps per pass over memory,
+                         bitwise equal to two single steps; odd step counts
+                         end with a single step; grids with nz > 256 take one
+                         step per launch while damage-coupled perfusion is
+                         on); 0 = automatic: 2 where nz <= 256 and no shape of
+                         the one-step kernels is asked for (0)               */
   int kernel;         /* 0 automatic, 1 reference one-thread-per-voxel,
                          2 tiled 2.5-D (0)                                   */
   int tile_y;         /* tiled kernel: y rows per work-group (4, 8, 16);
@@ -377,11 +379,15 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
 /* ---- Batched stepping of many grids (planning sweeps) ---------------------
  * A batch advances n independent grids -- each with its own shape, spacing,
  * tissue, needle and time step -- by the same number of steps.  Consecutive
- * grids are grouped up to a voxel budget (by default 8 Mi voxels, whose
- * stepping working set fits the 256 MB last-level cache); a group runs
- * all its steps before the next group starts, one kernel launch per step
- * over the concatenated work-item lists of its grids (two when some grids
- * carry a perfusion field and others do not).  The whole launch sequence of an
+ * grids are grouped up to a voxel budget; a group runs all its steps before
+ * the next group starts, over the concatenated work-item lists of its grids
+ * (one launch, or two when some grids carry a perfusion field and others do
+ * not).  By default a launch takes two steps (groups of at most 64 Mi
+ * voxels; an odd step count ends with a launch of one); a batch with a grid
+ * of nz > 256 or of damage-coupled perfusion, or with a launch shape set by
+ * rfa_batch_set_plan, takes one step per launch (groups of at most 8 Mi
+ * voxels by default, whose stepping working set fits the 256 MB last-level
+ * cache).  The whole launch sequence of an
  * rfa_batch_step call is captured once in a hipGraph and replayed on later
  * calls with the same step count.  The per-voxel
  * arithmetic is that of rfa_step (Eq. (CUDAbioheat3d), Alg. 1 and 2), so a
@@ -408,34 +414,32 @@ enum {
                           (y, z) plane; needs nz <= 32 * tile_y in every grid */
 };
 
-/* Launch shape of the batch kernel (default: RFA_BATCH_FLAT with 8 waves
- * when every grid has nz <= 256, else RFA_BATCH_TILES with 4 rows; 8 x
- * planes per work item; groups of at most 8 Mi voxels): layout (0: keep,
- * else RFA_BATCH_*),
+/* Launch shape of the one-step batch kernel (default: RFA_BATCH_FLAT with 8
+ * waves when every grid has nz <= 256, else RFA_BATCH_TILES with 4 rows; 8 x
+ * planes per work item): layout (0: keep, else RFA_BATCH_*),
  * tile_y waves per work-group (tiles: 4 or 8 rows; flat: 8 or 16; 0 keeps
  * the current value, or takes 4 / 8 when the layout changes), tile_x
  * planes per work item, workgroups > 0 persistent work-groups per launch
  * that walk the work list (0, the default: one work-group per work item),
  * group_voxels the grouping budget (0: all grids in one group, i.e.
- * lockstep; < 0: keep the current one).  On error the plan is unchanged.
- * Drops cached graphs. */
+ * lockstep; < 0: keep the current one).  Any of layout, tile_y, tile_x and
+ * workgroups makes the batch take one step per launch in that shape.  On
+ * error the plan is unchanged.  Drops cached graphs. */
 rfa_status rfa_batch_set_plan(rfa_batch b, int layout, int tile_y, int tile_x, int workgroups,
                               long long group_voxels);
 
-/* Current launch shape: layout, tile_y, tile_x, work items per step (all
- * groups), work-groups launched per step of all grids, number of groups
- * (each pointer nullable). */
+/* Current launch shape of the one-step kernel: layout, tile_y, tile_x, work
+ * items per step (all groups), work-groups launched per step of all grids;
+ * number of groups (each pointer nullable). */
 rfa_status rfa_batch_get_plan(rfa_batch b, int* layout, int* tile_y, int* tile_x, int* items,
                               int* workgroups, int* groups);
 
-/* Pick the batch's launch shape by timing: work-item layouts, tile rows and
- * x planes per item at the default grouping, then grouping budgets for the
+/* Pick the batch's launch shape by timing: two steps per launch and the
+ * one-step layouts, tile rows and x planes per item, then grouping budgets for the
  * fastest shape (0 included: lockstep), each over reps steps of all grids
  * (one untimed replay first); keeps the fastest.  The grids' states are
  * snapshotted in device memory (13 bytes per voxel) and restored, so the
- * batch and its grids are left exactly as they were apart from the plan.
- * Batch work items take one step per launch; see rfa_tune for the
- * single-grid temporal blocking depth. */
+ * batch and its grids are left exactly as they were apart from the plan. */
 rfa_status rfa_batch_tune(rfa_batch b, int reps);
 
 /* Device time of the last rfa_batch_step's graph, milliseconds (HIP events

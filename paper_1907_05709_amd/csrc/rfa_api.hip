@@ -61,6 +61,11 @@ constexpr size_t kFieldBudget = size_t(16) << 30;  // bytes of kept per-tine sou
 // class bytes, source, damage: ~29 B per voxel, 8 Mi voxels ~ 243 MB) stays
 // within the 256 MB last-level cache while its steps run.
 constexpr long long kBatchGroupVoxels = 8ll << 20;
+// The same for the two-step kernel, which moves half the bytes per step and
+// is bound by its arithmetic: there a group only has to be long enough to
+// fill the chip (64-grid sweep, 101 Mi voxels: 235 GVox/s with 8 Mi voxels a
+// group, 250 with 16, 266 with 64).
+constexpr long long kPairGroupVoxels = 64ll << 20;
 constexpr int kTimedBatch = 1024;  // launches between event read-backs
 constexpr double kTBodyK = 310.15;
 constexpr double kExponentClamp = 80.0;
@@ -153,6 +158,7 @@ struct rfa_grid_s {
   uint8_t* codes = nullptr;
   size_t codes_cap = 0;
   int codes_waves = 0, codes_v = 0;  // 0: none
+  int tissue_version = 0;            // bumped by rfa_set_tissue
 
   // step-kernel timing
   std::vector<hipEvent_t> events;
@@ -253,7 +259,9 @@ void split(double v, float& hi, float& lo) {
   lo = (float)(v - (double)hi);
 }
 
-// Per-dt coefficient tables (FP64 -> float-float).
+StepConst step_const(rfa_grid g, double dt);
+
+// Per-dt coefficient tables (FP64 -> float-float) and step constants.
 void build_tables(rfa_grid g, double dt) {
   Tables& T = g->tab_host;
   std::memset(&T, 0, sizeof T);
@@ -274,6 +282,7 @@ void build_tables(rfa_grid g, double dt) {
     split(dt * ta.h_perf / rc, bh, bl);
     T.cls[a] = make_float4(bh, bl, (float)(dt * ta.q_met / rc), (float)(rc * vol));
   }
+  T.K = step_const(g, dt);
 }
 
 StepConst step_const(rfa_grid g, double dt) {
@@ -466,6 +475,19 @@ rfa_status ensure_side_stream(rfa_grid g) {
   if (!g->side) HIP_TRY(hipStreamCreateWithFlags(&g->side, hipStreamNonBlocking));
   for (hipEvent_t& e : g->side_ev)
     if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  return RFA_OK;
+}
+
+// Room for the diagnostic partials of launches of nwg work-groups.
+rfa_status ensure_partials(rfa_grid g, int nwg) {
+  const size_t need = (size_t)nwg * 3 * kPartialSlots;
+  if (need <= g->partial_floats) return RFA_OK;
+  float* p = nullptr;
+  if (rfa_status s = dmalloc(&p, need); s != RFA_OK) return s;
+  HIP_TRY(hipStreamSynchronize(g->st));
+  (void)hipFree(g->partials);
+  g->partials = p;
+  g->partial_floats = need;
   return RFA_OK;
 }
 
@@ -755,7 +777,7 @@ rfa_status rfa_create_grid(int nx, int ny, int nz, double dx, double dy, double 
   }
   const size_t n = g->g.n();
   g->plan = plan_default(g->g, o.kernel, o.depth, o.tile_y, o.tile_x, o.z_vec, o.store_policy);
-  const size_t nwg = (size_t)plan_max_wg(g->g);
+  const size_t nwg = (size_t)std::max(plan_max_wg(g->g), g->plan.nwg);
   g->partial_floats = nwg * 3 * kPartialSlots;
   g->red_doubles = 4 * 1024 + 64;
   rfa_status s = RFA_OK;
@@ -843,6 +865,7 @@ rfa_status rfa_set_tissue(rfa_grid g, const uint8_t* labels, const rfa_tissue* t
   g->cp = cp;
   g->n_classes = n_classes;
   g->codes_waves = 0;
+  ++g->tissue_version;
   std::memcpy(g->table, table, n_classes * sizeof(rfa_tissue));
   g->has_tissue = true;
   g->cur = 0;
@@ -947,7 +970,10 @@ rfa_status rfa_set_perfusion_decay(rfa_grid g, int enable) {
     rfa_status s = unit_perf(g);
     if (s != RFA_OK) return s;
   }
-  if ((bool)enable != g->perf_decay) ++g->version;
+  if ((bool)enable != g->perf_decay) {
+    ++g->version;
+    g->tab_dt = -1.0;  // the tables carry the coupling constant
+  }
   g->perf_decay = enable != 0;
   return RFA_OK;
 }
@@ -1334,6 +1360,7 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   const TuneKey key{g->g.nx, g->g.ny, g->g.nz, g->perf ? 1 : 0, g->opt.depth == 1 ? 1 : 0};
   for (auto& kv : g_tuned)
     if (kv.first == key) {
+      if (rfa_status sp = ensure_partials(g, kv.second.nwg); sp != RFA_OK) return sp;
       g->plan = kv.second;
       return RFA_OK;
     }
@@ -1356,6 +1383,13 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   if ((s = ensure_events(g, 2)) != RFA_OK) { (void)hipFree(om2); (void)hipFree(lab2); return s; }
   StepPlan cand[128];
   const int nc = plan_candidates(g->g, g->opt.depth == 1 ? 1 : kMaxDepth, cand, 128);
+  int most = 0;
+  for (int c = 0; c < nc; ++c) most = std::max(most, cand[c].nwg);
+  if ((s = ensure_partials(g, most)) != RFA_OK) {
+    (void)hipFree(om2);
+    (void)hipFree(lab2);
+    return s;
+  }
   const StepConst K = step_const(g, dt);
   StepBuffers b{};
   b.hi_in = g->hi[g->cur];
@@ -1909,12 +1943,26 @@ struct rfa_batch_s {
   bool flat = false;                // items are flat plane segments (else 2.5-D tiles)
   int n_wg = 0;
   int req_wg = 0;                   // persistent work-groups (0: one per item)
-  long long group_budget = kBatchGroupVoxels;  // voxels per group (0: one group)
+  long long group_budget = -1;      // voxels per group (0: one group, -1: default)
   struct Group {
     int inst0, inst1;               // instances [inst0, inst1)
     int plain0, plain1;             // items of its grids without a perfusion field
     int perf0, perf1;               // items of its grids with one
+    int pplain0, pplain1, pperf0, pperf1;  // the same in the pair items
   };
+  // Two steps per launch with the pair kernel (single steps of odd counts
+  // take the one-step items): the default where every grid fits a kind of
+  // its work-groups and none has damage-coupled perfusion, until a shape of
+  // the one-step kernel is asked for.
+  bool want_pair = true;
+  int pwaves = 0, pv = 0;           // work-group kind (0: one step per launch)
+  std::vector<int> pfirst;          // pair item range of each instance
+  std::vector<int> tissue_version;  // of the grids when the codes were made
+  PairInstance* pinst_dev = nullptr;
+  PairItem* pitems_dev = nullptr;
+  int* pfirst_dev = nullptr;
+  uint8_t* codes = nullptr;         // wave codes of all instances
+  int n_pitems = 0;
   std::vector<Group> groups;
   int parity = 0;
   long long voxels = 0;
@@ -1948,12 +1996,159 @@ void batch_free_device(rfa_batch b) {
   f(b->partials);
   f(b->dacc);
   f(b->slot_acc);
+  f(b->pinst_dev);
+  f(b->pitems_dev);
+  f(b->pfirst_dev);
+  f(b->codes);
+  b->pinst_dev = nullptr;
+  b->pitems_dev = nullptr;
+  b->pfirst_dev = nullptr;
+  b->codes = nullptr;
+  b->pwaves = b->pv = 0;
+  b->n_pitems = 0;
   b->inst_dev = nullptr;
   b->items_dev = nullptr;
   b->first_dev = nullptr;
   b->partials = nullptr;
   b->dacc = nullptr;
   b->slot_acc = nullptr;
+}
+
+// Whether the batch takes two steps per launch: some kind (or the given one)
+// of the pair kernel's work-groups holds every grid, and none of them has
+// damage-coupled perfusion (whose second damage image a batch lacks).
+bool batch_pair_fits(rfa_batch b, int only = -1) {
+  if (!b->want_pair) return false;
+  for (rfa_grid g : b->grids)
+    if (g->perf_decay) return false;
+  int w, v;
+  for (int kind = only < 0 ? 0 : only; pair_kind(kind, &w, &v); ++kind) {
+    bool fits = true;
+    for (rfa_grid g : b->grids) fits = fits && pair_fits(g->g, w, v, std::min(64, g->g.nx));
+    if (fits) return true;
+    if (only >= 0) break;
+  }
+  return false;
+}
+
+// The pair kernel's instances, items and wave codes for the batch's groups
+// (b->inst and b->groups are built).  The kind of work-group is the one
+// with the least estimated time over the groups, each group with its own
+// chunk length; pwaves stays 0 where no kind takes every grid.
+rfa_status batch_build_pair(rfa_batch b) {
+  const int n = (int)b->grids.size();
+  if (!batch_pair_fits(b)) return RFA_OK;
+  // chunks of about xc planes, of equal length within a grid
+  auto shape_of = [&](int i, int w, int v, int xc) {
+    const Grid3 q = b->grids[i]->g;
+    const int chunks = (q.nx + xc - 1) / xc;
+    return pair_shape(q, w, v, (q.nx + chunks - 1) / chunks);
+  };
+  // estimated time of a group's launch
+  auto time_of = [&](const rfa_batch_s::Group& G, int w, int v, int xc) {
+    long long items = 0, planes = 0;  // planes marched, two more per item
+    int longest = 0;
+    for (int i = G.inst0; i < G.inst1; ++i) {
+      const PairShape s = shape_of(i, w, v, xc);
+      items += s.nwg;
+      planes += (long long)s.segs * (b->grids[i]->g.nx + 2 * s.chunks);
+      longest = std::max(longest, s.xc + 2);
+    }
+    return items > (1 << 22) ? 1e300 : pair_estimate_uneven(w, v, (int)items, planes, longest);
+  };
+  double best = 1e300;
+  std::vector<int> best_xc;
+  int w, v;
+  for (int kind = 0; pair_kind(kind, &w, &v); ++kind) {
+    if (!batch_pair_fits(b, kind)) continue;
+    double total = 0.0;
+    std::vector<int> xcs;
+    for (const auto& G : b->groups) {
+      double least = 1e300;
+      int at = 1;
+      for (int xc = 1; xc <= 64; ++xc) {
+        const double us = time_of(G, w, v, xc);
+        if (us < least) {
+          least = us;
+          at = xc;
+        }
+      }
+      total += least;
+      xcs.push_back(at);
+    }
+    if (total < best) {
+      best = total;
+      best_xc = xcs;
+      b->pwaves = w;
+      b->pv = v;
+    }
+  }
+  if (!b->pwaves) return RFA_OK;
+  w = b->pwaves;
+  v = b->pv;
+  std::vector<PairInstance> inst(n);
+  std::vector<PairItem> items;
+  std::vector<PairShape> shapes(n);
+  b->pfirst.assign(2 * (size_t)n, 0);
+  b->tissue_version.assign(n, 0);
+  size_t code_bytes = 0;
+  for (size_t gi = 0; gi < b->groups.size(); ++gi) {
+    auto& G = b->groups[gi];
+    for (int pass = 0; pass < 2; ++pass) {
+      (pass == 0 ? G.pplain0 : G.pperf0) = (int)items.size();
+      for (int i = G.inst0; i < G.inst1; ++i) {
+        rfa_grid g = b->grids[i];
+        if ((g->perf != nullptr) != (pass == 1)) continue;
+        shapes[i] = shape_of(i, w, v, best_xc[gi]);
+        code_bytes += pair_code_bytes(g->g, shapes[i]);
+        b->pfirst[2 * i] = (int)items.size();
+        for (int c = 0; c < shapes[i].chunks; ++c)
+          for (int sg = 0; sg < shapes[i].segs; ++sg) items.push_back(PairItem{i, sg, c, 0});
+        b->pfirst[2 * i + 1] = (int)items.size();
+      }
+      (pass == 0 ? G.pplain1 : G.pperf1) = (int)items.size();
+    }
+  }
+  b->n_pitems = (int)items.size();
+  rfa_status s;
+  if ((s = dmalloc(&b->codes, code_bytes)) || (s = dmalloc(&b->pinst_dev, n)) ||
+      (s = dmalloc(&b->pitems_dev, items.size())) || (s = dmalloc(&b->pfirst_dev, 2 * (size_t)n)))
+    return s;
+  size_t at = 0;
+  for (int i = 0; i < n; ++i) {
+    rfa_grid g = b->grids[i];
+    const BatchInstance& I = b->inst[i];
+    PairInstance& P = inst[i];
+    P = PairInstance{};
+    for (int k = 0; k < 2; ++k) {
+      P.hi[k] = I.hi[k];
+      P.lo[k] = I.lo[k];
+    }
+    P.lab = I.lab;
+    P.src = I.src;
+    P.om = I.om;
+    P.perf = I.perf;
+    P.tab = I.tab;
+    P.codes = b->codes + at;
+    P.n_classes = I.n_classes;
+    P.nx = I.nx;
+    P.ny = I.ny;
+    P.nz = I.nz;
+    P.xc = shapes[i].xc;
+    P.seg = shapes[i].seg;
+    P.segs = shapes[i].segs;
+    HIP_TRY(launch_pair_codes(g->g, shapes[i], g->lab, g->cp_dev, b->codes + at, b->st));
+    at += pair_code_bytes(g->g, shapes[i]);
+    b->tissue_version[i] = g->tissue_version;
+  }
+  HIP_TRY(hipMemcpyAsync(b->pinst_dev, inst.data(), n * sizeof(PairInstance),
+                         hipMemcpyHostToDevice, b->st));
+  HIP_TRY(hipMemcpyAsync(b->pitems_dev, items.data(), items.size() * sizeof(PairItem),
+                         hipMemcpyHostToDevice, b->st));
+  HIP_TRY(hipMemcpyAsync(b->pfirst_dev, b->pfirst.data(), 2 * (size_t)n * sizeof(int),
+                         hipMemcpyHostToDevice, b->st));
+  HIP_TRY(hipStreamSynchronize(b->st));
+  return RFA_OK;
 }
 
 // (Re)build the device descriptor table and work list from the grids'
@@ -1998,14 +2193,16 @@ rfa_status batch_build(rfa_batch b) {
   // grids without a perfusion field first, then those with one (two kernel
   // variants); each grid's items are contiguous.
   b->groups.clear();
+  const long long budget = b->group_budget >= 0 ? b->group_budget
+                           : batch_pair_fits(b) ? kPairGroupVoxels
+                                                : kBatchGroupVoxels;
   for (int i0 = 0; i0 < n;) {
     int i1 = i0 + 1;
     long long vox = (long long)b->grids[i0]->g.n();
-    while (i1 < n && b->group_budget > 0 &&
-           vox + (long long)b->grids[i1]->g.n() <= b->group_budget)
+    while (i1 < n && budget > 0 && vox + (long long)b->grids[i1]->g.n() <= budget)
       vox += (long long)b->grids[i1++]->g.n();
-    if (b->group_budget == 0) i1 = n;
-    rfa_batch_s::Group G{i0, i1, 0, 0, 0, 0};
+    if (budget == 0) i1 = n;
+    rfa_batch_s::Group G{i0, i1, 0, 0, 0, 0, 0, 0, 0, 0};
     for (int pass = 0; pass < 2; ++pass) {
       (pass == 0 ? G.plain0 : G.perf0) = (int)items.size();
       for (int i = i0; i < i1; ++i) {
@@ -2025,10 +2222,12 @@ rfa_status batch_build(rfa_batch b) {
     i0 = i1;
   }
   b->n_items = (int)items.size();
-  rfa_status s;
+  rfa_status s = b->want_pair ? batch_build_pair(b) : RFA_OK;
+  if (s != RFA_OK) return s;
   if ((s = dmalloc(&b->inst_dev, n)) || (s = dmalloc(&b->items_dev, items.size())) ||
       (s = dmalloc(&b->first_dev, 2 * (size_t)n)) ||
-      (s = dmalloc(&b->partials, (size_t)kPartialSlots * b->n_items * 3)) ||
+      (s = dmalloc(&b->partials,
+                   (size_t)kPartialSlots * std::max(b->n_items, b->n_pitems) * 3)) ||
       (s = dmalloc(&b->dacc, 3 * (size_t)n)) ||
       (s = dmalloc(&b->slot_acc, (size_t)kPartialSlots * 3 * n)))
     return s;
@@ -2053,7 +2252,8 @@ bool batch_in_sync(rfa_batch b) {
     const BatchInstance& I = b->inst[i];
     if (!g->has_tissue || I.hi[b->parity] != g->hi[g->cur] || I.lab != g->lab ||
         I.src != g->src || I.om != g->om || I.perf != g->perf || I.tab != g->tab_dev ||
-        I.n_classes != g->n_classes || g->tab_dt != b->dt[i] || g->src_dt != b->dt[i])
+        I.n_classes != g->n_classes || g->tab_dt != b->dt[i] || g->src_dt != b->dt[i] ||
+        (b->pwaves && g->tissue_version != b->tissue_version[i]))
       return false;
   }
   return true;
@@ -2077,25 +2277,35 @@ rfa_status batch_graph(rfa_batch b, int n_steps, bool diag, hipGraphExec_t* out)
     const int n_plain = G.plain1 - G.plain0, n_perf = G.perf1 - G.perf0;
     const int wg_plain = b->n_wg > 0 ? std::min(b->n_wg, n_plain) : 0;
     const int wg_perf = b->n_wg > 0 ? std::min(b->n_wg, n_perf) : 0;
-    int pending = 0;
-    for (int s = 0; s < n_steps && e == hipSuccess; ++s) {
+    int pending = 0, par = b->parity;
+    const int n_pair = b->pwaves ? n_steps / 2 : 0;
+    // fold the pending slots of items laid out by `first` into dacc
+    auto fold = [&](int n_items, const int* first) {
+      if (e == hipSuccess && diag && pending > 0)
+        e = launch_reduce_batch(b->partials, pending, n_items, first, G.inst0,
+                                G.inst1 - G.inst0, b->slot_acc, kPartialSlots, b->dacc, b->st);
+      pending = 0;
+    };
+    for (int s = 0; s < n_pair && e == hipSuccess; ++s, par ^= 1) {
+      float* part = diag ? b->partials + (size_t)pending * b->n_pitems * 3 : nullptr;
+      e = launch_pair_batch(b->pwaves, b->pv, b->pinst_dev, b->pitems_dev, G.pplain0,
+                            G.pplain1 - G.pplain0, false, par, part, b->st);
+      if (e == hipSuccess)
+        e = launch_pair_batch(b->pwaves, b->pv, b->pinst_dev, b->pitems_dev, G.pperf0,
+                              G.pperf1 - G.pperf0, true, par, part, b->st);
+      if (++pending == kPartialSlots) fold(b->n_pitems, b->pfirst_dev);
+    }
+    fold(b->n_pitems, b->pfirst_dev);
+    for (int s = 2 * n_pair; s < n_steps && e == hipSuccess; ++s, par ^= 1) {
       float* part = diag ? b->partials + (size_t)pending * b->n_items * 3 : nullptr;
-      const int par = (b->parity + s) & 1;
       e = launch_step_batch(b->ty, b->flat, false, b->inst_dev, b->items_dev, G.plain0,
                             n_plain, wg_plain, par, part, b->st);
       if (e == hipSuccess)
         e = launch_step_batch(b->ty, b->flat, true, b->inst_dev, b->items_dev, G.perf0, n_perf,
                               wg_perf, par, part, b->st);
-      if (e == hipSuccess && diag && ++pending == kPartialSlots) {
-        e = launch_reduce_batch(b->partials, pending, b->n_items, b->first_dev, G.inst0,
-                                G.inst1 - G.inst0, b->slot_acc, kPartialSlots, b->dacc,
-                                b->st);
-        pending = 0;
-      }
+      if (++pending == kPartialSlots) fold(b->n_items, b->first_dev);
     }
-    if (e == hipSuccess && diag && pending > 0)
-      e = launch_reduce_batch(b->partials, pending, b->n_items, b->first_dev, G.inst0,
-                              G.inst1 - G.inst0, b->slot_acc, kPartialSlots, b->dacc, b->st);
+    fold(b->n_items, b->first_dev);
   }
   hipGraph_t graph = nullptr;
   hipError_t e2 = hipStreamEndCapture(b->st, &graph);
@@ -2192,12 +2402,14 @@ rfa_status rfa_batch_step(rfa_batch b, int n_steps, rfa_diag* diags) {
   HIP_TRY(hipEventRecord(b->ev1, b->st));
   b->last_vs = b->voxels * n_steps;
   b->last_ms = -1.0;
-  b->parity = (b->parity + n_steps) & 1;
+  // image swaps: one per launch
+  const int swaps = b->pwaves ? n_steps / 2 + (n_steps & 1) : n_steps;
+  b->parity = (b->parity + swaps) & 1;
   for (int i = 0; i < n; ++i) {
     rfa_grid g = b->grids[i];
     // later work on the grid's own stream waits for the batch
     HIP_TRY(hipStreamWaitEvent(g->st, b->ev1, 0));
-    if (n_steps & 1) g->cur = 1 - g->cur;
+    if (swaps & 1) g->cur = 1 - g->cur;
     g->steps += n_steps;
     g->energy_valid = false;
     ++g->version;
@@ -2229,6 +2441,8 @@ rfa_status rfa_batch_set_plan(rfa_batch b, int layout, int tile_y, int tile_x, i
   const bool flat0 = b->flat;
   const int ty0 = b->ty, xc0 = b->xc, wg0 = b->req_wg;
   const long long gv0 = b->group_budget;
+  const bool pair0 = b->want_pair;
+  if (layout || tile_y || tile_x || workgroups) b->want_pair = false;  // a one-step shape
   b->flat = flat;
   b->ty = ty;
   if (tile_x) b->xc = tile_x;
@@ -2242,6 +2456,7 @@ rfa_status rfa_batch_set_plan(rfa_batch b, int layout, int tile_y, int tile_x, i
     b->xc = xc0;
     b->req_wg = wg0;
     b->group_budget = gv0;
+    b->want_pair = pair0;
     (void)batch_build(b);
     g_last_error = err;
   }
@@ -2316,13 +2531,19 @@ rfa_status rfa_batch_tune(rfa_batch b, int reps) {
     bool flat;
     int ty, xc;
     long long group;
+    bool pair;
   };
   bool flat_ok = true;
   for (rfa_grid g : b->grids) flat_ok = flat_ok && g->g.nz <= flat_max_nz(8);
   const long long g0 = kBatchGroupVoxels;
-  std::vector<Cand> shapes = {{false, 4, 8, g0}, {false, 8, 8, g0}, {false, 4, 16, g0}};
-  if (flat_ok) shapes.insert(shapes.begin(), {{true, 8, 8, g0}, {true, 8, 4, g0}, {true, 8, 16, g0}});
-  const Cand keep{b->flat, b->ty, b->xc, b->group_budget};
+  std::vector<Cand> shapes = {
+      {false, 4, 8, g0, false}, {false, 8, 8, g0, false}, {false, 4, 16, g0, false}};
+  if (flat_ok)
+    shapes.insert(shapes.begin(), {{true, 8, 8, g0, true},
+                                   {true, 8, 8, g0, false},
+                                   {true, 8, 4, g0, false},
+                                   {true, 8, 16, g0, false}});
+  const Cand keep{b->flat, b->ty, b->xc, b->group_budget, b->want_pair};
   const int keep_wg = b->req_wg;
   // time reps steps of one candidate (after one untimed replay), then put
   // the state back; ms < 0 on failure
@@ -2331,6 +2552,7 @@ rfa_status rfa_batch_tune(rfa_batch b, int reps) {
     b->ty = c.ty;
     b->xc = c.xc;
     b->group_budget = c.group;
+    b->want_pair = c.pair;
     b->req_wg = 0;
     rfa_status st = batch_build(b);
     if (st != RFA_OK) return st;
@@ -2365,7 +2587,7 @@ rfa_status rfa_batch_tune(rfa_batch b, int reps) {
     if ((s = consider(c)) != RFA_OK) break;
   if (s == RFA_OK) {
     const Cand shape = best;
-    for (long long gv : {4ll << 20, 6ll << 20, 10ll << 20, 0ll}) {
+    for (long long gv : {4ll << 20, 6ll << 20, 10ll << 20, kPairGroupVoxels, 0ll}) {
       Cand c = shape;
       c.group = gv;
       if ((s = consider(c)) != RFA_OK) break;
@@ -2379,6 +2601,7 @@ rfa_status rfa_batch_tune(rfa_batch b, int reps) {
     b->ty = keep.ty;
     b->xc = keep.xc;
     b->group_budget = keep.group;
+    b->want_pair = keep.pair;
     b->req_wg = keep_wg;
     (void)batch_build(b);
     g_last_error = err;
@@ -2389,6 +2612,7 @@ rfa_status rfa_batch_tune(rfa_batch b, int reps) {
   b->ty = best.ty;
   b->xc = best.xc;
   b->group_budget = best.group;
+  b->want_pair = best.pair;
   b->req_wg = 0;
   return batch_build(b);
 }

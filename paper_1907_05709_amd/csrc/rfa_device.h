@@ -43,12 +43,6 @@ __host__ __device__ constexpr unsigned class_of(unsigned lab) {
   return (lab & kClassMask) >> kClassShift;
 }
 
-// Per-dt coefficient tables, staged into LDS by every work-group.
-struct Tables {
-  float2 cf[3][kMaxClasses * kMaxClasses];  // [axis][a*16+b] = C(a,b) hi/lo
-  float4 cls[kMaxClasses];                  // {B hi, B lo, Qs, rho c V}
-};
-
 // Damage / latch constants of one dt.
 struct StepConst {
   float dtka;    // dt * k_a
@@ -59,6 +53,13 @@ struct StepConst {
   float thr;     // t_death - 37
   float decay2;  // log2(e) with damage-coupled perfusion, else 0
   float cold;    // |theta| below which the damage exponent rounds to 2^0 = 1
+};
+
+// Per-dt coefficient tables, staged into LDS by every work-group.
+struct Tables {
+  float2 cf[3][kMaxClasses * kMaxClasses];  // [axis][a*16+b] = C(a,b) hi/lo
+  float4 cls[kMaxClasses];                  // {B hi, B lo, Qs, rho c V}
+  StepConst K;  // for kernels that read their constants through the scalar cache
 };
 
 // Per-thread diagnostic partials of one step.

@@ -42,19 +42,63 @@ PairShape pair_shape(Grid3 g, int waves, int v, int xc);
 size_t pair_code_bytes(Grid3 g, const PairShape& s);
 hipError_t launch_pair_codes(Grid3 g, const PairShape& s, const uint8_t* lab,
                              const ClassParams* cp_dev, uint8_t* codes, hipStream_t st);
-// Two steps.  b.codes: the shape's wave codes; hi_mid: the image between the
+// Two steps, with the step constants of b.tab.  b.codes: the shape's wave codes; hi_mid: the image between the
 // steps (kPairKeep, kPairTemp).
-hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b,
-                            const StepConst& K, PairMode mode, float* hi_mid, int store,
-                            hipStream_t st);
+hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,
+                            float* hi_mid, int store, hipStream_t st);
+
+// One grid of a batch: its arrays, its shape's segments and chunk length.
+// Image 0 is the current image at batch parity 0; a launch at parity p reads
+// image p and writes image 1 - p.  No damage-coupled perfusion.
+struct PairInstance {
+  float* hi[2];
+  float* lo[2];
+  uint8_t* lab;
+  const float* src;
+  float* om;
+  const float* perf;
+  const Tables* tab;
+  const uint8_t* codes;
+  int n_classes;
+  int nx, ny, nz;
+  int xc, seg, segs;
+  int pad;
+};
+
+// One work item: segment sg over chunk `chunk` of an instance.
+struct PairItem {
+  int inst, sg, chunk, pad;
+};
+
+// Two steps of the items [first_item, first_item + n_items), all of instances
+// with (perf) or without a perfusion field, with work-groups of waves x v.
+// partials (nullable) receives 3 floats per item, indexed by item.
+hipError_t launch_pair_batch(int waves, int v, const PairInstance* inst, const PairItem* items,
+                             int first_item, int n_items, bool perf, int parity, float* partials,
+                             hipStream_t st);
+
+// Estimated time (us) of a launch of nwg work-groups that march xc planes,
+// and the kinds of work-group it knows (false: no kind `index`).
+bool pair_kind(int index, int* waves, int* v);
+double pair_estimate(int waves, int v, int nwg, int xc);
+// The same for nwg work-groups of different lengths: `planes` iterations in
+// all, `longest` in one of them.
+double pair_estimate_uneven(int waves, int v, int nwg, long long planes, int longest);
 
 // The kinds of work-group (waves x voxels per lane), for launch_step_pair().
 #define RFA_PAIR_LAUNCH(name)                                                             \
-  hipError_t name(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K, \
-                  PairMode mode, float* hi_mid, int store, hipStream_t st)
+  hipError_t name(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode, \
+                  float* hi_mid, int store, hipStream_t st)
 RFA_PAIR_LAUNCH(launch_pair_16x2);
 RFA_PAIR_LAUNCH(launch_pair_8x2);
 RFA_PAIR_LAUNCH(launch_pair_8x1);
 RFA_PAIR_LAUNCH(launch_pair_4x1);
+#define RFA_PAIR_BATCH(name)                                                              \
+  hipError_t name(const PairInstance* inst, const PairItem* items, int first_item,       \
+                  int n_items, bool perf, int parity, float* partials, hipStream_t st)
+RFA_PAIR_BATCH(launch_batch_16x2);
+RFA_PAIR_BATCH(launch_batch_8x2);
+RFA_PAIR_BATCH(launch_batch_8x1);
+RFA_PAIR_BATCH(launch_batch_4x1);
 
 }  // namespace rfa

@@ -57,13 +57,54 @@ __global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, const Cl
 
 namespace {
 
-// Work-groups built: {waves, voxels per lane, largest nz}.
+// Work-groups built, and what a launch of them takes.  A launch costs about
+// 5 us plus, per round of resident work-groups, xc + 2 plane iterations (the
+// first step runs on one plane more at either end of a chunk).  An
+// iteration's time grows with the work-groups m that share a compute unit,
+// a + b m; a and b fitted to 100-step runs of 11 grids from 32^3 to 256^3,
+// every kind and 16 chunk lengths (the fit holds to 10 % where it decides).
 struct PairKind {
   int waves, v, max_nz;
+  int per_cu;   // work-groups a compute unit holds
+  double a, b;  // us per iteration
 };
-constexpr PairKind kPairKinds[] = {{16, 2, 256}, {8, 2, 128}, {8, 1, 128}, {4, 1, 96}};
+constexpr PairKind kPairKinds[] = {{16, 2, 256, 1, 1.0, 1.8},
+                                   {8, 2, 128, 2, 1.0, 0.8},
+                                   {8, 1, 128, 2, 0.5, 0.45},
+                                   {4, 1, 96, 5, 0.35, 0.28}};
+constexpr int kCu = 256;
 
 }  // namespace
+
+bool pair_kind(int index, int* waves, int* v) {
+  if (index < 0 || index >= (int)(sizeof kPairKinds / sizeof kPairKinds[0])) return false;
+  *waves = kPairKinds[index].waves;
+  *v = kPairKinds[index].v;
+  return true;
+}
+
+double pair_estimate(int waves, int v, int nwg, int xc) {
+  for (const PairKind& k : kPairKinds) {
+    if (k.waves != waves || k.v != v) continue;
+    const int slots = kCu * k.per_cu, rest = nwg % slots;
+    double us = 5.0 + (nwg / slots) * (xc + 2) * (k.a + k.b * k.per_cu);
+    if (rest) us += (xc + 2) * (k.a + k.b * ((rest + kCu - 1) / kCu));
+    return us;
+  }
+  return 1e300;
+}
+
+double pair_estimate_uneven(int waves, int v, int nwg, long long planes, int longest) {
+  for (const PairKind& k : kPairKinds) {
+    if (k.waves != waves || k.v != v) continue;
+    const int slots = kCu * k.per_cu;
+    // one round: the longest; more: the slots share the work and, on average,
+    // wait for half of a last work-group
+    if (nwg <= slots) return 5.0 + longest * (k.a + k.b * ((nwg + kCu - 1) / kCu));
+    return 5.0 + ((double)planes / slots + 0.5 * longest) * (k.a + k.b * k.per_cu);
+  }
+  return 1e300;
+}
 
 bool pair_fits(Grid3 g, int waves, int v, int xc) {
   for (const PairKind& k : kPairKinds)
@@ -100,15 +141,28 @@ hipError_t launch_pair_codes(Grid3 g, const PairShape& s, const uint8_t* lab,
   return hipGetLastError();
 }
 
-hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b,
-                            const StepConst& K, PairMode mode, float* hi_mid, int store,
-                            hipStream_t st) {
+hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,
+                            float* hi_mid, int store, hipStream_t st) {
   if (!pair_fits(g, s.waves, s.v, s.xc) || !b.codes || (mode != kPairFull && !hi_mid))
     return hipErrorInvalidValue;
-  if (s.waves == 16 && s.v == 2) return launch_pair_16x2(s, g, b, K, mode, hi_mid, store, st);
-  if (s.waves == 8 && s.v == 2) return launch_pair_8x2(s, g, b, K, mode, hi_mid, store, st);
-  if (s.waves == 8 && s.v == 1) return launch_pair_8x1(s, g, b, K, mode, hi_mid, store, st);
-  if (s.waves == 4 && s.v == 1) return launch_pair_4x1(s, g, b, K, mode, hi_mid, store, st);
+  if (s.waves == 16 && s.v == 2) return launch_pair_16x2(s, g, b, mode, hi_mid, store, st);
+  if (s.waves == 8 && s.v == 2) return launch_pair_8x2(s, g, b, mode, hi_mid, store, st);
+  if (s.waves == 8 && s.v == 1) return launch_pair_8x1(s, g, b, mode, hi_mid, store, st);
+  if (s.waves == 4 && s.v == 1) return launch_pair_4x1(s, g, b, mode, hi_mid, store, st);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_pair_batch(int waves, int v, const PairInstance* inst, const PairItem* items,
+                             int first_item, int n_items, bool perf, int parity, float* partials,
+                             hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+  auto launch = [&](auto f) {
+    return f(inst, items, first_item, n_items, perf, parity, partials, st);
+  };
+  if (waves == 16 && v == 2) return launch(launch_batch_16x2);
+  if (waves == 8 && v == 2) return launch(launch_batch_8x2);
+  if (waves == 8 && v == 1) return launch(launch_batch_8x1);
+  if (waves == 4 && v == 1) return launch(launch_batch_4x1);
   return hipErrorInvalidValue;
 }
 

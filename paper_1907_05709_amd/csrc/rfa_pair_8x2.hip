@@ -4,7 +4,12 @@
 namespace rfa {
 
 RFA_PAIR_LAUNCH(launch_pair_8x2) {
-  return launch_store<512, 2, 128>(s, g, b, K, mode, hi_mid, store, st);
+  return launch_store<512, 2, 128>(s, g, b, mode, hi_mid, store, st);
+}
+
+RFA_PAIR_BATCH(launch_batch_8x2) {
+  return launch_batch<512, 2, 128>(inst, items, first_item, n_items, perf, parity, partials,
+                                  st);
 }
 
 }  // namespace rfa

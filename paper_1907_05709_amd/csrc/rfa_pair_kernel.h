@@ -86,6 +86,24 @@ __device__ __forceinline__ ClassCoef class_coef(const Tables* tab, unsigned c) {
   return r;
 }
 
+// The step constants, read where they are used: as kernel arguments they
+// would occupy eight scalar registers through the plane loop, which spills.
+__device__ __forceinline__ StepConst step_constants(const Tables* tab) {
+  uintptr_t p = (uintptr_t)tab;
+  asm volatile("" : "+s"(p));  // keeps the loads here
+  ConstF* q = (ConstF*)p + offsetof(Tables, K) / 4;
+  StepConst K;
+  K.dtka = q[0];
+  K.c2 = q[1];
+  K.tak = q[2];
+  K.clamp2 = q[3];
+  K.cap = q[4];
+  K.thr = q[5];
+  K.decay2 = q[6];
+  K.cold = q[7];
+  return K;
+}
+
 // min(v, m) for a wave-uniform bound m, without the canonicalisation
 // fminf() adds to each operand; v_min_f32 has fminf's NaN rule.
 __device__ __forceinline__ float min_uniform(float v, float m) {
@@ -100,20 +118,19 @@ __device__ __forceinline__ bool lane_of(unsigned long long m) {
 
 }  // namespace
 
+namespace {
+
+// The march of one work-group: segment sg of planes [x0, x1).  out: its
+// partial sums (DIAG).
 template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE>
-__global__ __launch_bounds__(NT, 4) void k_step_pair(
-    StepBuffers b, StepConst K, float* hi_mid, int nx, int ny, int nz, int xc, int seg, int segs,
-    int nwg) {
+__device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const StepBuffers& b,
+                                           float* hi_mid, int nx, int ny, int nz, int x0, int x1,
+                                           int seg, int segs, int sg, float* out) {
   using S = PairSmem<NT, V, MAXNZ>;
   constexpr bool TEMP = MODE == kPairTemp;
   constexpr bool KEEP = MODE != kPairFull;
   constexpr int P = S::P;
   constexpr int NW = NT / 64;
-  __shared__ S sm;
-  const int wg = remap_xcd(blockIdx.x, nwg);
-  const int sg = wg % segs;
-  const int x0 = (wg / segs) * xc;
-  const int x1 = min(x0 + xc, nx);
   const int xb = max(x0 - 2, 0);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -140,9 +157,8 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
 
   // Own voxels: column in the plane (0, a held corner, outside the grid),
   // store offsets (out of range unless owned)
-  unsigned col[V], own4[V], own1[V], omc[V];
+  unsigned col[V], own4[V];
   int cell[V];  // LDS cell
-  bool owned[V];
   unsigned long long ownm[V];  // lanes whose voxel is owned
   bool wave_owns = false, wave_valid = false;
 #pragma unroll
@@ -154,15 +170,11 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
     const int f = f0 - nz + q;
     const bool valid = f >= 0 && f < np;
     cell[v] = nz + q;
-    owned[v] = valid && q >= nz && q < nz + seg;
-    ownm[v] = __ballot(owned[v]);
+    const bool owned = valid && q >= nz && q < nz + seg;
+    ownm[v] = __ballot(owned);
     col[v] = valid ? (unsigned)f : 0u;
-    own4[v] = owned[v] ? (unsigned)f * 4u : kOob;
-    own1[v] = owned[v] ? (unsigned)f : kOob;
-    // the damage integral enters the temperature only through the coupling;
-    // without a field it is read on owned voxels alone
-    omc[v] = (PERF ? valid : owned[v]) ? (unsigned)f * 4u : kOob;
-    wave_owns = wave_owns || owned[v];
+    own4[v] = owned ? (unsigned)f * 4u : kOob;
+    wave_owns = wave_owns || owned;
     wave_valid = wave_valid || valid;
   }
   const bool do_mid = __ballot(wave_valid) != 0ull;  // uniform
@@ -201,7 +213,9 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       q.s[v] = ld_f32(r_src, (q.b[v] & kSource) ? col[v] * 4u : kOob, so4);
-      q.om[v] = TEMP ? 0.0f : ld_f32(r_om, omc[v], so4);
+      // the damage integral enters the temperature only through the coupling:
+      // without a field it is read on owned voxels alone
+      q.om[v] = TEMP ? 0.0f : ld_f32(r_om, PERF ? col[v] * 4u : own4[v], so4);
       if constexpr (PERF) q.pf[v] = ld_f32(r_pf, col[v] * 4u, so4);
     }
   };
@@ -252,14 +266,16 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
   // values, dn: difference to x + 1, dp: difference of x - 1 to the plane
   // (both from registers), tl / tp: class bytes of the plane and of x - 1 in
   // LDS, bn: of x + 1,
-  // heldm: lanes whose voxel is held, cntm: lanes whose sums count (free ones).
+  // heldm: lanes whose voxel is held, counted: the owned free voxels' sums count.
   auto step = [&](const float2* t, const uint8_t* tl, const uint8_t* tp, unsigned code,
                   const float (&h)[V],
                   const float (&l)[V], const unsigned (&lb)[V], float (&om)[V],
                   const float (&s)[V], const float (&pf)[V], const float (&dn)[V],
                   const float (&dp)[V], const unsigned (&bn)[V],
-                  const unsigned long long (&heldm)[V], const unsigned long long (&cntm)[V], float (&nh)[V], float (&nl)[V],
+                  const unsigned long long (&heldm)[V], bool counted, float (&nh)[V], float (&nl)[V],
                   unsigned (&nb)[V]) {
+    const StepConst K = step_constants(b.tab);
+    auto cntm = [&](int v) { return counted ? ownm[v] & ~heldm[v] : 0ull; };
     float f[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -278,18 +294,17 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
         const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h[v], l[v]),
                             ff_diff(yp.x, yp.y, h[v], l[v]), ff_diff(zm.x, zm.y, h[v], l[v]),
                             ff_diff(zp.x, zp.y, h[v], l[v])};
-        float h2, l2, cond, perf, inc;
-        thermal_update(h[v], l[v], k, coef.c, d, s[v], f[v], h2, l2, cond, perf, inc);
+        float h2, l2, cond, perf;
+        thermal_update(h[v], l[v], k, coef.c, d, s[v], f[v], h2, l2, cond, perf, incs[v]);
         const bool held = lane_of(heldm[v]);
         nh[v] = held ? h[v] : h2;
         nl[v] = held ? l[v] : l2;
         if constexpr (DIAG) {
           // lanes that do not count add 0 times a finite term
-          const float w = lane_of(cntm[v]) ? coef.c.w : 0.0f;
+          const float w = lane_of(cntm(v)) ? coef.c.w : 0.0f;
           acc.perf = __builtin_fmaf(w, perf, acc.perf);
           acc.bnd = __builtin_fmaf(w, cond, acc.bnd);
-          incs[v] = inc;
-          falls = falls || inc < 0.0f;
+          falls = falls || incs[v] < 0.0f;
         }
         warm = warm || !(fabsf(h[v]) < K.cold);
         hot = hot || nh[v] >= K.thr;
@@ -297,8 +312,7 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
       }
       if (DIAG && __ballot(falls) != 0ull) {
 #pragma unroll
-        for (int v = 0; v < V; ++v)
-          mono += __popcll(__ballot(cools(h[v], incs[v])) & cntm[v]);
+        for (int v = 0; v < V; ++v) mono += __popcll(__ballot(cools(h[v], incs[v])) & cntm(v));
       }
       if constexpr (!TEMP) {
         float rate[V];
@@ -336,8 +350,18 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
                              table_entry(sm.cf, 1, lb[v], tl[c + nz]),
                              table_entry(sm.cf, 2, lb[v], tl[c - 1]),
                              table_entry(sm.cf, 2, lb[v], tl[c + 1])};
-        voxel_thermal<DIAG>(h[v], l[v], lane_of(heldm[v]), k, sm.cls[class_of(lb[v])], d, s[v],
-                            f[v], nh[v], nl[v], acc, lane_of(cntm[v]));
+        const float4 c4 = sm.cls[class_of(lb[v])];
+        float h2, l2, cond, perf, inc;
+        thermal_update(h[v], l[v], k, c4, d, s[v], f[v], h2, l2, cond, perf, inc);
+        const bool held = lane_of(heldm[v]);
+        nh[v] = held ? h[v] : h2;
+        nl[v] = held ? l[v] : l2;
+        if constexpr (DIAG) {
+          const float w = lane_of(cntm(v)) ? c4.w : 0.0f;
+          acc.perf = __builtin_fmaf(w, perf, acc.perf);
+          acc.bnd = __builtin_fmaf(w, cond, acc.bnd);
+          mono += __popcll(__ballot(cools(h[v], inc)) & cntm(v));
+        }
         nb[v] = lb[v];
         if constexpr (!TEMP) {
           om[v] = damage_add<true>(om[v], damage_increment(h[v], K), (lb[v] & kTissue) != 0u, K);
@@ -377,21 +401,20 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
     // first step of plane x
     float nh[V], nl[V], nom[V], dn[V];
     unsigned nb[V];
-    unsigned long long held[V], cnt[V];
+    unsigned long long held[V];
     const bool in_chunk = x >= x0 && x < x1;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       dn[v] = ff_diff(N.h[v], N.l[v], C.h[v], C.l[v]);
       nom[v] = C.om[v];
       held[v] = __ballot((C.b[v] & kHeld) != 0u);
-      cnt[v] = in_chunk ? ownm[v] & ~held[v] : 0ull;
       nh[v] = C.h[v];
       nl[v] = C.l[v];
       nb[v] = C.b[v];
     }
     if (do_mid)
       step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C.h, C.l, C.b, nom, C.s, C.pf, dn, din, N.b,
-           held, cnt, nh, nl, nb);
+           held, in_chunk, nh, nl, nb);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       din[v] = dn[v];
@@ -416,12 +439,11 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
         oh[v] = mh[v];
         ol[v] = ml[v];
         ob[v] = mb[v];
-        cnt[v] = ownm[v] & ~mheld[v];
         lb1[v] = kOob;
       }
       if (do_out && out) {
         step(sm.mid[BUF ^ 1], sm.lab[SP], sm.lab[SA], pcode, mh, ml, mb, oom, B.s, B.pf, dm, dmid,
-             C.b, mheld, cnt, oh, ol, ob);
+             C.b, mheld, true, oh, ol, ob);
         if constexpr (!TEMP) {
           // class bytes are stored where a latch flipped in either step
           bool latched = false;
@@ -430,7 +452,7 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
           if (__ballot(latched) != 0ull) {
 #pragma unroll
             for (int v = 0; v < V; ++v)
-              lb1[v] = ob[v] != sm.lab[SP][cell[v]] ? own1[v] : kOob;
+              lb1[v] = lane_of(ownm[v]) && ob[v] != sm.lab[SP][cell[v]] ? col[v] : kOob;
           }
         }
       }
@@ -473,32 +495,80 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(
     if (x + 4 > x1) break;
   }
   if (DIAG && (tid & 63) == 0) acc.mono += mono;
-  if constexpr (DIAG) write_partials(acc, sm.red, NW, b.partials + (size_t)wg * 3);
+  if constexpr (DIAG) write_partials(acc, sm.red, NW, out);
+}
+
+}  // namespace
+
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE>
+__global__ __launch_bounds__(NT, 4) void k_step_pair(StepBuffers b, float* hi_mid, int nx, int ny,
+                                                     int nz, int xc, int seg, int segs,
+                                                     int nwg) {
+  __shared__ PairSmem<NT, V, MAXNZ> sm;
+  const int wg = remap_xcd(blockIdx.x, nwg);
+  const int x0 = (wg / segs) * xc;
+  pair_march<NT, V, MAXNZ, PERF, DIAG, AUX, MODE>(sm, b, hi_mid, nx, ny, nz, x0,
+                                                  min(x0 + xc, nx), seg, segs, wg % segs,
+                                                  DIAG ? b.partials + (size_t)wg * 3 : nullptr);
+}
+
+// The same over the work items of a batch group (one work-group per item, in
+// XCD-aware order).  Items and instances are read through the scalar cache.
+// Write-back stores: groups are sized to stay in the last-level cache.
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG>
+__global__ __launch_bounds__(NT, 4) void k_step_pair_batch(const PairInstance* inst,
+                                                           const PairItem* items, int first_item,
+                                                           int n_items, int parity,
+                                                           float* partials) {
+  __shared__ PairSmem<NT, V, MAXNZ> sm;
+  typedef const __attribute__((address_space(4))) PairInstance ConstInstance;
+  typedef const __attribute__((address_space(4))) PairItem ConstItem;
+  const int it = first_item + remap_xcd(blockIdx.x, n_items);
+  ConstItem* w = (ConstItem*)(uintptr_t)items + it;
+  ConstInstance* I = (ConstInstance*)(uintptr_t)inst + w->inst;
+  StepBuffers b;
+  b.hi_in = parity ? I->hi[1] : I->hi[0];
+  b.lo_in = parity ? I->lo[1] : I->lo[0];
+  b.hi_out = parity ? I->hi[0] : I->hi[1];
+  b.lo_out = parity ? I->lo[0] : I->lo[1];
+  b.lab = I->lab;
+  b.src = I->src;
+  b.omega = I->om;
+  b.omega_out = I->om;
+  b.perf = I->perf;
+  b.tab = I->tab;
+  b.n_classes = I->n_classes;
+  b.codes = I->codes;
+  b.partials = nullptr;
+  const int nx = I->nx, xc = I->xc;
+  const int x0 = w->chunk * xc;
+  pair_march<NT, V, MAXNZ, PERF, DIAG, kStoreBack, kPairFull>(
+      sm, b, nullptr, nx, I->ny, I->nz, x0, min(x0 + xc, nx), I->seg, I->segs, w->sg,
+      DIAG ? partials + (size_t)it * 3 : nullptr);
 }
 
 
 namespace {
 
 template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX>
-hipError_t launch_mode(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K,
-                       PairMode mode, float* hi_mid, hipStream_t st) {
+hipError_t launch_mode(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode, float* hi_mid, hipStream_t st) {
   const dim3 grid(s.nwg), block(NT);
   switch (mode) {
     case kPairFull:
       hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, DIAG, AUX, kPairFull>), grid, block, 0,
-                         st, b, K, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
+                         st, b, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
       break;
     case kPairKeep:
       if constexpr (!DIAG)
         hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, false, AUX, kPairKeep>), grid, block,
-                           0, st, b, K, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
+                           0, st, b, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
       else
         return hipErrorInvalidValue;
       break;
     case kPairTemp:
       if constexpr (!DIAG)
         hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, false, AUX, kPairTemp>), grid, block,
-                           0, st, b, K, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
+                           0, st, b, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
       else
         return hipErrorInvalidValue;
       break;
@@ -507,27 +577,44 @@ hipError_t launch_mode(const PairShape& s, Grid3 g, const StepBuffers& b, const 
 }
 
 template <int NT, int V, int MAXNZ, int AUX>
-hipError_t launch_kind(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K,
-                       PairMode mode, float* hi_mid, hipStream_t st) {
+hipError_t launch_kind(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode, float* hi_mid, hipStream_t st) {
   if (b.perf)
     return b.partials
-               ? launch_mode<NT, V, MAXNZ, true, true, AUX>(s, g, b, K, mode, hi_mid, st)
-               : launch_mode<NT, V, MAXNZ, true, false, AUX>(s, g, b, K, mode, hi_mid, st);
-  return b.partials ? launch_mode<NT, V, MAXNZ, false, true, AUX>(s, g, b, K, mode, hi_mid, st)
-                    : launch_mode<NT, V, MAXNZ, false, false, AUX>(s, g, b, K, mode, hi_mid, st);
+               ? launch_mode<NT, V, MAXNZ, true, true, AUX>(s, g, b, mode, hi_mid, st)
+               : launch_mode<NT, V, MAXNZ, true, false, AUX>(s, g, b, mode, hi_mid, st);
+  return b.partials ? launch_mode<NT, V, MAXNZ, false, true, AUX>(s, g, b, mode, hi_mid, st)
+                    : launch_mode<NT, V, MAXNZ, false, false, AUX>(s, g, b, mode, hi_mid, st);
 }
 
 template <int NT, int V, int MAXNZ>
-hipError_t launch_store(const PairShape& s, Grid3 g, const StepBuffers& b, const StepConst& K,
-                        PairMode mode, float* hi_mid, int store, hipStream_t st) {
+hipError_t launch_store(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode, float* hi_mid, int store, hipStream_t st) {
   switch (store) {
     case kPolicyThrough:
-      return launch_kind<NT, V, MAXNZ, kStoreThrough>(s, g, b, K, mode, hi_mid, st);
+      return launch_kind<NT, V, MAXNZ, kStoreThrough>(s, g, b, mode, hi_mid, st);
     case kPolicyStream:
-      return launch_kind<NT, V, MAXNZ, kStoreStream>(s, g, b, K, mode, hi_mid, st);
+      return launch_kind<NT, V, MAXNZ, kStoreStream>(s, g, b, mode, hi_mid, st);
     default:
-      return launch_kind<NT, V, MAXNZ, kStoreBack>(s, g, b, K, mode, hi_mid, st);
+      return launch_kind<NT, V, MAXNZ, kStoreBack>(s, g, b, mode, hi_mid, st);
   }
+}
+
+template <int NT, int V, int MAXNZ>
+hipError_t launch_batch(const PairInstance* inst, const PairItem* items, int first_item,
+                        int n_items, bool perf, int parity, float* partials, hipStream_t st) {
+  const dim3 grid(n_items), block(NT);
+  if (perf && partials)
+    hipLaunchKernelGGL((k_step_pair_batch<NT, V, MAXNZ, true, true>), grid, block, 0, st, inst,
+                       items, first_item, n_items, parity, partials);
+  else if (perf)
+    hipLaunchKernelGGL((k_step_pair_batch<NT, V, MAXNZ, true, false>), grid, block, 0, st, inst,
+                       items, first_item, n_items, parity, partials);
+  else if (partials)
+    hipLaunchKernelGGL((k_step_pair_batch<NT, V, MAXNZ, false, true>), grid, block, 0, st, inst,
+                       items, first_item, n_items, parity, partials);
+  else
+    hipLaunchKernelGGL((k_step_pair_batch<NT, V, MAXNZ, false, false>), grid, block, 0, st, inst,
+                       items, first_item, n_items, parity, partials);
+  return hipGetLastError();
 }
 
 }  // namespace

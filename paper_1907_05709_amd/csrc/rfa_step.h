@@ -43,7 +43,7 @@ StepPlan plan_default(Grid3 g, int kernel, int depth, int tile_y, int tile_x, in
                       int store = 0);
 // Candidate plans for tuning (depth 1, and depth 2 if max_depth >= 2).
 int plan_candidates(Grid3 g, int max_depth, StepPlan* out, int max_out);
-// Largest partial stride any plan of this grid can need.
+// Largest partial stride any plan of this grid but a pair plan can need.
 int plan_max_wg(Grid3 g);
 
 struct StepState {

@@ -120,41 +120,24 @@ StepPlan plan_one(const StepPlan& p) {
 
 namespace {
 
-// Two-step plan with the least estimated time, waves / v / tile_x as asked
-// (0: any); false if no work-group fits the grid.
-//
-// A launch costs about 5 us plus, per round of resident work-groups, xc + 2
-// plane iterations (the first step runs on one plane more at either end of
-// a chunk).  An iteration's time grows with the work-groups m that share a
-// compute unit, a + b m; a and b fitted to 100-step runs of 11 grids from
-// 32^3 to 256^3, every kind and 16 chunk lengths (the fit holds to 10 %
-// where it decides).  It picks e.g. 4 waves x 1 voxel at 32^3 (3.4 us a step;
-// one-step kernel 6.0), 8 x 1 at 64^3 (5.0; 6.4), 8 x 2 at 128^3 (12.8;
-// 13.3), 16 x 2 at 160^3 (19.4; 33.7) and 256^3 (68; 80).
-bool best_pair(Grid3 g, int waves, int v, int tile_x, StepPlan* out) {
-  struct Kind {
-    int waves, v, per_cu;  // per_cu: work-groups a compute unit holds
-    double a, b;           // us per iteration
-  };
-  constexpr Kind kinds[] = {{16, 2, 1, 1.0, 1.8},
-                            {8, 2, 2, 1.0, 0.8},
-                            {8, 1, 2, 0.5, 0.45},
-                            {4, 1, 5, 0.35, 0.28}};
-  constexpr int kCu = 256;
+// Two-step plan with the least estimated time, waves / tile_x as asked (0:
+// any); false if no work-group fits the grid.  It picks e.g. 4 waves x 1
+// voxel at 32^3 (3.4 us a step; one-step kernel 6.0), 8 x 1 at 64^3 (5.0;
+// 6.4), 8 x 2 at 128^3 (12.8; 13.3), 16 x 2 at 160^3 (19.4; 33.7) and 256^3
+// (66; 80).
+bool best_pair(Grid3 g, int waves, int tile_x, StepPlan* out) {
   double best = 1e300;
-  for (const Kind& k : kinds) {
-    if ((waves && waves != k.waves) || (v && v != k.v)) continue;
+  int w, v;
+  for (int kind = 0; pair_kind(kind, &w, &v); ++kind) {
+    if (waves && waves != w) continue;
     const int lo = tile_x ? std::min(tile_x, g.nx) : 1;
     const int hi = tile_x ? lo : std::min(g.nx, 64);
     for (int xc = lo; xc <= hi; ++xc) {
-      if (!pair_fits(g, k.waves, k.v, xc)) continue;
-      const int nwg = pair_shape(g, k.waves, k.v, xc).nwg;
-      const int slots = kCu * k.per_cu, rest = nwg % slots;
-      double us = 5.0 + (nwg / slots) * (xc + 2) * (k.a + k.b * k.per_cu);
-      if (rest) us += (xc + 2) * (k.a + k.b * ((rest + kCu - 1) / kCu));
+      if (!pair_fits(g, w, v, xc)) continue;
+      const double us = pair_estimate(w, v, pair_shape(g, w, v, xc).nwg, xc);
       if (us < best) {
         best = us;
-        *out = plan_pair(g, k.waves, k.v, xc);
+        *out = plan_pair(g, w, v, xc);
       }
     }
   }
@@ -166,8 +149,8 @@ StepPlan default_shape(Grid3 g, int kernel, int depth, int tile_y, int tile_x, i
   // two steps per launch wherever a work-group holds the rows (nz <= 256),
   // unless the options ask for one step or for a shape of its kernels
   StepPlan pair;
-  if (depth == 2 && best_pair(g, tile_y, 0, tile_x, &pair)) return pair;
-  if (depth == 0 && !tile_y && !tile_x && !zv && best_pair(g, 0, 0, 0, &pair)) return pair;
+  if (depth == 2 && best_pair(g, tile_y, tile_x, &pair)) return pair;
+  if (depth == 0 && !tile_y && !tile_x && !zv && best_pair(g, 0, 0, &pair)) return pair;
   // automatic: four z voxels per lane once a tile row spans 256 voxels, two
   // (with 8-row tiles) from 96
   if (zv == 0 && depth != 2 && g.nz >= 256 && g.nz % 4 == 0) zv = 4;
@@ -232,7 +215,7 @@ int plan_candidates(Grid3 g, int max_depth, StepPlan* out, int max_out) {
         if (xc <= g.nx && pair_fits(g, waves, v, xc)) out[n++] = plan_pair(g, waves, v, xc);
       }
   StepPlan pair;
-  if (n < max_out && best_pair(g, 0, 0, 0, &pair)) {
+  if (n < max_out && best_pair(g, 0, 0, &pair)) {
     out[n++] = pair;
     return n;
   }
@@ -253,9 +236,6 @@ int plan_max_wg(Grid3 g) {
   const int tys[] = {4, 8, 16};
   for (int ty : tys) m = std::max(m, tiled_shape(g, ty, 1).nwg);
   m = std::max(m, tiled2_shape(g, 8, 1).nwg);
-  for (int waves : {4, 8, 16})
-    for (int v : {1, 2})
-      if (pair_fits(g, waves, v, 1)) m = std::max(m, pair_shape(g, waves, v, 1).nwg);
   return m;
 }
 
@@ -263,7 +243,7 @@ hipError_t launch_plan(Grid3 g, const StepPlan& plan, const StepBuffers& b, cons
                        hipStream_t st) {
   if (plan.kind == kStepNaive) return launch_step_naive(g, b, K, st);
   if (plan.pv)
-    return launch_step_pair(pair_shape(g, plan.ty, plan.pv, plan.xc), g, b, K, kPairFull, nullptr,
+    return launch_step_pair(pair_shape(g, plan.ty, plan.pv, plan.xc), g, b, kPairFull, nullptr,
                             plan.store, st);
   if (plan.depth == 2)
     return launch_step_tiled2(tiled2_shape(g, plan.ty, plan.xc), g, b, K, plan.store, st);
@@ -276,7 +256,7 @@ hipError_t launch_plan(Grid3 g, const StepPlan& plan, const StepBuffers& b, cons
 hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuffers& b,
                                    float* hi_mid, const StepConst& K, hipStream_t st) {
   if (plan.pv)
-    return launch_step_pair(pair_shape(g, plan.ty, plan.pv, plan.xc), g, b, K, kPairTemp, hi_mid,
+    return launch_step_pair(pair_shape(g, plan.ty, plan.pv, plan.xc), g, b, kPairTemp, hi_mid,
                             plan.store, st);
   if (plan.kind != kStepNaive && plan.depth == 1 && plan.zv > 1)
     return launch_step_wide_temperature(plan.zv, wide_shape(g, plan.zv, plan.ty, plan.xc), g, b,
@@ -313,7 +293,7 @@ rfa_status run_steps(Grid3 g, const StepPlan& plan, StepState& s, const StepCons
     b.codes = s.codes;
     b.partials = part;
     const hipError_t e =
-        p.pv && s.traj ? launch_step_pair(pair_shape(g, p.ty, p.pv, p.xc), g, b, K, kPairKeep, mid,
+        p.pv && s.traj ? launch_step_pair(pair_shape(g, p.ty, p.pv, p.xc), g, b, kPairKeep, mid,
                                           p.store, st)
                        : launch_plan(g, p, b, K, st);
     if (e != hipSuccess) return e;

@@ -654,8 +654,8 @@ class Grid:
 
 
 class Batch:
-    """Lockstep stepping of several Grid objects (each with its own dt) by
-    one persistent launch per step, the step loop replayed from a hipGraph.
+    """Stepping of several Grid objects together (each with its own dt), two
+    steps per launch where the grids allow it, replayed from a hipGraph.
     The batch borrows the grids: close it before them."""
 
     def __init__(self, grids, dts):

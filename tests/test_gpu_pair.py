@@ -101,3 +101,49 @@ def test_adjoint_over_pair_steps_equals_reference(shape, every, steps):
     for a, b in zip(*out):
         assert np.array_equal(a, b)
     assert np.abs(out[0][2]).max() > 0
+
+
+@pytest.mark.parametrize("n_min, n_max, diag", [(24, 40, True), (40, 64, False), (90, 120, True),
+                                                (130, 140, False)])
+def test_batch_of_pair_launches_equals_single_grids(n_min, n_max, diag):
+    """The batch's default launches (two steps each) for every kind of
+    work-group, with and without perfusion fields, odd and even counts over a
+    reduction boundary, and after a grid was given another tissue."""
+    cases = [W.case_planning_instance(i, n_min=n_min, n_max=n_max, base_seed=4700)
+             for i in range(3)]
+
+    def grids():
+        out = []
+        for k, c in enumerate(cases):
+            g = rfa.Grid(c.shape, c.spacing)
+            g.load_case(c)
+            if k == 1:
+                g.set_perfusion(np.random.default_rng(2).uniform(0.5, 2.0, c.shape)
+                                .astype(np.float32))
+            out.append(g)
+        return out
+
+    alone, batched = grids(), grids()
+    dts = [0.9 * min(c.dt, g.dt_max()) for c, g in zip(cases, alone)]
+    b = rfa.Batch(batched, dts)
+    for n in (5, 131, 2):
+        d1 = [g.step(n, dt, diag=diag) for g, dt in zip(alone, dts)]
+        d2 = b.step(n, diag=diag)
+        for i, (g1, g2) in enumerate(zip(alone, batched)):
+            for a1, a2 in zip(g1.raw_state(), g2.raw_state()):
+                assert np.array_equal(a1, a2), (n, i)
+            assert np.array_equal(g1.omega(), g2.omega())
+            if diag:
+                assert d1[i]["mono_violations"] == d2[i]["mono_violations"]
+                # FP32 work-group sums in another order
+                scale = abs(d1[i]["injected_J"]) + abs(d1[i]["perfusion_J"])
+                assert abs(d1[i]["perfusion_J"] - d2[i]["perfusion_J"]) <= 1e-6 * scale
+        if n == 5:  # new tissue: the wave codes must follow
+            tissue = [dataclasses.replace(t, k=t.k * (1.0 + 0.1 * k))
+                      for k, t in enumerate(cases[0].tissue)]
+            labels = cases[0].labels[::-1].copy()
+            for g in (alone[0], batched[0]):
+                g.set_tissue(labels, tissue)
+    b.close()
+    for g in alone + batched:
+        g.close()
