@@ -294,7 +294,8 @@ rfa_status rfa_kernel_stats(rfa_grid g, double* kernel_ms, long long* launches,
 /* Adjoint-kernel timing accumulated since the last call (requires
  * rfa_options.time_kernels; kept-trajectory adjoints only, ckpt_every = 0):
  * total milliseconds measured with one pair of HIP events around each
- * adjoint's back-to-back step launches, and the number of those launches.
+ * adjoint's back-to-back step launches, and the number of adjoint steps they
+ * took (two per launch where the forward takes two).
  * Resets the counters.  Either argument may be NULL. */
 rfa_status rfa_adjoint_kernel_stats(rfa_grid g, double* kernel_ms, long long* launches);
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "rfa_kernels.h"
+#include "rfa_pair.h"
 
 namespace rfa {
 
@@ -11,6 +12,7 @@ struct AdjointBuffers {
   const float* lam_in;   // lambda^{n+1}
   float* lam_out;        // lambda^n
   const float* theta;    // theta^n (hi part of the recomputed state)
+  const float* theta_prev;  // theta^{n-1} (two-step kernel)
   const uint8_t* lab;
   const float* perf;     // perfusion multiplier, may be null
   const float* w;        // dL/dOmega^N, zeroed where it cannot act
@@ -22,6 +24,7 @@ struct AdjointBuffers {
   // sacc_all: on every free voxel (when a tine has zero power its density
   // is nonzero where the flagged increment is not)
   bool sacc_all;
+  const uint8_t* codes;  // two-step kernel: wave codes of its shape
 };
 
 hipError_t launch_bspline_eval(Grid3 g, const float* ctrl, int m, float* f, hipStream_t st);
@@ -42,6 +45,12 @@ hipError_t launch_adjoint_step(Grid3 g, const AdjointBuffers& a, const StepConst
 bool adjoint_tiled_fits(Grid3 g, int xc);
 hipError_t launch_adjoint_tiled(Grid3 g, int ty, int xc, const AdjointBuffers& a,
                                 const StepConst& K, hipStream_t st);
+// Two adjoint steps (n, then n - 1) in one launch; bitwise two of the others.
+// The work-groups are the forward's kinds (pair_fits, pair_shape), the
+// chunk length is chosen here.
+int adjoint_pair_chunk(Grid3 g, int waves, int v);
+hipError_t launch_adjoint_pair(const PairShape& s, Grid3 g, const AdjointBuffers& a,
+                               hipStream_t st);
 // partial[t * nblk + b]: per-block sums of g_t(p) sacc_p dt / (rho c)_p.
 hipError_t launch_source_dot(Grid3 g, double dx, double dy, double dz, const uint8_t* lab,
                              const Chord* chords, const int* tine_first, int n_tines,

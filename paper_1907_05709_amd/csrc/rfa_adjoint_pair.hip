@@ -1,0 +1,392 @@
+// rfa_adjoint_pair.hip -- two adjoint steps per pass over memory.
+//
+// The schedule of the two-step forward kernel (rfa_pair_kernel.h): a
+// work-group owns a flat segment of a (y, z) plane with nz halo voxels on
+// either side and marches along x; the first adjoint step (lambda^{n+1} ->
+// lambda^n) is computed on the footprint one plane ahead of the second
+// (lambda^n -> lambda^{n-1}) on the segment, with one barrier per plane.  It moves
+// lambda, the weight, the class byte, the perfusion factor and the
+// accumulators once for two steps (about 18 bytes per voxel-step instead of
+// 29).  Waves whose code gives one class use scalar coefficients: there a
+// held neighbour needs no test, since lambda is 0 on held voxels and adds
+// nothing.  Where such a wave is cold (|theta| below K.cold, so that T_aK +
+// theta = T_aK and 2^x = 1) the damage-rate derivative is one constant.
+//
+// The per-voxel operations and their order are those of adjoint_voxel(), so
+// two steps are bitwise two launches of the one-step kernels.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "rfa_adjoint.h"
+#include "rfa_adjoint_device.h"
+#include "rfa_tile_common.h"
+
+namespace rfa {
+
+namespace {
+
+using namespace tile;
+
+constexpr int kRing = 4;  // register sets: planes x - 1 .. x + 2
+
+template <int NT, int V, int MAXNZ>
+struct AdjPairSmem {
+  static constexpr int P = NT * V;
+  static constexpr int CELLS = P + 2 * MAXNZ;
+  float2 pc[3 * kMaxClasses * kMaxClasses];  // pair table
+  float4 cls[kMaxClasses];
+  float in[2][CELLS];   // lambda^{n+1}: footprint q at nz + q
+  float mid[2][CELLS];  // lambda^n
+  uint8_t lab[kRing][CELLS];
+};
+
+template <int V>
+struct AdjPairPlane {
+  float lam[V], th[V], w[V], pf[V], fa[V], sa[V];
+  unsigned b[V];
+  float hl;
+  unsigned hb, code;
+};
+
+typedef const __attribute__((address_space(4))) float ConstF;
+
+}  // namespace
+
+template <int NT, int V, int MAXNZ, bool PERF>
+__global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx, int ny, int nz,
+                                                        int xc, int seg, int segs, int nwg) {
+  using S = AdjPairSmem<NT, V, MAXNZ>;
+  constexpr int P = S::P;
+  constexpr int NW = NT / 64;
+  __shared__ S sm;
+  const int wg = remap_xcd(blockIdx.x, nwg);
+  const int sg = wg % segs;
+  const int x0 = (wg / segs) * xc;
+  const int x1 = min(x0 + xc, nx);
+  const int xb = max(x0 - 2, 0);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int np = ny * nz;
+  const int f0 = sg * seg;
+
+  __amdgpu_buffer_rsrc_t r_lam, r_lab, r_th, r_tp, r_w, r_pf, r_sa, r_fa, r_out, r_code;
+  {
+    const size_t off = (size_t)xb * np;
+    const size_t rest = (size_t)(nx - xb) * np;
+    r_lam = make_rsrc(a.lam_in + off, rest * 4);
+    r_lab = make_rsrc(a.lab + off, rest);
+    r_th = make_rsrc(a.theta + off, rest * 4);
+    r_tp = make_rsrc(a.theta_prev + off, rest * 4);
+    r_w = make_rsrc(a.w + off, rest * 4);
+    r_pf = PERF ? make_rsrc(a.perf + off, rest * 4) : r_w;
+    r_sa = make_rsrc(a.sacc + off, rest * 4);
+    r_fa = make_rsrc(a.facc + off, rest * 4);
+    r_out = make_rsrc(a.lam_out + off, rest * 4);
+    r_code = make_rsrc(a.codes + (size_t)xb * segs * NW, (size_t)(nx - xb) * segs * NW);
+  }
+
+  unsigned col[V], own4[V];
+  int cell[V];
+  unsigned long long ownm[V];
+  bool wave_owns = false, wave_valid = false;
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const int q = v * NT + ((v & 1) ? (NT - 64 - (tid & ~63)) + (tid & 63) : tid);
+    const int f = f0 - nz + q;
+    const bool valid = f >= 0 && f < np;
+    const bool owned = valid && q >= nz && q < nz + seg;
+    cell[v] = nz + q;
+    col[v] = valid ? (unsigned)f : 0u;
+    own4[v] = owned ? (unsigned)f * 4u : kOob;
+    ownm[v] = __ballot(owned);
+    wave_owns = wave_owns || owned;
+    wave_valid = wave_valid || valid;
+  }
+  const bool do_mid = __ballot(wave_valid) != 0ull;  // uniform
+  const bool do_out = __ballot(wave_owns) != 0ull;   // uniform
+  const bool has_halo = tid < 2 * nz;
+  int hcell = 0;
+  unsigned hoff = kOob;
+  if (has_halo) {
+    const int f = tid < nz ? f0 - 2 * nz + tid : f0 - 2 * nz + P + tid;
+    hcell = tid < nz ? tid : P + tid;
+    if (f >= 0 && f < np) hoff = (unsigned)f;
+  }
+  const unsigned hoff4 = hoff == kOob ? kOob : hoff * 4u;
+  const bool sacc_all = a.sacc_all;
+
+  auto plane_of = [&](int x) { return min(max(x, 0), nx - 1) - xb; };  // uniform
+  auto load = [&](int x, AdjPairPlane<V>& q) {
+    const int so1 = plane_of(x) * np, so4 = so1 * 4;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      q.b[v] = ld_u8(r_lab, col[v], so1);
+      q.lam[v] = ld_f32(r_lam, col[v] * 4u, so4);
+    }
+    q.code = ld_u8(r_code, 0u, (plane_of(x) * segs + sg) * NW + wave);
+    q.hl = ld_f32(r_lam, hoff4, so4);
+    q.hb = ld_u8(r_lab, hoff, so1);
+  };
+  // what only the own steps of plane x need
+  auto load_own = [&](int x, AdjPairPlane<V>& q) {
+    const int so4 = plane_of(x) * np * 4;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      q.th[v] = ld_f32(r_th, col[v] * 4u, so4);
+      q.w[v] = ld_f32(r_w, col[v] * 4u, so4);
+      q.pf[v] = PERF ? ld_f32(r_pf, col[v] * 4u, so4) : 1.0f;
+      q.fa[v] = ld_f32(r_fa, own4[v], so4);
+      q.sa[v] = ld_f32(r_sa, (sacc_all || (q.b[v] & kSource)) ? own4[v] : kOob, so4);
+    }
+  };
+
+  AdjPairPlane<V> ring[kRing];
+  const int xs = x0 - 1;
+  float lp[V];  // lambda^{n+1} of plane x - 1
+  {
+    const int so = plane_of(xs - 1) * np;
+    unsigned b0[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      lp[v] = ld_f32(r_lam, col[v] * 4u, so * 4);
+      b0[v] = ld_u8(r_lab, col[v], so);
+    }
+    load(xs, ring[0]);
+    load(xs + 1, ring[1]);
+    stage_pairs(sm.pc, sm.cls, a.tab, NT);
+    load_own(xs, ring[0]);
+#pragma unroll
+    for (int v = 0; v < V; ++v) sm.lab[3][cell[v]] = (uint8_t)b0[v];
+  }
+#pragma unroll
+  for (int v = 0; v < V; ++v) ring[3].w[v] = 0.0f, ring[3].pf[v] = 1.0f;
+  ring[3].code = 0u;
+  // halo cells of the first-step planes enter only lanes whose results are dropped
+  for (int c = tid; c < 2 * nz; c += NT) {
+    const int e = c < nz ? c : P + c;
+    sm.mid[0][e] = sm.mid[1][e] = 0.0f;
+  }
+  // first-step results of planes x - 1 and x - 2, accumulators of x - 1
+  float m1[V], m2[V], mfa[V], msa[V], tp[V];
+  unsigned mb[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    m1[v] = m2[v] = mfa[v] = msa[v] = tp[v] = 0.0f;
+    mb[v] = kHeld;
+  }
+
+  // One step of this lane's voxels: lambda l of the plane (t: in LDS, with
+  // class bytes tl, those of x - 1 in tpv), its x neighbours lm / ln, class
+  // bytes lb (and bn of x + 1), theta th, weight w.
+  auto step = [&](const float* t, const uint8_t* tl, const uint8_t* tpv, unsigned code,
+                  const float (&l)[V], const float (&lm)[V], const float (&ln)[V],
+                  const unsigned (&lb)[V], const unsigned (&bn)[V], const float (&th)[V],
+                  const float (&w)[V], const float (&pf)[V], float (&nl)[V], float (&sa)[V],
+                  float (&fa)[V]) {
+    uintptr_t tab = (uintptr_t)a.tab;
+    asm volatile("" : "+s"(tab));  // constants are read here, not kept in registers
+    ConstF* q = (ConstF*)tab + offsetof(Tables, K) / 4;
+    StepConst K;
+    K.dtka = q[0];
+    K.c2 = q[1];
+    K.tak = q[2];
+    K.clamp2 = q[3];
+    K.cold = q[7];
+    if (code != kPairIrregular) {
+      ConstF* c = (ConstF*)tab + offsetof(Tables, adj) / 4 + 4 * (code & (kMaxClasses - 1));
+      const float kx = c[0], ky = c[1], kz = c[2], B1 = c[3];
+      bool warm = false;
+      float off[V], diag[V], dr[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const int e = cell[v];
+        diag[v] = 1.0f - (PERF ? B1 * pf[v] : B1);
+        diag[v] -= kx;
+        diag[v] -= kx;
+        diag[v] -= ky;
+        diag[v] -= ky;
+        diag[v] -= kz;
+        diag[v] -= kz;
+        float o = kx * lm[v];
+        o = __builtin_fmaf(kx, ln[v], o);
+        o = __builtin_fmaf(ky, t[e - nz], o);
+        o = __builtin_fmaf(ky, t[e + nz], o);
+        o = __builtin_fmaf(kz, t[e - 1], o);
+        off[v] = __builtin_fmaf(kz, t[e + 1], o);
+        warm = warm || !(fabsf(th[v]) < K.cold);
+      }
+      const float kr = K.c2 * 0.69314718f;
+      const float r0 = __builtin_amdgcn_rcpf(K.tak);
+      const float cold = K.dtka * kr * K.tak * (r0 * r0);
+#pragma unroll
+      for (int v = 0; v < V; ++v) dr[v] = cold;
+      if (__ballot(warm) != 0ull) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const float r = __builtin_amdgcn_rcpf(K.tak + th[v]);
+          const float x = K.c2 * th[v] * r;
+          const float rate = K.dtka * __builtin_amdgcn_exp2f(fminf(x, K.clamp2));
+          const float dr0 = rate * kr * K.tak * (r * r);
+          dr[v] = x < K.clamp2 ? dr0 : 0.0f;
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const bool held = (lb[v] & kHeld) != 0u;
+        const float d = (lb[v] & kTissue) ? dr[v] : 0.0f;
+        const float lo = __builtin_fmaf(diag[v], l[v], off[v]) + w[v] * d;
+        nl[v] = held ? 0.0f : lo;
+        sa[v] = held ? sa[v] : sa[v] + l[v];
+        fa[v] = held ? fa[v] : __builtin_fmaf(-B1, th[v] * l[v], fa[v]);
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const int e = cell[v];
+        const float nlam[6] = {lm[v], ln[v], t[e - nz], t[e + nz], t[e - 1], t[e + 1]};
+        const unsigned nlab[6] = {tpv[e], bn[v], tl[e - nz], tl[e + nz], tl[e - 1], tl[e + 1]};
+        const float2* pc = sm.pc;
+        adjoint_voxel(
+            l[v], th[v], lb[v], pf[v], w[v], nlam, nlab,
+            [pc](int ax, unsigned cq, unsigned cp) { return pair_from_pairs(pc, ax, cq, cp); },
+            sm.cls, K, nl[v], sa[v], fa[v]);
+      }
+    }
+  };
+
+  auto publish = [&](auto SL_, const AdjPairPlane<V>& q) {
+    constexpr int SL = decltype(SL_)::value;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      sm.in[SL & 1][cell[v]] = q.lam[v];
+      sm.lab[SL][cell[v]] = (uint8_t)q.b[v];
+    }
+    if (has_halo) {
+      sm.in[SL & 1][hcell] = q.hl;
+      sm.lab[SL][hcell] = (uint8_t)q.hb;
+    }
+  };
+
+  // The buffers' reuse is that of the forward kernel: what iteration x writes
+  // was last read before its barrier.
+  auto iterate = [&](auto SL_, int x) {
+    constexpr int SL = decltype(SL_)::value;  // plane x
+    constexpr int SP = (SL + 3) % kRing;      // plane x - 1
+    constexpr int SN = (SL + 1) % kRing;      // plane x + 1
+    constexpr int SA = (SL + 2) % kRing;      // receives plane x + 2; in LDS still x - 2
+    constexpr int BUF = SL & 1;
+    AdjPairPlane<V>& C = ring[SL];
+    AdjPairPlane<V>& N = ring[SN];
+    const AdjPairPlane<V>& B = ring[SP];
+    __syncthreads();
+    load(x + 2, ring[SA]);
+    const unsigned code = __builtin_amdgcn_readfirstlane(C.code);
+    const unsigned pcode = __builtin_amdgcn_readfirstlane(B.code);
+    float n1[V], fa[V], sa[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      n1[v] = 0.0f;
+      fa[v] = C.fa[v];
+      sa[v] = C.sa[v];
+    }
+    if (do_mid)
+      step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C.lam, lp, N.lam, C.b, N.b, C.th, C.w, C.pf,
+           n1, sa, fa);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      lp[v] = C.lam[v];
+      sm.mid[BUF][cell[v]] = n1[v];
+    }
+    publish(std::integral_constant<int, SN>{}, N);
+    load_own(x + 1, N);
+    float tn[V];  // theta^{n-1} of plane x, for the next iteration
+#pragma unroll
+    for (int v = 0; v < V; ++v) tn[v] = ld_f32(r_tp, own4[v], plane_of(x) * np * 4);
+    {
+      float o[V];
+      const bool out = x > x0;  // uniform: plane x - 1 is in the chunk
+#pragma unroll
+      for (int v = 0; v < V; ++v) o[v] = 0.0f;
+      if (do_out && out)
+        step(sm.mid[BUF ^ 1], sm.lab[SP], sm.lab[SA], pcode, m1, m2, n1, mb, C.b, tp, B.w, B.pf, o,
+             msa, mfa);
+      const int so4 = plane_of(x - 1) * np * 4;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const unsigned v4 = out ? own4[v] : kOob;
+        st_f32(o[v], r_out, v4, so4);
+        st_f32(mfa[v], r_fa, v4, so4);
+        st_f32(msa[v], r_sa, (sacc_all || (mb[v] & kSource)) ? v4 : kOob, so4);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      m2[v] = m1[v];
+      m1[v] = n1[v];
+      mfa[v] = fa[v];
+      msa[v] = sa[v];
+      tp[v] = tn[v];
+      mb[v] = C.b[v];
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  static_assert(kRing == 4, "unrolled for a ring of four planes");
+  publish(I0{}, ring[0]);
+  for (int x = xs;; x += kRing) {
+    iterate(I0{}, x);
+    if (x + 1 > x1) break;
+    iterate(I1{}, x + 1);
+    if (x + 2 > x1) break;
+    iterate(I2{}, x + 2);
+    if (x + 3 > x1) break;
+    iterate(I3{}, x + 3);
+    if (x + 4 > x1) break;
+  }
+}
+
+namespace {
+
+template <int NT, int V, int MAXNZ>
+hipError_t launch_kind(const PairShape& s, Grid3 g, const AdjointBuffers& a, hipStream_t st) {
+  const dim3 grid(s.nwg), block(NT);
+  if (a.perf)
+    hipLaunchKernelGGL((k_adjoint_pair<NT, V, MAXNZ, true>), grid, block, 0, st, a, g.nx, g.ny,
+                       g.nz, s.xc, s.seg, s.segs, s.nwg);
+  else
+    hipLaunchKernelGGL((k_adjoint_pair<NT, V, MAXNZ, false>), grid, block, 0, st, a, g.nx, g.ny,
+                       g.nz, s.xc, s.seg, s.segs, s.nwg);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+int adjoint_pair_chunk(Grid3 g, int waves, int v) {
+  int best = 1;
+  double least = 1e300;
+  for (int xc = 1; xc <= std::min(g.nx, 64); ++xc) {
+    if (!pair_fits(g, waves, v, xc)) break;
+    const double us = pair_estimate(waves, v, pair_shape(g, waves, v, xc).nwg, xc);
+    if (us < least) {
+      least = us;
+      best = xc;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_adjoint_pair(const PairShape& s, Grid3 g, const AdjointBuffers& a,
+                               hipStream_t st) {
+  if (!pair_fits(g, s.waves, s.v, s.xc) || !a.codes || !a.theta_prev) return hipErrorInvalidValue;
+  if (s.waves == 16 && s.v == 2) return launch_kind<1024, 2, 256>(s, g, a, st);
+  if (s.waves == 8 && s.v == 2) return launch_kind<512, 2, 128>(s, g, a, st);
+  if (s.waves == 8 && s.v == 1) return launch_kind<512, 1, 128>(s, g, a, st);
+  if (s.waves == 4 && s.v == 1) return launch_kind<256, 1, 96>(s, g, a, st);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace rfa

@@ -282,6 +282,13 @@ void build_tables(rfa_grid g, double dt) {
     split(dt * ta.h_perf / rc, bh, bl);
     T.cls[a] = make_float4(bh, bl, (float)(dt * ta.q_met / rc), (float)(rc * vol));
   }
+  for (int a = 0; a < g->n_classes; ++a) {
+    auto own = [&](int ax) {
+      const float2 c = T.cf[ax][a * kMaxClasses + a];
+      return c.x + c.y;
+    };
+    T.adj[a] = make_float4(own(0), own(1), own(2), T.cls[a].x + T.cls[a].y);
+  }
   T.K = step_const(g, dt);
 }
 
@@ -296,9 +303,10 @@ StepConst step_const(rfa_grid g, double dt) {
   K.thr = (float)(g->opt.t_death - 37.0);
   K.decay2 = g->perf_decay ? (float)M_LOG2E : 0.0f;
   // |exponent| = c2 |theta| / (T_aK + theta) below 2^-29, where 2^x rounds
-  // to 1 whatever its sign
+  // to 1 whatever its sign, and |theta| below half an ulp of T_aK (1.5e-5), so
+  // that T_aK + theta rounds to T_aK
   const double c2 = c * M_LOG2E;
-  K.cold = (float)(c2 > 0.0 ? std::min(1.0, std::ldexp(0.5 * kTBodyK / c2, -29)) : 1.0);
+  K.cold = (float)(c2 > 0.0 ? std::min(1e-5, std::ldexp(0.5 * kTBodyK / c2, -29)) : 1e-5);
   return K;
 }
 
@@ -1779,22 +1787,43 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
   // zero power (its density then reaches voxels whose increment is 0)
   bool sacc_all = false;
   for (double p : g->power) sacc_all = sacc_all || !(p > 0.0);
-  // adjoint step from theta^t = traj[t]
-  auto adjoint_step = [&](const float* theta) {
-    AdjointBuffers a;
-    a.lam_in = lam[lc];
-    a.lam_out = lam[1 - lc];
-    a.theta = theta;
-    a.lab = g->lab;
-    a.perf = g->perf;
-    a.w = wv;
-    a.tab = g->tab_dev;
-    a.sacc = sacc;
-    a.facc = facc;
-    a.sacc_all = sacc_all;
-    lc = 1 - lc;
-    return tiled_adj ? launch_adjoint_tiled(g->g, adj_ty, adj_xc, a, K, g->st)
-                     : launch_adjoint_step(g->g, a, K, g->st);
+  // two adjoint steps per launch where the forward takes two
+  const bool pair_adj = g->plan.pv != 0;
+  PairShape adj_shape;
+  if (pair_adj) {
+    if ((s = ensure_pair(g, g->plan)) != RFA_OK) return s;
+    adj_shape = pair_shape(g->g, g->plan.ty, g->plan.pv,
+                           adjoint_pair_chunk(g->g, g->plan.ty, g->plan.pv));
+  }
+  // adjoint steps t1 .. t0 (descending) from theta^t = traj[t]
+  auto adjoint_steps = [&](const float* traj, int t1, int t0) -> hipError_t {
+    for (int t = t1; t >= t0;) {
+      AdjointBuffers a{};
+      a.lam_in = lam[lc];
+      a.lam_out = lam[1 - lc];
+      a.theta = traj + (size_t)t * n;
+      a.lab = g->lab;
+      a.perf = g->perf;
+      a.w = wv;
+      a.tab = g->tab_dev;
+      a.sacc = sacc;
+      a.facc = facc;
+      a.sacc_all = sacc_all;
+      a.codes = g->codes;
+      lc = 1 - lc;
+      hipError_t e;
+      if (pair_adj && t > t0) {
+        a.theta_prev = a.theta - n;
+        e = launch_adjoint_pair(adj_shape, g->g, a, g->st);
+        t -= 2;
+      } else {
+        e = tiled_adj ? launch_adjoint_tiled(g->g, adj_ty, adj_xc, a, K, g->st)
+                      : launch_adjoint_step(g->g, a, K, g->st);
+        --t;
+      }
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   };
   if (every == 0) {  // the forward kept every theta^t: no recomputation
     // with time_kernels, one event pair brackets the back-to-back launches
@@ -1803,8 +1832,7 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
       if ((s = ensure_events(g, 2)) != RFA_OK) return s;
       HIP_TRY(hipEventRecord(g->events[0], g->st));
     }
-    for (int t = g->adj_steps - 1; t >= 0; --t)
-      HIP_TRY(adjoint_step(g->traj + (size_t)t * n));
+    HIP_TRY(adjoint_steps(g->traj, g->adj_steps - 1, 0));
     if (timed) {
       float ms = 0.0f;
       HIP_TRY(hipEventRecord(g->events[1], g->st));
@@ -1841,7 +1869,7 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
       const float* c = g->ckpt + (size_t)seg * 2 * n;
       if (seg == g->adj_nckpt - 1 && g->adj_tail_kept) {
         // written by the forward itself: no recompute
-        for (int t = k - 1; t >= 0; --t) HIP_TRY(adjoint_step(traj + (size_t)t * n));
+        HIP_TRY(adjoint_steps(traj, k - 1, 0));
         HIP_TRY(hipEventRecord(read[half], g->st));
         used[half] = true;
         continue;
@@ -1871,7 +1899,7 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
       }
       HIP_TRY(hipEventRecord(ready[half], g->side));
       HIP_TRY(hipStreamWaitEvent(g->st, ready[half], 0));
-      for (int t = k - 1; t >= 0; --t) HIP_TRY(adjoint_step(traj + (size_t)t * n));
+      HIP_TRY(adjoint_steps(traj, k - 1, 0));
       HIP_TRY(hipEventRecord(read[half], g->st));
       used[half] = true;
     }

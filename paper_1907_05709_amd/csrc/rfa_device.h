@@ -52,14 +52,19 @@ struct StepConst {
   float cap;     // Omega cap
   float thr;     // t_death - 37
   float decay2;  // log2(e) with damage-coupled perfusion, else 0
-  float cold;    // |theta| below which the damage exponent rounds to 2^0 = 1
+  float cold;    // |theta| below which 2^x of the damage exponent x and T_aK + theta
+                 // round to 1 and T_aK
 };
 
 // Per-dt coefficient tables, staged into LDS by every work-group.
 struct Tables {
   float2 cf[3][kMaxClasses * kMaxClasses];  // [axis][a*16+b] = C(a,b) hi/lo
   float4 cls[kMaxClasses];                  // {B hi, B lo, Qs, rho c V}
-  StepConst K;  // for kernels that read their constants through the scalar cache
+  // for kernels that read uniform values through the scalar cache: the step
+  // constants, and per class the adjoint's coefficients {C(a,a) along x, y, z,
+  // B}, each float-float value rounded to float
+  StepConst K;
+  float4 adj[kMaxClasses];
 };
 
 // Per-thread diagnostic partials of one step.

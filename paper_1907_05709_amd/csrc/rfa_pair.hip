@@ -5,11 +5,12 @@
 namespace rfa {
 
 // Wave codes: for plane x, segment and wave of the footprint, the class that
-// all its free voxels share if every neighbour has that class's
-// conductivity (0 without free voxels) and which of its voxels are tissue;
-// kPairIrregular if neither holds.  The face coefficients of such a wave are all
-// C(c, c): the harmonic mean of equal conductivities over the own class's
-// heat capacity.
+// all its free voxels share if every neighbour has that class's conductivity
+// and every free one its heat capacity (0 without free voxels), and which of
+// its voxels are tissue; kPairIrregular otherwise.  The coefficients of such a
+// wave's free voxels are all C(c, c), the harmonic mean of equal
+// conductivities over equal heat capacities: those of their own rows, and
+// (for the adjoint) those of their free neighbours'.
 __global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, const ClassParams* cp,
                                                     int nx, int ny, int nz, int nt, int v, int seg,
                                                     int segs, size_t n_codes, uint8_t* codes) {
@@ -35,10 +36,12 @@ __global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, const Cl
       if (!(p[0] & kHeld)) {  // free voxels are never on the outer layer
         free = true;
         c = class_of(p[0]);
-        const double k = cp->k[c];
-        ok = cp->k[class_of(p[-1])] == k && cp->k[class_of(p[1])] == k &&
-             cp->k[class_of(p[-nz])] == k && cp->k[class_of(p[nz])] == k &&
-             cp->k[class_of(p[-(ptrdiff_t)np])] == k && cp->k[class_of(p[np])] == k;
+        const double k = cp->k[c], rc = cp->rc[c];
+        auto same = [&](ptrdiff_t o) {
+          const unsigned q = p[o], cq = class_of(q);
+          return cp->k[cq] == k && ((q & kHeld) || cp->rc[cq] == rc);
+        };
+        ok = same(-1) && same(1) && same(-nz) && same(nz) && same(-(ptrdiff_t)np) && same(np);
       }
     }
     none = none && __ballot(tissue) == 0ull;

@@ -80,21 +80,39 @@ def test_pair_kernel_bitwise_equals_reference(shape, kind, form, kw):
         g.close()
 
 
-@pytest.mark.parametrize("shape, every, steps", [((24, 30, 33), 5, 23), ((20, 40, 150), 8, 24),
-                                                 ((20, 40, 150), 0, 9)])
-def test_adjoint_over_pair_steps_equals_reference(shape, every, steps):
+@pytest.mark.parametrize("shape, kind, every, steps, spline, off", [
+    ((24, 30, 33), "regions", 5, 23, True, False),
+    ((20, 40, 150), "regions", 8, 24, True, False),
+    ((20, 40, 150), "held_tissue", 0, 9, False, False),
+    ((13, 21, 64), "random", 3, 10, True, True),
+    ((40, 64, 128), "regions", 0, 6, True, False),
+    ((60, 50, 70), "tissue_everywhere", 4, 9, False, True),
+])
+def test_adjoint_over_pair_steps_equals_reference(shape, kind, every, steps, spline, off):
     """Kept trajectories, checkpoints and recomputed segments (odd and even
-    lengths) of the two-step kernel give the reference kernels' gradients."""
-    case = _case("regions", shape, 9)
+    lengths) and the two-step adjoint give the reference kernels' gradients,
+    also with a tine switched off (its density reaches voxels without
+    source)."""
+    case = _case(kind, shape, 9)
+    power = case.needle.power.copy()
+    if off:
+        power[0] = 0.0
     out = []
     for kw in (dict(kernel=1), {}):
         g = rfa.Grid(case.shape, case.spacing, **kw)
         g.load_case(case)
-        g.set_perfusion_bspline(np.linspace(-0.3, 0.3, 125, dtype=np.float32).reshape(5, 5, 5))
-        g.forward_checkpointed(steps, 0.04, every)
+        if spline:
+            g.set_perfusion_bspline(np.linspace(-0.3, 0.3, 125, dtype=np.float32)
+                                    .reshape(5, 5, 5))
+        g.set_tine_powers(power)
+        dt = 0.9 * min(case.dt, g.dt_max())
+        g.forward_checkpointed(steps, dt, every)
         w = np.random.default_rng(4).uniform(0.5, 1.0, shape).astype(np.float32)
-        out.append((g.temperature(), g.omega()) + g.adjoint(w, 1, 5, want_dperf=True))
-        again = g.adjoint(w, 1, 5, want_dperf=True)
+        m = 5 if spline else 0
+        out.append((g.temperature(), g.omega())
+                   + tuple(x for x in g.adjoint(w, len(power), m, want_dperf=True)
+                           if x is not None))
+        again = [x for x in g.adjoint(w, len(power), m, want_dperf=True) if x is not None]
         for a, b in zip(out[-1][2:], again):
             assert np.array_equal(a, b)
         g.close()
