@@ -69,7 +69,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int np = ny * nz;
-  const int f0 = sg * seg;
+  const int fp = sg * seg;  // first voxel of the footprint; the segment starts a row later
 
   __amdgpu_buffer_rsrc_t r_lam, r_lab, r_th, r_tp, r_w, r_pf, r_sa, r_fa, r_out, r_code;
   {
@@ -94,9 +94,12 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     const int q = v * NT + ((v & 1) ? (NT - 64 - (tid & ~63)) + (tid & 63) : tid);
-    const int f = f0 - nz + q;
-    const bool valid = f >= 0 && f < np;
-    const bool owned = valid && q >= nz && q < nz + seg;
+    const int f = fp + q;
+    const bool valid = f < np;
+    // the plane's first and last rows are held (outer layer): they belong to
+    // the first and last segment, as part of their halo
+    const bool rows = (sg == 0 && f < nz) || (sg == segs - 1 && f >= np - nz);
+    const bool owned = valid && (rows || (q >= nz && q < nz + seg && f < np - nz));
     cell[v] = nz + q;
     col[v] = valid ? (unsigned)f : 0u;
     own4[v] = owned ? (unsigned)f * 4u : kOob;
@@ -110,7 +113,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
   int hcell = 0;
   unsigned hoff = kOob;
   if (has_halo) {
-    const int f = tid < nz ? f0 - 2 * nz + tid : f0 - 2 * nz + P + tid;
+    const int f = tid < nz ? fp - nz + tid : fp - nz + P + tid;
     hcell = tid < nz ? tid : P + tid;
     if (f >= 0 && f < np) hoff = (unsigned)f;
   }

@@ -9,8 +9,10 @@
 namespace rfa {
 
 // Footprint of a work-group of the two-step kernel: waves * 64 * v
-// consecutive voxels of a (y, z) plane, of which it owns seg (the plane's
-// segments are seg voxels apart) and nz on either side are its halo.
+// consecutive voxels of a (y, z) plane, starting at a multiple of seg; its
+// segment, seg voxels, starts one row (nz voxels) later, and nz voxels on
+// either side are its halo.  The plane's first and last rows, which are held,
+// lie in the halo of the first and the last segment and are stored by them.
 struct PairShape {
   int waves = 0;   // wavefronts per work-group
   int v = 0;       // voxels per lane

@@ -26,8 +26,8 @@ __global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, const Cl
   bool none = true, only_free = true, all = true;  // which voxels are tissue
   for (int j = 0; j < v; ++j) {
     // the kernel's mapping: odd j runs through the waves in reverse
-    const int f = sg * seg - nz + j * nt + ((j & 1) ? nw - 1 - wave : wave) * 64 + lane;
-    const bool valid = f >= 0 && f < np;
+    const int f = sg * seg + j * nt + ((j & 1) ? nw - 1 - wave : wave) * 64 + lane;
+    const bool valid = f < np;
     bool free = false, ok = true, tissue = false;
     unsigned c = 0u;
     if (valid) {
@@ -124,9 +124,11 @@ PairShape pair_shape(Grid3 g, int waves, int v, int xc) {
   s.xc = xc;
   const int np = g.ny * g.nz;
   const int most = (64 * waves * v - 2 * g.nz) / 32 * 32;
-  s.segs = (np + most - 1) / most;
-  s.seg = ((np + s.segs - 1) / s.segs + 31) / 32 * 32;
-  s.segs = (np + s.seg - 1) / s.seg;
+  // the plane's first and last rows are held and go along as halo
+  const int inner = np - 2 * g.nz;
+  s.segs = (inner + most - 1) / most;
+  s.seg = ((inner + s.segs - 1) / s.segs + 31) / 32 * 32;
+  s.segs = (inner + s.seg - 1) / s.seg;
   s.chunks = (g.nx + xc - 1) / xc;
   s.nwg = s.segs * s.chunks;
   return s;

@@ -27,6 +27,16 @@
 //    scalars: no neighbour class bytes, no table reads.  Where such a wave
 //    is also cold (|theta| below K.cold everywhere, so that the damage
 //    exponent rounds to 2^0), the transcendentals are skipped.
+//
+// What bounds it: vector instructions, about 72 a voxel step (86 with sums)
+// issued at some 70 % of the rate of the chip; the first step on halo rows
+// and planes is computed twice, so the footprint is trimmed to what the
+// second step reads (held rows at a plane's ends belong to nobody's segment,
+// and halo voxels pass on a temperature but no damage, latch or sum:
+// 128^3 12.9 -> 12.2 us a step, 256^3 60.6 -> 59.3).  Against one step a
+// pass (us a step, with sums): 32^3 6.0 -> 3.4, 64^3 6.4 -> 5.0, 96^3
+// 12.0 -> 8.0, 128^3 13.3 -> 12.2, 161x149x117 without sums 20.6 -> 13.4,
+// 160x152x144 coupled 35.7 -> 18.5, 256x256x234 91 -> 59.6, 256^3 80 -> 66.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -136,7 +146,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int np = ny * nz;
   const unsigned psz = (unsigned)np;
-  const int f0 = sg * seg;
+  const int fp = sg * seg;  // first voxel of the footprint; the segment starts a row later
 
   __amdgpu_buffer_rsrc_t r_hi, r_lo, r_lab, r_src, r_om, r_omo, r_pf, r_hio, r_loo, r_mid, r_code;
   {
@@ -167,10 +177,13 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     // ends, which hold only halo voxels, are the same ones and skip the
     // second step
     const int q = v * NT + ((v & 1) ? (NT - 64 - (tid & ~63)) + (tid & 63) : tid);
-    const int f = f0 - nz + q;
-    const bool valid = f >= 0 && f < np;
+    const int f = fp + q;
+    const bool valid = f < np;
     cell[v] = nz + q;
-    const bool owned = valid && q >= nz && q < nz + seg;
+    // the plane's first and last rows are held (outer layer): they belong to
+    // the first and last segment, as part of their halo
+    const bool rows = (sg == 0 && f < nz) || (sg == segs - 1 && f >= np - nz);
+    const bool owned = valid && (rows || (q >= nz && q < nz + seg && f < np - nz));
     ownm[v] = __ballot(owned);
     col[v] = valid ? (unsigned)f : 0u;
     own4[v] = owned ? (unsigned)f * 4u : kOob;
@@ -186,7 +199,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   int hcell = 0;
   unsigned hoff = kOob;
   if (has_halo) {
-    const int f = tid < nz ? f0 - 2 * nz + tid : f0 - 2 * nz + P + tid;
+    const int f = tid < nz ? fp - nz + tid : fp - nz + P + tid;
     hcell = tid < nz ? tid : P + tid;
     if (f >= 0 && f < np) hoff = (unsigned)f;
   }
@@ -265,17 +278,19 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   // One step of this lane's V voxels.  t: plane in LDS, h/l/b/om: own
   // values, dn: difference to x + 1, dp: difference of x - 1 to the plane
   // (both from registers), tl / tp: class bytes of the plane and of x - 1 in
-  // LDS, bn: of x + 1,
-  // heldm: lanes whose voxel is held, counted: the owned free voxels' sums count.
+  // LDS, bn: of x + 1, heldm: lanes whose voxel is held, own: damage, latches
+  // and sums are wanted.  They are where the plane and some of the wave's
+  // voxels are the work-group's own; halo voxels pass on their temperature
+  // alone.
   auto step = [&](const float2* t, const uint8_t* tl, const uint8_t* tp, unsigned code,
                   const float (&h)[V],
                   const float (&l)[V], const unsigned (&lb)[V], float (&om)[V],
                   const float (&s)[V], const float (&pf)[V], const float (&dn)[V],
                   const float (&dp)[V], const unsigned (&bn)[V],
-                  const unsigned long long (&heldm)[V], bool counted, float (&nh)[V], float (&nl)[V],
+                  const unsigned long long (&heldm)[V], bool own, float (&nh)[V], float (&nl)[V],
                   unsigned (&nb)[V]) {
     const StepConst K = step_constants(b.tab);
-    auto cntm = [&](int v) { return counted ? ownm[v] & ~heldm[v] : 0ull; };
+    auto cntm = [&](int v) { return ownm[v] & ~heldm[v]; };
     float f[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -299,7 +314,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
         const bool held = lane_of(heldm[v]);
         nh[v] = held ? h[v] : h2;
         nl[v] = held ? l[v] : l2;
-        if constexpr (DIAG) {
+        if (DIAG && own) {
           // lanes that do not count add 0 times a finite term
           const float w = lane_of(cntm(v)) ? coef.c.w : 0.0f;
           acc.perf = __builtin_fmaf(w, perf, acc.perf);
@@ -310,11 +325,11 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
         hot = hot || nh[v] >= K.thr;
         nb[v] = lb[v];
       }
-      if (DIAG && __ballot(falls) != 0ull) {
+      if (DIAG && own && __ballot(falls) != 0ull) {
 #pragma unroll
         for (int v = 0; v < V; ++v) mono += __popcll(__ballot(cools(h[v], incs[v])) & cntm(v));
       }
-      if constexpr (!TEMP) {
+      if (!TEMP && own) {
         float rate[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) rate[v] = K.dtka;
@@ -356,14 +371,14 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
         const bool held = lane_of(heldm[v]);
         nh[v] = held ? h[v] : h2;
         nl[v] = held ? l[v] : l2;
-        if constexpr (DIAG) {
+        if (DIAG && own) {
           const float w = lane_of(cntm(v)) ? c4.w : 0.0f;
           acc.perf = __builtin_fmaf(w, perf, acc.perf);
           acc.bnd = __builtin_fmaf(w, cond, acc.bnd);
           mono += __popcll(__ballot(cools(h[v], inc)) & cntm(v));
         }
         nb[v] = lb[v];
-        if constexpr (!TEMP) {
+        if (!TEMP && own) {
           om[v] = damage_add<true>(om[v], damage_increment(h[v], K), (lb[v] & kTissue) != 0u, K);
           nb[v] = latch(lb[v], nh[v], nl[v], K);
         }
@@ -414,7 +429,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     }
     if (do_mid)
       step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C.h, C.l, C.b, nom, C.s, C.pf, dn, din, N.b,
-           held, in_chunk, nh, nl, nb);
+           held, do_out && in_chunk, nh, nl, nb);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       din[v] = dn[v];
