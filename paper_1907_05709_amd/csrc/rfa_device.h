@@ -119,8 +119,9 @@ __device__ __forceinline__ void thermal_update(float hi, float lo, const float2 
   const float s1 = hi + t;
   const float v = s1 - hi;
   const float e = (hi - (s1 - v)) + (t - v);
-  h2 = s1 + e;
-  l2 = e - (h2 - s1);
+  // e is the exact error of s1, at most half its ulp: the pair is normalised
+  h2 = s1;
+  l2 = e;
 }
 
 // Whether a free voxel's increment counts as cooling.

@@ -28,15 +28,19 @@
 //    is also cold (|theta| below K.cold everywhere, so that the damage
 //    exponent rounds to 2^0), the transcendentals are skipped.
 //
-// What bounds it: vector instructions, about 72 a voxel step (86 with sums)
-// issued at some 70 % of the rate of the chip; the first step on halo rows
-// and planes is computed twice, so the footprint is trimmed to what the
-// second step reads (held rows at a plane's ends belong to nobody's segment,
-// and halo voxels pass on a temperature but no damage, latch or sum:
-// 128^3 12.9 -> 12.2 us a step, 256^3 60.6 -> 59.3).  Against one step a
-// pass (us a step, with sums): 32^3 6.0 -> 3.4, 64^3 6.4 -> 5.0, 96^3
-// 12.0 -> 8.0, 128^3 13.3 -> 12.2, 161x149x117 without sums 20.6 -> 13.4,
-// 160x152x144 coupled 35.7 -> 18.5, 256x256x234 91 -> 59.6, 256^3 80 -> 66.
+// What bounds it: vector instructions, issued at some three quarters of the
+// chip's rate (256^3: about 210 a wave and plane for two steps of two voxels,
+// 87 scalar ones beside them); uniform branches cost as much as the few
+// instructions they skip, so there are few.  The first step on halo rows and
+// planes is computed twice, so the footprint is trimmed to what the second
+// step reads: held rows at a plane's ends belong to nobody's segment, and
+// halo voxels pass on a temperature but no damage, latch or sum (128^3 12.9
+// -> 12.2 us a step).  Planes are updated in place in their registers, and
+// what few waves need is selected by lane masks (256^3 without sums 59 ->
+// 56.5, 192^3 26.4 -> 25.1).  Against one step a pass (us a step, with
+// sums): 32^3 6.0 -> 3.4, 64^3 6.4 -> 5.0, 96^3 12.0 -> 7.7, 128^3 13.3 ->
+// 11.8, 161x149x117 without sums 20.6 -> 12.7, 160x152x144 coupled 35.7 ->
+// 17.9, 256x256x234 91 -> 57.4, 256^3 80 -> 62.8.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -60,9 +64,9 @@ struct PairSmem {
   static constexpr int CELLS = P + 2 * MAXNZ;
   float2 cf[3 * kMaxClasses * kMaxClasses];
   float4 cls[kMaxClasses];
+  uint8_t lab[kPairRing][CELLS];
   float2 in[2][CELLS];    // input planes: footprint q at nz + q
   float2 mid[2][CELLS];   // first-step planes, footprint q at nz + q (halo cells unused)
-  uint8_t lab[kPairRing][CELLS];
   float red[3 * NT / 64];
 };
 
@@ -191,7 +195,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     wave_valid = wave_valid || valid;
   }
   const bool do_mid = __ballot(wave_valid) != 0ull;  // uniform
-  const bool do_out = __ballot(wave_owns) != 0ull;   // uniform
+  const unsigned long long out_lanes = __ballot(wave_owns);  // 0: the wave stores nothing
 
   // Halo element: the nz voxels before and after the footprint.  Elements
   // outside the plane stand next to held voxels only: any finite value.
@@ -252,18 +256,15 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
 #pragma unroll
     for (int v = 0; v < V; ++v) din[v] = ff_diff(ring[0].h[v], ring[0].l[v], ph[v], pl[v]);
   }
-  // first-step results of the plane before: temperature, damage, class byte
-  float mh[V], ml[V], mom[V];
-  unsigned mb[V];
-  unsigned long long mheld[V];  // held lanes of that plane
+  unsigned long long mheld[V];  // held lanes of the plane before
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    mh[v] = ml[v] = mom[v] = dmid[v] = 0.0f;
-    mb[v] = 0u;
+    dmid[v] = 0.0f;
     mheld[v] = 0ull;
+    ring[3].h[v] = ring[3].l[v] = ring[3].om[v] = ring[3].s[v] = 0.0f;
+    ring[3].pf[v] = 1.0f;
+    ring[3].b[v] = 0u;
   }
-#pragma unroll
-  for (int v = 0; v < V; ++v) ring[3].s[v] = 0.0f, ring[3].pf[v] = 1.0f;
   ring[3].code = 0u;
 
   Partial acc{0.0f, 0.0f, 0u};
@@ -275,114 +276,118 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     sm.mid[0][e] = sm.mid[1][e] = make_float2(0.0f, 0.0f);
   }
 
-  // One step of this lane's V voxels.  t: plane in LDS, h/l/b/om: own
-  // values, dn: difference to x + 1, dp: difference of x - 1 to the plane
-  // (both from registers), tl / tp: class bytes of the plane and of x - 1 in
-  // LDS, bn: of x + 1, heldm: lanes whose voxel is held, own: damage, latches
-  // and sums are wanted.  They are where the plane and some of the wave's
-  // voxels are the work-group's own; halo voxels pass on their temperature
-  // alone.
+  // One step of this lane's V voxels, in place in q.  t: plane in LDS, dn:
+  // difference to x + 1, dp: difference of x - 1 to the plane (both from
+  // registers), tl / tp: class bytes of the plane and of x - 1 in LDS, bn: of
+  // x + 1 (latch bits of either step; they are not read), heldm: lanes whose
+  // voxel is held, own: not 0 where damage, latches and sums are wanted.
+  // That is where the plane and some of the wave's voxels are the
+  // work-group's own; halo voxels pass on their temperature alone.
+  // Results are formed first and selected by lane masks: a branch costs more
+  // than the few instructions it would save.
   auto step = [&](const float2* t, const uint8_t* tl, const uint8_t* tp, unsigned code,
-                  const float (&h)[V],
-                  const float (&l)[V], const unsigned (&lb)[V], float (&om)[V],
-                  const float (&s)[V], const float (&pf)[V], const float (&dn)[V],
-                  const float (&dp)[V], const unsigned (&bn)[V],
-                  const unsigned long long (&heldm)[V], bool own, float (&nh)[V], float (&nl)[V],
-                  unsigned (&nb)[V]) {
+                  PairPlane<V>& q, const float (&dn)[V], const float (&dp)[V],
+                  const unsigned (&bn)[V], const unsigned long long (&heldm)[V],
+                  unsigned long long own) {
     const StepConst K = step_constants(b.tab);
     auto cntm = [&](int v) { return ownm[v] & ~heldm[v]; };
     float f[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       f[v] = 1.0f;
-      if constexpr (PERF) f[v] = pf[v] * __builtin_amdgcn_exp2f(-om[v] * K.decay2);
+      if constexpr (PERF) f[v] = q.pf[v] * __builtin_amdgcn_exp2f(-q.om[v] * K.decay2);
     }
+    float nh[V], nl[V];
     if (code != kPairIrregular) {
       const ClassCoef coef = class_coef(b.tab, code & (kMaxClasses - 1));
       const float2 k[6] = {coef.k[0], coef.k[0], coef.k[1], coef.k[1], coef.k[2], coef.k[2]};
-      bool warm = false, hot = false, falls = false;
+      unsigned long long warm = 0ull, falls = 0ull;
       float incs[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) {
+        const float h = q.h[v], l = q.l[v];
         const int c = cell[v];
         const float2 ym = t[c - nz], yp = t[c + nz], zm = t[c - 1], zp = t[c + 1];
-        const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h[v], l[v]),
-                            ff_diff(yp.x, yp.y, h[v], l[v]), ff_diff(zm.x, zm.y, h[v], l[v]),
-                            ff_diff(zp.x, zp.y, h[v], l[v])};
+        const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h, l), ff_diff(yp.x, yp.y, h, l),
+                            ff_diff(zm.x, zm.y, h, l), ff_diff(zp.x, zp.y, h, l)};
         float h2, l2, cond, perf;
-        thermal_update(h[v], l[v], k, coef.c, d, s[v], f[v], h2, l2, cond, perf, incs[v]);
-        const bool held = lane_of(heldm[v]);
-        nh[v] = held ? h[v] : h2;
-        nl[v] = held ? l[v] : l2;
-        if (DIAG && own) {
+        thermal_update(h, l, k, coef.c, d, q.s[v], f[v], h2, l2, cond, perf, incs[v]);
+        nh[v] = lane_of(heldm[v]) ? h : h2;
+        nl[v] = lane_of(heldm[v]) ? l : l2;
+        if (DIAG && own != 0ull) {
           // lanes that do not count add 0 times a finite term
           const float w = lane_of(cntm(v)) ? coef.c.w : 0.0f;
           acc.perf = __builtin_fmaf(w, perf, acc.perf);
           acc.bnd = __builtin_fmaf(w, cond, acc.bnd);
-          falls = falls || incs[v] < 0.0f;
+          falls |= __ballot(incs[v] < 0.0f);
         }
-        warm = warm || !(fabsf(h[v]) < K.cold);
-        hot = hot || nh[v] >= K.thr;
-        nb[v] = lb[v];
+        warm |= __ballot(!(fabsf(h) < K.cold));
       }
-      if (DIAG && own && __ballot(falls) != 0ull) {
+      if (DIAG && own != 0ull && falls != 0ull) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) mono += __popcll(__ballot(cools(h[v], incs[v])) & cntm(v));
+        for (int v = 0; v < V; ++v) mono += __popcll(__ballot(cools(q.h[v], incs[v])) & cntm(v));
       }
-      if (!TEMP && own) {
-        float rate[V];
-#pragma unroll
-        for (int v = 0; v < V; ++v) rate[v] = K.dtka;
-        if (__ballot(warm) != 0ull) {
-#pragma unroll
-          for (int v = 0; v < V; ++v) {
-            const float x = K.c2 * h[v] * __builtin_amdgcn_rcpf(K.tak + h[v]);
-            rate[v] = K.dtka * __builtin_amdgcn_exp2f(min_uniform(x, K.clamp2));
-          }
-        }
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
+      if (!TEMP && own != 0ull) {
+        auto add = [&](int v, float rate) {
+          const float o = min_uniform(q.om[v] + rate, K.cap);
           const unsigned long long tism =
               (code & kPairTissueAll) ? ~0ull : ((code & kPairTissueFree) ? ~heldm[v] : 0ull);
-          om[v] = lane_of(tism) ? min_uniform(om[v] + rate[v], K.cap) : om[v];
-        }
-        if (__ballot(hot) != 0ull) {
+          q.om[v] = lane_of(tism) ? o : q.om[v];
+        };
+        if (warm != 0ull) {
 #pragma unroll
-          for (int v = 0; v < V; ++v) nb[v] = latch(lb[v], nh[v], nl[v], K);
+          for (int v = 0; v < V; ++v) {
+            const float x = K.c2 * q.h[v] * __builtin_amdgcn_rcpf(K.tak + q.h[v]);
+            add(v, K.dtka * __builtin_amdgcn_exp2f(min_uniform(x, K.clamp2)));
+          }
+        } else {
+#pragma unroll
+          for (int v = 0; v < V; ++v) add(v, K.dtka);
+        }
+        unsigned long long hot = 0ull;
+#pragma unroll
+        for (int v = 0; v < V; ++v) hot |= __ballot(nh[v] >= K.thr);
+        if (hot != 0ull) {
+#pragma unroll
+          for (int v = 0; v < V; ++v) q.b[v] = latch(q.b[v], nh[v], nl[v], K);
         }
       }
     } else {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
+        const float h = q.h[v], l = q.l[v];
+        const unsigned lb = q.b[v];
         const int c = cell[v];
         const float2 ym = t[c - nz], yp = t[c + nz], zm = t[c - 1], zp = t[c + 1];
-        const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h[v], l[v]),
-                            ff_diff(yp.x, yp.y, h[v], l[v]), ff_diff(zm.x, zm.y, h[v], l[v]),
-                            ff_diff(zp.x, zp.y, h[v], l[v])};
-        const float2 k[6] = {table_entry(sm.cf, 0, lb[v], tp[c]),
-                             table_entry(sm.cf, 0, lb[v], bn[v]),
-                             table_entry(sm.cf, 1, lb[v], tl[c - nz]),
-                             table_entry(sm.cf, 1, lb[v], tl[c + nz]),
-                             table_entry(sm.cf, 2, lb[v], tl[c - 1]),
-                             table_entry(sm.cf, 2, lb[v], tl[c + 1])};
-        const float4 c4 = sm.cls[class_of(lb[v])];
+        const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h, l), ff_diff(yp.x, yp.y, h, l),
+                            ff_diff(zm.x, zm.y, h, l), ff_diff(zp.x, zp.y, h, l)};
+        const float2 k[6] = {table_entry(sm.cf, 0, lb, tp[c]),
+                             table_entry(sm.cf, 0, lb, bn[v]),
+                             table_entry(sm.cf, 1, lb, tl[c - nz]),
+                             table_entry(sm.cf, 1, lb, tl[c + nz]),
+                             table_entry(sm.cf, 2, lb, tl[c - 1]),
+                             table_entry(sm.cf, 2, lb, tl[c + 1])};
+        const float4 c4 = sm.cls[class_of(lb)];
         float h2, l2, cond, perf, inc;
-        thermal_update(h[v], l[v], k, c4, d, s[v], f[v], h2, l2, cond, perf, inc);
-        const bool held = lane_of(heldm[v]);
-        nh[v] = held ? h[v] : h2;
-        nl[v] = held ? l[v] : l2;
-        if (DIAG && own) {
+        thermal_update(h, l, k, c4, d, q.s[v], f[v], h2, l2, cond, perf, inc);
+        nh[v] = lane_of(heldm[v]) ? h : h2;
+        nl[v] = lane_of(heldm[v]) ? l : l2;
+        if (DIAG && own != 0ull) {
           const float w = lane_of(cntm(v)) ? c4.w : 0.0f;
           acc.perf = __builtin_fmaf(w, perf, acc.perf);
           acc.bnd = __builtin_fmaf(w, cond, acc.bnd);
-          mono += __popcll(__ballot(cools(h[v], inc)) & cntm(v));
+          mono += __popcll(__ballot(cools(h, inc)) & cntm(v));
         }
-        nb[v] = lb[v];
-        if (!TEMP && own) {
-          om[v] = damage_add<true>(om[v], damage_increment(h[v], K), (lb[v] & kTissue) != 0u, K);
-          nb[v] = latch(lb[v], nh[v], nl[v], K);
+        if (!TEMP && own != 0ull) {
+          q.om[v] = damage_add<true>(q.om[v], damage_increment(h, K), (lb & kTissue) != 0u, K);
+          q.b[v] = latch(lb, nh[v], nl[v], K);
         }
       }
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      q.h[v] = nh[v];
+      q.l[v] = nl[v];
     }
   };
 
@@ -408,66 +413,58 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     constexpr int BUF = SL & 1;
     PairPlane<V>& C = ring[SL];
     PairPlane<V>& N = ring[SN];
-    const PairPlane<V>& B = ring[SP];
+    PairPlane<V>& B = ring[SP];  // after its first step
     __syncthreads();
     load(x + 2, ring[SA]);
     const unsigned code = __builtin_amdgcn_readfirstlane(C.code);
     const unsigned pcode = __builtin_amdgcn_readfirstlane(B.code);
     // first step of plane x
-    float nh[V], nl[V], nom[V], dn[V];
-    unsigned nb[V];
+    float dn[V];
     unsigned long long held[V];
     const bool in_chunk = x >= x0 && x < x1;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       dn[v] = ff_diff(N.h[v], N.l[v], C.h[v], C.l[v]);
-      nom[v] = C.om[v];
       held[v] = __ballot((C.b[v] & kHeld) != 0u);
-      nh[v] = C.h[v];
-      nl[v] = C.l[v];
-      nb[v] = C.b[v];
     }
+    unsigned long long own = in_chunk ? out_lanes : 0ull;
+    // a scalar, tested where it is used (with sums it would be spilled)
+    if constexpr (!DIAG) asm("" : "+s"(own));
     if (do_mid)
-      step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C.h, C.l, C.b, nom, C.s, C.pf, dn, din, N.b,
-           held, do_out && in_chunk, nh, nl, nb);
+      step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C, dn, din, N.b, held, own);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       din[v] = dn[v];
-      sm.mid[BUF][cell[v]] = make_float2(nh[v], nl[v]);
+      sm.mid[BUF][cell[v]] = make_float2(C.h[v], C.l[v]);
     }
     publish(std::integral_constant<int, SN>{}, N);
     load_s(x + 1, N);
     if constexpr (KEEP) {
       const int so = plane_of(x) * (int)psz * 4;
 #pragma unroll
-      for (int v = 0; v < V; ++v) st_f32<AUX>(nh[v], r_mid, in_chunk ? own4[v] : kOob, so);
+      for (int v = 0; v < V; ++v) st_f32<AUX>(C.h[v], r_mid, in_chunk ? own4[v] : kOob, so);
     }
     // second step of plane x - 1
     {
-      float oh[V], ol[V], oom[V], dm[V];
-      unsigned ob[V], lb1[V];
+      float dm[V];
+      unsigned lb1[V];
       const bool out = x > x0;  // uniform: plane x - 1 is in the chunk
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        dm[v] = ff_diff(nh[v], nl[v], mh[v], ml[v]);
-        oom[v] = mom[v];
-        oh[v] = mh[v];
-        ol[v] = ml[v];
-        ob[v] = mb[v];
+        dm[v] = ff_diff(C.h[v], C.l[v], B.h[v], B.l[v]);
         lb1[v] = kOob;
       }
-      if (do_out && out) {
-        step(sm.mid[BUF ^ 1], sm.lab[SP], sm.lab[SA], pcode, mh, ml, mb, oom, B.s, B.pf, dm, dmid,
-             C.b, mheld, true, oh, ol, ob);
+      if (out_lanes != 0ull && out) {
+        step(sm.mid[BUF ^ 1], sm.lab[SP], sm.lab[SA], pcode, B, dm, dmid, C.b, mheld, out_lanes);
         if constexpr (!TEMP) {
           // class bytes are stored where a latch flipped in either step
-          bool latched = false;
+          unsigned long long latched = 0ull;
 #pragma unroll
-          for (int v = 0; v < V; ++v) latched = latched || (ob[v] & kLatch);
-          if (__ballot(latched) != 0ull) {
+          for (int v = 0; v < V; ++v) latched |= __ballot((B.b[v] & kLatch) != 0u);
+          if (latched != 0ull) {
 #pragma unroll
             for (int v = 0; v < V; ++v)
-              lb1[v] = lane_of(ownm[v]) && ob[v] != sm.lab[SP][cell[v]] ? col[v] : kOob;
+              lb1[v] = lane_of(ownm[v]) && B.b[v] != sm.lab[SP][cell[v]] ? col[v] : kOob;
           }
         }
       }
@@ -475,22 +472,15 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const unsigned v4 = out ? own4[v] : kOob;
-        st_f32<AUX>(oh[v], r_hio, v4, so * 4);
-        st_f32<AUX>(ol[v], r_loo, v4, so * 4);
+        st_f32<AUX>(B.h[v], r_hio, v4, so * 4);
+        st_f32<AUX>(B.l[v], r_loo, v4, so * 4);
         if constexpr (!TEMP) {
-          st_f32<AUX>(oom[v], r_omo, v4, so * 4);
-          st_u8<AUX>(ob[v], r_lab, lb1[v], so);
+          st_f32<AUX>(B.om[v], r_omo, v4, so * 4);
+          st_u8<AUX>(B.b[v], r_lab, lb1[v], so);
         }
         dmid[v] = dm[v];
+        mheld[v] = held[v];
       }
-    }
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      mh[v] = nh[v];
-      ml[v] = nl[v];
-      mom[v] = nom[v];
-      mb[v] = nb[v];
-      mheld[v] = held[v];
     }
   };
   using I0 = std::integral_constant<int, 0>;
