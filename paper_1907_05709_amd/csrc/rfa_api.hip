@@ -143,10 +143,12 @@ struct rfa_grid_s {
   // scratch
   float* partials = nullptr;
   size_t partial_floats = 0;
-  double* dacc = nullptr;          // [3] step partial accumulators
+  double* dacc = nullptr;          // [4] step partial accumulators, then out4
   double* red = nullptr;           // reduction partials
   size_t red_doubles = 0;
-  double* out4 = nullptr;          // [4] state reduction result
+  double* out4 = nullptr;          // [4] state reduction result (in dacc's allocation)
+  void* stage = nullptr;           // staging and scratch of single calls (see Scratch)
+  size_t stage_bytes = 0;
   unsigned long long* counts = nullptr;  // [32]
   unsigned* bad = nullptr;
   double energy = 0.0;
@@ -205,7 +207,7 @@ void free_all(rfa_grid g) {
   f(g->partials);
   f(g->dacc);
   f(g->red);
-  f(g->out4);
+  f(g->stage);
   f(g->counts);
   f(g->bad);
   f(g->chords_dev);
@@ -241,6 +243,45 @@ rfa_status dmalloc(T** p, size_t count) {
   }
   return RFA_OK;
 }
+
+// Device memory of one call: the grid's kept buffer, grown as calls ask for
+// more, up to kStageBytes; beyond that allocated for the call.  The buffer is
+// used in the order of the grid's stream, and calls that hand it out wait for
+// the stream before they return.  Kept because a hipMalloc and the waiting
+// hipFree cost more than small calls themselves: a step and readout of a 48^3
+// host grid 115 -> 103 us, 60 steps and their gradients on 88x80x75 1.35 ->
+// 1.26 ms.
+constexpr size_t kStageBytes = size_t(256) << 20;
+
+struct Scratch {
+  void* p = nullptr;
+  bool own = false;
+  Scratch() = default;
+  ~Scratch() {
+    if (own) (void)hipFree(p);
+  }
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  rfa_status get(rfa_grid g, size_t bytes) {
+    char* q = nullptr;
+    if (bytes > kStageBytes) {
+      const rfa_status s = dmalloc(&q, bytes);
+      p = q;
+      own = s == RFA_OK;
+      return s;
+    }
+    if (bytes > g->stage_bytes || !g->stage) {
+      if (g->stage) (void)hipFree(g->stage);  // waits for its users
+      g->stage = nullptr;
+      g->stage_bytes = 0;
+      if (const rfa_status s = dmalloc(&q, bytes); s != RFA_OK) return s;
+      g->stage = q;
+      g->stage_bytes = bytes;
+    }
+    p = g->stage;
+    return RFA_OK;
+  }
+};
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
@@ -603,24 +644,24 @@ rfa_status ensure_energy(rfa_grid g) {
   return RFA_OK;
 }
 
-// Fill an rfa_diag from accumulated step partials acc[3] (perfusion J,
-// heat from held voxels J, cooling voxel count) and a fresh state reduction.
-rfa_status finish_diag(rfa_grid g, const double* acc, double e0, double dt, int n_steps,
-                       rfa_diag* diag);
+// Energy (J), extremes and non-finite voxels of the state into out[4] (device).
+hipError_t launch_reduction(rfa_grid g, double* out) {
+  return launch_state_reduce(g->g, g->lab, g->hi[g->cur], g->lo[g->cur], g->cp_dev,
+                             g->dx * g->dy * g->dz, g->red, out, g->st);
+}
 
 rfa_status state_reduce(rfa_grid g, double out[4]) {
-  HIP_TRY(launch_state_reduce(g->g, g->lab, g->hi[g->cur], g->lo[g->cur], g->cp_dev,
-                              g->dx * g->dy * g->dz, g->red, g->out4, g->st));
+  HIP_TRY(launch_reduction(g, g->out4));
   HIP_TRY(hipMemcpyAsync(out, g->out4, 4 * sizeof(double), hipMemcpyDeviceToHost, g->st));
   HIP_TRY(hipStreamSynchronize(g->st));
   return RFA_OK;
 }
 
-rfa_status finish_diag(rfa_grid g, const double* acc, double e0, double dt, int n_steps,
-                       rfa_diag* diag) {
-  double r[4];
-  rfa_status s = state_reduce(g, r);
-  if (s != RFA_OK) return s;
+// Fill an rfa_diag from accumulated step partials acc[3] (perfusion J,
+// heat from held voxels J, cooling voxel count) and a state reduction r[4]
+// made after the steps.
+rfa_status finish_diag(rfa_grid g, const double* acc, const double* r, double e0, double dt,
+                       int n_steps, rfa_diag* diag) {
   g->energy = r[0];
   g->energy_valid = true;
   const double vol = g->dx * g->dy * g->dz;
@@ -793,13 +834,14 @@ rfa_status rfa_create_grid(int nx, int ny, int nz, double dx, double dy, double 
       (s = dmalloc(&g->hi[1], n)) || (s = dmalloc(&g->lo[0], n)) || (s = dmalloc(&g->lo[1], n)) ||
       (s = dmalloc(&g->om, n)) || (s = dmalloc(&g->src, n)) || (s = dmalloc(&g->q64, n)) ||
       (s = dmalloc(&g->tab_dev, 1)) || (s = dmalloc(&g->partials, g->partial_floats)) ||
-      (s = dmalloc(&g->dacc, 4)) || (s = dmalloc(&g->red, g->red_doubles)) ||
-      (s = dmalloc(&g->out4, 4)) || (s = dmalloc(&g->counts, 2 * kMaxClasses)) ||
+      (s = dmalloc(&g->dacc, 8)) || (s = dmalloc(&g->red, g->red_doubles)) ||
+      (s = dmalloc(&g->counts, 2 * kMaxClasses)) ||
       (s = dmalloc(&g->bad, 1))) {
     free_all(g);
     delete g;
     return s;
   }
+  g->out4 = g->dacc + 4;
   *out = g;
   return RFA_OK;
 }
@@ -1017,9 +1059,12 @@ rfa_status rfa_step(rfa_grid g, int n_steps, double dt, rfa_diag* diag) {
     ++g->version;
   }
   if (diag) {
-    double acc[4] = {0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(acc, g->dacc, 3 * sizeof(double), hipMemcpyDeviceToHost, g->st));
-    return finish_diag(g, acc, e0, dt, n_steps, diag);
+    // one copy and one wait for the step sums and the state's
+    double acc[8] = {};
+    HIP_TRY(launch_reduction(g, g->out4));
+    HIP_TRY(hipMemcpyAsync(acc, g->dacc, sizeof acc, hipMemcpyDeviceToHost, g->st));
+    HIP_TRY(hipStreamSynchronize(g->st));
+    return finish_diag(g, acc, acc + 4, e0, dt, n_steps, diag);
   }
   return RFA_OK;
 }
@@ -1029,12 +1074,13 @@ rfa_status rfa_damage(rfa_grid g, uint8_t* mask, float* omega, double* dead_m3) 
   if (!g->has_tissue) return fail(RFA_ERR_STATE, "no tissue");
   const size_t n = g->g.n();
   uint8_t* dmask = nullptr;
+  Scratch stage;
   if (mask) {
     if (g->opt.inputs_on_device) {
       dmask = mask;
     } else {
-      rfa_status s = dmalloc(&dmask, n);
-      if (s != RFA_OK) return s;
+      if (const rfa_status s = stage.get(g, n); s != RFA_OK) return s;
+      dmask = (uint8_t*)stage.p;
     }
   }
   hipError_t e = hipSuccess;
@@ -1055,7 +1101,6 @@ rfa_status rfa_damage(rfa_grid g, uint8_t* mask, float* omega, double* dead_m3) 
                                        g->st)) != hipSuccess) break;
     if (host_out && (e = hipStreamSynchronize(g->st)) != hipSuccess) break;
   } while (false);
-  if (dmask && dmask != mask) (void)hipFree(dmask);
   if (e != hipSuccess) return fail(RFA_ERR_HIP, "damage failed: %s", hipGetErrorString(e));
   if (dead_m3) {
     const double vol = g->dx * g->dy * g->dz;
@@ -1072,18 +1117,16 @@ rfa_status rfa_get_temperature(rfa_grid g, double* t_C, float* hi, float* lo) {
   if (!g->has_tissue) return fail(RFA_ERR_STATE, "no tissue");
   const size_t n = g->g.n();
   if (t_C) {
-    double* dt = nullptr;
-    if (g->opt.inputs_on_device) {
-      dt = t_C;
-    } else {
-      rfa_status s = dmalloc(&dt, n);
-      if (s != RFA_OK) return s;
+    double* dt = t_C;
+    Scratch stage;
+    if (!g->opt.inputs_on_device) {
+      if (const rfa_status s = stage.get(g, n * sizeof(double)); s != RFA_OK) return s;
+      dt = (double*)stage.p;
     }
     hipError_t e = launch_temperature_out(g->g, g->hi[g->cur], g->lo[g->cur], dt, g->st);
     if (e == hipSuccess && dt != t_C)
       e = hipMemcpyAsync(t_C, dt, n * sizeof(double), hipMemcpyDeviceToHost, g->st);
     if (e == hipSuccess) e = hipStreamSynchronize(g->st);
-    if (dt != t_C) (void)hipFree(dt);
     if (e != hipSuccess) return fail(RFA_ERR_HIP, "get_temperature: %s", hipGetErrorString(e));
   }
   if (hi) HIP_TRY(hipMemcpyAsync(hi, g->hi[g->cur], n * sizeof(float), kind_out(g), g->st));
@@ -1101,21 +1144,17 @@ rfa_status rfa_set_temperature(rfa_grid g, const double* t_C) {
       if (!std::isfinite(t_C[p])) return fail(RFA_ERR_ARG, "temperature not finite at %zu", p);
   }
   const double* src = t_C;
-  double* tmp = nullptr;
+  Scratch stage;
   if (!g->opt.inputs_on_device) {
-    rfa_status s = dmalloc(&tmp, n);
-    if (s != RFA_OK) return s;
-    hipError_t e = hipMemcpyAsync(tmp, t_C, n * sizeof(double), hipMemcpyHostToDevice, g->st);
-    if (e != hipSuccess) {
-      (void)hipFree(tmp);
+    if (const rfa_status s = stage.get(g, n * sizeof(double)); s != RFA_OK) return s;
+    hipError_t e = hipMemcpyAsync(stage.p, t_C, n * sizeof(double), hipMemcpyHostToDevice, g->st);
+    if (e != hipSuccess)
       return fail(RFA_ERR_HIP, "set_temperature: %s", hipGetErrorString(e));
-    }
-    src = tmp;
+    src = (const double*)stage.p;
   }
   hipError_t e = launch_temperature_in(g->g, src, g->hi[g->cur], g->lo[g->cur], g->lab,
                                        (float)(g->opt.t_death - 37.0), g->st);
   if (e == hipSuccess) e = hipStreamSynchronize(g->st);
-  if (tmp) (void)hipFree(tmp);
   if (e != hipSuccess) return fail(RFA_ERR_HIP, "set_temperature: %s", hipGetErrorString(e));
   g->energy_valid = false;
   ++g->version;
@@ -1572,13 +1611,14 @@ rfa_status rfa_set_perfusion_bspline(rfa_grid g, int m, const float* ctrl) {
   }
   if (!g->perf && (s = dmalloc(&g->perf, g->g.n())) != RFA_OK) return s;
   HIP_TRY(hipMemcpyAsync(g->bs_ctrl, ctrl, nc * sizeof(float), hipMemcpyHostToDevice, g->st));
-  HIP_TRY(hipMemcpyAsync(g->bs_vfirst, vfirst.data(), vfirst.size() * sizeof(int),
-                         hipMemcpyHostToDevice, g->st));
+  if (g->bs_m != m)  // the spans depend on m and the grid alone
+    HIP_TRY(hipMemcpyAsync(g->bs_vfirst, vfirst.data(), vfirst.size() * sizeof(int),
+                           hipMemcpyHostToDevice, g->st));
   HIP_TRY(launch_bspline_eval(g->g, g->bs_ctrl, m, g->perf, g->st));
-  HIP_TRY(hipStreamSynchronize(g->st));
-  g->bs_m = m;
   ++g->version;
-  return compute_dt_max(g);
+  s = compute_dt_max(g);  // waits for the stream
+  g->bs_m = s == RFA_OK ? m : 0;
+  return s;
 }
 
 rfa_status rfa_reset_state(rfa_grid g) {
@@ -1907,47 +1947,44 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
     // of this forward recomputes every segment
     g->adj_tail_kept = false;
   }
+  // gradients: both contractions and their copies, then one wait
+  const int nt = dL_dP ? (int)g->power.size() : 0;
+  constexpr int kBlk = 512;
+  const int m = g->bs_m;
+  const size_t np = (size_t)nt * kBlk;
+  const size_t nc = dL_dctrl ? (size_t)m * m * m : 0;
+  const size_t scratch = dL_dctrl ? bspline_grad_scratch(g->g, m) : 0;
+  Scratch stage;
+  std::vector<double> host(np);
+  if (np + nc > 0 && (s = stage.get(g, (np + nc + scratch) * sizeof(double))) != RFA_OK) return s;
+  double* part = (double*)stage.p;
+  double* gc = part + np;
+  hipError_t e = hipSuccess;
   if (dL_dP) {
-    const int nt = (int)g->power.size();
-    constexpr int kBlk = 512;
-    double* part = nullptr;
-    if ((s = dmalloc(&part, (size_t)nt * kBlk)) != RFA_OK) return s;
-    std::vector<double> host((size_t)nt * kBlk);
-    hipError_t e = g->fields_ok
-                       ? launch_source_dot_fields(g->g, g->lab, g->fields, nt, sacc, g->cp_dev,
-                                                  g->adj_dt, part, kBlk, g->st)
-                       : launch_source_dot(g->g, g->dx, g->dy, g->dz, g->lab, g->chords_dev,
-                                           g->first_dev, nt, g->sigma, sacc, g->cp_dev,
-                                           g->adj_dt, part, kBlk, g->st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(host.data(), part, host.size() * sizeof(double), hipMemcpyDeviceToHost,
-                         g->st);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->st);
-    (void)hipFree(part);
+    e = g->fields_ok ? launch_source_dot_fields(g->g, g->lab, g->fields, nt, sacc, g->cp_dev,
+                                                g->adj_dt, part, kBlk, g->st)
+                     : launch_source_dot(g->g, g->dx, g->dy, g->dz, g->lab, g->chords_dev,
+                                         g->first_dev, nt, g->sigma, sacc, g->cp_dev, g->adj_dt,
+                                         part, kBlk, g->st);
     if (e != hipSuccess) return fail(RFA_ERR_HIP, "adjoint dL/dP: %s", hipGetErrorString(e));
-    for (int t = 0; t < nt; ++t) {
-      double acc = 0.0;
-      for (int b = 0; b < kBlk; ++b) acc += host[(size_t)t * kBlk + b];
-      dL_dP[t] = acc / g->tine_sums[t];
-    }
   }
-  if (dL_dperf)
-    HIP_TRY(hipMemcpyAsync(dL_dperf, facc, n * sizeof(float), kind_out(g), g->st));
   if (dL_dctrl) {
-    const int m = g->bs_m;
-    const size_t nc = (size_t)m * m * m;
-    double* gc = nullptr;
-    if ((s = dmalloc(&gc, nc + bspline_grad_scratch(g->g, m))) != RFA_OK) return s;
-    hipError_t e = launch_bspline_grad(g->g, facc, g->perf, m, g->bs_vfirst,
-                                       g->bs_vfirst + (m - 2), g->bs_vfirst + 2 * (m - 2),
-                                       gc + nc, gc, g->st);
+    e = launch_bspline_grad(g->g, facc, g->perf, m, g->bs_vfirst, g->bs_vfirst + (m - 2),
+                            g->bs_vfirst + 2 * (m - 2), gc + nc, gc, g->st);
     if (e == hipSuccess)
       e = hipMemcpyAsync(dL_dctrl, gc, nc * sizeof(double), hipMemcpyDeviceToHost, g->st);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->st);
-    (void)hipFree(gc);
     if (e != hipSuccess) return fail(RFA_ERR_HIP, "adjoint dL/dctrl: %s", hipGetErrorString(e));
   }
+  if (dL_dP)
+    HIP_TRY(hipMemcpyAsync(host.data(), part, np * sizeof(double), hipMemcpyDeviceToHost, g->st));
+  if (dL_dperf)
+    HIP_TRY(hipMemcpyAsync(dL_dperf, facc, n * sizeof(float), kind_out(g), g->st));
   HIP_TRY(hipStreamSynchronize(g->st));
+  for (int t = 0; t < nt; ++t) {
+    double acc = 0.0;
+    for (int b = 0; b < kBlk; ++b) acc += host[(size_t)t * kBlk + b];
+    dL_dP[t] = acc / g->tine_sums[t];
+  }
   return RFA_OK;
 }
 
@@ -1963,7 +2000,7 @@ struct rfa_batch_s {
   BatchItem* items_dev = nullptr;
   int* first_dev = nullptr;
   float* partials = nullptr;        // [kPartialSlots][n_items][3]
-  double* dacc = nullptr;           // [n][3]
+  double* dacc = nullptr;           // [n][3], then the grids' state reductions [n][4]
   double* slot_acc = nullptr;       // [n][kPartialSlots][3] reduction scratch
   int n_items = 0;
   int ty = 4;
@@ -2256,7 +2293,7 @@ rfa_status batch_build(rfa_batch b) {
       (s = dmalloc(&b->first_dev, 2 * (size_t)n)) ||
       (s = dmalloc(&b->partials,
                    (size_t)kPartialSlots * std::max(b->n_items, b->n_pitems) * 3)) ||
-      (s = dmalloc(&b->dacc, 3 * (size_t)n)) ||
+      (s = dmalloc(&b->dacc, 7 * (size_t)n)) ||
       (s = dmalloc(&b->slot_acc, (size_t)kPartialSlots * 3 * n)))
     return s;
   HIP_TRY(hipMemcpyAsync(b->inst_dev, b->inst.data(), n * sizeof(BatchInstance),
@@ -2443,12 +2480,17 @@ rfa_status rfa_batch_step(rfa_batch b, int n_steps, rfa_diag* diags) {
     ++g->version;
   }
   if (diags) {
-    HIP_TRY(hipStreamSynchronize(b->st));
-    std::vector<double> acc(3 * (size_t)n);
+    // all grids' reductions side by side on their own streams, one copy back
+    // (24 grids, 40 steps: 8.92 -> 8.46 ms against one wait per grid)
+    for (int i = 0; i < n; ++i)
+      HIP_TRY(launch_reduction(b->grids[i], b->dacc + 3 * (size_t)n + 4 * (size_t)i));
+    for (int i = 0; i < n; ++i) HIP_TRY(hipStreamSynchronize(b->grids[i]->st));
+    std::vector<double> acc(7 * (size_t)n);
     HIP_TRY(hipMemcpy(acc.data(), b->dacc, acc.size() * sizeof(double), hipMemcpyDeviceToHost));
     rfa_status worst = RFA_OK;
     for (int i = 0; i < n; ++i) {
-      s = finish_diag(b->grids[i], &acc[3 * i], e0[i], b->dt[i], n_steps, &diags[i]);
+      s = finish_diag(b->grids[i], &acc[3 * (size_t)i], &acc[3 * (size_t)n + 4 * (size_t)i],
+                      e0[i], b->dt[i], n_steps, &diags[i]);
       if (s != RFA_OK) worst = s;
     }
     if (worst != RFA_OK) return worst;
