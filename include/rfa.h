@@ -449,6 +449,26 @@ rfa_status rfa_batch_last_time(rfa_batch b, double* ms, long long* voxel_steps);
 
 void rfa_batch_destroy(rfa_batch b);
 
+/* Coverage loss of a damage integral, on device arrays and a stream of the
+ * caller (NULL: the default stream); nothing waits.  omega[n], labels[n] (one
+ * class byte a voxel), tumour and liver in 0 .. 255, with the damaged fraction
+ * d = Omega^4 / (1 + Omega^4):
+ *   loss[0] = sum_tumour (1 - d) / max(N_tumour, 1)
+ *             + healthy_weight * voxel_cm3 * sum_liver d,
+ *   per_tumour[0] = 1 / max(N_tumour, 1).
+ * codes[n] (nullable) receives what rfa_coverage_grad needs of the labels;
+ * work: RFA_COVERAGE_WORK doubles. */
+#define RFA_COVERAGE_WORK 1536
+rfa_status rfa_coverage_loss(const float* omega, const uint8_t* labels, long long n, int tumour,
+                             int liver, double voxel_cm3, double healthy_weight, uint8_t* codes,
+                             double* work, double* loss, double* per_tumour, void* stream);
+
+/* out[n] = grad[0] * dloss/domega, from omega and the codes and per_tumour of
+ * rfa_coverage_loss (all device arrays). */
+rfa_status rfa_coverage_grad(const float* omega, const uint8_t* codes, long long n,
+                             double voxel_cm3, double healthy_weight, const double* per_tumour,
+                             const double* grad, float* out, void* stream);
+
 void rfa_destroy_grid(rfa_grid g);
 const char* rfa_status_string(rfa_status s);
 const char* rfa_last_error(void);

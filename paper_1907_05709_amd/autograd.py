@@ -44,11 +44,10 @@ class RfaFunction(torch.autograd.Function):
         return gP, gc, None, None, None, None
 
 
-def coverage_loss(omega, labels, voxel_m3: float, tumour: int = 2, liver: int = 1,
-                  healthy_weight: float = 0.1):
-    """Soft undertreatment of the tumour plus healthy_weight x healthy-liver
-    damage volume in cm^3, with the damaged fraction d = sigmoid(4 ln Omega)
-    = Omega^4 / (1 + Omega^4).  omega, labels: tensors of the grid's shape."""
+def _coverage_ops(omega, labels, voxel_m3: float, tumour: int, liver: int,
+                  healthy_weight: float):
+    """coverage_loss as tensor operations: any device, type, layout and
+    transform that torch takes."""
     om = omega.double().clamp_min(0.0)
     # sigmoid(4 ln Omega) written without the logarithm (Omega may be 0)
     d = 1.0 / (1.0 + torch.where(om > 0, om, torch.ones_like(om)).pow(-4.0))
@@ -59,6 +58,85 @@ def coverage_loss(omega, labels, voxel_m3: float, tumour: int = 2, liver: int = 
     u = ((1.0 - d) * tum).sum() / tum.sum().clamp_min(1.0)  # 0 without tumour voxels
     dv = (d * liv).sum() * (voxel_m3 * 1e6)
     return u + healthy_weight * dv
+
+
+def _plain(*tensors) -> bool:
+    """Whether the tensors are ordinary contiguous ones on one GPU, outside
+    tracing, functional transforms, forward-mode levels and dispatch modes:
+    what a kernel may read through their pointers."""
+    return (all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda
+                and t.layout == torch.strided and t.device == tensors[0].device
+                and torch._C._has_storage(t) and t.is_contiguous() and not t.is_neg()
+                for t in tensors)
+            and torch._C._functorch.peek_interpreter_stack() is None
+            and torch.autograd.forward_ad._current_level < 0
+            and torch._C._len_torch_dispatch_stack() == 0
+            and torch._C._len_torch_function_stack() == 0 and not torch.jit.is_tracing())
+
+
+class _Coverage(torch.autograd.Function):
+    """coverage_loss of a contiguous float32 tensor on the GPU, in two
+    launches and one for its gradient.  omega is the caller's copy, so that
+    what is kept for the gradient is nobody else's to change."""
+
+    @staticmethod
+    def forward(ctx, omega, labels, voxel_cm3, tumour, liver, healthy_weight, keep):
+        new = lambda *s, **kw: torch.empty(*s, device=omega.device, **kw)  # noqa: E731
+        codes = new(omega.shape, dtype=torch.uint8) if keep else None
+        work = new(rfa.COVERAGE_WORK, dtype=torch.float64)
+        loss, per_tumour = new((), dtype=torch.float64), new((), dtype=torch.float64)
+        with torch.cuda.device(omega.device):
+            rfa.rfa_coverage_loss(omega, labels, tumour, liver, voxel_cm3, healthy_weight, codes,
+                                  work, loss, per_tumour)
+        if keep:
+            ctx.save_for_backward(omega, codes, per_tumour)
+            ctx.voxel_cm3, ctx.healthy_weight = voxel_cm3, healthy_weight
+        return loss
+
+    @staticmethod
+    def backward(ctx, grad):
+        omega, codes, per_tumour = ctx.saved_tensors
+        rest = (None,) * 6
+        if (not torch.is_grad_enabled() and _plain(grad, omega, codes, per_tumour)
+                and (omega.dtype, codes.dtype) == (torch.float32, torch.uint8)
+                and grad.dtype == per_tumour.dtype == torch.float64):
+            out = torch.empty_like(omega)
+            with torch.cuda.device(omega.device):
+                rfa.rfa_coverage_grad(omega, codes, ctx.voxel_cm3, ctx.healthy_weight, per_tumour,
+                                      grad, out)
+            return (out, *rest)
+        # a gradient that is itself differentiated or transformed
+        om = omega.double()
+        om = torch.where(om > 0, om, torch.zeros_like(om))
+        pos = torch.where(om > 0, om, torch.ones_like(om))
+        d = 1.0 / (1.0 + pos.pow(-4.0))
+        w = (ctx.healthy_weight * ctx.voxel_cm3) * (codes & 2).ne(0) - per_tumour * (codes & 1)
+        slope = torch.where(om > 0, 4.0 * d * d * pos.pow(-5.0), torch.zeros_like(d))
+        return ((grad * w * slope).to(omega.dtype), *rest)
+
+
+def _coverage_kernels_fit(omega, labels, voxel_m3, tumour, liver, healthy_weight) -> bool:
+    """float32 damage and byte labels on one GPU, as the library returns and
+    takes them, go through its kernels (128^3: loss and gradient 0.43 ms of
+    45 tensor passes shorter); everything else through tensor operations."""
+    return (_plain(omega, labels) and omega.numel() > 0 and omega.shape == labels.shape
+            and (omega.dtype, labels.dtype) == (torch.float32, torch.uint8)
+            and all(isinstance(c, int) and 0 <= c <= 255 for c in (tumour, liver))
+            and all(isinstance(v, (int, float)) for v in (voxel_m3, healthy_weight)))
+
+
+def coverage_loss(omega, labels, voxel_m3: float, tumour: int = 2, liver: int = 1,
+                  healthy_weight: float = 0.1):
+    """Soft undertreatment of the tumour plus healthy_weight x healthy-liver
+    damage volume in cm^3, with the damaged fraction d = sigmoid(4 ln Omega)
+    = Omega^4 / (1 + Omega^4).  omega, labels: tensors of the grid's shape."""
+    if not torch.jit.is_scripting() and not torch.compiler.is_compiling():
+        if _coverage_kernels_fit(omega, labels, voxel_m3, tumour, liver, healthy_weight):
+            keep = omega.requires_grad and torch.is_grad_enabled()
+            return _Coverage.apply(omega.clone() if keep else omega.detach(), labels,
+                                   float(voxel_m3 * 1e6), int(tumour), int(liver),
+                                   float(healthy_weight), keep)
+    return _coverage_ops(omega, labels, voxel_m3, tumour, liver, healthy_weight)
 
 
 def optimise_plan(grid, labels, voxel_m3: float, powers, ctrl, n_steps: int, dt: float,

@@ -22,7 +22,7 @@ BUILD_DIR = os.path.join(PKG, "_build")
 SOURCES = ["rfa_api.hip", "rfa_kernels.hip", "rfa_step.hip", "rfa_tiled.hip", "rfa_tiled2.hip",
            "rfa_wide.hip", "rfa_pair.hip", "rfa_pair_16x2.hip", "rfa_pair_8x2.hip",
            "rfa_pair_8x1.hip", "rfa_pair_4x1.hip",
-           "rfa_adjoint.hip", "rfa_adjoint_pair.hip", "rfa_warp.hip"]
+           "rfa_adjoint.hip", "rfa_adjoint_pair.hip", "rfa_warp.hip", "rfa_coverage.hip"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

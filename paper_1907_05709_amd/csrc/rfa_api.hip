@@ -21,6 +21,7 @@
 #include "rfa_kernels.h"
 #include "rfa_adjoint.h"
 #include "rfa_step.h"
+#include "rfa_coverage.h"
 #include "rfa_warp.h"
 
 using namespace rfa;
@@ -1985,6 +1986,33 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
     for (int b = 0; b < kBlk; ++b) acc += host[(size_t)t * kBlk + b];
     dL_dP[t] = acc / g->tine_sums[t];
   }
+  return RFA_OK;
+}
+
+// ---- coverage loss -----------------------------------------------------------
+static_assert(RFA_COVERAGE_WORK == 3 * kCoverageBlocks, "the header states the work size");
+
+rfa_status rfa_coverage_loss(const float* omega, const uint8_t* labels, long long n, int tumour,
+                             int liver, double voxel_cm3, double healthy_weight, uint8_t* codes,
+                             double* work, double* loss, double* per_tumour, void* stream) {
+  if (!omega || !labels || !work || !loss || !per_tumour)
+    return fail(RFA_ERR_ARG, "omega, labels, work, loss and per_tumour are required");
+  if (n < 1) return fail(RFA_ERR_ARG, "n >= 1");
+  if (tumour < 0 || tumour > 255 || liver < 0 || liver > 255)
+    return fail(RFA_ERR_ARG, "tumour and liver are class bytes");
+  HIP_TRY(launch_coverage(omega, labels, n, tumour, liver, voxel_cm3, healthy_weight, codes, work,
+                          loss, per_tumour, (hipStream_t)stream));
+  return RFA_OK;
+}
+
+rfa_status rfa_coverage_grad(const float* omega, const uint8_t* codes, long long n,
+                             double voxel_cm3, double healthy_weight, const double* per_tumour,
+                             const double* grad, float* out, void* stream) {
+  if (!omega || !codes || !per_tumour || !grad || !out)
+    return fail(RFA_ERR_ARG, "omega, codes, per_tumour, grad and out are required");
+  if (n < 1) return fail(RFA_ERR_ARG, "n >= 1");
+  HIP_TRY(launch_coverage_grad(omega, codes, n, voxel_cm3, healthy_weight, per_tumour, grad, out,
+                               (hipStream_t)stream));
   return RFA_OK;
 }
 

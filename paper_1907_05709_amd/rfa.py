@@ -104,6 +104,10 @@ _SIGS = {
     "rfa_batch_tune": [C.c_void_p, C.c_int],
     "rfa_batch_last_time": [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_longlong)],
     "rfa_batch_destroy": [C.c_void_p],
+    "rfa_coverage_loss": [C.c_void_p, C.c_void_p, C.c_longlong, C.c_int, C.c_int, C.c_double,
+                          C.c_double] + [C.c_void_p] * 5,
+    "rfa_coverage_grad": [C.c_void_p, C.c_void_p, C.c_longlong, C.c_double, C.c_double]
+    + [C.c_void_p] * 4,
     "rfa_destroy_grid": [C.c_void_p],
     "rfa_status_string": [C.c_int],
     "rfa_last_error": [],
@@ -289,6 +293,33 @@ def rfa_warp(g, v_ptr, beta: float, out_ptr, timed: bool = False):
     ms = C.c_double(0.0)
     _check(lib().rfa_warp(g, v_ptr, float(beta), out_ptr, C.byref(ms) if timed else None))
     return ms.value if timed else None
+
+
+COVERAGE_WORK = 1536  # doubles of scratch of rfa_coverage_loss
+
+
+def _dev(t):
+    return None if t is None else C.c_void_p(t.data_ptr())
+
+
+def rfa_coverage_loss(omega, labels, tumour: int, liver: int, voxel_cm3: float,
+                      healthy_weight: float, codes, work, loss, per_tumour):
+    """Coverage loss of contiguous tensors on the current GPU and torch's
+    current stream (codes may be None)."""
+    import torch
+    _check(lib().rfa_coverage_loss(
+        _dev(omega), _dev(labels), omega.numel(), tumour, liver, voxel_cm3, healthy_weight,
+        _dev(codes), _dev(work), _dev(loss), _dev(per_tumour),
+        C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+
+
+def rfa_coverage_grad(omega, codes, voxel_cm3: float, healthy_weight: float, per_tumour, grad,
+                      out):
+    """out = grad * dloss/domega, tensors as for rfa_coverage_loss."""
+    import torch
+    _check(lib().rfa_coverage_grad(
+        _dev(omega), _dev(codes), omega.numel(), voxel_cm3, healthy_weight, _dev(per_tumour),
+        _dev(grad), _dev(out), C.c_void_p(torch.cuda.current_stream().cuda_stream)))
 
 
 def rfa_warp2(g, v1_ptr, beta1: float, v2_ptr, beta2: float, out_ptr, timed: bool = False):
