@@ -554,7 +554,7 @@ rfa_status ensure_pair(rfa_grid g, const StepPlan& p) {
     if (g->codes) (void)hipFree(g->codes);
     g->codes_cap = 0;
     g->codes_waves = 0;
-    if ((s = dmalloc(&g->codes, need)) != RFA_OK) return s;
+    if ((s = dmalloc(&g->codes, need + 4)) != RFA_OK) return s;  // read as dwords
     g->codes_cap = need;
   }
   HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp_dev, g->codes, g->st));
@@ -2204,7 +2204,7 @@ rfa_status batch_build_pair(rfa_batch b) {
   }
   b->n_pitems = (int)items.size();
   rfa_status s;
-  if ((s = dmalloc(&b->codes, code_bytes)) || (s = dmalloc(&b->pinst_dev, n)) ||
+  if ((s = dmalloc(&b->codes, code_bytes + 4)) || (s = dmalloc(&b->pinst_dev, n)) ||
       (s = dmalloc(&b->pitems_dev, items.size())) || (s = dmalloc(&b->pfirst_dev, 2 * (size_t)n)))
     return s;
   size_t at = 0;

@@ -76,7 +76,6 @@ struct PairPlane {
   unsigned b[V];
   float hh, hl;  // halo element
   unsigned hb;
-  unsigned code;
 };
 
 // Coefficients of one class, read through the scalar cache (uniform class
@@ -98,6 +97,16 @@ __device__ __forceinline__ ClassCoef class_coef(const Tables* tab, unsigned c) {
   ConstF* q = t + offsetof(Tables, cls) / 4 + 4 * c;
   r.c = make_float4(q[0], q[1], q[2], q[3]);
   return r;
+}
+
+// The aligned dword of the wave codes that holds byte i, and the shift that
+// brings the byte down: through the scalar cache, as a vector load and its
+// lane read would cost as much as a plane's temperatures.
+__device__ __forceinline__ unsigned code_word(const uint8_t* codes, size_t i, unsigned& shift) {
+  typedef const __attribute__((address_space(4))) unsigned ConstU;
+  const uintptr_t p = (uintptr_t)codes + i;
+  shift = 8u * (unsigned)(p & 3);
+  return *(ConstU*)(p & ~(uintptr_t)3);
 }
 
 // The step constants, read where they are used: as kernel arguments they
@@ -152,7 +161,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   const unsigned psz = (unsigned)np;
   const int fp = sg * seg;  // first voxel of the footprint; the segment starts a row later
 
-  __amdgpu_buffer_rsrc_t r_hi, r_lo, r_lab, r_src, r_om, r_omo, r_pf, r_hio, r_loo, r_mid, r_code;
+  __amdgpu_buffer_rsrc_t r_hi, r_lo, r_lab, r_src, r_om, r_omo, r_pf, r_hio, r_loo, r_mid;
   {
     const size_t off = (size_t)xb * psz;
     const size_t rest = (size_t)(nx - xb) * psz;
@@ -166,7 +175,6 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     r_hio = make_rsrc(b.hi_out + off, rest * 4);
     r_loo = make_rsrc(b.lo_out + off, rest * 4);
     r_mid = KEEP ? make_rsrc(hi_mid + off, rest * 4) : r_hio;
-    r_code = make_rsrc(b.codes + (size_t)xb * segs * NW, (size_t)(nx - xb) * segs * NW);
   }
 
   // Own voxels: column in the plane (0, a held corner, outside the grid),
@@ -218,7 +226,6 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
       q.h[v] = ld_f32(r_hi, col[v] * 4u, so4);
       q.l[v] = ld_f32(r_lo, col[v] * 4u, so4);
     }
-    q.code = ld_u8(r_code, 0u, (plane_of(x) * segs + sg) * NW + wave);
     q.hh = ld_f32(r_hi, hoff4, so4);
     q.hl = ld_f32(r_lo, hoff4, so4);
     q.hb = ld_u8(r_lab, hoff, so1);
@@ -265,7 +272,6 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     ring[3].pf[v] = 1.0f;
     ring[3].b[v] = 0u;
   }
-  ring[3].code = 0u;
 
   Partial acc{0.0f, 0.0f, 0u};
   unsigned mono = 0u;  // cooling voxels of the wave (scalar)
@@ -405,6 +411,14 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     }
   };
 
+  unsigned code = 0u, code_next, code_shift;
+  auto fetch_code = [&](int x) {
+    code_next = code_word(b.codes, ((size_t)(plane_of(x) + xb) * segs + sg) * NW + wave,
+                          code_shift);
+  };
+  auto next_code = [&]() { return (code_next >> code_shift) & 0xffu; };
+  fetch_code(xs);
+
   auto iterate = [&](auto SL_, int x) {
     constexpr int SL = decltype(SL_)::value;   // plane x
     constexpr int SP = (SL + 3) % kPairRing;   // plane x - 1
@@ -416,8 +430,10 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     PairPlane<V>& B = ring[SP];  // after its first step
     __syncthreads();
     load(x + 2, ring[SA]);
-    const unsigned code = __builtin_amdgcn_readfirstlane(C.code);
-    const unsigned pcode = __builtin_amdgcn_readfirstlane(B.code);
+    // wave codes of planes x - 1 and x; that of x + 1 is under way
+    const unsigned pcode = code;
+    code = next_code();
+    fetch_code(x + 1);
     // first step of plane x
     float dn[V];
     unsigned long long held[V];
@@ -447,24 +463,25 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     // second step of plane x - 1
     {
       float dm[V];
-      unsigned lb1[V];
       const bool out = x > x0;  // uniform: plane x - 1 is in the chunk
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         dm[v] = ff_diff(C.h[v], C.l[v], B.h[v], B.l[v]);
-        lb1[v] = kOob;
       }
       if (out_lanes != 0ull && out) {
         step(sm.mid[BUF ^ 1], sm.lab[SP], sm.lab[SA], pcode, B, dm, dmid, C.b, mheld, out_lanes);
         if constexpr (!TEMP) {
-          // class bytes are stored where a latch flipped in either step
+          // class bytes are stored where a latch flipped in either step: a
+          // branch, as few waves hold a latched voxel
           unsigned long long latched = 0ull;
 #pragma unroll
           for (int v = 0; v < V; ++v) latched |= __ballot((B.b[v] & kLatch) != 0u);
           if (latched != 0ull) {
 #pragma unroll
             for (int v = 0; v < V; ++v)
-              lb1[v] = lane_of(ownm[v]) && B.b[v] != sm.lab[SP][cell[v]] ? col[v] : kOob;
+              st_u8<AUX>(B.b[v], r_lab,
+                         lane_of(ownm[v]) && B.b[v] != sm.lab[SP][cell[v]] ? col[v] : kOob,
+                         plane_of(x - 1) * (int)psz);
           }
         }
       }
@@ -476,7 +493,6 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
         st_f32<AUX>(B.l[v], r_loo, v4, so * 4);
         if constexpr (!TEMP) {
           st_f32<AUX>(B.om[v], r_omo, v4, so * 4);
-          st_u8<AUX>(B.b[v], r_lab, lb1[v], so);
         }
         dmid[v] = dm[v];
         mheld[v] = held[v];
