@@ -47,7 +47,7 @@ struct AdjPairPlane {
   float lam[V], th[V], w[V], pf[V], fa[V], sa[V];
   unsigned b[V];
   float hl;
-  unsigned hb, code;
+  unsigned hb;
 };
 
 typedef const __attribute__((address_space(4))) float ConstF;
@@ -69,9 +69,10 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int np = ny * nz;
-  const int fp = sg * seg;  // first voxel of the footprint; the segment starts a row later
+  const int lead = pair_lead(nz, V);
+  const int fp = sg * seg;  // first voxel of the footprint; the segment starts lead later
 
-  __amdgpu_buffer_rsrc_t r_lam, r_lab, r_th, r_tp, r_w, r_pf, r_sa, r_fa, r_out, r_code;
+  __amdgpu_buffer_rsrc_t r_lam, r_lab, r_th, r_tp, r_w, r_pf, r_sa, r_fa, r_out;
   {
     const size_t off = (size_t)xb * np;
     const size_t rest = (size_t)(nx - xb) * np;
@@ -84,29 +85,20 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
     r_sa = make_rsrc(a.sacc + off, rest * 4);
     r_fa = make_rsrc(a.facc + off, rest * 4);
     r_out = make_rsrc(a.lam_out + off, rest * 4);
-    r_code = make_rsrc(a.codes + (size_t)xb * segs * NW, (size_t)(nx - xb) * segs * NW);
   }
 
-  unsigned col[V], own4[V];
-  int cell[V];
-  unsigned long long ownm[V];
-  bool wave_owns = false, wave_valid = false;
+  // the forward kernel's lanes (rfa_pair_kernel.h)
+  const int first = pair_first(fp + V * tid, V, np);
+  const int cell = nz + first - fp;
+  const unsigned col = first < np ? (unsigned)first : 0u;
+  bool owns = false;
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    const int q = v * NT + ((v & 1) ? (NT - 64 - (tid & ~63)) + (tid & 63) : tid);
-    const int f = fp + q;
-    const bool valid = f < np;
-    // the plane's first and last rows are held (outer layer): they belong to
-    // the first and last segment, as part of their halo
-    const bool rows = (sg == 0 && f < nz) || (sg == segs - 1 && f >= np - nz);
-    const bool owned = valid && (rows || (q >= nz && q < nz + seg && f < np - nz));
-    cell[v] = nz + q;
-    col[v] = valid ? (unsigned)f : 0u;
-    own4[v] = owned ? (unsigned)f * 4u : kOob;
-    ownm[v] = __ballot(owned);
-    wave_owns = wave_owns || owned;
-    wave_valid = wave_valid || valid;
+    const int f = first + v, q = f - fp;
+    owns = owns || (f < np && (q >= lead || sg == 0) && (q < lead + seg || sg == segs - 1));
   }
+  const unsigned col4 = col * 4u, own4 = owns ? col4 : kOob;
+  const bool wave_valid = first < np, wave_owns = owns;
   const bool do_mid = __ballot(wave_valid) != 0ull;  // uniform
   const bool do_out = __ballot(wave_owns) != 0ull;   // uniform
   const bool has_halo = tid < 2 * nz;
@@ -119,30 +111,38 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
   }
   const unsigned hoff4 = hoff == kOob ? kOob : hoff * 4u;
   const bool sacc_all = a.sacc_all;
+  // class bytes of voxels whose Lambda is summed: free, and flagged unless all are
+  const unsigned sum_bits = sacc_all ? kHeld : kHeld | kSource;
+  const unsigned sum_want = sacc_all ? 0u : kSource;
 
   auto plane_of = [&](int x) { return min(max(x, 0), nx - 1) - xb; };  // uniform
   auto load = [&](int x, AdjPairPlane<V>& q) {
     const int so1 = plane_of(x) * np, so4 = so1 * 4;
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      q.b[v] = ld_u8(r_lab, col[v], so1);
-      q.lam[v] = ld_f32(r_lam, col[v] * 4u, so4);
-    }
-    q.code = ld_u8(r_code, 0u, (plane_of(x) * segs + sg) * NW + wave);
+    ld_u8v<V>(q.b, r_lab, col, so1);
+    ld_f32v<V>(q.lam, r_lam, col4, so4);
     q.hl = ld_f32(r_lam, hoff4, so4);
     q.hb = ld_u8(r_lab, hoff, so1);
+  };
+  // Whether a lane's Lambda moves: all, or where one of its voxels is flagged.
+  auto sums_at = [&](const unsigned (&b)[V]) {
+    unsigned any = 0u;
+#pragma unroll
+    for (int v = 0; v < V; ++v) any |= b[v];
+    return sacc_all || (any & kSource) != 0u;
   };
   // what only the own steps of plane x need
   auto load_own = [&](int x, AdjPairPlane<V>& q) {
     const int so4 = plane_of(x) * np * 4;
+    ld_f32v<V>(q.th, r_th, col4, so4);
+    ld_f32v<V>(q.w, r_w, col4, so4);
+    if constexpr (PERF) {
+      ld_f32v<V>(q.pf, r_pf, col4, so4);
+    } else {
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      q.th[v] = ld_f32(r_th, col[v] * 4u, so4);
-      q.w[v] = ld_f32(r_w, col[v] * 4u, so4);
-      q.pf[v] = PERF ? ld_f32(r_pf, col[v] * 4u, so4) : 1.0f;
-      q.fa[v] = ld_f32(r_fa, own4[v], so4);
-      q.sa[v] = ld_f32(r_sa, (sacc_all || (q.b[v] & kSource)) ? own4[v] : kOob, so4);
+      for (int v = 0; v < V; ++v) q.pf[v] = 1.0f;
     }
+    ld_f32v<V>(q.fa, r_fa, own4, so4);
+    ld_f32v<V>(q.sa, r_sa, sums_at(q.b) ? own4 : kOob, so4);
   };
 
   AdjPairPlane<V> ring[kRing];
@@ -151,25 +151,27 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
   {
     const int so = plane_of(xs - 1) * np;
     unsigned b0[V];
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      lp[v] = ld_f32(r_lam, col[v] * 4u, so * 4);
-      b0[v] = ld_u8(r_lab, col[v], so);
-    }
+    ld_f32v<V>(lp, r_lam, col4, so * 4);
+    ld_u8v<V>(b0, r_lab, col, so);
     load(xs, ring[0]);
     load(xs + 1, ring[1]);
     stage_pairs(sm.pc, sm.cls, a.tab, NT);
     load_own(xs, ring[0]);
 #pragma unroll
-    for (int v = 0; v < V; ++v) sm.lab[3][cell[v]] = (uint8_t)b0[v];
+    for (int v = 0; v < V; ++v) sm.lab[3][cell + v] = (uint8_t)b0[v];
   }
 #pragma unroll
   for (int v = 0; v < V; ++v) ring[3].w[v] = 0.0f, ring[3].pf[v] = 1.0f;
-  ring[3].code = 0u;
   // halo cells of the first-step planes enter only lanes whose results are dropped
   for (int c = tid; c < 2 * nz; c += NT) {
     const int e = c < nz ? c : P + c;
     sm.mid[0][e] = sm.mid[1][e] = 0.0f;
+  }
+  // nor is the cell after a voxel that two lanes share ever written
+  if (first != fp + V * tid) {
+    sm.in[0][cell + V] = sm.in[1][cell + V] = sm.mid[0][cell + V] = sm.mid[1][cell + V] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kRing; ++k) sm.lab[k][cell + V] = 0;
   }
   // first-step results of planes x - 1 and x - 2, accumulators of x - 1
   float m1[V], m2[V], mfa[V], msa[V], tp[V];
@@ -204,7 +206,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
       float off[V], diag[V], dr[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const int e = cell[v];
+        const int e = cell + v;
         diag[v] = 1.0f - (PERF ? B1 * pf[v] : B1);
         diag[v] -= kx;
         diag[v] -= kx;
@@ -216,8 +218,8 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
         o = __builtin_fmaf(kx, ln[v], o);
         o = __builtin_fmaf(ky, t[e - nz], o);
         o = __builtin_fmaf(ky, t[e + nz], o);
-        o = __builtin_fmaf(kz, t[e - 1], o);
-        off[v] = __builtin_fmaf(kz, t[e + 1], o);
+        o = __builtin_fmaf(kz, v > 0 ? l[v - 1] : t[cell - 1], o);
+        off[v] = __builtin_fmaf(kz, v < V - 1 ? l[v + 1] : t[cell + V], o);
         warm = warm || !(fabsf(th[v]) < K.cold);
       }
       const float kr = K.c2 * 0.69314718f;
@@ -241,20 +243,22 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
         const float d = (lb[v] & kTissue) ? dr[v] : 0.0f;
         const float lo = __builtin_fmaf(diag[v], l[v], off[v]) + w[v] * d;
         nl[v] = held ? 0.0f : lo;
-        sa[v] = held ? sa[v] : sa[v] + l[v];
+        sa[v] = (lb[v] & sum_bits) == sum_want ? sa[v] + l[v] : sa[v];
         fa[v] = held ? fa[v] : __builtin_fmaf(-B1, th[v] * l[v], fa[v]);
       }
     } else {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const int e = cell[v];
+        const int e = cell + v;
         const float nlam[6] = {lm[v], ln[v], t[e - nz], t[e + nz], t[e - 1], t[e + 1]};
         const unsigned nlab[6] = {tpv[e], bn[v], tl[e - nz], tl[e + nz], tl[e - 1], tl[e + 1]};
         const float2* pc = sm.pc;
+        const float sa0 = sa[v];
         adjoint_voxel(
             l[v], th[v], lb[v], pf[v], w[v], nlam, nlab,
             [pc](int ax, unsigned cq, unsigned cp) { return pair_from_pairs(pc, ax, cq, cp); },
             sm.cls, K, nl[v], sa[v], fa[v]);
+        sa[v] = (lb[v] & sum_bits) == sum_want ? sa[v] : sa0;
       }
     }
   };
@@ -263,14 +267,22 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
     constexpr int SL = decltype(SL_)::value;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      sm.in[SL & 1][cell[v]] = q.lam[v];
-      sm.lab[SL][cell[v]] = (uint8_t)q.b[v];
+      sm.in[SL & 1][cell + v] = q.lam[v];
+      sm.lab[SL][cell + v] = (uint8_t)q.b[v];
     }
     if (has_halo) {
       sm.in[SL & 1][hcell] = q.hl;
       sm.lab[SL][hcell] = (uint8_t)q.hb;
     }
   };
+
+  // wave codes of planes x - 1 and x, and the dword with that of x + 1
+  unsigned code = 0u, code_next, code_shift;
+  auto fetch_code = [&](int x) {
+    code_next = code_word(a.codes, ((size_t)(plane_of(x) + xb) * segs + sg) * NW + wave,
+                          code_shift);
+  };
+  fetch_code(xs);
 
   // The buffers' reuse is that of the forward kernel: what iteration x writes
   // was last read before its barrier.
@@ -285,8 +297,9 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
     const AdjPairPlane<V>& B = ring[SP];
     __syncthreads();
     load(x + 2, ring[SA]);
-    const unsigned code = __builtin_amdgcn_readfirstlane(C.code);
-    const unsigned pcode = __builtin_amdgcn_readfirstlane(B.code);
+    const unsigned pcode = code;
+    code = (code_next >> code_shift) & 0xffu;
+    fetch_code(x + 1);
     float n1[V], fa[V], sa[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -300,13 +313,12 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       lp[v] = C.lam[v];
-      sm.mid[BUF][cell[v]] = n1[v];
+      sm.mid[BUF][cell + v] = n1[v];
     }
     publish(std::integral_constant<int, SN>{}, N);
     load_own(x + 1, N);
     float tn[V];  // theta^{n-1} of plane x, for the next iteration
-#pragma unroll
-    for (int v = 0; v < V; ++v) tn[v] = ld_f32(r_tp, own4[v], plane_of(x) * np * 4);
+    ld_f32v<V>(tn, r_tp, own4, plane_of(x) * np * 4);
     {
       float o[V];
       const bool out = x > x0;  // uniform: plane x - 1 is in the chunk
@@ -316,13 +328,10 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
         step(sm.mid[BUF ^ 1], sm.lab[SP], sm.lab[SA], pcode, m1, m2, n1, mb, C.b, tp, B.w, B.pf, o,
              msa, mfa);
       const int so4 = plane_of(x - 1) * np * 4;
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const unsigned v4 = out ? own4[v] : kOob;
-        st_f32(o[v], r_out, v4, so4);
-        st_f32(mfa[v], r_fa, v4, so4);
-        st_f32(msa[v], r_sa, (sacc_all || (mb[v] & kSource)) ? v4 : kOob, so4);
-      }
+      const unsigned v4 = out ? own4 : kOob;
+      st_f32v<kStoreThrough, V>(o, r_out, v4, so4);
+      st_f32v<kStoreThrough, V>(mfa, r_fa, v4, so4);
+      st_f32v<kStoreThrough, V>(msa, r_sa, sums_at(mb) ? v4 : kOob, so4);
     }
 #pragma unroll
     for (int v = 0; v < V; ++v) {

@@ -9,10 +9,21 @@
 namespace rfa {
 
 // Footprint of a work-group of the two-step kernel: waves * 64 * v
-// consecutive voxels of a (y, z) plane, starting at a multiple of seg; its
-// segment, seg voxels, starts one row (nz voxels) later, and nz voxels on
-// either side are its halo.  The plane's first and last rows, which are held,
-// lie in the halo of the first and the last segment and are stored by them.
+// consecutive voxels of a (y, z) plane, starting at a multiple of seg, v
+// consecutive ones a lane.  Its segment, seg voxels, starts pair_lead()
+// voxels later (a row, rounded up so that a lane owns all its voxels or
+// none), and at least nz voxels on either side are its halo.  The plane's
+// first and last rows, which are held, lie in the halo of the first and the
+// last segment and are stored by them.
+__host__ __device__ __forceinline__ int pair_lead(int nz, int v) { return (nz + v - 1) / v * v; }
+
+// First voxel of the footprint's lane i, f = base + v i.  Where the plane's
+// voxels are odd in number, two a lane would run over its end: that lane
+// starts one voxel earlier and shares it with its neighbour, to the same bits.
+__device__ __forceinline__ int pair_first(int f, int v, int np) {
+  return v == 2 && f == np - 1 ? f - 1 : f;
+}
+
 struct PairShape {
   int waves = 0;   // wavefronts per work-group
   int v = 0;       // voxels per lane

@@ -25,8 +25,7 @@ __global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, const Cl
   bool found = false, regular = true;
   bool none = true, only_free = true, all = true;  // which voxels are tissue
   for (int j = 0; j < v; ++j) {
-    // the kernel's mapping: odd j runs through the waves in reverse
-    const int f = sg * seg + j * nt + ((j & 1) ? nw - 1 - wave : wave) * 64 + lane;
+    const int f = pair_first(sg * seg + v * (wave * 64 + lane), v, np) + j;  // the kernel's
     const bool valid = f < np;
     bool free = false, ok = true, tissue = false;
     unsigned c = 0u;
@@ -112,7 +111,7 @@ double pair_estimate_uneven(int waves, int v, int nwg, long long planes, int lon
 bool pair_fits(Grid3 g, int waves, int v, int xc) {
   for (const PairKind& k : kPairKinds)
     if (k.waves == waves && k.v == v)
-      return g.nz <= k.max_nz && 2 * g.nz <= 64 * waves && 64 * waves * v - 2 * g.nz >= 64 &&
+      return g.nz <= k.max_nz && 2 * g.nz <= 64 * waves && 64 * waves * v - pair_lead(g.nz, v) - g.nz >= 64 &&
              (double)(xc + 6) * g.ny * g.nz * 4.0 < 2147483647.0;
   return false;
 }
@@ -123,9 +122,10 @@ PairShape pair_shape(Grid3 g, int waves, int v, int xc) {
   s.v = v;
   s.xc = xc;
   const int np = g.ny * g.nz;
-  const int most = (64 * waves * v - 2 * g.nz) / 32 * 32;
+  const int lead = pair_lead(g.nz, v);
+  const int most = (64 * waves * v - lead - g.nz) / 32 * 32;
   // the plane's first and last rows are held and go along as halo
-  const int inner = np - 2 * g.nz;
+  const int inner = np - lead - g.nz;
   s.segs = (inner + most - 1) / most;
   s.seg = ((inner + s.segs - 1) / s.segs + 31) / 32 * 32;
   s.segs = (inner + s.seg - 1) / s.seg;

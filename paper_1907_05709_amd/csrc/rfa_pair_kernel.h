@@ -99,16 +99,6 @@ __device__ __forceinline__ ClassCoef class_coef(const Tables* tab, unsigned c) {
   return r;
 }
 
-// The aligned dword of the wave codes that holds byte i, and the shift that
-// brings the byte down: through the scalar cache, as a vector load and its
-// lane read would cost as much as a plane's temperatures.
-__device__ __forceinline__ unsigned code_word(const uint8_t* codes, size_t i, unsigned& shift) {
-  typedef const __attribute__((address_space(4))) unsigned ConstU;
-  const uintptr_t p = (uintptr_t)codes + i;
-  shift = 8u * (unsigned)(p & 3);
-  return *(ConstU*)(p & ~(uintptr_t)3);
-}
-
 // The step constants, read where they are used: as kernel arguments they
 // would occupy eight scalar registers through the plane loop, which spills.
 __device__ __forceinline__ StepConst step_constants(const Tables* tab) {
@@ -159,7 +149,8 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int np = ny * nz;
   const unsigned psz = (unsigned)np;
-  const int fp = sg * seg;  // first voxel of the footprint; the segment starts a row later
+  const int lead = pair_lead(nz, V);
+  const int fp = sg * seg;  // first voxel of the footprint; the segment starts lead later
 
   __amdgpu_buffer_rsrc_t r_hi, r_lo, r_lab, r_src, r_om, r_omo, r_pf, r_hio, r_loo, r_mid;
   {
@@ -177,31 +168,27 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     r_mid = KEEP ? make_rsrc(hi_mid + off, rest * 4) : r_hio;
   }
 
-  // Own voxels: column in the plane (0, a held corner, outside the grid),
-  // store offsets (out of range unless owned)
-  unsigned col[V], own4[V];
-  int cell[V];  // LDS cell
+  // Own voxels, V consecutive ones: the first's column in the plane (0, a
+  // held corner, outside the grid) and store offset (out of range unless
+  // owned)
+  const int first = pair_first(fp + V * tid, V, np);
+  const int cell = nz + first - fp;  // LDS cell of the first
+  const unsigned col = first < np ? (unsigned)first : 0u;
   unsigned long long ownm[V];  // lanes whose voxel is owned
-  bool wave_owns = false, wave_valid = false;
+  bool owns = false;
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    // odd v: waves in reverse order, so that the waves at the footprint's two
-    // ends, which hold only halo voxels, are the same ones and skip the
-    // second step
-    const int q = v * NT + ((v & 1) ? (NT - 64 - (tid & ~63)) + (tid & 63) : tid);
-    const int f = fp + q;
-    const bool valid = f < np;
-    cell[v] = nz + q;
+    const int f = first + v, q = f - fp;
     // the plane's first and last rows are held (outer layer): they belong to
-    // the first and last segment, as part of their halo
-    const bool rows = (sg == 0 && f < nz) || (sg == segs - 1 && f >= np - nz);
-    const bool owned = valid && (rows || (q >= nz && q < nz + seg && f < np - nz));
+    // the first and last segment, as part of their halo; a voxel shared by
+    // two lanes is the first one's
+    const bool owned = f < np && (q >= lead || sg == 0) && (q < lead + seg || sg == segs - 1) &&
+                       q >= V * tid;
     ownm[v] = __ballot(owned);
-    col[v] = valid ? (unsigned)f : 0u;
-    own4[v] = owned ? (unsigned)f * 4u : kOob;
-    wave_owns = wave_owns || owned;
-    wave_valid = wave_valid || valid;
+    owns = owns || owned;
   }
+  const unsigned col4 = col * 4u, own4 = owns ? col4 : kOob;
+  const bool wave_valid = first < np, wave_owns = owns;
   const bool do_mid = __ballot(wave_valid) != 0ull;  // uniform
   const unsigned long long out_lanes = __ballot(wave_owns);  // 0: the wave stores nothing
 
@@ -220,28 +207,29 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   auto plane_of = [&](int x) { return min(max(x, 0), nx - 1) - xb; };  // uniform
   auto load = [&](int x, PairPlane<V>& q) {
     const int so1 = plane_of(x) * (int)psz, so4 = so1 * 4;
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      q.b[v] = ld_u8(r_lab, col[v], so1);
-      q.h[v] = ld_f32(r_hi, col[v] * 4u, so4);
-      q.l[v] = ld_f32(r_lo, col[v] * 4u, so4);
-    }
+    ld_u8v<V>(q.b, r_lab, col, so1);
+    ld_f32v<V>(q.h, r_hi, col4, so4);
+    ld_f32v<V>(q.l, r_lo, col4, so4);
     q.hh = ld_f32(r_hi, hoff4, so4);
     q.hl = ld_f32(r_lo, hoff4, so4);
     q.hb = ld_u8(r_lab, hoff, so1);
   };
-  // what only the own step of plane x needs: source increments on flagged
-  // voxels (its class bytes are there), damage integral, perfusion factor
+  // what only the own step of plane x needs: source increments of lanes with
+  // a flagged voxel (its class bytes are there; 0 on others), damage
+  // integral, perfusion factor
   auto load_s = [&](int x, PairPlane<V>& q) {
     const int so4 = plane_of(x) * (int)psz * 4;
+    unsigned any = 0u;
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      q.s[v] = ld_f32(r_src, (q.b[v] & kSource) ? col[v] * 4u : kOob, so4);
-      // the damage integral enters the temperature only through the coupling:
-      // without a field it is read on owned voxels alone
-      q.om[v] = TEMP ? 0.0f : ld_f32(r_om, PERF ? col[v] * 4u : own4[v], so4);
-      if constexpr (PERF) q.pf[v] = ld_f32(r_pf, col[v] * 4u, so4);
-    }
+    for (int v = 0; v < V; ++v) any |= q.b[v];
+    ld_f32v<V>(q.s, r_src, (any & kSource) ? col4 : kOob, so4);
+    // the damage integral enters the temperature only through the coupling:
+    // without a field it is read on owned voxels alone
+    if constexpr (!TEMP) ld_f32v<V>(q.om, r_om, PERF ? col4 : own4, so4);
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if constexpr (TEMP) q.om[v] = 0.0f;
+    if constexpr (PERF) ld_f32v<V>(q.pf, r_pf, col4, so4);
   };
 
   PairPlane<V> ring[kPairRing];
@@ -249,13 +237,13 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   float din[V], dmid[V];  // difference to the x + 1 neighbour of the plane before
   {
     float ph[V], pl[V];
+    unsigned pb[V];
     const int so4 = plane_of(xs - 1) * (int)psz * 4;
+    ld_f32v<V>(ph, r_hi, col4, so4);
+    ld_f32v<V>(pl, r_lo, col4, so4);
+    ld_u8v<V>(pb, r_lab, col, so4 / 4);  // plane xs - 1
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      ph[v] = ld_f32(r_hi, col[v] * 4u, so4);
-      pl[v] = ld_f32(r_lo, col[v] * 4u, so4);
-      sm.lab[3][cell[v]] = (uint8_t)ld_u8(r_lab, col[v], so4 / 4);  // plane xs - 1
-    }
+    for (int v = 0; v < V; ++v) sm.lab[3][cell + v] = (uint8_t)pb[v];
     load(xs, ring[0]);
     load(xs + 1, ring[1]);
     stage_tables(sm.cf, sm.cls, b.tab, b.n_classes, NT);
@@ -281,6 +269,14 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     const int e = c < nz ? c : P + c;
     sm.mid[0][e] = sm.mid[1][e] = make_float2(0.0f, 0.0f);
   }
+  // nor does a lane write the cell after a shared voxel
+  if (first != fp + V * tid) {
+    const float2 zero = make_float2(0.0f, 0.0f);
+    sm.in[0][cell + V] = sm.in[1][cell + V] = zero;
+    sm.mid[0][cell + V] = sm.mid[1][cell + V] = zero;
+#pragma unroll
+    for (int k = 0; k < kPairRing; ++k) sm.lab[k][cell + V] = 0;
+  }
 
   // One step of this lane's V voxels, in place in q.  t: plane in LDS, dn:
   // difference to x + 1, dp: difference of x - 1 to the plane (both from
@@ -304,6 +300,16 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
       if constexpr (PERF) f[v] = q.pf[v] * __builtin_amdgcn_exp2f(-q.om[v] * K.decay2);
     }
     float nh[V], nl[V];
+    // differences along z, each formed once: to the voxel before the lane's,
+    // between them, to the one after (a difference reversed is its negative)
+    float dz[V + 1];
+    {
+      const float2 zm = t[cell - 1], zp = t[cell + V];
+      dz[0] = -ff_diff(zm.x, zm.y, q.h[0], q.l[0]);
+#pragma unroll
+      for (int v = 1; v < V; ++v) dz[v] = ff_diff(q.h[v], q.l[v], q.h[v - 1], q.l[v - 1]);
+      dz[V] = ff_diff(zp.x, zp.y, q.h[V - 1], q.l[V - 1]);
+    }
     if (code != kPairIrregular) {
       const ClassCoef coef = class_coef(b.tab, code & (kMaxClasses - 1));
       const float2 k[6] = {coef.k[0], coef.k[0], coef.k[1], coef.k[1], coef.k[2], coef.k[2]};
@@ -312,10 +318,9 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const float h = q.h[v], l = q.l[v];
-        const int c = cell[v];
-        const float2 ym = t[c - nz], yp = t[c + nz], zm = t[c - 1], zp = t[c + 1];
+        const float2 ym = t[cell + v - nz], yp = t[cell + v + nz];
         const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h, l), ff_diff(yp.x, yp.y, h, l),
-                            ff_diff(zm.x, zm.y, h, l), ff_diff(zp.x, zp.y, h, l)};
+                            -dz[v], dz[v + 1]};
         float h2, l2, cond, perf;
         thermal_update(h, l, k, coef.c, d, q.s[v], f[v], h2, l2, cond, perf, incs[v]);
         nh[v] = lane_of(heldm[v]) ? h : h2;
@@ -363,10 +368,10 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
       for (int v = 0; v < V; ++v) {
         const float h = q.h[v], l = q.l[v];
         const unsigned lb = q.b[v];
-        const int c = cell[v];
-        const float2 ym = t[c - nz], yp = t[c + nz], zm = t[c - 1], zp = t[c + 1];
+        const int c = cell + v;
+        const float2 ym = t[c - nz], yp = t[c + nz];
         const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h, l), ff_diff(yp.x, yp.y, h, l),
-                            ff_diff(zm.x, zm.y, h, l), ff_diff(zp.x, zp.y, h, l)};
+                            -dz[v], dz[v + 1]};
         const float2 k[6] = {table_entry(sm.cf, 0, lb, tp[c]),
                              table_entry(sm.cf, 0, lb, bn[v]),
                              table_entry(sm.cf, 1, lb, tl[c - nz]),
@@ -402,8 +407,8 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     constexpr int SL = decltype(SL_)::value;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      sm.in[SL & 1][cell[v]] = make_float2(q.h[v], q.l[v]);
-      sm.lab[SL][cell[v]] = (uint8_t)q.b[v];
+      sm.in[SL & 1][cell + v] = make_float2(q.h[v], q.l[v]);
+      sm.lab[SL][cell + v] = (uint8_t)q.b[v];
     }
     if (has_halo) {
       sm.in[SL & 1][hcell] = make_float2(q.hh, q.hl);
@@ -451,14 +456,13 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       din[v] = dn[v];
-      sm.mid[BUF][cell[v]] = make_float2(C.h[v], C.l[v]);
+      sm.mid[BUF][cell + v] = make_float2(C.h[v], C.l[v]);
     }
     publish(std::integral_constant<int, SN>{}, N);
     load_s(x + 1, N);
     if constexpr (KEEP) {
       const int so = plane_of(x) * (int)psz * 4;
-#pragma unroll
-      for (int v = 0; v < V; ++v) st_f32<AUX>(C.h[v], r_mid, in_chunk ? own4[v] : kOob, so);
+      st_f32v<AUX, V>(C.h, r_mid, in_chunk ? own4 : kOob, so);
     }
     // second step of plane x - 1
     {
@@ -480,20 +484,18 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
 #pragma unroll
             for (int v = 0; v < V; ++v)
               st_u8<AUX>(B.b[v], r_lab,
-                         lane_of(ownm[v]) && B.b[v] != sm.lab[SP][cell[v]] ? col[v] : kOob,
+                         lane_of(ownm[v]) && B.b[v] != sm.lab[SP][cell + v] ? col + v : kOob,
                          plane_of(x - 1) * (int)psz);
           }
         }
       }
       const int so = plane_of(x - 1) * (int)psz;
+      const unsigned v4 = out ? own4 : kOob;
+      st_f32v<AUX, V>(B.h, r_hio, v4, so * 4);
+      st_f32v<AUX, V>(B.l, r_loo, v4, so * 4);
+      if constexpr (!TEMP) st_f32v<AUX, V>(B.om, r_omo, v4, so * 4);
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const unsigned v4 = out ? own4[v] : kOob;
-        st_f32<AUX>(B.h[v], r_hio, v4, so * 4);
-        st_f32<AUX>(B.l[v], r_loo, v4, so * 4);
-        if constexpr (!TEMP) {
-          st_f32<AUX>(B.om[v], r_omo, v4, so * 4);
-        }
         dmid[v] = dm[v];
         mheld[v] = held[v];
       }

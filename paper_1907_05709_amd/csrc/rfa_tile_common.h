@@ -65,6 +65,53 @@ __device__ __forceinline__ void st_u8(unsigned v, __amdgpu_buffer_rsrc_t r, unsi
   __builtin_amdgcn_raw_buffer_store_b8((uint8_t)v, r, (int)voff, soff, AUX);
 }
 
+// The aligned dword of the wave codes that holds byte i, and the shift that
+// brings the byte down: through the scalar cache, as a vector load and its
+// lane read would cost as much as a plane's temperatures.
+__device__ __forceinline__ unsigned code_word(const uint8_t* codes, size_t i, unsigned& shift) {
+  typedef const __attribute__((address_space(4))) unsigned ConstU;
+  const uintptr_t p = (uintptr_t)codes + i;
+  shift = 8u * (unsigned)(p & 3);
+  return *(ConstU*)(p & ~(uintptr_t)3);
+}
+
+// One or two consecutive values a lane, in one instruction (a multi-byte
+// access needs no alignment beyond its elements').
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+template <int V>
+__device__ __forceinline__ void ld_f32v(float (&o)[V], __amdgpu_buffer_rsrc_t r, unsigned voff,
+                                        int soff) {
+  static_assert(V == 1 || V == 2, "one or two values a lane");
+  if constexpr (V == 1) {
+    o[0] = ld_f32(r, voff, soff);
+  } else {
+    const u32x2 u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, soff, 0);
+    o[0] = __uint_as_float(u.x);
+    o[1] = __uint_as_float(u.y);
+  }
+}
+template <int V>
+__device__ __forceinline__ void ld_u8v(unsigned (&o)[V], __amdgpu_buffer_rsrc_t r, unsigned voff,
+                                       int soff) {
+  if constexpr (V == 1) {
+    o[0] = ld_u8(r, voff, soff);
+  } else {
+    const unsigned u = (unsigned)__builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, soff, 0);
+    o[0] = u & 0xffu;
+    o[1] = u >> 8;
+  }
+}
+template <int AUX, int V>
+__device__ __forceinline__ void st_f32v(const float (&v)[V], __amdgpu_buffer_rsrc_t r,
+                                        unsigned voff, int soff) {
+  if constexpr (V == 1) {
+    st_f32<AUX>(v[0], r, voff, soff);
+  } else {
+    const u32x2 u = {__float_as_uint(v[0]), __float_as_uint(v[1])};
+    __builtin_amdgcn_raw_buffer_store_b64(u, r, (int)voff, soff, AUX);
+  }
+}
+
 // Stage the coefficient tables of the nc classes in use into LDS.
 __device__ __forceinline__ void stage_tables(float2* cf, float4* cls, const Tables* tab, int nc,
                                              int nthreads) {

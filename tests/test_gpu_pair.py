@@ -53,6 +53,9 @@ def _perfusion(g, form, shape):
     ((5, 6, 7), "random", "class", {}),
     ((9, 40, 60), "regions", "class", dict(depth=2, tile_y=8, tile_x=1)),
     ((21, 40, 200), "held_tissue", "field", dict(depth=2, tile_y=16, tile_x=64)),
+    # planes of an odd number of voxels: two lanes share one, rows start anywhere
+    ((30, 41, 129), "regions", "coupled", {}),
+    ((9, 121, 113), "held_tissue", "field", dict(depth=2, tile_y=8, tile_x=4)),
 ])
 def test_pair_kernel_bitwise_equals_reference(shape, kind, form, kw):
     case = _case(kind, shape, 5)
@@ -87,6 +90,8 @@ def test_pair_kernel_bitwise_equals_reference(shape, kind, form, kw):
     ((13, 21, 64), "random", 3, 10, True, True),
     ((40, 64, 128), "regions", 0, 6, True, False),
     ((60, 50, 70), "tissue_everywhere", 4, 9, False, True),
+    ((13, 21, 133), "random", 3, 10, True, False),
+    ((40, 121, 117), "regions", 0, 7, True, True),
 ])
 def test_adjoint_over_pair_steps_equals_reference(shape, kind, every, steps, spline, off):
     """Kept trajectories, checkpoints and recomputed segments (odd and even
