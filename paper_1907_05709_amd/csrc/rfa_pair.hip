@@ -60,20 +60,22 @@ __global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, const Cl
 namespace {
 
 // Work-groups built, and what a launch of them takes.  A launch costs about
-// 5 us plus, per round of resident work-groups, xc + 2 plane iterations (the
+// 3 us plus, per round of resident work-groups, xc + 2 plane iterations (the
 // first step runs on one plane more at either end of a chunk).  An
 // iteration's time grows with the work-groups m that share a compute unit,
-// a + b m; a and b fitted to 100-step runs of 11 grids from 32^3 to 256^3,
-// every kind and 16 chunk lengths (the fit holds to 10 % where it decides).
+// a + b m; a and b fitted to runs of 19 grids from 32^3 to 256^3, every kind
+// and up to 22 chunk lengths.  Over those grids the pick is within 1 % of
+// the fastest (geometric mean; 4.6 % at worst).
 struct PairKind {
   int waves, v, max_nz;
   int per_cu;   // work-groups a compute unit holds
   double a, b;  // us per iteration
 };
-constexpr PairKind kPairKinds[] = {{16, 2, 256, 1, 1.0, 1.8},
-                                   {8, 2, 128, 2, 1.0, 0.8},
-                                   {8, 1, 128, 2, 0.5, 0.45},
-                                   {4, 1, 96, 5, 0.35, 0.28}};
+constexpr PairKind kPairKinds[] = {{16, 2, 256, 1, 1.2, 1.15},
+                                   {8, 2, 128, 2, 0.98, 0.57},
+                                   {8, 1, 128, 2, 0.64, 0.34},
+                                   {4, 1, 96, 5, 0.7, 0.155}};
+constexpr double kLaunchUs = 2.8;
 constexpr int kCu = 256;
 
 }  // namespace
@@ -89,7 +91,7 @@ double pair_estimate(int waves, int v, int nwg, int xc) {
   for (const PairKind& k : kPairKinds) {
     if (k.waves != waves || k.v != v) continue;
     const int slots = kCu * k.per_cu, rest = nwg % slots;
-    double us = 5.0 + (nwg / slots) * (xc + 2) * (k.a + k.b * k.per_cu);
+    double us = kLaunchUs + (nwg / slots) * (xc + 2) * (k.a + k.b * k.per_cu);
     if (rest) us += (xc + 2) * (k.a + k.b * ((rest + kCu - 1) / kCu));
     return us;
   }
@@ -102,8 +104,8 @@ double pair_estimate_uneven(int waves, int v, int nwg, long long planes, int lon
     const int slots = kCu * k.per_cu;
     // one round: the longest; more: the slots share the work and, on average,
     // wait for half of a last work-group
-    if (nwg <= slots) return 5.0 + longest * (k.a + k.b * ((nwg + kCu - 1) / kCu));
-    return 5.0 + ((double)planes / slots + 0.5 * longest) * (k.a + k.b * k.per_cu);
+    if (nwg <= slots) return kLaunchUs + longest * (k.a + k.b * ((nwg + kCu - 1) / kCu));
+    return kLaunchUs + ((double)planes / slots + 0.5 * longest) * (k.a + k.b * k.per_cu);
   }
   return 1e300;
 }
