@@ -37,8 +37,8 @@ struct AdjPairSmem {
   static constexpr int CELLS = P + 2 * MAXNZ;
   float2 pc[3 * kMaxClasses * kMaxClasses];  // pair table
   float4 cls[kMaxClasses];
-  float in[2][CELLS];   // lambda^{n+1}: footprint q at nz + q
-  float mid[2][CELLS];  // lambda^n
+  alignas(8) float in[2][CELLS];   // lambda^{n+1}: footprint q at pair_lead + q
+  alignas(8) float mid[2][CELLS];  // lambda^n
   uint8_t lab[kRing][CELLS];
 };
 
@@ -54,7 +54,9 @@ typedef const __attribute__((address_space(4))) float ConstF;
 
 }  // namespace
 
-template <int NT, int V, int MAXNZ, bool PERF>
+// EVEN: rows of an even number of voxels and two voxels a lane, whose cells are
+// then one aligned access in every row (as in the forward kernel).
+template <int NT, int V, int MAXNZ, bool PERF, bool EVEN>
 __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx, int ny, int nz,
                                                         int xc, int seg, int segs, int nwg) {
   using S = AdjPairSmem<NT, V, MAXNZ>;
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
 
   // the forward kernel's lanes (rfa_pair_kernel.h)
   const int first = pair_first(fp + V * tid, V, np);
-  const int cell = nz + first - fp;
+  const int cell = lead + first - fp;
   const unsigned col = first < np ? (unsigned)first : 0u;
   bool owns = false;
 #pragma unroll
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
   unsigned hoff = kOob;
   if (has_halo) {
     const int f = tid < nz ? fp - nz + tid : fp - nz + P + tid;
-    hcell = tid < nz ? tid : P + tid;
+    hcell = lead - nz + (tid < nz ? tid : P + tid);
     if (f >= 0 && f < np) hoff = (unsigned)f;
   }
   const unsigned hoff4 = hoff == kOob ? kOob : hoff * 4u;
@@ -164,7 +166,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
   for (int v = 0; v < V; ++v) ring[3].w[v] = 0.0f, ring[3].pf[v] = 1.0f;
   // halo cells of the first-step planes enter only lanes whose results are dropped
   for (int c = tid; c < 2 * nz; c += NT) {
-    const int e = c < nz ? c : P + c;
+    const int e = lead - nz + (c < nz ? c : P + c);
     sm.mid[0][e] = sm.mid[1][e] = 0.0f;
   }
   // nor is the cell after a voxel that two lanes share ever written
@@ -199,6 +201,15 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
     K.tak = q[2];
     K.clamp2 = q[3];
     K.cold = q[7];
+    float2 rm, rp;  // rows y - 1 and y + 1
+    if constexpr (EVEN) {
+      rm = *reinterpret_cast<const float2*>(t + (cell - nz));
+      rp = *reinterpret_cast<const float2*>(t + (cell + nz));
+    }
+    auto row = [&](int v, int o, const float2& r) {
+      if constexpr (EVEN) return v == 0 ? r.x : r.y;
+      return t[cell + v + o];
+    };
     if (code != kPairIrregular) {
       ConstF* c = (ConstF*)tab + offsetof(Tables, adj) / 4 + 4 * (code & (kMaxClasses - 1));
       const float kx = c[0], ky = c[1], kz = c[2], B1 = c[3];
@@ -206,7 +217,6 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
       float off[V], diag[V], dr[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const int e = cell + v;
         diag[v] = 1.0f - (PERF ? B1 * pf[v] : B1);
         diag[v] -= kx;
         diag[v] -= kx;
@@ -216,8 +226,8 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
         diag[v] -= kz;
         float o = kx * lm[v];
         o = __builtin_fmaf(kx, ln[v], o);
-        o = __builtin_fmaf(ky, t[e - nz], o);
-        o = __builtin_fmaf(ky, t[e + nz], o);
+        o = __builtin_fmaf(ky, row(v, -nz, rm), o);
+        o = __builtin_fmaf(ky, row(v, nz, rp), o);
         o = __builtin_fmaf(kz, v > 0 ? l[v - 1] : t[cell - 1], o);
         off[v] = __builtin_fmaf(kz, v < V - 1 ? l[v + 1] : t[cell + V], o);
         warm = warm || !(fabsf(th[v]) < K.cold);
@@ -250,7 +260,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const int e = cell + v;
-        const float nlam[6] = {lm[v], ln[v], t[e - nz], t[e + nz], t[e - 1], t[e + 1]};
+        const float nlam[6] = {lm[v], ln[v], row(v, -nz, rm), row(v, nz, rp), t[e - 1], t[e + 1]};
         const unsigned nlab[6] = {tpv[e], bn[v], tl[e - nz], tl[e + nz], tl[e - 1], tl[e + 1]};
         const float2* pc = sm.pc;
         const float sa0 = sa[v];
@@ -263,13 +273,20 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
     }
   };
 
+  auto put = [&](float* p, const float (&l)[V]) {
+    if constexpr (EVEN) {
+      *reinterpret_cast<float2*>(p) = make_float2(l[0], l[1]);
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v) p[v] = l[v];
+    }
+  };
+
   auto publish = [&](auto SL_, const AdjPairPlane<V>& q) {
     constexpr int SL = decltype(SL_)::value;
+    put(sm.in[SL & 1] + cell, q.lam);
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      sm.in[SL & 1][cell + v] = q.lam[v];
-      sm.lab[SL][cell + v] = (uint8_t)q.b[v];
-    }
+    for (int v = 0; v < V; ++v) sm.lab[SL][cell + v] = (uint8_t)q.b[v];
     if (has_halo) {
       sm.in[SL & 1][hcell] = q.hl;
       sm.lab[SL][hcell] = (uint8_t)q.hb;
@@ -310,11 +327,9 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
     if (do_mid)
       step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C.lam, lp, N.lam, C.b, N.b, C.th, C.w, C.pf,
            n1, sa, fa);
+    put(sm.mid[BUF] + cell, n1);
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      lp[v] = C.lam[v];
-      sm.mid[BUF][cell + v] = n1[v];
-    }
+    for (int v = 0; v < V; ++v) lp[v] = C.lam[v];
     publish(std::integral_constant<int, SN>{}, N);
     load_own(x + 1, N);
     float tn[V];  // theta^{n-1} of plane x, for the next iteration
@@ -366,13 +381,17 @@ namespace {
 template <int NT, int V, int MAXNZ>
 hipError_t launch_kind(const PairShape& s, Grid3 g, const AdjointBuffers& a, hipStream_t st) {
   const dim3 grid(s.nwg), block(NT);
-  if (a.perf)
-    hipLaunchKernelGGL((k_adjoint_pair<NT, V, MAXNZ, true>), grid, block, 0, st, a, g.nx, g.ny,
-                       g.nz, s.xc, s.seg, s.segs, s.nwg);
-  else
-    hipLaunchKernelGGL((k_adjoint_pair<NT, V, MAXNZ, false>), grid, block, 0, st, a, g.nx, g.ny,
-                       g.nz, s.xc, s.seg, s.segs, s.nwg);
-  return hipGetLastError();
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, a, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs,
+                       s.nwg);
+    return hipGetLastError();
+  };
+  if constexpr (V == 2)
+    if (g.nz % 2 == 0)
+      return a.perf ? go(k_adjoint_pair<NT, V, MAXNZ, true, true>)
+                    : go(k_adjoint_pair<NT, V, MAXNZ, false, true>);
+  return a.perf ? go(k_adjoint_pair<NT, V, MAXNZ, true, false>)
+                : go(k_adjoint_pair<NT, V, MAXNZ, false, false>);
 }
 
 }  // namespace

@@ -28,19 +28,21 @@
 //    is also cold (|theta| below K.cold everywhere, so that the damage
 //    exponent rounds to 2^0), the transcendentals are skipped.
 //
-// What bounds it: vector instructions, issued at some three quarters of the
-// chip's rate (256^3: about 210 a wave and plane for two steps of two voxels,
-// 87 scalar ones beside them); uniform branches cost as much as the few
+// What bounds it: on large grids memory and issue alike (256^3 without sums
+// 50.9 us a step, 4.1 TB/s at 12.5 bytes a voxel step; vector instructions
+// take two thirds of the cycles, about 200 a wave and plane for two steps of
+// two voxels), on small ones the planes computed twice and the latency of a
+// plane.  A vector memory instruction costs as much as 16 arithmetic ones, so
+// a lane's two voxels are consecutive and move as one access (11 a wave and
+// plane; 22 with single ones); uniform branches cost as much as the few
 // instructions they skip, so there are few.  The first step on halo rows and
 // planes is computed twice, so the footprint is trimmed to what the second
 // step reads: held rows at a plane's ends belong to nobody's segment, and
-// halo voxels pass on a temperature but no damage, latch or sum (128^3 12.9
-// -> 12.2 us a step).  Planes are updated in place in their registers, and
-// what few waves need is selected by lane masks (256^3 without sums 59 ->
-// 56.5, 192^3 26.4 -> 25.1).  Against one step a pass (us a step, with
-// sums): 32^3 6.0 -> 3.4, 64^3 6.4 -> 5.0, 96^3 12.0 -> 7.7, 128^3 13.3 ->
-// 11.8, 161x149x117 without sums 20.6 -> 12.7, 160x152x144 coupled 35.7 ->
-// 17.9, 256x256x234 91 -> 57.4, 256^3 80 -> 62.8.
+// halo voxels pass on a temperature but no damage, latch or sum.  Against one
+// step a pass (us a step, with sums): 32^3 6.0 -> 3.3, 48^3 6.4 -> 3.9, 64^3
+// 6.4 -> 4.9, 96^3 12.0 -> 7.1, 128^3 13.3 -> 10.8, 161x149x117 without sums
+// 20.6 -> 12.5, 160x152x144 coupled 35.7 -> 16.6, 256x256x234 91 -> 52.4,
+// 256^3 80 -> 57.0.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -65,8 +67,8 @@ struct PairSmem {
   float2 cf[3 * kMaxClasses * kMaxClasses];
   float4 cls[kMaxClasses];
   uint8_t lab[kPairRing][CELLS];
-  float2 in[2][CELLS];    // input planes: footprint q at nz + q
-  float2 mid[2][CELLS];   // first-step planes, footprint q at nz + q (halo cells unused)
+  alignas(16) float2 in[2][CELLS];    // input planes: footprint q at pair_lead + q
+  alignas(16) float2 mid[2][CELLS];   // first-step planes, footprint q at pair_lead + q (halo cells unused)
   float red[3 * NT / 64];
 };
 
@@ -135,7 +137,11 @@ namespace {
 
 // The march of one work-group: segment sg of planes [x0, x1).  out: its
 // partial sums (DIAG).
-template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE>
+// EVEN: rows of an even number of voxels and two voxels a lane, whose LDS cells
+// are then 16-byte aligned in every row and move as one access.  As two of 8
+// bytes, 16 apart from lane to lane, they meet in the same banks (128^3: 41 %
+// of the LDS cycles; 11.5 us a step against 10.7).
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE, bool EVEN>
 __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const StepBuffers& b,
                                            float* hi_mid, int nx, int ny, int nz, int x0, int x1,
                                            int seg, int segs, int sg, float* out) {
@@ -172,7 +178,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   // held corner, outside the grid) and store offset (out of range unless
   // owned)
   const int first = pair_first(fp + V * tid, V, np);
-  const int cell = nz + first - fp;  // LDS cell of the first
+  const int cell = lead + first - fp;  // LDS cell of the first
   const unsigned col = first < np ? (unsigned)first : 0u;
   unsigned long long ownm[V];  // lanes whose voxel is owned
   bool owns = false;
@@ -199,7 +205,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   unsigned hoff = kOob;
   if (has_halo) {
     const int f = tid < nz ? fp - nz + tid : fp - nz + P + tid;
-    hcell = tid < nz ? tid : P + tid;
+    hcell = lead - nz + (tid < nz ? tid : P + tid);
     if (f >= 0 && f < np) hoff = (unsigned)f;
   }
   const unsigned hoff4 = hoff == kOob ? kOob : hoff * 4u;
@@ -266,7 +272,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
   // halo cells of the first-step planes are never written: they enter only
   // lanes whose results are dropped, but must be finite
   for (int c = tid; c < 2 * nz; c += NT) {
-    const int e = c < nz ? c : P + c;
+    const int e = lead - nz + (c < nz ? c : P + c);
     sm.mid[0][e] = sm.mid[1][e] = make_float2(0.0f, 0.0f);
   }
   // nor does a lane write the cell after a shared voxel
@@ -300,6 +306,16 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
       if constexpr (PERF) f[v] = q.pf[v] * __builtin_amdgcn_exp2f(-q.om[v] * K.decay2);
     }
     float nh[V], nl[V];
+    // rows y - 1 and y + 1 (EVEN: both voxels in one 16-byte read)
+    float4 rm, rp;
+    if constexpr (EVEN) {
+      rm = *reinterpret_cast<const float4*>(t + (cell - nz));
+      rp = *reinterpret_cast<const float4*>(t + (cell + nz));
+    }
+    auto row = [&](int v, int o, const float4& r) {
+      if constexpr (EVEN) return v == 0 ? make_float2(r.x, r.y) : make_float2(r.z, r.w);
+      return t[cell + v + o];
+    };
     // differences along z, each formed once: to the voxel before the lane's,
     // between them, to the one after (a difference reversed is its negative)
     float dz[V + 1];
@@ -318,7 +334,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const float h = q.h[v], l = q.l[v];
-        const float2 ym = t[cell + v - nz], yp = t[cell + v + nz];
+        const float2 ym = row(v, -nz, rm), yp = row(v, nz, rp);
         const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h, l), ff_diff(yp.x, yp.y, h, l),
                             -dz[v], dz[v + 1]};
         float h2, l2, cond, perf;
@@ -369,7 +385,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
         const float h = q.h[v], l = q.l[v];
         const unsigned lb = q.b[v];
         const int c = cell + v;
-        const float2 ym = t[c - nz], yp = t[c + nz];
+        const float2 ym = row(v, -nz, rm), yp = row(v, nz, rp);
         const float d[6] = {-dp[v], dn[v], ff_diff(ym.x, ym.y, h, l), ff_diff(yp.x, yp.y, h, l),
                             -dz[v], dz[v + 1]};
         const float2 k[6] = {table_entry(sm.cf, 0, lb, tp[c]),
@@ -402,14 +418,22 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     }
   };
 
+  // a lane's temperatures to LDS
+  auto put = [&](float2* p, const PairPlane<V>& q) {
+    if constexpr (EVEN) {
+      *reinterpret_cast<float4*>(p) = make_float4(q.h[0], q.l[0], q.h[1], q.l[1]);
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v) p[v] = make_float2(q.h[v], q.l[v]);
+    }
+  };
+
   // input plane q (of ring slot SL) to LDS
   auto publish = [&](auto SL_, const PairPlane<V>& q) {
     constexpr int SL = decltype(SL_)::value;
+    put(sm.in[SL & 1] + cell, q);
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      sm.in[SL & 1][cell + v] = make_float2(q.h[v], q.l[v]);
-      sm.lab[SL][cell + v] = (uint8_t)q.b[v];
-    }
+    for (int v = 0; v < V; ++v) sm.lab[SL][cell + v] = (uint8_t)q.b[v];
     if (has_halo) {
       sm.in[SL & 1][hcell] = make_float2(q.hh, q.hl);
       sm.lab[SL][hcell] = (uint8_t)q.hb;
@@ -453,11 +477,9 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
     if constexpr (!DIAG) asm("" : "+s"(own));
     if (do_mid)
       step(sm.in[BUF], sm.lab[SL], sm.lab[SP], code, C, dn, din, N.b, held, own);
+    put(sm.mid[BUF] + cell, C);
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      din[v] = dn[v];
-      sm.mid[BUF][cell + v] = make_float2(C.h[v], C.l[v]);
-    }
+    for (int v = 0; v < V; ++v) din[v] = dn[v];
     publish(std::integral_constant<int, SN>{}, N);
     load_s(x + 1, N);
     if constexpr (KEEP) {
@@ -523,16 +545,16 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
 
 }  // namespace
 
-template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE>
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE, bool EVEN>
 __global__ __launch_bounds__(NT, 4) void k_step_pair(StepBuffers b, float* hi_mid, int nx, int ny,
                                                      int nz, int xc, int seg, int segs,
                                                      int nwg) {
   __shared__ PairSmem<NT, V, MAXNZ> sm;
   const int wg = remap_xcd(blockIdx.x, nwg);
   const int x0 = (wg / segs) * xc;
-  pair_march<NT, V, MAXNZ, PERF, DIAG, AUX, MODE>(sm, b, hi_mid, nx, ny, nz, x0,
-                                                  min(x0 + xc, nx), seg, segs, wg % segs,
-                                                  DIAG ? b.partials + (size_t)wg * 3 : nullptr);
+  pair_march<NT, V, MAXNZ, PERF, DIAG, AUX, MODE, EVEN>(
+      sm, b, hi_mid, nx, ny, nz, x0, min(x0 + xc, nx), seg, segs, wg % segs,
+      DIAG ? b.partials + (size_t)wg * 3 : nullptr);
 }
 
 // The same over the work items of a batch group (one work-group per item, in
@@ -565,38 +587,42 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair_batch(const PairInstance* i
   b.partials = nullptr;
   const int nx = I->nx, xc = I->xc;
   const int x0 = w->chunk * xc;
-  pair_march<NT, V, MAXNZ, PERF, DIAG, kStoreBack, kPairFull>(
-      sm, b, nullptr, nx, I->ny, I->nz, x0, min(x0 + xc, nx), I->seg, I->segs, w->sg,
-      DIAG ? partials + (size_t)it * 3 : nullptr);
+  float* out = DIAG ? partials + (size_t)it * 3 : nullptr;
+  // a batch mixes even and odd rows; both forms in one kernel spill scalar
+  // registers (24 grids of 64 .. 160, with sums: 177 us a step against 171)
+  pair_march<NT, V, MAXNZ, PERF, DIAG, kStoreBack, kPairFull, false>(
+      sm, b, nullptr, nx, I->ny, I->nz, x0, min(x0 + xc, nx), I->seg, I->segs, w->sg, out);
 }
 
 
 namespace {
 
-template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX>
-hipError_t launch_mode(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode, float* hi_mid, hipStream_t st) {
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX, int MODE>
+hipError_t launch_rows(const PairShape& s, Grid3 g, const StepBuffers& b, float* hi_mid,
+                       hipStream_t st) {
   const dim3 grid(s.nwg), block(NT);
-  switch (mode) {
-    case kPairFull:
-      hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, DIAG, AUX, kPairFull>), grid, block, 0,
-                         st, b, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
-      break;
-    case kPairKeep:
-      if constexpr (!DIAG)
-        hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, false, AUX, kPairKeep>), grid, block,
-                           0, st, b, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
-      else
-        return hipErrorInvalidValue;
-      break;
-    case kPairTemp:
-      if constexpr (!DIAG)
-        hipLaunchKernelGGL((k_step_pair<NT, V, MAXNZ, PERF, false, AUX, kPairTemp>), grid, block,
-                           0, st, b, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg, s.segs, s.nwg);
-      else
-        return hipErrorInvalidValue;
-      break;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, b, hi_mid, g.nx, g.ny, g.nz, s.xc, s.seg,
+                       s.segs, s.nwg);
+    return hipGetLastError();
+  };
+  if constexpr (V == 2)
+    if (g.nz % 2 == 0) return go(k_step_pair<NT, V, MAXNZ, PERF, DIAG, AUX, MODE, true>);
+  return go(k_step_pair<NT, V, MAXNZ, PERF, DIAG, AUX, MODE, false>);
+}
+
+template <int NT, int V, int MAXNZ, bool PERF, bool DIAG, int AUX>
+hipError_t launch_mode(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,
+                       float* hi_mid, hipStream_t st) {
+  if (mode == kPairFull)
+    return launch_rows<NT, V, MAXNZ, PERF, DIAG, AUX, kPairFull>(s, g, b, hi_mid, st);
+  if constexpr (!DIAG) {
+    if (mode == kPairKeep)
+      return launch_rows<NT, V, MAXNZ, PERF, false, AUX, kPairKeep>(s, g, b, hi_mid, st);
+    if (mode == kPairTemp)
+      return launch_rows<NT, V, MAXNZ, PERF, false, AUX, kPairTemp>(s, g, b, hi_mid, st);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 template <int NT, int V, int MAXNZ, int AUX>
