@@ -23,7 +23,8 @@ share of the 256^3 case (its middle y slab, 256x34x256).
 
 Prints one JSON line: voxel-updates/s over the timed steps, the dominant
 kernel's roofline (algorithmic bytes per launch over its HIP-event-timed
-average duration), and the FP64 oracle timed on this host's cores (all of
+average duration; a launch of the default plans takes two steps in one pass
+over memory), and the FP64 oracle timed on this host's cores (all of
 them, and one) on a bounded sample of the same workload.
 """
 from __future__ import annotations
@@ -53,14 +54,10 @@ SOURCE_BYTES = 4
 # on the source's support only.
 ADJ_BYTES_PER_VOXEL_STEP = 29
 ADJ_SOURCE_BYTES = 8
-# Adjoint launch on the 128^3 differentiation grid: 8-row tiles of 64 z, 16 x
-# planes per work-group, 256 work-groups.
-ADJ_PLAN = {"rows": 8, "z": 64, "x_planes": 16, "workgroups": 256}
-# forward launch plan of the differentiation workload (z voxels per lane,
-# tile rows, x planes): with a perfusion field the step kernel carries one
-# more stream, and 4-row tiles of 8 planes run 12 % faster than the 8-row,
-# 4-plane tiles the plain 128^3 step uses
-ADJ_FWD_PLAN = (2, 4, 8)
+# A launch of the two-step kernels moves these once for two steps, apart from
+# theta of the second adjoint step (4), and the temperature between the steps
+# where a trajectory is kept (4).
+THETA_BYTES = 4
 HBM_PEAK_GBPS = 8000.0
 # Step-kernel launches per HIP-event-timed block (one event pair per block).
 # A divisor of the library's 64-step diagnostic reduction period keeps those
@@ -77,6 +74,10 @@ KERNEL_SOURCES = {
     "k_step_batch": ("rfa_tiled.hip", "rfa_tiled.h") + _SHARED,
     "k_warp": ("rfa_warp.hip", "rfa_warp.h") + _SHARED,
     "k_adjoint_tiled": ("rfa_adjoint.hip", "rfa_adjoint.h", "rfa_tiled.h") + _SHARED,
+    "k_step_pair": ("rfa_pair_kernel.h", "rfa_pair.h") + _SHARED,
+    "k_step_pair_batch": ("rfa_pair_kernel.h", "rfa_pair.h") + _SHARED,
+    "k_adjoint_pair": ("rfa_adjoint_pair.hip", "rfa_adjoint_device.h", "rfa_adjoint.h",
+                       "rfa_pair.h") + _SHARED,
 }
 
 
@@ -89,17 +90,17 @@ def kernel_hash(kernel: str) -> str:
 
 
 # One-step launch plans (z voxels per lane, tile rows, x planes per
-# work-group) of the single-grid workloads: the fastest of rfa_tune's
-# candidates on the MI355X, fixed so that the committed counter summaries
-# refer to the timed launch shape.
+# work-group) of the single-grid workloads, for --one-step: the fastest of the
+# one-step candidates on the MI355X, which the committed counter summaries
+# refer to.  The workloads run the library's automatic plan.
 PLANS = {2: (2, 8, 4), 3: (4, 4, 32), 7: (2, 4, 4)}
 
 
 def kernel_name(plan: dict) -> str:
     if plan["kernel"] != 2:
         return "k_step_naive"
-    if plan["depth"] == 2:
-        return "k_step_tiled2"
+    if plan["depth"] == 2:  # every workload's rows fit the flat two-step kernel
+        return "k_step_pair"
     return "k_step_wide" if plan["z_vec"] > 1 else "k_step_tiled"
 
 
@@ -212,7 +213,8 @@ def mix_ceiling(roof: dict, mix_gbps: float) -> dict:
 
 
 def run_single(config: int, steps: int, warmup: int, plan_arg: str = "", tune: bool = False,
-               time_steps: int = 0, cpu: bool = True, cpu_steps: int = 0) -> dict:
+               time_steps: int = 0, cpu: bool = True, cpu_steps: int = 0,
+               one_step: bool = False) -> dict:
     """One grid stepped by its whole duration per bench step (configs 2, 3,
     7); returns the result fields of its JSON line."""
     import torch
@@ -221,10 +223,11 @@ def run_single(config: int, steps: int, warmup: int, plan_arg: str = "", tune: b
     if time_steps > 0:
         case.n_steps = time_steps
         name += f" [profiling run: {time_steps} time steps per bench step]"
-    # one step per launch: the HBM-bound kernel whose roofline is reported
-    zv, ty, xc = (tuple(int(t) for t in plan_arg.split(",")) if plan_arg else PLANS[config])
-    g = rfa.Grid(case.shape, case.spacing, device=False, depth=1, z_vec=zv, tile_y=ty,
-                 tile_x=xc, time_kernels=TIME_PERIOD)
+    shape = {}
+    if plan_arg or one_step:
+        zv, ty, xc = tuple(int(t) for t in plan_arg.split(",")) if plan_arg else PLANS[config]
+        shape = dict(depth=1, z_vec=zv, tile_y=ty, tile_x=xc)
+    g = rfa.Grid(case.shape, case.spacing, device=False, time_kernels=TIME_PERIOD, **shape)
     g.load_case(case)
     if tune:
         g.tune(case.dt, reps=10)
@@ -249,6 +252,7 @@ def run_single(config: int, steps: int, warmup: int, plan_arg: str = "", tune: b
     avg_ms = kms / launches
     roof = roofline_dict(BYTES_PER_VOXEL_STEP * case.n_voxels + SOURCE_BYTES * support, avg_ms,
                          kernel_name(plan), launches_timed=launches,
+                         steps_per_launch=plan["depth"],
                          copy_ceiling_GBps=round(copy_gbps, 1), source_support_voxels=support)
     roof.update(mix_ceiling(roof, mix_gbps))
     roof["traffic"] = traffic_record(config, plan, kernel_name(plan))
@@ -256,8 +260,9 @@ def run_single(config: int, steps: int, warmup: int, plan_arg: str = "", tune: b
     ws_mb = case.n_voxels * (16 + 1 + 4 + 4) / 1e6
     if ws_mb < 200.0:
         roof["note"] = (f"the {ws_mb:.0f} MB working set stays in the 256 MB last-level "
-                        f"cache: the launch is latency bound and 'hbm' names the peak it is "
-                        f"priced against, not the level that serves it")
+                        f"cache: the launch is bound by latency and by the instructions it "
+                        f"issues, and 'hbm' names the peak it is priced against, not the "
+                        f"level that serves it")
         roof["cache_resident"] = True
     out = {
         "value": round(value, 3),
@@ -299,9 +304,12 @@ def main():
     ap.add_argument("--no-legs", action="store_true",
                     help="--config 4: leave out the 256^3 and differentiation legs")
     ap.add_argument("--tune", action="store_true",
-                    help="re-tune the launch plan instead of the fixed one")
+                    help="tune the launch plan instead of the automatic one")
     ap.add_argument("--plan", default="",
-                    help="launch plan zv,ty,xc for --config 2/3 instead of the fixed one")
+                    help="one-step launch plan zv,ty,xc for --config 2/3/7 instead of the "
+                         "automatic one")
+    ap.add_argument("--one-step", action="store_true",
+                    help="--config 2/3/7: the fixed one-step plans")
     ap.add_argument("--time-steps", type=int, default=0,
                     help="override the workload's time steps per bench step (profiling runs)")
     args = ap.parse_args()
@@ -334,7 +342,8 @@ def main():
     if args.config not in (2, 3, 7):
         raise SystemExit("--config must be 2, 3, 4, 5, 6 or 7")
     fields = run_single(args.config, args.steps, args.warmup, args.plan, args.tune,
-                        args.time_steps, cpu=not args.no_cpu, cpu_steps=args.cpu_steps)
+                        args.time_steps, cpu=not args.no_cpu, cpu_steps=args.cpu_steps,
+                        one_step=args.one_step)
     print(json.dumps(line(fields, args.steps, args.warmup)), flush=True)
 
 
@@ -346,8 +355,8 @@ SWEEP_CPU_SAMPLE = tuple(range(0, 64, 8))
 def bench_batch(args) -> dict:
     """Planning sweep: 64 uneven grids (64^3..160^3, 0.5..1 mm, own needle,
     dt = 0.01 s (dx / 0.5 mm)^2), 2000 steps each; one bench step is one
-    batched call advancing every grid by its 2000 steps (grids grouped to
-    the last-level cache, each group's steps back to back, one hipGraph).
+    batched call advancing every grid by its 2000 steps (grids in groups,
+    each group's steps back to back, two a launch, one hipGraph).
     The plain stepper (each grid stepped on its own, one after another) is
     timed beside it."""
     import torch
@@ -390,10 +399,12 @@ def bench_batch(args) -> dict:
     wall = time.perf_counter() - t0
     value = total_vox * n_steps * args.steps / wall / 1e9
     plan = b.plan()
-    # one launch per group and step (grids of a group share a launch; all of
-    # the sweep's grids carry no perfusion field): device time of the graph
+    # one launch per group and two steps (grids of a group share a launch; all
+    # of the sweep's grids carry no perfusion field; an odd last step and a
+    # shape found by --tune take one step a launch): device time of the graph
     # per launch, algorithmic bytes per launch averaged over the groups
-    launches = plan["groups"] * n_steps * args.steps
+    depth = 1 if args.tune else 2
+    launches = plan["groups"] * (n_steps // depth + n_steps % depth) * args.steps
     avg_launch_ms = dev_ms / launches
     support = sum(g.source_support() for g in grids)
     bytes_per_launch = (BYTES_PER_VOXEL_STEP * total_vox + SOURCE_BYTES * support) / plan["groups"]
@@ -402,15 +413,16 @@ def bench_batch(args) -> dict:
     for g in grids:
         g.close()
     mix_gbps = rfa.rfa_mix_bandwidth(total_vox // plan["groups"], 10)
-    roof = roofline_dict(bytes_per_launch, avg_launch_ms, "k_step_batch",
-                         launches_timed=launches, copy_ceiling_GBps=round(copy_gbps, 1),
+    kernel = "k_step_batch" if args.tune else "k_step_pair_batch"
+    roof = roofline_dict(bytes_per_launch, avg_launch_ms, kernel, launches_timed=launches,
+                         steps_per_launch=depth, copy_ceiling_GBps=round(copy_gbps, 1),
                          source_support_voxels=support,
-                         note="groups of grids sized to the 256 MB last-level cache run "
-                              "their steps back to back; traffic counts bytes below L2, "
-                              "which that cache may serve; the mix ceiling is taken over "
-                              "one average group's voxels")
+                         note="a launch takes two steps in one pass over a group's grids and "
+                              "is bound by the instructions it issues as much as by its "
+                              "bytes (with --tune it is priced as one step a launch); the "
+                              "mix ceiling is taken over one average group's voxels")
     roof.update(mix_ceiling(roof, mix_gbps))
-    roof["traffic"] = traffic_record(4, plan, "k_step_batch")
+    roof["traffic"] = traffic_record(4, plan, kernel)
     out = {
         "value": round(value, 3),
         "unit": "GVoxel-updates/s",
@@ -460,9 +472,7 @@ def bench_adjoint(args, steps: int, warmup: int) -> dict:
     n_steps = args.time_steps if args.time_steps > 0 else 600
     case = W.case_differentiation(n_steps=n_steps)
     m, ckpt = 16, 50
-    zv, ty, xc = ADJ_FWD_PLAN
-    g = rfa.Grid(case.shape, case.spacing, device=True, time_kernels=TIME_PERIOD, z_vec=zv,
-                 tile_y=ty, tile_x=xc)
+    g = rfa.Grid(case.shape, case.spacing, device=True, time_kernels=TIME_PERIOD)
     g.load_case(case)
     g.set_perfusion_bspline(np.zeros((m, m, m), np.float32))
     plan = g.plan()
@@ -501,16 +511,22 @@ def bench_adjoint(args, steps: int, warmup: int) -> dict:
     support = g.source_support()
     copy_gbps = rfa.rfa_copy_bandwidth(1 << 30, 10)
     g.close()
+    depth = plan["depth"]
     avg_ms = kms / max(launches, 1)
-    adj_avg_ms = adj_ms / max(adj_launches, 1)
-    # the perfusion factor field adds one float read per voxel-step
-    fwd = roofline_dict((BYTES_PER_VOXEL_STEP + 4) * case.n_voxels + SOURCE_BYTES * support,
-                        avg_ms, kernel_name(plan) + " (forward)", launches_timed=launches,
+    adj_avg_ms = adj_ms * depth / max(adj_launches, 1)  # the statistics count steps
+    # the perfusion factor field adds one float read per voxel, the kept
+    # trajectory the temperature between two steps
+    between = THETA_BYTES * (depth - 1)
+    fwd = roofline_dict((BYTES_PER_VOXEL_STEP + 4 + between) * case.n_voxels
+                        + SOURCE_BYTES * support, avg_ms, kernel_name(plan) + " (forward)",
+                        launches_timed=launches, steps_per_launch=depth,
                         source_support_voxels=support)
-    adj = roofline_dict(ADJ_BYTES_PER_VOXEL_STEP * case.n_voxels + ADJ_SOURCE_BYTES * support,
-                        adj_avg_ms, "k_adjoint_tiled (adjoint)", launches_timed=adj_launches,
+    adj_kernel = "k_adjoint_pair" if depth == 2 else "k_adjoint_tiled"
+    adj = roofline_dict((ADJ_BYTES_PER_VOXEL_STEP + between) * case.n_voxels
+                        + ADJ_SOURCE_BYTES * support, adj_avg_ms, adj_kernel + " (adjoint)",
+                        launches_timed=adj_launches // depth, steps_per_launch=depth,
                         copy_ceiling_GBps=round(copy_gbps, 1), source_support_voxels=support)
-    adj["traffic"] = traffic_record(5, ADJ_PLAN, "k_adjoint_tiled")
+    adj["traffic"] = traffic_record(5, plan, adj_kernel)
     # the dominant kernel (more time in the timed region) carries the roofline
     dominant, other = (adj, fwd) if adj_ms > kms else (fwd, adj)
     out = {
@@ -573,7 +589,7 @@ def cpu_baseline_adjoint() -> dict:
 # (here the walls' zero-displacement voxels, under 2 %), not counted
 WARP_BYTES_PER_VOXEL = 20
 WARP2_BYTES_PER_VOXEL = 32  # two fields
-WARP_PLAN = {"threads": 256, "tile_z": 64, "tile_y": 4, "x_voxels_per_thread": 4}
+WARP_PLAN = {"threads": 256, "z_voxels_per_thread": 4}
 WARP_FRAMES_PER_CYCLE = 100
 
 
