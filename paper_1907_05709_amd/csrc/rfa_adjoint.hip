@@ -221,7 +221,8 @@ struct AdjSmem {
 
 }  // namespace
 
-// Adjoint step with the production step kernel's schedule: a work-group of
+// Adjoint step with the tiled one-step kernel's schedule (the two-step kernel,
+// rfa_adjoint_pair.hip, leaves it odd last steps and long rows): a work-group of
 // TY waves owns a 64 (z) x TY (y) tile and marches along x; y and z
 // neighbours of lambda and the class byte come from a double-buffered LDS
 // plane with a one-voxel halo, x neighbours from registers, loads are

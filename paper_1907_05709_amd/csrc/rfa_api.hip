@@ -64,8 +64,8 @@ constexpr size_t kFieldBudget = size_t(16) << 30;  // bytes of kept per-tine sou
 constexpr long long kBatchGroupVoxels = 8ll << 20;
 // The same for the two-step kernel, which moves half the bytes per step and
 // is bound by its arithmetic: there a group only has to be long enough to
-// fill the chip (64-grid sweep, 101 Mi voxels: 235 GVox/s with 8 Mi voxels a
-// group, 250 with 16, 266 with 64).
+// fill the chip (64-grid sweep, 101 Mi voxels: 259 GVox/s with 8 Mi voxels a
+// group, 278 with 16, 292 with 64).
 constexpr long long kPairGroupVoxels = 64ll << 20;
 constexpr int kTimedBatch = 1024;  // launches between event read-backs
 constexpr double kTBodyK = 310.15;

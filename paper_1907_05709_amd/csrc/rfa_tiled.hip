@@ -1,4 +1,6 @@
-// rfa_tiled.hip -- the production step kernel: 2.5-D tiles marching along x.
+// rfa_tiled.hip -- one step per launch: 2.5-D tiles marching along x, and the
+// one-step batch kernel.  Runs where the two-step kernel does not: rows of more
+// than 256 voxels, odd last steps, and shapes asked for.
 //
 // A work-group of TY wavefronts owns a tile of 64 (z, one voxel per lane)
 // by TY (y, one row per wave) voxel columns and marches along x over a
