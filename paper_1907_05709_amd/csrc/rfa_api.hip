@@ -2051,6 +2051,7 @@ struct rfa_batch_s {
   int pwaves = 0, pv = 0;           // work-group kind (0: one step per launch)
   std::vector<int> pfirst;          // pair item range of each instance
   std::vector<int> tissue_version;  // of the grids when the codes were made
+  std::vector<char> coupled;        // perf_decay of the grids when the items were made
   PairInstance* pinst_dev = nullptr;
   PairItem* pitems_dev = nullptr;
   int* pfirst_dev = nullptr;
@@ -2251,6 +2252,7 @@ rfa_status batch_build(rfa_batch b) {
   const int n = (int)b->grids.size();
   b->inst.assign(n, BatchInstance{});
   b->first.assign(2 * (size_t)n, 0);
+  b->coupled.assign(n, 0);
   std::vector<BatchItem> items;
   b->voxels = 0;
   for (int i = 0; i < n; ++i) {
@@ -2269,6 +2271,7 @@ rfa_status batch_build(rfa_batch b) {
     I.perf = g->perf;
     I.tab = g->tab_dev;
     I.K = step_const(g, b->dt[i]);
+    b->coupled[i] = g->perf_decay;
     I.n_classes = g->n_classes;
     I.nx = g->g.nx;
     I.ny = g->g.ny;
@@ -2338,7 +2341,10 @@ rfa_status batch_build(rfa_batch b) {
 }
 
 // Whether the grids still match the descriptor table (nobody stepped or
-// re-tissued a grid outside the batch, no dt change).
+// re-tissued a grid outside the batch, no dt change).  The coupling is
+// compared by itself: it decides how many steps a launch may take and sits in
+// the one-step items, and steps of the grid alone renew its tables without
+// the batch's knowledge.
 bool batch_in_sync(rfa_batch b) {
   for (size_t i = 0; i < b->grids.size(); ++i) {
     rfa_grid g = b->grids[i];
@@ -2346,6 +2352,7 @@ bool batch_in_sync(rfa_batch b) {
     if (!g->has_tissue || I.hi[b->parity] != g->hi[g->cur] || I.lab != g->lab ||
         I.src != g->src || I.om != g->om || I.perf != g->perf || I.tab != g->tab_dev ||
         I.n_classes != g->n_classes || g->tab_dt != b->dt[i] || g->src_dt != b->dt[i] ||
+        (b->coupled[i] != 0) != g->perf_decay ||
         (b->pwaves && g->tissue_version != b->tissue_version[i]))
       return false;
   }
