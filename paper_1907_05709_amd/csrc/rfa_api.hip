@@ -92,7 +92,8 @@ struct rfa_grid_s {
   float* lo[2] = {nullptr, nullptr};
   int cur = 0;
   float* om = nullptr;
-  float* om_alt = nullptr;  // second damage image (damage-coupled grids on pair plans)
+  float* om_alt = nullptr;  // second damage image (damage-coupled grids on pair plans);
+                            // scratch of a call's launches: om holds the state between calls
   float* src = nullptr;
   double* q64 = nullptr;
   float* perf = nullptr;  // null = no perfusion multiplier
@@ -589,7 +590,8 @@ rfa_status ensure_events(rfa_grid g, int count);
 // not touched).
 rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
                        float* traj = nullptr, int* traj_t = nullptr) {
-  StepState ss{g->hi, g->lo, &g->cur, g->lab, g->src, &g->om, g->perf, g->tab_dev,
+  float* om = g->om;  // the damage image as the launches pass it on
+  StepState ss{g->hi, g->lo, &g->cur, g->lab, g->src, &om, g->perf, g->tab_dev,
                g->n_classes};
   // the 2.5-D two-step kernel takes neither the kept trajectory nor
   // damage-coupled perfusion (it reads the damage integral of its halo
@@ -600,7 +602,8 @@ rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
   if (n_steps >= plan.depth)  // fewer steps run on the one-step plan
     if (rfa_status sp = ensure_pair(g, plan); sp != RFA_OK) return sp;
   ss.codes = g->codes;
-  ss.om_alt = g->perf_decay ? &g->om_alt : nullptr;
+  float* alt = g->om_alt;
+  ss.om_alt = g->perf_decay ? &alt : nullptr;
   if (traj) {
     ss.traj = traj;
     ss.traj_t = traj_t;
@@ -632,6 +635,11 @@ rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
     done += batch;
     g->steps += batch;
   }
+  // an odd number of launches that swap the damage images: back to the grid's
+  // own, whose address captured graphs and batches hold (8 bytes a voxel, once
+  // a call)
+  if (om != g->om)
+    HIP_TRY(hipMemcpyAsync(g->om, om, g->g.n() * sizeof(float), hipMemcpyDeviceToDevice, g->st));
   return RFA_OK;
 }
 

@@ -65,7 +65,8 @@ struct StepState {
   const uint8_t* codes = nullptr;  // wave codes of a pair plan's shape
   // second damage image (damage-coupled grids on a pair plan, whose launches
   // read the damage integral of neighbouring work-groups' voxels): a launch
-  // reads *om and writes *om_alt, then the two are swapped
+  // reads *om and writes *om_alt, then the two are swapped (the caller's state
+  // is the image *om ends at)
   float** om_alt = nullptr;
 };
 
