@@ -1455,7 +1455,6 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   b.lab = lab2;
   b.src = g->src;
   b.omega = om2;
-  b.omega_out = om2;  // timing only: the scratch damage is not read back
   b.perf = g->perf;
   b.tab = g->tab_dev;
   b.n_classes = g->n_classes;
@@ -1468,8 +1467,11 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   for (int c = 0; c < nc && e == hipSuccess; ++c) {
     if ((e = hipMemcpyAsync(om2, g->om, n * sizeof(float), hipMemcpyDeviceToDevice, g->st))) break;
     if ((e = hipMemcpyAsync(lab2, g->lab, n, hipMemcpyDeviceToDevice, g->st))) break;
+    // the 2.5-D two-step kernel does not take damage-coupled steps
+    if (g->perf_decay && cand[c].depth == 2 && !cand[c].pv) continue;
     if ((s = ensure_pair(g, cand[c])) != RFA_OK) break;
     b.codes = g->codes;
+    b.omega_out = g->perf_decay && cand[c].pv ? g->om_alt : om2;  // as the steps do
     if ((e = launch_plan(g->g, cand[c], b, K, g->st))) break;  // warm-up
     if ((e = hipEventRecord(g->events[0], g->st))) break;
     for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch_plan(g->g, cand[c], b, K, g->st);

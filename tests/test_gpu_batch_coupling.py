@@ -62,3 +62,28 @@ def test_coupling_switched_in_a_live_batch(between, first):
     b.close()
     for g in alone + batched + never:
         g.close()
+
+
+@pytest.mark.parametrize("shape", [(26, 33, 40), (9, 20, 260)])
+def test_tuning_a_coupled_grid_in_a_live_batch(shape):
+    """Tuning times the coupled launches on scratch images of their own and
+    leaves state and batch as they were."""
+    case = dataclasses.replace(W.random_tissue_case(33, shape=shape, n_classes=4, n_tines=2),
+                               perfusion_decay=False)
+    (alone,), (grid,) = _grids([case], kernel=1), _grids([case])
+    dt = 0.9 * min(case.dt, alone.dt_max())
+    b = rfa.Batch([grid], [dt])
+    for g in (alone, grid):
+        g.set_perfusion_decay(True)
+    grid.tune(dt, reps=2)
+    for n in (7, 6):
+        alone.step(n, dt, diag=False)
+        b.step(n)
+        _same([alone], [grid], n)
+        alone.step(n, dt, diag=False)
+        grid.step(n, dt, diag=False)
+        _same([alone], [grid], n)
+        grid.tune(dt, reps=2)
+    b.close()
+    for g in (alone, grid):
+        g.close()
