@@ -542,10 +542,16 @@ rfa_status ensure_partials(rfa_grid g, int nwg) {
   return RFA_OK;
 }
 
-// The wave codes a pair plan's launches read, and the second damage image
-// that damage-coupled grids need there.
+// Whether the plan's launches have what they read beside the state: a pair
+// plan the wave codes of its shape, and on a damage-coupled grid the second
+// damage image.
+bool pair_ready(rfa_grid g, const StepPlan& p) {
+  return !p.pv || (g->codes_waves == p.ty && g->codes_v == p.pv && (!g->perf_decay || g->om_alt));
+}
+
+// Makes them.
 rfa_status ensure_pair(rfa_grid g, const StepPlan& p) {
-  if (!p.pv) return RFA_OK;
+  if (pair_ready(g, p)) return RFA_OK;
   rfa_status s;
   if (g->perf_decay && !g->om_alt && (s = dmalloc(&g->om_alt, g->g.n())) != RFA_OK) return s;
   if (g->codes_waves == p.ty && g->codes_v == p.pv) return RFA_OK;
@@ -553,6 +559,7 @@ rfa_status ensure_pair(rfa_grid g, const StepPlan& p) {
   const size_t need = pair_code_bytes(g->g, sh);
   if (g->codes_cap < need) {
     if (g->codes) (void)hipFree(g->codes);
+    g->codes = nullptr;
     g->codes_cap = 0;
     g->codes_waves = 0;
     if ((s = dmalloc(&g->codes, need + 4)) != RFA_OK) return s;  // read as dwords
@@ -563,6 +570,17 @@ rfa_status ensure_pair(rfa_grid g, const StepPlan& p) {
   g->codes_v = p.pv;
   return RFA_OK;
 }
+
+// The same for the grid's plan, wherever tissue, coupling or plan are set:
+// steps then allocate nothing (they may be captured in a graph).  A grid
+// without the memory takes its one-step launches.
+rfa_status prepare_pair(rfa_grid g) {
+  const rfa_status s = ensure_pair(g, g->plan);
+  return s == RFA_ERR_OOM ? RFA_OK : s;
+}
+
+// The grid's plan, or its one-step plan where its launches cannot be made.
+StepPlan plan_now(rfa_grid g) { return pair_ready(g, g->plan) ? g->plan : plan_one(g->plan); }
 
 // Per-dt coefficient tables and source increment of grid g.
 rfa_status prepare_dt(rfa_grid g, double dt) {
@@ -598,9 +616,7 @@ rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
   // voxels while the neighbouring work-groups overwrite it, harmless while
   // the damage integral feeds no temperature)
   const bool single = g->plan.depth == 2 && !g->plan.pv && (traj || g->perf_decay);
-  const StepPlan plan = single ? plan_one(g->plan) : g->plan;
-  if (n_steps >= plan.depth)  // fewer steps run on the one-step plan
-    if (rfa_status sp = ensure_pair(g, plan); sp != RFA_OK) return sp;
+  const StepPlan plan = single ? plan_one(g->plan) : plan_now(g);
   ss.codes = g->codes;
   float* alt = g->om_alt;
   ss.om_alt = g->perf_decay ? &alt : nullptr;
@@ -939,6 +955,7 @@ rfa_status rfa_set_tissue(rfa_grid g, const uint8_t* labels, const rfa_tissue* t
   HIP_TRY(hipMemcpyAsync(g->free_count, g->counts, kMaxClasses * sizeof(unsigned long long),
                          hipMemcpyDeviceToHost, g->st));
   HIP_TRY(hipStreamSynchronize(g->st));
+  if ((s = prepare_pair(g)) != RFA_OK) return s;
   if ((s = compute_dt_max(g)) != RFA_OK) return s;
   return rasterise(g);
 }
@@ -1034,7 +1051,7 @@ rfa_status rfa_set_perfusion_decay(rfa_grid g, int enable) {
     g->tab_dt = -1.0;  // the tables carry the coupling constant
   }
   g->perf_decay = enable != 0;
-  return RFA_OK;
+  return prepare_pair(g);
 }
 
 rfa_status rfa_dt_max(rfa_grid g, double* dt_max) {
@@ -1418,7 +1435,7 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
     if (kv.first == key) {
       if (rfa_status sp = ensure_partials(g, kv.second.nwg); sp != RFA_OK) return sp;
       g->plan = kv.second;
-      return RFA_OK;
+      return prepare_pair(g);
     }
   if (dt != g->tab_dt) {
     build_tables(g, dt);
@@ -1469,7 +1486,11 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
     if ((e = hipMemcpyAsync(lab2, g->lab, n, hipMemcpyDeviceToDevice, g->st))) break;
     // the 2.5-D two-step kernel does not take damage-coupled steps
     if (g->perf_decay && cand[c].depth == 2 && !cand[c].pv) continue;
-    if ((s = ensure_pair(g, cand[c])) != RFA_OK) break;
+    if ((s = ensure_pair(g, cand[c])) == RFA_ERR_OOM) {
+      s = RFA_OK;  // not to be had
+      continue;
+    }
+    if (s != RFA_OK) break;
     b.codes = g->codes;
     b.omega_out = g->perf_decay && cand[c].pv ? g->om_alt : om2;  // as the steps do
     if ((e = launch_plan(g->g, cand[c], b, K, g->st))) break;  // warm-up
@@ -1489,11 +1510,13 @@ rfa_status rfa_tune(rfa_grid g, double dt, int reps) {
   (void)hipStreamSynchronize(g->st);
   (void)hipFree(om2);
   (void)hipFree(lab2);
-  if (e != hipSuccess) return fail(RFA_ERR_HIP, "tune failed: %s", hipGetErrorString(e));
-  if (s != RFA_OK) return s;
+  if (e != hipSuccess || s != RFA_OK) {
+    (void)prepare_pair(g);  // the codes may be a candidate's
+    return s != RFA_OK ? s : fail(RFA_ERR_HIP, "tune failed: %s", hipGetErrorString(e));
+  }
   g->plan = best;
   g_tuned.push_back({key, best});
-  return RFA_OK;
+  return prepare_pair(g);
 }
 
 rfa_status rfa_copy_bandwidth(size_t bytes, int reps, double* gbps) {
@@ -1839,10 +1862,10 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
   bool sacc_all = false;
   for (double p : g->power) sacc_all = sacc_all || !(p > 0.0);
   // two adjoint steps per launch where the forward takes two
-  const bool pair_adj = g->plan.pv != 0;
+  const StepPlan now = plan_now(g);
+  const bool pair_adj = now.pv != 0;
   PairShape adj_shape;
   if (pair_adj) {
-    if ((s = ensure_pair(g, g->plan)) != RFA_OK) return s;
     adj_shape = pair_shape(g->g, g->plan.ty, g->plan.pv,
                            adjoint_pair_chunk(g->g, g->plan.ty, g->plan.pv));
   }
@@ -1905,8 +1928,7 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
   if (every > 0) {
     if ((s = ensure_side_stream(g)) != RFA_OK) return s;
     const StepPlan one = plan_one(g->plan);
-    const StepPlan re = g->plan.pv ? g->plan : one;
-    if ((s = ensure_pair(g, re)) != RFA_OK) return s;
+    const StepPlan re = now.pv ? now : one;
     hipEvent_t start = g->side_ev[0];
     hipEvent_t ready[2] = {g->side_ev[1], g->side_ev[2]};
     hipEvent_t read[2] = {g->side_ev[3], g->side_ev[4]};

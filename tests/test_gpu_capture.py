@@ -57,3 +57,27 @@ def test_captured_damage_follows_coupled_steps():
         assert last is None or not torch.equal(omega, last), n
         last = omega.clone()
     g.close()
+
+
+@pytest.mark.parametrize("coupled", [False, True])
+def test_steps_allocate_nothing(coupled):
+    """A program that has taken single steps only may capture a longer call:
+    what two steps a launch need is there since the tissue was set."""
+    case = _case((26, 33, 40), coupled)
+    stream = torch.cuda.Stream()
+    g, ref = _grid(case, stream), _grid(case, stream, kernel=1)
+    dt = 0.9 * min(case.dt, g.dt_max())
+    assert g.plan()["depth"] == 2
+    for x in (g, ref):
+        x.step(1, dt, diag=False)
+    torch.cuda.synchronize()
+    graph, _ = _captured(stream, lambda: g.step(4, dt, diag=False))
+    for _ in range(3):
+        graph.replay()
+        ref.step(4, dt, diag=False)
+        torch.cuda.synchronize()
+        for a, b in zip(g.raw_state(), ref.raw_state()):
+            assert torch.equal(a, b)
+        assert torch.equal(g.omega(), ref.omega())
+    for x in (g, ref):
+        x.close()
