@@ -2090,6 +2090,7 @@ struct rfa_batch_s {
   uint8_t* codes = nullptr;         // wave codes of all instances
   int n_pitems = 0;
   std::vector<Group> groups;
+  bool built = false;               // the tables below are those of inst (a build may fail half way)
   int parity = 0;
   long long voxels = 0;
   hipStream_t st = nullptr;
@@ -2106,6 +2107,17 @@ struct rfa_batch_s {
 
 namespace {
 
+// The two-step part of the tables.
+void batch_free_pair(rfa_batch b) {
+  for (void* p : {(void*)b->pinst_dev, (void*)b->pitems_dev, (void*)b->pfirst_dev, (void*)b->codes})
+    if (p) (void)hipFree(p);
+  b->pinst_dev = nullptr;
+  b->pitems_dev = nullptr;
+  b->pfirst_dev = nullptr;
+  b->codes = nullptr;
+  b->pwaves = b->pv = 0;
+  b->n_pitems = 0;
+}
 
 void batch_free_device(rfa_batch b) {
   for (auto& c : b->graphs) {
@@ -2122,16 +2134,7 @@ void batch_free_device(rfa_batch b) {
   f(b->partials);
   f(b->dacc);
   f(b->slot_acc);
-  f(b->pinst_dev);
-  f(b->pitems_dev);
-  f(b->pfirst_dev);
-  f(b->codes);
-  b->pinst_dev = nullptr;
-  b->pitems_dev = nullptr;
-  b->pfirst_dev = nullptr;
-  b->codes = nullptr;
-  b->pwaves = b->pv = 0;
-  b->n_pitems = 0;
+  batch_free_pair(b);
   b->inst_dev = nullptr;
   b->items_dev = nullptr;
   b->first_dev = nullptr;
@@ -2280,6 +2283,7 @@ rfa_status batch_build_pair(rfa_batch b) {
 // (Re)build the device descriptor table and work list from the grids'
 // current state; resets the batch parity and drops cached graphs.
 rfa_status batch_build(rfa_batch b) {
+  b->built = false;
   batch_free_device(b);
   const int n = (int)b->grids.size();
   b->inst.assign(n, BatchInstance{});
@@ -2351,6 +2355,10 @@ rfa_status batch_build(rfa_batch b) {
   }
   b->n_items = (int)items.size();
   rfa_status s = b->want_pair ? batch_build_pair(b) : RFA_OK;
+  if (s == RFA_ERR_OOM) {  // without memory for its tables one step a launch
+    batch_free_pair(b);
+    s = RFA_OK;
+  }
   if (s != RFA_OK) return s;
   if ((s = dmalloc(&b->inst_dev, n)) || (s = dmalloc(&b->items_dev, items.size())) ||
       (s = dmalloc(&b->first_dev, 2 * (size_t)n)) ||
@@ -2369,6 +2377,7 @@ rfa_status batch_build(rfa_batch b) {
   // persistent work-groups if requested, else one work-group per work item
   b->n_wg = b->req_wg > 0 ? std::min(b->req_wg, b->n_items) : 0;
   b->parity = 0;
+  b->built = true;
   return RFA_OK;
 }
 
@@ -2378,6 +2387,7 @@ rfa_status batch_build(rfa_batch b) {
 // the one-step items, and steps of the grid alone renew its tables without
 // the batch's knowledge.
 bool batch_in_sync(rfa_batch b) {
+  if (!b->built) return false;
   for (size_t i = 0; i < b->grids.size(); ++i) {
     rfa_grid g = b->grids[i];
     const BatchInstance& I = b->inst[i];
