@@ -191,7 +191,11 @@ rfa_status rfa_set_perfusion_decay(rfa_grid g, int enable);
 /* Advance n_steps explicit steps of length dt seconds (Eq. (CUDAbioheat3d),
  * Alg. 1 and 2).  dt above the bound min over free voxels of
  * rho c / (sum_faces K_face / d^2 + h) gives RFA_ERR_UNSTABLE.  diag may be
- * NULL; if given, the call also sums per-step diagnostics and synchronises. */
+ * NULL; if given, the call also sums per-step diagnostics and synchronises.
+ * Without diag and time_kernels, a call with the time step of the one before
+ * only enqueues kernels and may be captured in a HIP graph: replays advance an
+ * even n_steps each (the graph is of the image current at the capture, which
+ * an even number of steps leaves current). */
 rfa_status rfa_step(rfa_grid g, int n_steps, double dt, rfa_diag* diag);
 
 /* Largest dt accepted by rfa_step for the current tissue and perfusion. */

@@ -91,6 +91,7 @@ struct rfa_grid_s {
   float* hi[2] = {nullptr, nullptr};
   float* lo[2] = {nullptr, nullptr};
   int cur = 0;
+  bool held = false;        // a captured graph holds the images' addresses (see note_capture)
   float* om = nullptr;
   float* om_alt = nullptr;  // second damage image (damage-coupled grids on pair plans);
                             // scratch of a call's launches: om holds the state between calls
@@ -542,6 +543,18 @@ rfa_status ensure_partials(rfa_grid g, int nwg) {
   return RFA_OK;
 }
 
+// Calls that only enqueue may be captured in a graph, which then holds the
+// address of the image that was current: replays are right as long as n steps
+// leave image n mod 2 current.  Two steps a launch swap the images half as
+// often, so once a call of the grid was captured its launches of two come in
+// even numbers (up to two more single steps a call).
+void note_capture(rfa_grid g) {
+  if (g->held || !g->st) return;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(g->st, &status) != hipSuccess) (void)hipGetLastError();
+  g->held = status == hipStreamCaptureStatusActive;
+}
+
 // Whether the plan's launches have what they read beside the state: a pair
 // plan the wave codes of its shape, and on a damage-coupled grid the second
 // damage image.
@@ -618,6 +631,7 @@ rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
   const bool single = g->plan.depth == 2 && !g->plan.pv && (traj || g->perf_decay);
   const StepPlan plan = single ? plan_one(g->plan) : plan_now(g);
   ss.codes = g->codes;
+  ss.even = g->held;
   float* alt = g->om_alt;
   ss.om_alt = g->perf_decay ? &alt : nullptr;
   if (traj) {
@@ -1069,6 +1083,7 @@ rfa_status rfa_step(rfa_grid g, int n_steps, double dt, rfa_diag* diag) {
   if (!finite_pos(dt)) return fail(RFA_ERR_ARG, "dt must be finite and positive");
   if (dt > g->dt_max)
     return fail(RFA_ERR_UNSTABLE, "dt %.6g s exceeds the stability bound %.6g s", dt, g->dt_max);
+  note_capture(g);
   rfa_status sp = prepare_dt(g, dt);
   if (sp != RFA_OK) return sp;
   const StepConst K = step_const(g, dt);
@@ -1222,6 +1237,7 @@ rfa_status warp_impl(rfa_grid g, const float* v, double beta, const float* v2, d
     }
     dv2 = v2 ? dv + 3 * n : nullptr;
   }
+  note_capture(g);
   hipEvent_t ev[2] = {nullptr, nullptr};
   hipError_t e = hipSuccess;
   if (!dev) e = hipMemcpyAsync(dv, v, 3 * n * sizeof(float), hipMemcpyHostToDevice, g->st);
@@ -1658,6 +1674,7 @@ rfa_status rfa_set_perfusion_bspline(rfa_grid g, int m, const float* ctrl) {
 rfa_status rfa_reset_state(rfa_grid g) {
   if (!g) return fail(RFA_ERR_ARG, "grid is NULL");
   if (!g->has_tissue) return fail(RFA_ERR_STATE, "no tissue");
+  note_capture(g);
   g->cur = 0;
   g->steps = 0;
   g->energy_valid = false;
@@ -1711,6 +1728,7 @@ rfa_status rfa_forward_checkpointed(rfa_grid g, int n_steps, double dt, int ckpt
   if (!finite_pos(dt)) return fail(RFA_ERR_ARG, "dt must be finite and positive");
   if (dt > g->dt_max)
     return fail(RFA_ERR_UNSTABLE, "dt %.6g s exceeds the stability bound %.6g s", dt, g->dt_max);
+  note_capture(g);
   rfa_status s = prepare_dt(g, dt);
   if (s != RFA_OK) return s;
   const size_t n = g->g.n();
@@ -2098,7 +2116,7 @@ struct rfa_batch_s {
   double last_ms = 0.0;
   long long last_vs = 0;
   struct Cached {
-    int n_steps, parity, diag;
+    int n_steps, n_pair, parity, diag;
     hipGraph_t graph;
     hipGraphExec_t exec;
   };
@@ -2401,9 +2419,18 @@ bool batch_in_sync(rfa_batch b) {
   return true;
 }
 
+// Launches of two among n_steps, an even number where a grid asks for it.
+int batch_pairs(rfa_batch b, int n_steps) {
+  const int n_pair = b->pwaves ? n_steps / 2 : 0;
+  for (rfa_grid g : b->grids)
+    if (g->held) return n_pair & ~1;
+  return n_pair;
+}
+
 rfa_status batch_graph(rfa_batch b, int n_steps, bool diag, hipGraphExec_t* out) {
+  const int n_pair = batch_pairs(b, n_steps);
   for (auto& c : b->graphs)
-    if (c.n_steps == n_steps && c.parity == b->parity && c.diag == (int)diag) {
+    if (c.n_steps == n_steps && c.n_pair == n_pair && c.parity == b->parity && c.diag == (int)diag) {
       *out = c.exec;
       return RFA_OK;
     }
@@ -2420,7 +2447,6 @@ rfa_status batch_graph(rfa_batch b, int n_steps, bool diag, hipGraphExec_t* out)
     const int wg_plain = b->n_wg > 0 ? std::min(b->n_wg, n_plain) : 0;
     const int wg_perf = b->n_wg > 0 ? std::min(b->n_wg, n_perf) : 0;
     int pending = 0, par = b->parity;
-    const int n_pair = b->pwaves ? n_steps / 2 : 0;
     // fold the pending slots of items laid out by `first` into dacc
     auto fold = [&](int n_items, const int* first) {
       if (e == hipSuccess && diag && pending > 0)
@@ -2462,7 +2488,7 @@ rfa_status batch_graph(rfa_batch b, int n_steps, bool diag, hipGraphExec_t* out)
     (void)hipGraphDestroy(graph);
     return fail(RFA_ERR_HIP, "batch graph instantiate failed: %s", hipGetErrorString(e));
   }
-  b->graphs.push_back(rfa_batch_s::Cached{n_steps, b->parity, (int)diag, graph, exec});
+  b->graphs.push_back(rfa_batch_s::Cached{n_steps, n_pair, b->parity, (int)diag, graph, exec});
   *out = exec;
   return RFA_OK;
 }
@@ -2545,7 +2571,7 @@ rfa_status rfa_batch_step(rfa_batch b, int n_steps, rfa_diag* diags) {
   b->last_vs = b->voxels * n_steps;
   b->last_ms = -1.0;
   // image swaps: one per launch
-  const int swaps = b->pwaves ? n_steps / 2 + (n_steps & 1) : n_steps;
+  const int swaps = n_steps - batch_pairs(b, n_steps);
   b->parity = (b->parity + swaps) & 1;
   for (int i = 0; i < n; ++i) {
     rfa_grid g = b->grids[i];

@@ -68,6 +68,7 @@ struct StepState {
   // reads *om and writes *om_alt, then the two are swapped (the caller's state
   // is the image *om ends at)
   float** om_alt = nullptr;
+  bool even = false;  // launches of two steps in even numbers: n steps swap the images n times mod 2
 };
 
 // One launch of the plan (plan.depth steps) from b's input to its output image.
@@ -80,8 +81,8 @@ hipError_t launch_plan(Grid3 g, const StepPlan& plan, const StepBuffers& b, cons
 hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuffers& b,
                                    float* hi_mid, const StepConst& K, hipStream_t st);
 
-// Advance n_steps: n_steps / depth launches of the plan, then the rest with
-// its one-step plan.  partials (nullable) has room for `slots` launches and
+// Advance n_steps: n_steps / depth launches of the plan (one fewer if s.even
+// asks for it), then the rest with its one-step plan.  partials (nullable) has room for `slots` launches and
 // is folded into dacc[3] every `slots` launches and at the end.  If events
 // is not null, each block of `period` consecutive launches of the plan (the
 // last one may be shorter) is bracketed by the event pair events[2j],

@@ -302,7 +302,8 @@ rfa_status run_steps(Grid3 g, const StepPlan& plan, StepState& s, const StepCons
     if (swap_om) std::swap(*s.om, *s.om_alt);
     return hipSuccess;
   };
-  const int n_main = n_steps / plan.depth;
+  int n_main = n_steps / plan.depth;
+  if (s.even && plan.depth == 2) n_main &= ~1;
   const int n_rest = n_steps - n_main * plan.depth;
   int pending = 0;
   int timed = 0;
