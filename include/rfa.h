@@ -291,6 +291,8 @@ rfa_status rfa_source_support(rfa_grid g, long long* voxels);
  * rfa_options.time_kernels): total milliseconds measured with HIP events
  * around blocks of consecutive step-kernel launches (diagnostic reductions
  * excluded), number of launches in those blocks, voxel-steps they advanced.
+ * An automatic plan of two steps a launch times the single steps of a call as
+ * well (one launch each); with depth 2 asked for or tuned they are left out.
  * Resets the counters.  Any argument may be NULL. */
 rfa_status rfa_kernel_stats(rfa_grid g, double* kernel_ms, long long* launches,
                             long long* voxel_steps);

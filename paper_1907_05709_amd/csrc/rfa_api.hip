@@ -647,9 +647,9 @@ rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
       if ((s = ensure_events(g, 2 * batch)) != RFA_OK) return s;
       ev = g->events.data();
     }
-    int timed = 0, launches = 0;
+    int timed = 0, launches = 0, steps = 0;
     s = run_steps(g->g, plan, ss, K, batch, diag ? g->partials : nullptr, kPartialSlots,
-                  g->dacc, ev, g->opt.time_kernels, &timed, &launches, g->st);
+                  g->dacc, ev, g->opt.time_kernels, &timed, &launches, &steps, g->st);
     if (s != RFA_OK)
       return fail(s, "step launch failed: %s", hipGetErrorString(hipGetLastError()));
     if (ev && timed > 0) {
@@ -660,7 +660,7 @@ rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
         g->kernel_ms += ms;
       }
       g->kernel_launches += launches;
-      g->kernel_voxel_steps += (long long)launches * plan.depth * (long long)g->g.n();
+      g->kernel_voxel_steps += (long long)steps * (long long)g->g.n();
     }
     done += batch;
     g->steps += batch;

@@ -25,6 +25,7 @@ struct StepPlan {
   int pv = 0;      // depth 2: voxels per lane of the pair kernel (its work-groups
                    // have ty waves), 0 for the 2.5-D two-step kernel
   int store = 0;   // StorePolicy of the step launches
+  bool time_rest = false;  // time the one-step launches of a call as well (automatic plans)
   // one-step plan for step counts not divisible by depth (equal to the
   // plan itself when depth == 1)
   int one_kind = 0, one_ty = 4, one_xc = 1, one_nwg = 0, one_zv = 1;
@@ -86,11 +87,12 @@ hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuff
 // is folded into dacc[3] every `slots` launches and at the end.  If events
 // is not null, each block of `period` consecutive launches of the plan (the
 // last one may be shorter) is bracketed by the event pair events[2j],
-// events[2j+1] (j = 0, 1, ...; *n_timed receives the number of blocks and
-// *n_launches the launches inside them); one-step launches are not timed.
+// events[2j+1] (j = 0, 1, ...; *n_timed receives the number of blocks,
+// *n_launches the launches inside them, *n_timed_steps their steps); one-step
+// launches that follow them are timed, each by itself, if plan.time_rest.
 rfa_status run_steps(Grid3 g, const StepPlan& plan, StepState& s, const StepConst& K,
                      int n_steps, float* partials, int slots, double* dacc,
                      hipEvent_t* events, int period, int* n_timed, int* n_launches,
-                     hipStream_t st);
+                     int* n_timed_steps, hipStream_t st);
 
 }  // namespace rfa

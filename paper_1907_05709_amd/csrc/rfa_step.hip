@@ -150,7 +150,10 @@ StepPlan default_shape(Grid3 g, int kernel, int depth, int tile_y, int tile_x, i
   // unless the options ask for one step or for a shape of its kernels
   StepPlan pair;
   if (depth == 2 && best_pair(g, tile_y, tile_x, &pair)) return pair;
-  if (depth == 0 && !tile_y && !tile_x && !zv && best_pair(g, 0, 0, &pair)) return pair;
+  if (depth == 0 && !tile_y && !tile_x && !zv && best_pair(g, 0, 0, &pair)) {
+    pair.time_rest = true;
+    return pair;
+  }
   // automatic: four z voxels per lane once a tile row spans 256 voxels, two
   // (with 8-row tiles) from 96
   if (zv == 0 && depth != 2 && g.nz >= 256 && g.nz % 4 == 0) zv = 4;
@@ -266,7 +269,8 @@ hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuff
 
 rfa_status run_steps(Grid3 g, const StepPlan& plan, StepState& s, const StepConst& K,
                      int n_steps, float* partials, int slots, double* dacc, hipEvent_t* events,
-                     int period, int* n_timed, int* n_launches, hipStream_t st) {
+                     int period, int* n_timed, int* n_launches, int* n_timed_steps,
+                     hipStream_t st) {
   if (s.traj && plan.depth != 1 && !plan.pv) return RFA_ERR_ARG;
   // one launch of p with the current images, which it then swaps
   auto launch = [&](const StepPlan& p, float* part) -> hipError_t {
@@ -329,13 +333,18 @@ rfa_status run_steps(Grid3 g, const StepPlan& plan, StepState& s, const StepCons
     if (launch_reduce_partials(partials, pending, plan.nwg, dacc, st) != hipSuccess)
       return RFA_ERR_HIP;
   const StepPlan one = plan_one(plan);
+  const bool time_rest = events && plan.time_rest;
   for (int r = 0; r < n_rest; ++r) {
+    if (time_rest && hipEventRecord(events[2 * timed], st) != hipSuccess) return RFA_ERR_HIP;
     if (launch(one, partials) != hipSuccess) return RFA_ERR_HIP;
+    if (time_rest && hipEventRecord(events[2 * timed++ + 1], st) != hipSuccess) return RFA_ERR_HIP;
     if (partials && launch_reduce_partials(partials, 1, one.nwg, dacc, st) != hipSuccess)
       return RFA_ERR_HIP;
   }
   if (n_timed) *n_timed = timed;
-  if (n_launches) *n_launches = events ? n_main : 0;
+  const int rest = time_rest ? n_rest : 0;
+  if (n_launches) *n_launches = events ? n_main + rest : 0;
+  if (n_timed_steps) *n_timed_steps = events ? n_main * plan.depth + rest : 0;
   return RFA_OK;
 }
 
