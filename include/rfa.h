@@ -306,10 +306,16 @@ rfa_status rfa_kernel_stats(rfa_grid g, double* kernel_ms, long long* launches,
 rfa_status rfa_adjoint_kernel_stats(rfa_grid g, double* kernel_ms, long long* launches);
 
 /* Current launch plan: kernel (1 reference, 2 tiled), steps per launch,
- * tile rows, x planes per work-group, work-groups per launch, z voxels per
- * lane. */
+ * tile rows (depth 2: wavefronts per work-group; automatic plans also take
+ * 4), x planes per work-group, work-groups per launch, z voxels per lane. */
 rfa_status rfa_get_plan(rfa_grid g, int* kernel, int* depth, int* tile_y, int* tile_x,
                         int* workgroups, int* z_vec);
+
+/* Work-groups of the two-step kernel over flat plane segments: wavefronts and
+ * z voxels per lane; both 0 if the grid's launches are of another kernel (one
+ * step each, or the 2.5-D two-step kernel of rows beyond nz = 256).  Either
+ * may be NULL. */
+rfa_status rfa_get_pair_plan(rfa_grid g, int* waves, int* lane_voxels);
 
 /* Time the candidate launch plans of this grid's shape on scratch copies of
  * its state (the state is not advanced) and keep the fastest per step: the
@@ -440,6 +446,13 @@ rfa_status rfa_batch_set_plan(rfa_batch b, int layout, int tile_y, int tile_x, i
  * number of groups (each pointer nullable). */
 rfa_status rfa_batch_get_plan(rfa_batch b, int* layout, int* tile_y, int* tile_x, int* items,
                               int* workgroups, int* groups);
+
+/* Current work-groups of the two-step launches, which take the steps of a
+ * call but an odd last one: wavefronts, z voxels per lane and work items per
+ * launch of all groups (one work-group each).  All 0 if the batch takes one
+ * step per launch, in the shape of rfa_batch_get_plan.  As of the last build
+ * of its tables; each may be NULL. */
+rfa_status rfa_batch_get_pair_plan(rfa_batch b, int* waves, int* lane_voxels, int* items);
 
 /* Pick the batch's launch shape by timing: two steps per launch and the
  * one-step layouts, tile rows and x planes per item, then grouping budgets for the

@@ -1426,7 +1426,14 @@ rfa_status rfa_get_plan(rfa_grid g, int* kernel, int* depth, int* tile_y, int* t
   if (tile_y) *tile_y = g->plan.ty;
   if (tile_x) *tile_x = g->plan.xc;
   if (workgroups) *workgroups = g->plan.nwg;
-  if (z_vec) *z_vec = g->plan.zv;
+  if (z_vec) *z_vec = g->plan.pv ? g->plan.pv : g->plan.zv;
+  return RFA_OK;
+}
+
+rfa_status rfa_get_pair_plan(rfa_grid g, int* waves, int* lane_voxels) {
+  if (!g) return fail(RFA_ERR_ARG, "grid is NULL");
+  if (waves) *waves = g->plan.pv ? g->plan.ty : 0;
+  if (lane_voxels) *lane_voxels = g->plan.pv;
   return RFA_OK;
 }
 
@@ -2652,6 +2659,14 @@ rfa_status rfa_batch_get_plan(rfa_batch b, int* layout, int* tile_y, int* tile_x
     *workgroups = w;
   }
   if (groups) *groups = (int)b->groups.size();
+  return RFA_OK;
+}
+
+rfa_status rfa_batch_get_pair_plan(rfa_batch b, int* waves, int* lane_voxels, int* items) {
+  if (!b) return fail(RFA_ERR_ARG, "batch is NULL");
+  if (waves) *waves = b->pwaves;
+  if (lane_voxels) *lane_voxels = b->pv;
+  if (items) *items = b->n_pitems;
   return RFA_OK;
 }
 

@@ -84,6 +84,7 @@ _SIGS = {
     "rfa_kernel_stats": [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_longlong),
                          C.POINTER(C.c_longlong)],
     "rfa_get_plan": [C.c_void_p] + [C.POINTER(C.c_int)] * 6,
+    "rfa_get_pair_plan": [C.c_void_p] + [C.POINTER(C.c_int)] * 2,
     "rfa_tune": [C.c_void_p, C.c_double, C.c_int],
     "rfa_copy_bandwidth": [C.c_size_t, C.c_int, C.POINTER(C.c_double)],
     "rfa_mix_bandwidth": [C.c_longlong, C.c_int, C.POINTER(C.c_double)],
@@ -101,6 +102,7 @@ _SIGS = {
     "rfa_batch_step": [C.c_void_p, C.c_int, C.c_void_p],
     "rfa_batch_set_plan": [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_longlong],
     "rfa_batch_get_plan": [C.c_void_p] + [C.POINTER(C.c_int)] * 6,
+    "rfa_batch_get_pair_plan": [C.c_void_p] + [C.POINTER(C.c_int)] * 3,
     "rfa_batch_tune": [C.c_void_p, C.c_int],
     "rfa_batch_last_time": [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_longlong)],
     "rfa_batch_destroy": [C.c_void_p],
@@ -283,6 +285,18 @@ def rfa_get_plan(g):
                     [x.value for x in v]))
 
 
+def _pair_name(waves: int, lane_voxels: int):
+    return f"{waves}x{lane_voxels}" if waves else None
+
+
+def rfa_get_pair_plan(g):
+    """Work-groups of the flat two-step kernel as "waves x voxels per lane"
+    ("16x2"), None where the grid's launches are of another kernel."""
+    v = [C.c_int() for _ in range(2)]
+    _check(lib().rfa_get_pair_plan(g, *[C.byref(x) for x in v]))
+    return _pair_name(*[x.value for x in v])
+
+
 def rfa_tune(g, dt: float, reps: int = 20):
     _check(lib().rfa_tune(g, float(dt), int(reps)))
 
@@ -417,6 +431,15 @@ def rfa_batch_get_plan(b) -> dict:
                  [x.value for x in v]))
     d["layout"] = "flat" if d["layout"] == RFA_BATCH_FLAT else "tiles"
     return d
+
+
+def rfa_batch_get_pair_plan(b):
+    """(work-groups as in rfa_get_pair_plan, work items per launch of all
+    groups) of the batch's two-step launches; (None, 0) without them."""
+    v = [C.c_int() for _ in range(3)]
+    _check(lib().rfa_batch_get_pair_plan(b, *[C.byref(x) for x in v]))
+    waves, lane_voxels, items = [x.value for x in v]
+    return _pair_name(waves, lane_voxels), items
 
 
 def rfa_batch_tune(b, reps: int = 20):
@@ -671,7 +694,7 @@ class Grid:
         return rfa_adjoint_kernel_stats(self.h)
 
     def plan(self) -> dict:
-        return rfa_get_plan(self.h)
+        return {**rfa_get_plan(self.h), "pair": rfa_get_pair_plan(self.h)}
 
     def source_support(self) -> int:
         """rfa_source_support: voxels on which the step reads the source."""
@@ -706,7 +729,11 @@ class Batch:
         return self.plan()
 
     def plan(self) -> dict:
-        return rfa_batch_get_plan(self.h)
+        """The one-step launch shape, and beside it the steps a launch takes
+        (depth) and the work-groups and items of the two-step launches."""
+        pair, items = rfa_batch_get_pair_plan(self.h)
+        return {**rfa_batch_get_plan(self.h), "depth": 2 if pair else 1, "pair": pair,
+                "pair_items": items}
 
     def tune(self, reps: int = 20) -> dict:
         """Time candidate launch shapes and keep the fastest (grids unchanged)."""
