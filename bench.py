@@ -99,9 +99,17 @@ PLANS = {2: (2, 8, 4), 3: (4, 4, 32), 7: (2, 4, 4)}
 def kernel_name(plan: dict) -> str:
     if plan["kernel"] != 2:
         return "k_step_naive"
-    if plan["depth"] == 2:  # every workload's rows fit the flat two-step kernel
-        return "k_step_pair"
+    if plan["depth"] == 2:
+        return "k_step_pair" if plan["pair"] else "k_step_tiled2"
     return "k_step_wide" if plan["z_vec"] > 1 else "k_step_tiled"
+
+
+def batch_launches(plan: dict, n_steps: int):
+    """Dominant kernel of a batched call and its launches: one per group and
+    plan["depth"] steps (an odd last step is a launch of its own)."""
+    depth = plan["depth"]
+    return ("k_step_pair_batch" if depth == 2 else "k_step_batch",
+            plan["groups"] * (n_steps // depth + n_steps % depth))
 
 
 def workload(config: int):
@@ -147,7 +155,7 @@ def traffic_record(config: int, plan: dict, kernel: str):
     with open(path) as f:
         rec = json.load(f)
     if (kernel not in KERNEL_SOURCES or rec.get("kernel_hash") != kernel_hash(kernel)
-            or rec.get("plan") != plan):
+            or rec.get("plan") != {k: plan[k] for k in rec.get("plan", {}) if k in plan}):
         return None
     return rec.get("hbm_bytes_per_launch")
 
@@ -400,11 +408,11 @@ def bench_batch(args) -> dict:
     value = total_vox * n_steps * args.steps / wall / 1e9
     plan = b.plan()
     # one launch per group and two steps (grids of a group share a launch; all
-    # of the sweep's grids carry no perfusion field; an odd last step and a
-    # shape found by --tune take one step a launch): device time of the graph
-    # per launch, algorithmic bytes per launch averaged over the groups
-    depth = 1 if args.tune else 2
-    launches = plan["groups"] * (n_steps // depth + n_steps % depth) * args.steps
+    # of the sweep's grids carry no perfusion field; --tune may find a shape of
+    # one step a launch): device time of the graph per launch, algorithmic
+    # bytes per launch averaged over the groups
+    kernel, launches = batch_launches(plan, n_steps)
+    launches *= args.steps
     avg_launch_ms = dev_ms / launches
     support = sum(g.source_support() for g in grids)
     bytes_per_launch = (BYTES_PER_VOXEL_STEP * total_vox + SOURCE_BYTES * support) / plan["groups"]
@@ -413,14 +421,13 @@ def bench_batch(args) -> dict:
     for g in grids:
         g.close()
     mix_gbps = rfa.rfa_mix_bandwidth(total_vox // plan["groups"], 10)
-    kernel = "k_step_batch" if args.tune else "k_step_pair_batch"
     roof = roofline_dict(bytes_per_launch, avg_launch_ms, kernel, launches_timed=launches,
-                         steps_per_launch=depth, copy_ceiling_GBps=round(copy_gbps, 1),
+                         steps_per_launch=plan["depth"], copy_ceiling_GBps=round(copy_gbps, 1),
                          source_support_voxels=support,
-                         note="a launch takes two steps in one pass over a group's grids and "
-                              "is bound by the instructions it issues as much as by its "
-                              "bytes (with --tune it is priced as one step a launch); the "
-                              "mix ceiling is taken over one average group's voxels")
+                         note="a launch takes steps_per_launch steps in one pass over a "
+                              "group's grids (two: bound by the instructions it issues as "
+                              "much as by its bytes); the mix ceiling is taken over one "
+                              "average group's voxels")
     roof.update(mix_ceiling(roof, mix_gbps))
     roof["traffic"] = traffic_record(4, plan, kernel)
     out = {

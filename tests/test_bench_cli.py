@@ -58,3 +58,14 @@ def test_one_gpu_slab_is_the_middle_y_slab_of_the_256_case():
     yf = W.voxel_axes(full.shape, full.spacing)[1][111:145]
     assert np.array_equal(ys, yf)
     assert np.array_equal(slab.needle.pts, full.needle.pts) and slab.n_steps == full.n_steps
+
+
+def test_batch_is_priced_by_the_launches_it_takes():
+    """Kernel name and launch count follow the batch's plan, tuned or not."""
+    sys.path.insert(0, ROOT)
+    import bench
+    two = {"groups": 3, "depth": 2, "pair": "8x2"}
+    one = {"groups": 3, "depth": 1, "pair": None}
+    assert bench.batch_launches(two, 2000) == ("k_step_pair_batch", 3000)
+    assert bench.batch_launches(two, 7) == ("k_step_pair_batch", 12)
+    assert bench.batch_launches(one, 7) == ("k_step_batch", 21)
