@@ -2727,7 +2727,9 @@ rfa_status rfa_batch_tune(rfa_batch b, int reps) {
   std::vector<Cand> shapes = {
       {false, 4, 8, g0, false}, {false, 8, 8, g0, false}, {false, 4, 16, g0, false}};
   if (flat_ok)
-    shapes.insert(shapes.begin(), {{true, 8, 8, g0, true},
+    // two steps a launch in the groups that are its default (-1): in cache-sized
+    // ones it is a tenth slower (see kPairGroupVoxels)
+    shapes.insert(shapes.begin(), {{true, 8, 8, -1, true},
                                    {true, 8, 8, g0, false},
                                    {true, 8, 4, g0, false},
                                    {true, 8, 16, g0, false}});
