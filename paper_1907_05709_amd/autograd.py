@@ -63,15 +63,19 @@ def _coverage_ops(omega, labels, voxel_m3: float, tumour: int, liver: int,
 def _plain(*tensors) -> bool:
     """Whether the tensors are ordinary contiguous ones on one GPU, outside
     tracing, functional transforms, forward-mode levels and dispatch modes:
-    what a kernel may read through their pointers."""
-    return (all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda
-                and t.layout == torch.strided and t.device == tensors[0].device
-                and torch._C._has_storage(t) and t.is_contiguous() and not t.is_neg()
-                for t in tensors)
-            and torch._C._functorch.peek_interpreter_stack() is None
-            and torch.autograd.forward_ad._current_level < 0
-            and torch._C._len_torch_dispatch_stack() == 0
-            and torch._C._len_torch_function_stack() == 0 and not torch.jit.is_tracing())
+    what a kernel may read through their pointers.  Torch says most of that
+    only through names of its own; one without any of them gives no."""
+    try:
+        return (all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda
+                    and t.layout == torch.strided and t.device == tensors[0].device
+                    and torch._C._has_storage(t) and t.is_contiguous() and not t.is_neg()
+                    for t in tensors)
+                and torch._C._functorch.peek_interpreter_stack() is None
+                and torch.autograd.forward_ad._current_level < 0
+                and torch._C._len_torch_dispatch_stack() == 0
+                and torch._C._len_torch_function_stack() == 0 and not torch.jit.is_tracing())
+    except AttributeError:
+        return False
 
 
 class _Coverage(torch.autograd.Function):
