@@ -242,7 +242,7 @@ rfa_status rfa_set_temperature(rfa_grid g, const double* t_C);
  * out[x] = T(x + beta v(x)) in degC, T taken trilinearly between voxel
  * centres from the temperature state, sample positions beyond the grid
  * taken on its walls.  Accuracy: within 1e-4 K of the exact interpolant of
- * the float-float state (sample positions formed as float-float pairs; the
+ * the float-float state (sample positions formed in double; the
  * lo words of the state enter in cells with a corner at or above 1024 degC,
  * elsewhere they are below half an ulp of the hi word; the result rounded
  * once to float).  A sample exactly on a voxel centre (zero displacement,
@@ -262,8 +262,8 @@ rfa_status rfa_warp(rfa_grid g, const float* v, double beta, float* out, double*
  * beta1 v1(x) + beta2 v2(x): the keyframe form of the motion model (two
  * consecutive phase fields weighted 1 - a and a) or a regression on two
  * surrogate signals (Sec. "Consideration of Breathing Motion").  v1, v2 as v
- * above (v2 required); beta2 v2 is added to the float-float position
- * beta1 v1 by an exact two-sum, so beta2 = 0 gives exactly
+ * above (v2 required); beta2 v2 is added to the position of beta1 v1 by one
+ * fused multiply-add in double, so beta2 = 0 gives exactly
  * rfa_warp(v1, beta1).
  * Errors as rfa_warp. */
 rfa_status rfa_warp2(rfa_grid g, const float* v1, double beta1, const float* v2, double beta2,
@@ -366,9 +366,9 @@ rfa_status rfa_reset_state(rfa_grid g);
 rfa_status rfa_set_tine_powers(rfa_grid g, const double* power);
 
 /* n_steps forward steps (as rfa_step) keeping, for rfa_adjoint, the
- * temperature (hi word) of every step when ckpt_every = 0 (one step per
- * launch, written straight into the kept trajectory; RFA_ERR_OOM if it does
- * not fit: use checkpoints), else the state at steps 0, ckpt_every,
+ * temperature (hi word) of every step when ckpt_every = 0 (the launches, of
+ * two steps by default, write it straight into the kept trajectory;
+ * RFA_ERR_OOM if it does not fit: use checkpoints), else the state at steps 0, ckpt_every,
  * 2 ckpt_every, ... plus the hi word of every step of the last segment,
  * written into the adjoint's segment buffer (2 (ckpt_every + 1) images,
  * allocated here), so the first rfa_adjoint after it recomputes every

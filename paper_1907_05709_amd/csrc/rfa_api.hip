@@ -616,9 +616,9 @@ rfa_status ensure_events(rfa_grid g, int count);
 // Advance the grid's current state n_steps with its launch plan (step
 // partials into g->dacc when diag), timing launch blocks with HIP events
 // when the grid was created with time_kernels.  Updates the step count.
-// With traj: one step per launch, the hi image of step *traj_t read from
-// traj[*traj_t] and written to traj[*traj_t + 1] (the grid's hi images are
-// not touched).
+// With traj: every step's hi image goes to traj, from the one at
+// traj[*traj_t] on (the grid's hi images are not touched; pair plans keep two
+// steps a launch).
 rfa_status timed_steps(rfa_grid g, const StepConst& K, int n_steps, bool diag,
                        float* traj = nullptr, int* traj_t = nullptr) {
   float* om = g->om;  // the damage image as the launches pass it on
@@ -1864,14 +1864,15 @@ rfa_status rfa_adjoint(rfa_grid g, const float* w_omega, double* dL_dP, double* 
   HIP_TRY(hipMemcpyAsync(g->lab_scratch, g->lab, n, hipMemcpyDeviceToDevice, g->st));
   if ((s = prepare_dt(g, g->adj_dt)) != RFA_OK) return s;
   const StepConst K = step_const(g, g->adj_dt);
-  // adjoint schedule: the tiled kernel (8 rows, x chunks sized for about
-  // one work-group per compute unit; at 128^3: 256 work-groups of 16 planes,
-  // 8 % faster than 1024 work-groups of 4 rows x 8 planes) unless the grid
-  // asked for the reference kernels.  Beside the segment recomputes (which
-  // leave each compute unit fewer free cycles) two work-groups per compute
-  // unit of half the length finish sooner: 512 work-groups of 8 planes at
-  // 128^3 (the recompute-and-adjoint phase 5 % shorter; alone both widths
-  // take the same time)
+  // One adjoint step a launch (grids whose forward takes one step a launch, and
+  // the odd last step of the others): the tiled kernel (8 rows, x chunks sized
+  // for about one work-group per compute unit; 128^3: 256 work-groups of 16
+  // planes, 8 % faster than 1024 of 4 rows x 8 planes) unless the grid asked
+  // for the reference kernels.  Beside segment recomputes, which leave each
+  // compute unit fewer free cycles, two work-groups per compute unit of half
+  // the length finish sooner (128^3, one step a launch throughout: the
+  // recompute-and-adjoint phase 5 % shorter; alone both widths take the same
+  // time).
   constexpr int adj_ty = 8;
   int adj_xc = 4;
   {

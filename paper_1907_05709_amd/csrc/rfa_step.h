@@ -57,9 +57,10 @@ struct StepState {
   const float* perf;
   const Tables* tab;
   int n_classes;
-  // Trajectory mode (traj not null; one-step and pair plans): the hi image of
-  // step *traj_t is read from traj[*traj_t] and written to traj[*traj_t + 1]
-  // (images of traj_n voxels); lo keeps ping-ponging in lo[2].
+  // Trajectory mode (traj not null; one-step and pair plans): a launch reads the
+  // hi image of step *traj_t from traj[*traj_t] and writes those of its one or
+  // two steps to the images that follow (of traj_n voxels); lo keeps
+  // ping-ponging in lo[2].
   float* traj = nullptr;
   int* traj_t = nullptr;
   size_t traj_n = 0;

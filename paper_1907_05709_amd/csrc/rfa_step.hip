@@ -122,9 +122,8 @@ namespace {
 
 // Two-step plan with the least estimated time, waves / tile_x as asked (0:
 // any); false if no work-group fits the grid.  It picks e.g. 4 waves x 1
-// voxel at 32^3 (3.4 us a step; one-step kernel 6.0), 8 x 1 at 64^3 (5.0;
-// 6.4), 8 x 2 at 128^3 (12.8; 13.3), 16 x 2 at 160^3 (19.4; 33.7) and 256^3
-// (66; 80).
+// voxel at 32^3 (3.3 us a step; one-step kernel 6.0), 8 x 1 at 64^3 (4.9;
+// 6.4), 16 x 2 at 128^3 (10.8; 13.3) and 256^3 (57.0; 80).
 bool best_pair(Grid3 g, int waves, int tile_x, StepPlan* out) {
   double best = 1e300;
   int w, v;
