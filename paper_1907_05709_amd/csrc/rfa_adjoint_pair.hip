@@ -12,9 +12,12 @@
 // nothing.  Where such a wave is cold (|theta| below K.cold, so that T_aK +
 // theta = T_aK and 2^x = 1) the damage-rate derivative is one constant.
 //
-// What bounds it: the latency of a plane and the planes computed twice; half
-// the vector memory instructions (two voxels a lane in one access, 25 -> 13 a
-// wave and plane) left 128^3 at 10.1 us a step, aligned LDS accesses on even
+// What bounds it: the latency of a plane and the planes computed twice (128^3,
+// 5 planes a work-group: 105 MB a launch below the L2, 1.49 times the 33 bytes
+// a voxel, since the planes at a chunk's ends are read by both sides: 5.2 TB/s
+// from the last-level cache; vector instructions issue in 0.55 of the cycles).
+// Half the vector memory instructions (two voxels a lane in one access, 25 -> 13
+// a wave and plane) left 128^3 at 10.1 us a step, aligned LDS accesses on even
 // rows 9.95.  Against one step a launch: 128^3 16.5 -> 9.95 us a step, 88x80x75
 // 13.0 -> 5.0, 64^3 6.35 -> 3.85.
 //

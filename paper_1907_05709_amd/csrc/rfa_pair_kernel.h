@@ -28,11 +28,12 @@
 //    is also cold (|theta| below K.cold everywhere, so that the damage
 //    exponent rounds to 2^0), the transcendentals are skipped.
 //
-// What bounds it: on large grids memory and issue alike (256^3 without sums
-// 50.9 us a step, 4.1 TB/s at 12.5 bytes a voxel step; vector instructions
-// take two thirds of the cycles, about 200 a wave and plane for two steps of
-// two voxels), on small ones the planes computed twice and the latency of a
-// plane.  A vector memory instruction costs as much as 16 arithmetic ones, so
+// What bounds it: on large grids memory and issue alike (256^3 with sums 57.0
+// us a step: 452 MB a launch below the L2, 1.08 times the 25 bytes a voxel, is
+// 4.0 TB/s; vector instructions issue in 0.80 of a busy compute unit's cycles,
+// 224 a wave and plane for two steps of two voxels), on small ones the planes
+// computed twice and the latency of a plane (128^3: 0.71 of the cycles, 2.1
+// waves a SIMD, 44 % of their time spent waiting; 63 MB a launch, 1.19 times).  A vector memory instruction costs as much as 16 arithmetic ones, so
 // a lane's two voxels are consecutive and move as one access (11 a wave and
 // plane; 22 with single ones); uniform branches cost as much as the few
 // instructions they skip, so there are few.  The first step on halo rows and
