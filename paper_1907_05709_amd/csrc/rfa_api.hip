@@ -2107,9 +2107,12 @@ struct rfa_batch_s {
   // the one-step kernel is asked for.
   bool want_pair = true;
   int pwaves = 0, pv = 0;           // work-group kind (0: one step per launch)
+  std::vector<PairInstance> pinst;  // host copy of the pair kernel's descriptor table
   std::vector<int> pfirst;          // pair item range of each instance
   std::vector<int> tissue_version;  // of the grids when the codes were made
-  std::vector<char> coupled;        // perf_decay of the grids when the items were made
+  // what the items were laid out for, besides shapes that do not change: whether
+  // each grid has a perfusion field and whether its perfusion is coupled
+  std::vector<char> field, coupled;
   PairInstance* pinst_dev = nullptr;
   PairItem* pitems_dev = nullptr;
   int* pfirst_dev = nullptr;
@@ -2194,20 +2197,28 @@ rfa_status batch_build_pair(rfa_batch b) {
   const int n = (int)b->grids.size();
   if (!batch_pair_fits(b)) return RFA_OK;
   // chunks of about xc planes, of equal length within a grid
-  auto shape_of = [&](int i, int w, int v, int xc) {
-    const Grid3 q = b->grids[i]->g;
-    const int chunks = (q.nx + xc - 1) / xc;
-    return pair_shape(q, w, v, (q.nx + chunks - 1) / chunks);
+  struct Chunks {
+    int xc, n;
   };
+  auto chunks_of = [](int nx, int xc) {
+    const int n = (nx + xc - 1) / xc, len = (nx + n - 1) / n;
+    return Chunks{len, (nx + len - 1) / len};
+  };
+  constexpr int kLongest = 64;
+  std::vector<Chunks> chunks((size_t)n * kLongest);  // [grid][xc - 1]
+  for (int i = 0; i < n; ++i)
+    for (int xc = 1; xc <= kLongest; ++xc)
+      chunks[(size_t)i * kLongest + xc - 1] = chunks_of(b->grids[i]->g.nx, xc);
+  std::vector<int> segs(n);  // of the kind under consideration
   // estimated time of a group's launch
   auto time_of = [&](const rfa_batch_s::Group& G, int w, int v, int xc) {
     long long items = 0, planes = 0;  // planes marched, two more per item
     int longest = 0;
     for (int i = G.inst0; i < G.inst1; ++i) {
-      const PairShape s = shape_of(i, w, v, xc);
-      items += s.nwg;
-      planes += (long long)s.segs * (b->grids[i]->g.nx + 2 * s.chunks);
-      longest = std::max(longest, s.xc + 2);
+      const Chunks c = chunks[(size_t)i * kLongest + xc - 1];
+      items += (long long)segs[i] * c.n;
+      planes += (long long)segs[i] * (b->grids[i]->g.nx + 2 * c.n);
+      longest = std::max(longest, c.xc + 2);
     }
     return items > (1 << 22) ? 1e300 : pair_estimate_uneven(w, v, (int)items, planes, longest);
   };
@@ -2216,12 +2227,13 @@ rfa_status batch_build_pair(rfa_batch b) {
   int w, v;
   for (int kind = 0; pair_kind(kind, &w, &v); ++kind) {
     if (!batch_pair_fits(b, kind)) continue;
+    for (int i = 0; i < n; ++i) segs[i] = pair_shape(b->grids[i]->g, w, v, 1).segs;
     double total = 0.0;
     std::vector<int> xcs;
     for (const auto& G : b->groups) {
       double least = 1e300;
       int at = 1;
-      for (int xc = 1; xc <= 64; ++xc) {
+      for (int xc = 1; xc <= kLongest; ++xc) {
         const double us = time_of(G, w, v, xc);
         if (us < least) {
           least = us;
@@ -2241,7 +2253,7 @@ rfa_status batch_build_pair(rfa_batch b) {
   if (!b->pwaves) return RFA_OK;
   w = b->pwaves;
   v = b->pv;
-  std::vector<PairInstance> inst(n);
+  b->pinst.assign(n, PairInstance{});
   std::vector<PairItem> items;
   std::vector<PairShape> shapes(n);
   b->pfirst.assign(2 * (size_t)n, 0);
@@ -2253,8 +2265,8 @@ rfa_status batch_build_pair(rfa_batch b) {
       (pass == 0 ? G.pplain0 : G.pperf0) = (int)items.size();
       for (int i = G.inst0; i < G.inst1; ++i) {
         rfa_grid g = b->grids[i];
-        if ((g->perf != nullptr) != (pass == 1)) continue;
-        shapes[i] = shape_of(i, w, v, best_xc[gi]);
+        if ((b->field[i] != 0) != (pass == 1)) continue;
+        shapes[i] = pair_shape(g->g, w, v, chunks_of(g->g.nx, best_xc[gi]).xc);
         code_bytes += pair_code_bytes(g->g, shapes[i]);
         b->pfirst[2 * i] = (int)items.size();
         for (int c = 0; c < shapes[i].chunks; ++c)
@@ -2271,33 +2283,17 @@ rfa_status batch_build_pair(rfa_batch b) {
     return s;
   size_t at = 0;
   for (int i = 0; i < n; ++i) {
-    rfa_grid g = b->grids[i];
-    const BatchInstance& I = b->inst[i];
-    PairInstance& P = inst[i];
-    P = PairInstance{};
-    for (int k = 0; k < 2; ++k) {
-      P.hi[k] = I.hi[k];
-      P.lo[k] = I.lo[k];
-    }
-    P.lab = I.lab;
-    P.src = I.src;
-    P.om = I.om;
-    P.perf = I.perf;
-    P.tab = I.tab;
+    PairInstance& P = b->pinst[i];
     P.codes = b->codes + at;
-    P.n_classes = I.n_classes;
-    P.nx = I.nx;
-    P.ny = I.ny;
-    P.nz = I.nz;
+    P.nx = b->inst[i].nx;
+    P.ny = b->inst[i].ny;
+    P.nz = b->inst[i].nz;
     P.xc = shapes[i].xc;
     P.seg = shapes[i].seg;
     P.segs = shapes[i].segs;
-    HIP_TRY(launch_pair_codes(g->g, shapes[i], g->lab, g->cp_dev, b->codes + at, b->st));
-    at += pair_code_bytes(g->g, shapes[i]);
-    b->tissue_version[i] = g->tissue_version;
+    at += pair_code_bytes(b->grids[i]->g, shapes[i]);
+    b->tissue_version[i] = b->grids[i]->tissue_version - 1;  // no codes yet
   }
-  HIP_TRY(hipMemcpyAsync(b->pinst_dev, inst.data(), n * sizeof(PairInstance),
-                         hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipMemcpyAsync(b->pitems_dev, items.data(), items.size() * sizeof(PairItem),
                          hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipMemcpyAsync(b->pfirst_dev, b->pfirst.data(), 2 * (size_t)n * sizeof(int),
@@ -2306,17 +2302,12 @@ rfa_status batch_build_pair(rfa_batch b) {
   return RFA_OK;
 }
 
-// (Re)build the device descriptor table and work list from the grids'
-// current state; resets the batch parity and drops cached graphs.
-rfa_status batch_build(rfa_batch b) {
-  b->built = false;
-  batch_free_device(b);
+// Descriptors of the grids' current state, on host and device (and the wave
+// codes of grids with a new tissue): what a batch that is laid out needs after
+// a grid was stepped, re-tissued or given another source.  Image 0 is then the
+// current one.
+rfa_status batch_describe(rfa_batch b) {
   const int n = (int)b->grids.size();
-  b->inst.assign(n, BatchInstance{});
-  b->first.assign(2 * (size_t)n, 0);
-  b->coupled.assign(n, 0);
-  std::vector<BatchItem> items;
-  b->voxels = 0;
   for (int i = 0; i < n; ++i) {
     rfa_grid g = b->grids[i];
     rfa_status s = prepare_dt(g, b->dt[i]);
@@ -2333,8 +2324,52 @@ rfa_status batch_build(rfa_batch b) {
     I.perf = g->perf;
     I.tab = g->tab_dev;
     I.K = step_const(g, b->dt[i]);
-    b->coupled[i] = g->perf_decay;
     I.n_classes = g->n_classes;
+    if (!b->pwaves) continue;
+    PairInstance& P = b->pinst[i];
+    for (int k = 0; k < 2; ++k) {
+      P.hi[k] = I.hi[k];
+      P.lo[k] = I.lo[k];
+    }
+    P.lab = I.lab;
+    P.src = I.src;
+    P.om = I.om;
+    P.perf = I.perf;
+    P.tab = I.tab;
+    P.n_classes = I.n_classes;
+    if (b->tissue_version[i] != g->tissue_version) {
+      const PairShape sh = pair_shape(g->g, b->pwaves, b->pv, P.xc);
+      HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp_dev, const_cast<uint8_t*>(P.codes), b->st));
+      b->tissue_version[i] = g->tissue_version;
+    }
+  }
+  HIP_TRY(hipMemcpyAsync(b->inst_dev, b->inst.data(), n * sizeof(BatchInstance),
+                         hipMemcpyHostToDevice, b->st));
+  if (b->pwaves)
+    HIP_TRY(hipMemcpyAsync(b->pinst_dev, b->pinst.data(), n * sizeof(PairInstance),
+                           hipMemcpyHostToDevice, b->st));
+  HIP_TRY(hipStreamSynchronize(b->st));
+  b->parity = 0;
+  return RFA_OK;
+}
+
+// Lay the batch out: work lists, buffers and descriptors from the grids'
+// current state; drops cached graphs.
+rfa_status batch_build(rfa_batch b) {
+  b->built = false;
+  batch_free_device(b);
+  const int n = (int)b->grids.size();
+  b->inst.assign(n, BatchInstance{});
+  b->first.assign(2 * (size_t)n, 0);
+  b->field.assign(n, 0);
+  b->coupled.assign(n, 0);
+  std::vector<BatchItem> items;
+  b->voxels = 0;
+  for (int i = 0; i < n; ++i) {
+    rfa_grid g = b->grids[i];
+    BatchInstance& I = b->inst[i];
+    b->field[i] = g->perf != nullptr;
+    b->coupled[i] = g->perf_decay;
     I.nx = g->g.nx;
     I.ny = g->g.ny;
     I.nz = g->g.nz;
@@ -2365,7 +2400,7 @@ rfa_status batch_build(rfa_batch b) {
       (pass == 0 ? G.plain0 : G.perf0) = (int)items.size();
       for (int i = i0; i < i1; ++i) {
         const BatchInstance& I = b->inst[i];
-        if ((I.perf != nullptr) != (pass == 1)) continue;
+        if ((b->field[i] != 0) != (pass == 1)) continue;
         const TiledShape sh = b->flat ? flat_shape(b->grids[i]->g, b->ty, I.xc)
                                       : tiled_shape(b->grids[i]->g, b->ty, I.xc);
         b->first[2 * i] = (int)items.size();
@@ -2393,38 +2428,42 @@ rfa_status batch_build(rfa_batch b) {
       (s = dmalloc(&b->dacc, 7 * (size_t)n)) ||
       (s = dmalloc(&b->slot_acc, (size_t)kPartialSlots * 3 * n)))
     return s;
-  HIP_TRY(hipMemcpyAsync(b->inst_dev, b->inst.data(), n * sizeof(BatchInstance),
-                         hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipMemcpyAsync(b->items_dev, items.data(), items.size() * sizeof(BatchItem),
                          hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipMemcpyAsync(b->first_dev, b->first.data(), 2 * (size_t)n * sizeof(int),
                          hipMemcpyHostToDevice, b->st));
-  HIP_TRY(hipStreamSynchronize(b->st));
+  if ((s = batch_describe(b)) != RFA_OK) return s;  // waits for the copies
   // persistent work-groups if requested, else one work-group per work item
   b->n_wg = b->req_wg > 0 ? std::min(b->req_wg, b->n_items) : 0;
-  b->parity = 0;
   b->built = true;
   return RFA_OK;
 }
 
-// Whether the grids still match the descriptor table (nobody stepped or
-// re-tissued a grid outside the batch, no dt change).  The coupling is
-// compared by itself: it decides how many steps a launch may take and sits in
-// the one-step items, and steps of the grid alone renew its tables without
-// the batch's knowledge.
-bool batch_in_sync(rfa_batch b) {
-  if (!b->built) return false;
-  for (size_t i = 0; i < b->grids.size(); ++i) {
+// Brings the tables up to what the grids are now.  A field set or taken away
+// and a switched coupling change the layout (launch variants, and how many
+// steps a launch may take): the coupling is compared by itself, since calls of
+// the grid alone renew its tables without the batch's knowledge.  Anything else
+// (steps of a grid alone, a new tissue, source or time step) only changes
+// descriptors: work lists, buffers and graphs stay, as the graphs hold the
+// tables' addresses.
+rfa_status batch_sync(rfa_batch b) {
+  bool laid_out = b->built, same = true;
+  for (size_t i = 0; i < b->grids.size() && laid_out; ++i) {
     rfa_grid g = b->grids[i];
     const BatchInstance& I = b->inst[i];
-    if (!g->has_tissue || I.hi[b->parity] != g->hi[g->cur] || I.lab != g->lab ||
-        I.src != g->src || I.om != g->om || I.perf != g->perf || I.tab != g->tab_dev ||
-        I.n_classes != g->n_classes || g->tab_dt != b->dt[i] || g->src_dt != b->dt[i] ||
-        (b->coupled[i] != 0) != g->perf_decay ||
-        (b->pwaves && g->tissue_version != b->tissue_version[i]))
-      return false;
+    laid_out = (b->field[i] != 0) == (g->perf != nullptr) &&
+               (b->coupled[i] != 0) == g->perf_decay;
+    same = same && I.hi[b->parity] == g->hi[g->cur] && I.lab == g->lab && I.src == g->src &&
+           I.om == g->om && I.perf == g->perf && I.tab == g->tab_dev &&
+           I.n_classes == g->n_classes && g->tab_dt == b->dt[i] && g->src_dt == b->dt[i] &&
+           (!b->pwaves || g->tissue_version == b->tissue_version[i]);
   }
-  return true;
+  if (!laid_out) return batch_build(b);
+  if (same) return RFA_OK;
+  b->built = false;  // half described if the call fails
+  const rfa_status s = batch_describe(b);
+  b->built = s == RFA_OK;
+  return s;
 }
 
 // Launches of two among n_steps, an even number where a grid asks for it.
@@ -2562,7 +2601,7 @@ rfa_status rfa_batch_step(rfa_batch b, int n_steps, rfa_diag* diags) {
     HIP_TRY(hipStreamSynchronize(g->st));
   }
   rfa_status s;
-  if (!batch_in_sync(b) && (s = batch_build(b)) != RFA_OK) return s;
+  if ((s = batch_sync(b)) != RFA_OK) return s;
   std::vector<double> e0(n, 0.0);
   if (diags) {
     for (int i = 0; i < n; ++i) {
@@ -2676,7 +2715,7 @@ rfa_status rfa_batch_tune(rfa_batch b, int reps) {
   if (reps < 1) return fail(RFA_ERR_ARG, "reps must be >= 1");
   const int n = (int)b->grids.size();
   rfa_status s;
-  if (!batch_in_sync(b) && (s = batch_build(b)) != RFA_OK) return s;
+  if ((s = batch_sync(b)) != RFA_OK) return s;
   // snapshot of what a step reads and writes: the current images, damage
   // and latch bytes (the other images are scratch to the batch)
   std::vector<void*> snap(4 * (size_t)n, nullptr);
