@@ -578,7 +578,7 @@ rfa_status ensure_pair(rfa_grid g, const StepPlan& p) {
     if ((s = dmalloc(&g->codes, need + 4)) != RFA_OK) return s;  // read as dwords
     g->codes_cap = need;
   }
-  HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp_dev, g->codes, g->st));
+  HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp, g->codes, g->st));
   g->codes_waves = p.ty;
   g->codes_v = p.pv;
   return RFA_OK;
@@ -2339,7 +2339,7 @@ rfa_status batch_describe(rfa_batch b) {
     P.n_classes = I.n_classes;
     if (b->tissue_version[i] != g->tissue_version) {
       const PairShape sh = pair_shape(g->g, b->pwaves, b->pv, P.xc);
-      HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp_dev, const_cast<uint8_t*>(P.codes), b->st));
+      HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp, const_cast<uint8_t*>(P.codes), b->st));
       b->tissue_version[i] = g->tissue_version;
     }
   }

@@ -54,7 +54,7 @@ PairShape pair_shape(Grid3 g, int waves, int v, int xc);
 // change of the labels or the class table).
 size_t pair_code_bytes(Grid3 g, const PairShape& s);
 hipError_t launch_pair_codes(Grid3 g, const PairShape& s, const uint8_t* lab,
-                             const ClassParams* cp_dev, uint8_t* codes, hipStream_t st);
+                             const ClassParams& cp, uint8_t* codes, hipStream_t st);
 // Two steps, with the step constants of b.tab.  b.codes: the shape's wave codes; hi_mid: the image between the
 // steps (kPairKeep, kPairTemp).
 hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,
