@@ -123,12 +123,15 @@ __global__ __launch_bounds__(192) void k_coverage_finish(const double* __restric
   }
 }
 
-// dL/dOmega = grad[0] (weight_liver - 1 / N on the tumour) 4 d^2 Omega^-5.
+// dL/dOmega = grad[0] (weight_liver - 1 / N on the tumour) 4 d^2 Omega^-5.  The
+// classes multiply rather than select, so that a factor that is not finite
+// shows on every voxel with damage, as it does in the tensor operations.
 __device__ __forceinline__ float slope(float omega, unsigned code, double in_tumour,
                                        double in_liver) {
   const double om = (double)omega;
-  if (code == 0u || !(om > 0.0)) return 0.0f;
-  const double w = ((code & kTumour) ? in_tumour : 0.0) + ((code & kLiver) ? in_liver : 0.0);
+  if (!(om > 0.0)) return 0.0f;
+  const double w = in_tumour * ((code & kTumour) ? 1.0 : 0.0) +
+                   in_liver * ((code & kLiver) ? 1.0 : 0.0);
   const double p = inverse4(om), d = 1.0 / (1.0 + p);
   return (float)(w * (4.0 * (d * d) * (p / om)));
 }

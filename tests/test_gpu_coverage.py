@@ -139,3 +139,23 @@ def test_compilers_and_tracers_take_the_tensor_operations(how):
         from torch.fx.experimental.proxy_tensor import make_fx
         got = make_fx(f)(om)(om)
     assert torch.allclose(got, f(om), rtol=1e-12)
+
+
+@pytest.mark.parametrize("upstream, weight", [(np.inf, 0.1), (-np.inf, 0.0), (np.nan, 0.1),
+                                              (1.0, np.inf), (1.0, np.nan)])
+def test_gradients_that_are_not_finite(upstream, weight):
+    """A factor that is not finite shows where it does in the tensor
+    operations: on every voxel with damage, whatever its class."""
+    om, labels = _inputs((7, 5, 3))
+    om = torch.nan_to_num(om, nan=0.5, posinf=2.0, neginf=0.0).clamp_max(1e3)
+    grads = []
+    for f in (lambda o: autograd.coverage_loss(o, labels, VOX, healthy_weight=weight),
+              lambda o: autograd._coverage_ops(o, labels, VOX, 2, 1, weight)):
+        o = om.clone().requires_grad_(True)
+        f(o).backward(torch.tensor(upstream, dtype=torch.float64, device="cuda"))
+        grads.append(o.grad)
+    a, b = grads
+    assert torch.equal(a.isnan(), b.isnan()) and bool(b.isnan().any())
+    assert torch.equal(a.isinf(), b.isinf())
+    finite = b.isfinite()
+    assert torch.allclose(a[finite], b[finite], rtol=1.2e-7, atol=1e-44)
