@@ -125,16 +125,20 @@ __device__ __forceinline__ float rel(float h, float l, float b) { return (h - b)
 // nz - VZ, so that where VZ does not divide nz a few voxels are computed
 // twice, to the same bits); XCD k takes the k-th eighth of every plane's
 // threads (part.d of them), plane by plane.
-// kBuf: every offset fits a 32-bit buffer descriptor (n < 2^29), so the
-// eight corner gathers share one vector offset and take the row and plane
-// strides as scalar offsets; indices and strides are below 2^24 (24-bit
-// multiplies).
-template <bool kTwo, bool kBuf, int VZ>
+// ACCESS: kBuffer if every offset fits a 32-bit buffer descriptor (n < 2^29),
+// so that the eight corner gathers share one vector offset and take the row and
+// plane strides as scalar offsets, with indices and strides below 2^24 (24-bit
+// multiplies); kBufferWide the same where a plane has 2^24 voxels or more
+// (8x4200x4200: 694 us, 741 with plain loads; 896 and 1080 where neighbouring
+// displacements differ by voxels); kPlain otherwise.
+enum Access { kPlain, kBuffer, kBufferWide };
+template <bool kTwo, Access ACCESS, int VZ>
 __global__ __launch_bounds__(kWarpThreads) void k_warp(const float* __restrict__ hi,
                                                        const float* __restrict__ lo,
                                                        WarpField a, WarpField b,
                                                        float* __restrict__ out, int nx, int ny,
                                                        int nz, Divisor groups, Divisor part) {
+  constexpr bool kBuf = ACCESS != kPlain;
   const unsigned t = blockIdx.x / kXcds * kWarpThreads + threadIdx.x;
   const unsigned x = quotient(t, part);
   const unsigned q = (blockIdx.x % kXcds) * part.d + (t - x * part.d);
@@ -143,7 +147,10 @@ __global__ __launch_bounds__(kWarpThreads) void k_warp(const float* __restrict__
   const int z0 = min((int)(q - y * groups.d) * VZ, nz - VZ);
   const unsigned sy = (unsigned)nz, sx = (unsigned)ny * (unsigned)nz;
   auto mul = [](unsigned u, unsigned w) { return kBuf ? __umul24(u, w) : u * w; };
-  const unsigned o = mul(x, sx) + (mul(y, sy) + (unsigned)z0);
+  auto mul_x = [](unsigned u, unsigned w) {
+    return ACCESS == kBuffer ? __umul24(u, w) : u * w;
+  };
+  const unsigned o = mul_x(x, sx) + (mul(y, sy) + (unsigned)z0);
   const unsigned n = sx * (unsigned)nx;
   __amdgpu_buffer_rsrc_t rh, rl, ro;
   if constexpr (kBuf) {
@@ -216,7 +223,7 @@ __global__ __launch_bounds__(kWarpThreads) void k_warp(const float* __restrict__
       locate(px, nx, tx, kx, fx[j]);
       locate(py, ny, ty, ky, fy[j]);
       locate(pz, nz, tz, kz, fz[j]);
-      cc[j] = mul((unsigned)kx, sx) + (mul((unsigned)ky, sy) + (unsigned)kz);
+      cc[j] = mul_x((unsigned)kx, sx) + (mul((unsigned)ky, sy) + (unsigned)kz);
       corners(hi, rh, cc[j], h[j][0], h[j][1], h[j][2], h[j][3]);
     }
   }
@@ -317,14 +324,14 @@ __global__ __launch_bounds__(kWarpThreads) void k_warp(const float* __restrict__
   }
 }
 
-template <bool kTwo, bool kBuf, int VZ>
+template <bool kTwo, Access ACCESS, int VZ>
 hipError_t launch(Grid3 g, const float* hi, const float* lo, const WarpField& a,
                   const WarpField& b, float* out, hipStream_t st) {
   const size_t groups = (size_t)(g.nz + VZ - 1) / VZ;
   const size_t part = (groups * g.ny + kXcds - 1) / kXcds;  // of a plane, per XCD
   const size_t nwg = (part * g.nx + kWarpThreads - 1) / kWarpThreads * kXcds;
   if (nwg > 0x7fffffffu) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_warp<kTwo, kBuf, VZ>), dim3((unsigned)nwg), dim3(kWarpThreads), 0, st,
+  hipLaunchKernelGGL((k_warp<kTwo, ACCESS, VZ>), dim3((unsigned)nwg), dim3(kWarpThreads), 0, st,
                      hi, lo, a, b, out, g.nx, g.ny, g.nz, divisor((unsigned)groups),
                      divisor((unsigned)part));
   return hipGetLastError();
@@ -341,22 +348,25 @@ hipError_t launch_warp(Grid3 g, const float* hi, const float* lo, const float* v
   auto field = [&](const float* w, const double(&c)[3]) {
     return WarpField{w, w + n, w + 2 * n, {c[0], c[1], c[2]}};
   };
-  const bool buf = n * 4 <= 0x7fffffffu && g.nx < (1 << 24) && g.nz < (1 << 24) &&
-                   (size_t)g.ny * g.nz < (size_t(1) << 24);
+  const unsigned k24 = 1u << 24;
+  const bool buf = n * 4 <= 0x7fffffffu && (unsigned)g.ny < k24 && (unsigned)g.nz < k24;
+  const bool wide = (unsigned)g.nx >= k24 || (size_t)g.ny * g.nz >= k24;
   const WarpField a = field(v, scale);
   const WarpField b = v2 ? field(v2, scale2) : a;
-  auto go = [&](auto two, auto bufs, auto vz) {
-    return launch<decltype(two)::value, decltype(bufs)::value, decltype(vz)::value>(
-        g, hi, lo, a, b, out, st);
+  auto go = [&](auto access, auto vz) {
+    constexpr Access A = decltype(access)::value;
+    return v2 ? launch<true, A, decltype(vz)::value>(g, hi, lo, a, b, out, st)
+              : launch<false, A, decltype(vz)::value>(g, hi, lo, a, b, out, st);
   };
-  using T = std::true_type;
-  using F = std::false_type;
+  using Plain = std::integral_constant<Access, kPlain>;
+  using Buffer = std::integral_constant<Access, kBuffer>;
+  using BufferWide = std::integral_constant<Access, kBufferWide>;
   using One = std::integral_constant<int, 1>;
   using Four = std::integral_constant<int, 4>;
   // rows of two or three voxels hold no group of four
-  if (g.nz < 4) return v2 ? go(T{}, F{}, One{}) : go(F{}, F{}, One{});
-  if (buf) return v2 ? go(T{}, T{}, Four{}) : go(F{}, T{}, Four{});
-  return v2 ? go(T{}, F{}, Four{}) : go(F{}, F{}, Four{});
+  if (g.nz < 4) return go(Plain{}, One{});
+  if (!buf) return go(Plain{}, Four{});
+  return wide ? go(BufferWide{}, Four{}) : go(Buffer{}, Four{});
 }
 
 }  // namespace rfa

@@ -71,3 +71,40 @@ def test_displacements_that_are_not_finite():
     assert np.abs(out.astype(np.float64) - ref).max() <= GATE
     assert np.array_equal(out, g.warp(torch.from_numpy(far).cuda(), 1.0).cpu().numpy())
     g.close()
+
+
+@pytest.mark.parametrize("shape", [(3, 4097, 4099), (5, 3, 1 << 23), (3, 4096, 4096)])
+def test_planes_of_2_24_voxels_and_more(shape):
+    """Plane strides that 24-bit multiplies do not take: sampled voxels, the
+    last ones of rows, planes and grid among them, against the interpolant in
+    double."""
+    from paper_1907_05709_amd import rfa
+    spacing = (0.8e-3, 0.9e-3, 0.7e-3)
+    gen = torch.Generator("cuda").manual_seed(5)
+    T = 37.0 + 300.0 * torch.rand(shape, dtype=torch.float64, device="cuda", generator=gen)
+    v = 6e-3 * (torch.rand((3, *shape), device="cuda", generator=gen) - 0.5)
+    g = rfa.Grid(shape, spacing, device=True)
+    g.set_tissue(torch.ones(shape, dtype=torch.uint8, device="cuda"), W.standard_tissue())
+    g.set_temperature(T)
+    out = g.warp(v, 0.7)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(6)
+    at = np.stack([rng.integers(0, n, 20000) for n in shape])
+    ends = np.array([(i, j, k) for i in (0, shape[0] - 1) for j in (0, shape[1] - 1)
+                     for k in (0, 1, shape[2] - 2, shape[2] - 1)]).T
+    at = torch.from_numpy(np.concatenate([at, ends], axis=1)).cuda()
+    base, frac = [], []
+    for a in range(3):
+        s = at[a].double() + (0.7 / spacing[a]) * v[a][tuple(at)].double()
+        s = s.clamp(0.0, shape[a] - 1.0)
+        k = s.floor().long().clamp_max(shape[a] - 2)
+        base.append(k)
+        frac.append(s - k)
+    want = torch.zeros_like(frac[0])
+    for c in range(8):
+        w = torch.ones_like(want)
+        for a in range(3):
+            w = w * (frac[a] if c >> a & 1 else 1.0 - frac[a])
+        want += w * T[tuple(base[a] + (c >> a & 1) for a in range(3))]
+    assert (out[tuple(at)].double() - want).abs().max() <= GATE
+    g.close()
