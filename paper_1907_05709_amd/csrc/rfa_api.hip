@@ -109,17 +109,18 @@ struct rfa_grid_s {
   std::vector<double> pts, power;
   double sigma = 0.0;
   double rf_power = 0.0;
-  Chord* chords_dev = nullptr;     // chords of the rasterised needle
+  // device memory of the rasterised needle: one block, and what lies in it
+  char* needle_dev = nullptr;
+  size_t needle_cap = 0;
+  Chord* chords_dev = nullptr;     // chords
   int* first_dev = nullptr;        // first chord of each tine (+ end)
+  double* weight_dev = nullptr;    // power / integral of each tine
   std::vector<double> tine_sums;   // integral of each tine's unnormalised density, m
   // unnormalised densities of the tines (if kept), their capacity in
   // (tine, voxel) pairs, and whether they are the current needle's
   SourceFields fields{};
   size_t fields_cap = 0;
   bool fields_ok = false;
-  double* tine_dev = nullptr;      // [3][n_tines] power, integral, power / integral
-  size_t tine_cap = 0;             // tines allocated at tine_dev (and first_dev)
-  size_t chords_cap = 0;           // chords allocated at chords_dev
 
   // perfusion-correction B-spline (m^3 control points), if set
   int bs_m = 0;
@@ -184,7 +185,7 @@ namespace {
 
 void free_fields(rfa_grid g) {
   SourceFields& f = g->fields;
-  for (void* p : {(void*)f.u, (void*)f.active, (void*)f.list, (void*)f.count, (void*)f.partial})
+  for (void* p : {(void*)f.u, (void*)f.active, (void*)f.list, (void*)f.partial})
     if (p) (void)hipFree(p);
   f = SourceFields{};
   g->fields_cap = 0;
@@ -213,10 +214,8 @@ void free_all(rfa_grid g) {
   f(g->stage);
   f(g->counts);
   f(g->bad);
-  f(g->chords_dev);
-  f(g->first_dev);
+  f(g->needle_dev);
   free_fields(g);
-  f(g->tine_dev);
   f(g->bs_ctrl);
   f(g->bs_vfirst);
   f(g->ckpt);
@@ -389,8 +388,7 @@ bool ensure_fields(rfa_grid g, int nt) {
   const bool ok = hipMalloc((void**)&f.u, nu * sizeof(double)) == hipSuccess &&
                   hipMalloc((void**)&f.active, pairs) == hipSuccess &&
                   hipMalloc((void**)&f.list, pairs * sizeof(int2)) == hipSuccess &&
-                  hipMalloc((void**)&f.partial, pairs * sizeof(double)) == hipSuccess &&
-                  hipMalloc((void**)&f.count, sizeof(unsigned)) == hipSuccess;
+                  hipMalloc((void**)&f.partial, pairs * sizeof(double)) == hipSuccess;
   (void)hipGetLastError();
   if (!ok) {
     free_fields(g);
@@ -435,30 +433,32 @@ rfa_status rasterise(rfa_grid g) {
     }
   }
   first[nt] = (int)chords.size();
-  // device copies of the chords (also read by the adjoint's dL/dP), tine
-  // ranges and powers; grown, kept with the grid
+  // The needle's block, kept with the grid and grown: powers, chords (also read
+  // by the adjoint's dL/dP), tine ranges and a zero for the length of the list
+  // of tiles in one upload, then the integrals and weights formed there (a new
+  // needle of one chord on 24^3: 53 us; 80 with a copy for each and a fill).
   rfa_status s;
-  if (g->chords_cap < chords.size()) {
-    Chord* c = nullptr;
-    if ((s = dmalloc(&c, chords.size())) != RFA_OK) return s;
-    if (g->chords_dev) (void)hipFree(g->chords_dev);
-    g->chords_dev = c;
-    g->chords_cap = chords.size();
+  const size_t at_chords = nt * sizeof(double);
+  const size_t at_first = at_chords + chords.size() * sizeof(Chord);
+  const size_t at_count = at_first + first.size() * sizeof(int);
+  const size_t upload = (at_count + sizeof(unsigned) + 7) / 8 * 8;
+  const size_t need = upload + 2 * (size_t)nt * sizeof(double);
+  if (g->needle_cap < need) {
+    char* p = nullptr;
+    if ((s = dmalloc(&p, need)) != RFA_OK) return s;
+    if (g->needle_dev) (void)hipFree(g->needle_dev);
+    g->needle_dev = p;
+    g->needle_cap = need;
   }
-  if (g->tine_cap < (size_t)nt) {
-    int* f = nullptr;
-    double* d = nullptr;
-    if ((s = dmalloc(&f, first.size())) != RFA_OK) return s;
-    if ((s = dmalloc(&d, 3 * (size_t)nt)) != RFA_OK) { (void)hipFree(f); return s; }
-    if (g->first_dev) (void)hipFree(g->first_dev);
-    if (g->tine_dev) (void)hipFree(g->tine_dev);
-    g->first_dev = f;
-    g->tine_dev = d;
-    g->tine_cap = nt;
-  }
-  double* d_power = g->tine_dev;
-  double* d_sums = g->tine_dev + nt;
-  double* d_weight = g->tine_dev + 2 * nt;
+  g->chords_dev = (Chord*)(g->needle_dev + at_chords);
+  g->first_dev = (int*)(g->needle_dev + at_first);
+  double* d_power = (double*)g->needle_dev;
+  double* d_sums = (double*)(g->needle_dev + upload);
+  double* d_weight = g->weight_dev = d_sums + nt;
+  std::vector<char> host(upload, 0);
+  std::memcpy(host.data(), g->power.data(), nt * sizeof(double));
+  std::memcpy(host.data() + at_chords, chords.data(), chords.size() * sizeof(Chord));
+  std::memcpy(host.data() + at_first, first.data(), first.size() * sizeof(int));
   // Keep the per-tine densities when they fit the budget: new tine powers
   // then only recombine them, and dL/dP reads them instead of recomputing.
   const size_t nu = (size_t)nt * g->g.n();
@@ -469,12 +469,9 @@ rfa_status rasterise(rfa_grid g) {
   hipError_t e = hipSuccess;
   int nblk = 0;
   do {
-    if ((e = hipMemcpyAsync(g->chords_dev, chords.data(), chords.size() * sizeof(Chord),
-                            hipMemcpyHostToDevice, g->st)) != hipSuccess) break;
-    if ((e = hipMemcpyAsync(g->first_dev, first.data(), first.size() * sizeof(int),
-                            hipMemcpyHostToDevice, g->st)) != hipSuccess) break;
-    if ((e = hipMemcpyAsync(d_power, g->power.data(), nt * sizeof(double),
-                            hipMemcpyHostToDevice, g->st)) != hipSuccess) break;
+    if ((e = hipMemcpyAsync(g->needle_dev, host.data(), upload, hipMemcpyHostToDevice, g->st)) !=
+        hipSuccess) break;
+    g->fields.count = (unsigned*)(g->needle_dev + at_count);
     e = keep ? launch_source_fields(g->g, g->dx, g->dy, g->dz, g->lab, g->chords_dev,
                                     g->first_dev, nt, g->sigma, d_power, g->fields, d_sums,
                                     d_weight, g->st)
@@ -1702,7 +1699,7 @@ rfa_status rfa_set_tine_powers(rfa_grid g, const double* power) {
     // recombine the kept per-tine densities with the new powers
     std::vector<double> scale(nt);
     for (size_t t = 0; t < nt; ++t) scale[t] = power[t] / g->tine_sums[t];
-    double* d_weight = g->tine_dev + 2 * nt;
+    double* d_weight = g->weight_dev;
     HIP_TRY(hipMemcpyAsync(d_weight, scale.data(), nt * sizeof(double), hipMemcpyHostToDevice,
                            g->st));
     HIP_TRY(launch_source_combine(g->g, g->lab, g->fields, (int)nt, d_weight, g->q64, g->st));

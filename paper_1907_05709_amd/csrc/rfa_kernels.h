@@ -119,7 +119,7 @@ struct SourceFields {
   double* u;          // [n_tines][n], 0 on held voxels of active tiles
   uint8_t* active;    // [n_tines][tiles]
   int2* list;         // scratch [n_tines * tiles]: active (tile, tine)
-  unsigned* count;    // scratch: length of list
+  unsigned* count;    // scratch: length of list, 0 before launch_source_fields
   double* partial;    // scratch [n_tines * tiles]
 };
 // The densities, their integrals sums[t] and weight[t] = power[t] / sums[t].

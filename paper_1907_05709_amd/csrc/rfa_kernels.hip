@@ -654,9 +654,27 @@ __global__ __launch_bounds__(256) void k_source_combine(const uint8_t* lab, cons
       const int t = t0 + (int)(threadIdx.x & 63);
       unsigned long long on =
           __ballot(t < n_tines && active[(size_t)(t < n_tines ? t : t0) * n_tiles + tile] != 0);
-      for (; on != 0ull; on &= on - 1ull) {
-        const int tine = t0 + __builtin_ctzll(on);
-        if (inside && free) v += scale[tine] * u[(size_t)tine * n + p];
+      // eight tines' reads in flight, added in their order (a call with new
+      // powers of 200 tines, 64^3 82 -> 51 us, 24^3 82 -> 45)
+      while (on != 0ull) {
+        constexpr int kU = 8;
+        const int m = min((int)__popcll(on), kU);
+        double s[kU], w[kU];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+          s[k] = w[k] = 0.0;
+          if (k < m) {  // uniform
+            const int tine = t0 + __builtin_ctzll(on);
+            on &= on - 1ull;
+            s[k] = scale[tine];
+            if (inside && free) w[k] = u[(size_t)tine * n + p];
+          }
+        }
+        if (inside && free) {
+#pragma unroll
+          for (int k = 0; k < kU; ++k)
+            if (k < m) v += s[k] * w[k];
+        }
       }
     }
     if (inside) q[p] = v;
@@ -668,8 +686,6 @@ hipError_t launch_source_fields(Grid3 g, double dx, double dy, double dz, const 
                                 double sigma, const double* power, const SourceFields& f,
                                 double* sums, double* weight, hipStream_t st) {
   const int tiles = source_tiles(g);
-  hipError_t e = hipMemsetAsync(f.count, 0, sizeof(unsigned), st);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_source_cull, dim3((tiles + 255) / 256, n_tines), dim3(256), 0, st, chords,
                      tine_first, sigma, g.nx, g.ny, g.nz, dx, dy, dz, tiles, f.active, f.list,
                      f.count, f.partial);

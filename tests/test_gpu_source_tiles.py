@@ -57,3 +57,31 @@ def test_source_matches_oracle(shape, spacing, n_tines, n_points):
     g.set_tine_powers(p2)
     check(p2)
     g.close()
+
+
+def test_one_needle_after_another():
+    """Needles that grow, shrink and fail on one grid: source and gradients as
+    on a grid of their own."""
+    shape, spacing = (20, 17, 33), (1e-3, 0.9e-3, 1.1e-3)
+    cases = [_case(shape, spacing, t, p, 60 + t) for t, p in ((2, 3), (40, 20), (1, 2), (9, 65))]
+    g = rfa.Grid(shape, spacing)
+    g.load_case(cases[0])
+    outside = W.Needle(np.array([0, 2], np.int32), np.full((2, 3), 1.0), np.array([1.0]), 1e-3)
+    w = np.random.default_rng(8).uniform(0.5, 1.0, shape).astype(np.float32)
+    for case in cases + cases[::-1]:
+        own = rfa.Grid(shape, spacing)
+        own.load_case(case)
+        g.set_needle(case.needle)
+        with pytest.raises(rfa.RfaError):  # no weight on the grid: the needle stays
+            g.set_needle(outside)
+        powers = case.needle.power * 1.5
+        out = []
+        for x in (g, own):
+            x.set_tine_powers(powers)
+            x.reset_state()
+            x.forward_checkpointed(6, case.dt, 0)
+            out.append((*x.raw_state(), x.omega(), x.adjoint(w, len(powers), 0)[0]))
+        for a, b in zip(*out):
+            assert np.array_equal(a, b)
+        own.close()
+    g.close()
