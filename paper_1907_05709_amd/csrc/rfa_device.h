@@ -160,8 +160,11 @@ __device__ __forceinline__ float damage_increment(float hi, const StepConst& K) 
 // The damage update has two forms with the same bits: branch-free (the
 // default, one basic block per plane, fewer live registers in the kernels
 // with one or two voxels per lane) and a select that lets the compiler
-// branch around the transcendentals off tissue (kSelectDamage, fewer live
-// registers where each lane carries four voxels).
+// branch around the transcendentals off tissue (where each lane carries four
+// voxels).  The select is kept apart in damage_add() or written in
+// voxel_step(), which moves the branches: k_step_wide<4, 4> has 200
+// registers and 109 waits one way, 243 and 83 the other.
+enum DamageForm { kDamageFlat, kDamageSelect, kDamageSelectApart };
 template <bool kSelectDamage>
 __device__ __forceinline__ float damage_add(float om, float rate, bool tissue,
                                             const StepConst& K) {
@@ -194,7 +197,7 @@ __device__ __forceinline__ float2 table_entry(const float2* __restrict__ cf, int
 // the coupling off (K.decay2 = 0) the factor is exp2(-0) = 1 and pf * 1 = pf
 // exactly, for every finite om >= 0 (callers pass a finite damage integral,
 // also into scratch recomputations).
-template <bool kSelectDamage = false>
+template <DamageForm kDamage = kDamageFlat>
 __device__ __forceinline__ void voxel_step(
     float hi, float lo, unsigned lab,
     float hxm, float lxm, unsigned bxm, float hxp, float lxp, unsigned bxp,
@@ -213,8 +216,17 @@ __device__ __forceinline__ void voxel_step(
   const float4 c = cls[class_of(lab)];
   const bool held = (lab & kHeld) != 0u;
   voxel_thermal(hi, lo, held, k, c, d, s, pf, nh, nl, acc, !held);
-  om = damage_add<kSelectDamage>(om, damage_increment(hi, K), (lab & kTissue) != 0u, K);
-  nlab = latch(lab, nh, nl, K);
+  if constexpr (kDamage == kDamageSelect) {
+    const float rate = damage_increment(hi, K);
+    const bool tissue = (lab & kTissue) != 0u;
+    om = tissue ? fminf(om + rate, K.cap) : om;
+    const bool reached = (nh > K.thr) | ((nh == K.thr) & (nl >= 0.0f));  // as in latch()
+    nlab = (tissue && reached) ? (lab | kLatch) : lab;
+  } else {
+    om = damage_add<kDamage == kDamageSelectApart>(om, damage_increment(hi, K),
+                                                   (lab & kTissue) != 0u, K);
+    nlab = latch(lab, nh, nl, K);
+  }
 }
 
 // Wave sums through DPP lane moves instead of LDS permutes: lanes ^ 1 and
