@@ -490,7 +490,7 @@ rfa_status rasterise(rfa_grid g) {
     scale[t] = g->power[t] / sums[t];
   }
   if (keep) {
-    e = launch_source_combine(g->g, g->lab, g->fields, nt, d_weight, g->q64, g->st);
+    e = launch_source_combine(g->g, g->fields, nt, d_weight, g->q64, g->st);
   } else {
     e = hipMemcpyAsync(d_weight, scale.data(), nt * sizeof(double), hipMemcpyHostToDevice,
                        g->st);
@@ -1702,7 +1702,7 @@ rfa_status rfa_set_tine_powers(rfa_grid g, const double* power) {
     double* d_weight = g->weight_dev;
     HIP_TRY(hipMemcpyAsync(d_weight, scale.data(), nt * sizeof(double), hipMemcpyHostToDevice,
                            g->st));
-    HIP_TRY(launch_source_combine(g->g, g->lab, g->fields, (int)nt, d_weight, g->q64, g->st));
+    HIP_TRY(launch_source_combine(g->g, g->fields, (int)nt, d_weight, g->q64, g->st));
     HIP_TRY(hipStreamSynchronize(g->st));
     g->power.assign(power, power + nt);
     g->src_dt = -1.0;

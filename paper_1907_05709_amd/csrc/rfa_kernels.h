@@ -128,8 +128,8 @@ hipError_t launch_source_fields(Grid3 g, double dx, double dy, double dz, const 
                                 double sigma, const double* power, const SourceFields& f,
                                 double* sums, double* weight, hipStream_t st);
 // q = sum_t scale[t] u_t.
-hipError_t launch_source_combine(Grid3 g, const uint8_t* lab, const SourceFields& f, int n_tines,
-                                 const double* scale, double* q, hipStream_t st);
+hipError_t launch_source_combine(Grid3 g, const SourceFields& f, int n_tines, const double* scale,
+                                 double* q, hipStream_t st);
 // partial[t * nblk + b]: per-block sums of u_t(p) sacc_p dt / (rho c)_p.
 hipError_t launch_source_dot_fields(Grid3 g, const uint8_t* lab, const SourceFields& f,
                                     int n_tines, const float* sacc, const ClassParams* cp_dev,

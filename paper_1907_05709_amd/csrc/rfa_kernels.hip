@@ -634,26 +634,41 @@ __global__ __launch_bounds__(1024) void k_tine_sums(const double* partial, int n
   }
 }
 
-// q[p] = sum_t scale[t] u_t(p) on free voxels, in the order of
-// k_source_write; one work-group per tile, inactive pairs not read.  A wave
-// fetches the flags of 64 tines at once: one after another, each load waited
-// for the branch on the one before (9 tines, 192^3 51 -> 26 us, bound by the
-// 57 MB written).
-__global__ __launch_bounds__(256) void k_source_combine(const uint8_t* lab, const double* u,
-                                                        const uint8_t* active, int n_tiles,
-                                                        int n_tines, const double* scale,
-                                                        double* q, int nx, int ny, int nz) {
+// q[p] = sum_t scale[t] u_t(p), in the order of k_source_write; inactive pairs
+// are not read (u is zero on held voxels of active tiles: no class bytes
+// either).  A wave fetches the flags of 64 tines at once, and a work-group
+// those of four tiles before it uses any: one after another, each load waited
+// for the branch on the one before.  New powers of one tine at 192^3 take
+// 33.5 us a call (40.6 with one tile a work-group and class bytes, 35.3 with
+// the densities of every voxel kept), bound by the 57 MB written.  Grids of fewer
+// tiles than fill the chip that way keep one tile a work-group (kTiles 1).
+template <int kTiles>
+__global__ __launch_bounds__(256) void k_source_combine(const double* u, const uint8_t* active,
+                                                        int n_tiles, int n_tines,
+                                                        const double* scale, double* q, int nx,
+                                                        int ny, int nz) {
   const size_t n = (size_t)nx * ny * nz;
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    int i, j, k;
-    size_t p;
-    const bool inside = tile_voxel(source_tile(tile, ny, nz), nx, ny, nz, i, j, k, p);
-    const bool free = !(lab[inside ? p : 0] & kHeld);
-    double v = 0.0;
-    for (int t0 = 0; t0 < n_tines; t0 += 64) {
-      const int t = t0 + (int)(threadIdx.x & 63);
-      unsigned long long on =
-          __ballot(t < n_tines && active[(size_t)(t < n_tines ? t : t0) * n_tiles + tile] != 0);
+  const int tile0 = blockIdx.x * kTiles;
+  bool inside[kTiles];
+  size_t p[kTiles];
+  double v[kTiles];
+#pragma unroll
+  for (int j = 0; j < kTiles; ++j) {
+    int x, y, z;
+    inside[j] = tile_voxel(source_tile(min(tile0 + j, n_tiles - 1), ny, nz), nx, ny, nz, x, y, z,
+                           p[j]) &&
+                tile0 + j < n_tiles;
+    v[j] = 0.0;
+  }
+  for (int t0 = 0; t0 < n_tines; t0 += 64) {
+    const int t = t0 + (int)(threadIdx.x & 63);
+    const uint8_t* flags = active + (size_t)(t < n_tines ? t : t0) * n_tiles;
+    unsigned f[kTiles];
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j) f[j] = flags[min(tile0 + j, n_tiles - 1)];
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j) {
+      unsigned long long on = __ballot(t < n_tines && f[j] != 0u);
       // eight tines' reads in flight, added in their order (a call with new
       // powers of 200 tines, 64^3 82 -> 51 us, 24^3 82 -> 45)
       while (on != 0ull) {
@@ -667,18 +682,18 @@ __global__ __launch_bounds__(256) void k_source_combine(const uint8_t* lab, cons
             const int tine = t0 + __builtin_ctzll(on);
             on &= on - 1ull;
             s[k] = scale[tine];
-            if (inside && free) w[k] = u[(size_t)tine * n + p];
+            if (inside[j]) w[k] = u[(size_t)tine * n + p[j]];
           }
         }
-        if (inside && free) {
 #pragma unroll
-          for (int k = 0; k < kU; ++k)
-            if (k < m) v += s[k] * w[k];
-        }
+        for (int k = 0; k < kU; ++k)
+          if (k < m) v[j] += s[k] * w[k];
       }
     }
-    if (inside) q[p] = v;
   }
+#pragma unroll
+  for (int j = 0; j < kTiles; ++j)
+    if (inside[j]) q[p[j]] = v[j];
 }
 
 hipError_t launch_source_fields(Grid3 g, double dx, double dy, double dz, const uint8_t* lab,
@@ -698,10 +713,13 @@ hipError_t launch_source_fields(Grid3 g, double dx, double dy, double dz, const 
   return hipGetLastError();
 }
 
-hipError_t launch_source_combine(Grid3 g, const uint8_t* lab, const SourceFields& f, int n_tines,
-                                 const double* scale, double* q, hipStream_t st) {
+hipError_t launch_source_combine(Grid3 g, const SourceFields& f, int n_tines, const double* scale,
+                                 double* q, hipStream_t st) {
   const int tiles = source_tiles(g);
-  hipLaunchKernelGGL(k_source_combine, dim3(std::min(tiles, 16384)), dim3(256), 0, st, lab, f.u,
+  constexpr int kTiles = 4;
+  const bool wide = tiles >= kTiles * 1024;
+  hipLaunchKernelGGL(wide ? k_source_combine<kTiles> : k_source_combine<1>,
+                     dim3(wide ? (tiles + kTiles - 1) / kTiles : tiles), dim3(256), 0, st, f.u,
                      f.active, tiles, n_tines, scale, q, g.nx, g.ny, g.nz);
   return hipGetLastError();
 }

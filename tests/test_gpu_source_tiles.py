@@ -59,6 +59,29 @@ def test_source_matches_oracle(shape, spacing, n_tines, n_points):
     g.close()
 
 
+@pytest.mark.parametrize("shape", [(68, 66, 225), (100, 103, 101), (64, 64, 256)])
+def test_tiles_by_fours(shape):
+    """New powers on grids of 4096 source tiles and more, whose work-groups take
+    four tiles each: a last group of three, two and four tiles."""
+    case = _case(shape, (1e-3, 1e-3, 1e-3), 2, 3, 91)
+    g = rfa.Grid(case.shape, case.spacing)
+    g.load_case(case)
+    powers = case.needle.power[::-1].copy()
+    g.set_tine_powers(powers)
+    g.step(1, case.dt)
+    got = g.temperature() - 37.0
+    ref = O.source(dataclasses.replace(
+        case, needle=dataclasses.replace(case.needle, power=powers))) * case.dt
+    ref /= W.RHO_LIVER * W.C_LIVER
+    free = np.zeros(shape, bool)
+    free[1:-1, 1:-1, 1:-1] = True
+    # the bounds of the small grids: one float32 rounding, exact zeros where held
+    tol = 2.0 ** -23 * np.abs(ref) + 1e-12 * ref.max() + 1e-14
+    assert np.all(np.abs(got - ref)[free] <= tol[free])
+    assert np.all(got[~free] == 0.0)
+    g.close()
+
+
 def test_one_needle_after_another():
     """Needles that grow, shrink and fail on one grid: source and gradients as
     on a grid of their own."""
