@@ -2104,8 +2104,13 @@ struct rfa_batch_s {
   // the one-step kernel is asked for.
   bool want_pair = true;
   int pwaves = 0, pv = 0;           // work-group kind (0: one step per launch)
-  std::vector<PairInstance> pinst;  // host copy of the pair kernel's descriptor table
-  std::vector<int> pfirst;          // pair item range of each instance
+  // The two-step tables in one block, with a host copy up to the codes:
+  // instances, jobs that make their wave codes, items, item range of each
+  // instance, wave codes
+  std::vector<char> pair_host;
+  char* pair_dev = nullptr;
+  size_t pair_jobs = 0;             // offset of the jobs
+  PairInstance* pinst = nullptr;    // in pair_host
   std::vector<int> tissue_version;  // of the grids when the codes were made
   // what the items were laid out for, besides shapes that do not change: whether
   // each grid has a perfusion field and whether its perfusion is coupled
@@ -2113,7 +2118,6 @@ struct rfa_batch_s {
   PairInstance* pinst_dev = nullptr;
   PairItem* pitems_dev = nullptr;
   int* pfirst_dev = nullptr;
-  uint8_t* codes = nullptr;         // wave codes of all instances
   int n_pitems = 0;
   std::vector<Group> groups;
   bool built = false;               // the tables below are those of inst (a build may fail half way)
@@ -2135,12 +2139,12 @@ namespace {
 
 // The two-step part of the tables.
 void batch_free_pair(rfa_batch b) {
-  for (void* p : {(void*)b->pinst_dev, (void*)b->pitems_dev, (void*)b->pfirst_dev, (void*)b->codes})
-    if (p) (void)hipFree(p);
+  if (b->pair_dev) (void)hipFree(b->pair_dev);
+  b->pair_dev = nullptr;
+  b->pinst = nullptr;
   b->pinst_dev = nullptr;
   b->pitems_dev = nullptr;
   b->pfirst_dev = nullptr;
-  b->codes = nullptr;
   b->pwaves = b->pv = 0;
   b->n_pitems = 0;
 }
@@ -2202,19 +2206,28 @@ rfa_status batch_build_pair(rfa_batch b) {
     return Chunks{len, (nx + len - 1) / len};
   };
   constexpr int kLongest = 64;
-  std::vector<Chunks> chunks((size_t)n * kLongest);  // [grid][xc - 1]
+  // grids of one length count as one with their segments in all
+  std::vector<int> lengths, length_of(n);
+  for (int i = 0; i < n; ++i) lengths.push_back(b->grids[i]->g.nx);
+  std::sort(lengths.begin(), lengths.end());
+  lengths.erase(std::unique(lengths.begin(), lengths.end()), lengths.end());
+  const int nl = (int)lengths.size();
   for (int i = 0; i < n; ++i)
-    for (int xc = 1; xc <= kLongest; ++xc)
-      chunks[(size_t)i * kLongest + xc - 1] = chunks_of(b->grids[i]->g.nx, xc);
-  std::vector<int> segs(n);  // of the kind under consideration
+    length_of[i] = (int)(std::lower_bound(lengths.begin(), lengths.end(), b->grids[i]->g.nx) -
+                         lengths.begin());
+  std::vector<Chunks> chunks((size_t)nl * kLongest);  // [xc - 1][length]
+  for (int xc = 1; xc <= kLongest; ++xc)
+    for (int l = 0; l < nl; ++l) chunks[(size_t)(xc - 1) * nl + l] = chunks_of(lengths[l], xc);
+  std::vector<long long> segs(nl);  // of a group in the kind under consideration
   // estimated time of a group's launch
-  auto time_of = [&](const rfa_batch_s::Group& G, int w, int v, int xc) {
+  auto time_of = [&](int w, int v, int xc) {
     long long items = 0, planes = 0;  // planes marched, two more per item
     int longest = 0;
-    for (int i = G.inst0; i < G.inst1; ++i) {
-      const Chunks c = chunks[(size_t)i * kLongest + xc - 1];
-      items += (long long)segs[i] * c.n;
-      planes += (long long)segs[i] * (b->grids[i]->g.nx + 2 * c.n);
+    for (int l = 0; l < nl; ++l) {
+      if (segs[l] == 0) continue;
+      const Chunks c = chunks[(size_t)(xc - 1) * nl + l];
+      items += segs[l] * c.n;
+      planes += segs[l] * (lengths[l] + 2 * c.n);
       longest = std::max(longest, c.xc + 2);
     }
     return items > (1 << 22) ? 1e300 : pair_estimate_uneven(w, v, (int)items, planes, longest);
@@ -2224,14 +2237,16 @@ rfa_status batch_build_pair(rfa_batch b) {
   int w, v;
   for (int kind = 0; pair_kind(kind, &w, &v); ++kind) {
     if (!batch_pair_fits(b, kind)) continue;
-    for (int i = 0; i < n; ++i) segs[i] = pair_shape(b->grids[i]->g, w, v, 1).segs;
     double total = 0.0;
     std::vector<int> xcs;
     for (const auto& G : b->groups) {
+      std::fill(segs.begin(), segs.end(), 0);
+      for (int i = G.inst0; i < G.inst1; ++i)
+        segs[length_of[i]] += pair_shape(b->grids[i]->g, w, v, 1).segs;
       double least = 1e300;
       int at = 1;
       for (int xc = 1; xc <= kLongest; ++xc) {
-        const double us = time_of(G, w, v, xc);
+        const double us = time_of(w, v, xc);
         if (us < least) {
           least = us;
           at = xc;
@@ -2250,10 +2265,9 @@ rfa_status batch_build_pair(rfa_batch b) {
   if (!b->pwaves) return RFA_OK;
   w = b->pwaves;
   v = b->pv;
-  b->pinst.assign(n, PairInstance{});
   std::vector<PairItem> items;
   std::vector<PairShape> shapes(n);
-  b->pfirst.assign(2 * (size_t)n, 0);
+  std::vector<int> pfirst(2 * (size_t)n, 0);
   b->tissue_version.assign(n, 0);
   size_t code_bytes = 0;
   for (size_t gi = 0; gi < b->groups.size(); ++gi) {
@@ -2265,23 +2279,33 @@ rfa_status batch_build_pair(rfa_batch b) {
         if ((b->field[i] != 0) != (pass == 1)) continue;
         shapes[i] = pair_shape(g->g, w, v, chunks_of(g->g.nx, best_xc[gi]).xc);
         code_bytes += pair_code_bytes(g->g, shapes[i]);
-        b->pfirst[2 * i] = (int)items.size();
+        pfirst[2 * i] = (int)items.size();
         for (int c = 0; c < shapes[i].chunks; ++c)
           for (int sg = 0; sg < shapes[i].segs; ++sg) items.push_back(PairItem{i, sg, c, 0});
-        b->pfirst[2 * i + 1] = (int)items.size();
+        pfirst[2 * i + 1] = (int)items.size();
       }
       (pass == 0 ? G.pplain1 : G.pperf1) = (int)items.size();
     }
   }
   b->n_pitems = (int)items.size();
-  rfa_status s;
-  if ((s = dmalloc(&b->codes, code_bytes + 4)) || (s = dmalloc(&b->pinst_dev, n)) ||
-      (s = dmalloc(&b->pitems_dev, items.size())) || (s = dmalloc(&b->pfirst_dev, 2 * (size_t)n)))
-    return s;
+  b->pair_jobs = n * sizeof(PairInstance);
+  const size_t at_items = b->pair_jobs + n * sizeof(PairCodeJob);
+  const size_t at_first = at_items + items.size() * sizeof(PairItem);
+  const size_t at_codes = at_first + pfirst.size() * sizeof(int);
+  // the codes are read as dwords
+  if (const rfa_status s = dmalloc(&b->pair_dev, at_codes + code_bytes + 4); s != RFA_OK) return s;
+  b->pair_host.assign(at_codes, 0);
+  std::memcpy(b->pair_host.data() + at_items, items.data(), items.size() * sizeof(PairItem));
+  std::memcpy(b->pair_host.data() + at_first, pfirst.data(), pfirst.size() * sizeof(int));
+  b->pinst = (PairInstance*)b->pair_host.data();
+  b->pinst_dev = (PairInstance*)b->pair_dev;
+  b->pitems_dev = (PairItem*)(b->pair_dev + at_items);
+  b->pfirst_dev = (int*)(b->pair_dev + at_first);
+  const uint8_t* codes = (const uint8_t*)b->pair_dev + at_codes;
   size_t at = 0;
   for (int i = 0; i < n; ++i) {
     PairInstance& P = b->pinst[i];
-    P.codes = b->codes + at;
+    P.codes = codes + at;
     P.nx = b->inst[i].nx;
     P.ny = b->inst[i].ny;
     P.nz = b->inst[i].nz;
@@ -2291,20 +2315,18 @@ rfa_status batch_build_pair(rfa_batch b) {
     at += pair_code_bytes(b->grids[i]->g, shapes[i]);
     b->tissue_version[i] = b->grids[i]->tissue_version - 1;  // no codes yet
   }
-  HIP_TRY(hipMemcpyAsync(b->pitems_dev, items.data(), items.size() * sizeof(PairItem),
-                         hipMemcpyHostToDevice, b->st));
-  HIP_TRY(hipMemcpyAsync(b->pfirst_dev, b->pfirst.data(), 2 * (size_t)n * sizeof(int),
-                         hipMemcpyHostToDevice, b->st));
-  HIP_TRY(hipStreamSynchronize(b->st));
   return RFA_OK;
 }
 
 // Descriptors of the grids' current state, on host and device (and the wave
 // codes of grids with a new tissue): what a batch that is laid out needs after
 // a grid was stepped, re-tissued or given another source.  Image 0 is then the
-// current one.
-rfa_status batch_describe(rfa_batch b) {
+// current one.  laid_out: the two-step items go to the device as well.
+rfa_status batch_describe(rfa_batch b, bool laid_out) {
   const int n = (int)b->grids.size();
+  auto* jobs = (PairCodeJob*)(b->pair_host.data() + b->pair_jobs);
+  int n_jobs = 0;
+  unsigned job_wg = 0;
   for (int i = 0; i < n; ++i) {
     rfa_grid g = b->grids[i];
     rfa_status s = prepare_dt(g, b->dt[i]);
@@ -2336,15 +2358,24 @@ rfa_status batch_describe(rfa_batch b) {
     P.n_classes = I.n_classes;
     if (b->tissue_version[i] != g->tissue_version) {
       const PairShape sh = pair_shape(g->g, b->pwaves, b->pv, P.xc);
-      HIP_TRY(launch_pair_codes(g->g, sh, g->lab, g->cp, const_cast<uint8_t*>(P.codes), b->st));
+      PairCodeJob& job = jobs[n_jobs++];
+      job = pair_code_job(g->g, sh, g->lab, g->cp, const_cast<uint8_t*>(P.codes));
+      job.first = job_wg;
+      job_wg += pair_code_wg(job);
       b->tissue_version[i] = g->tissue_version;
     }
   }
   HIP_TRY(hipMemcpyAsync(b->inst_dev, b->inst.data(), n * sizeof(BatchInstance),
                          hipMemcpyHostToDevice, b->st));
-  if (b->pwaves)
-    HIP_TRY(hipMemcpyAsync(b->pinst_dev, b->pinst.data(), n * sizeof(PairInstance),
-                           hipMemcpyHostToDevice, b->st));
+  if (b->pwaves) {
+    const size_t described = b->pair_jobs + n_jobs * sizeof(PairCodeJob);
+    HIP_TRY(hipMemcpyAsync(b->pair_dev, b->pair_host.data(),
+                           laid_out ? b->pair_host.size() : described, hipMemcpyHostToDevice,
+                           b->st));
+    if (n_jobs)
+      HIP_TRY(launch_pair_code_jobs(b->pwaves, b->pv, (PairCodeJob*)(b->pair_dev + b->pair_jobs),
+                                    n_jobs, job_wg, b->st));
+  }
   HIP_TRY(hipStreamSynchronize(b->st));
   b->parity = 0;
   return RFA_OK;
@@ -2429,7 +2460,7 @@ rfa_status batch_build(rfa_batch b) {
                          hipMemcpyHostToDevice, b->st));
   HIP_TRY(hipMemcpyAsync(b->first_dev, b->first.data(), 2 * (size_t)n * sizeof(int),
                          hipMemcpyHostToDevice, b->st));
-  if ((s = batch_describe(b)) != RFA_OK) return s;  // waits for the copies
+  if ((s = batch_describe(b, true)) != RFA_OK) return s;  // waits for the copies
   // persistent work-groups if requested, else one work-group per work item
   b->n_wg = b->req_wg > 0 ? std::min(b->req_wg, b->n_items) : 0;
   b->built = true;
@@ -2458,7 +2489,7 @@ rfa_status batch_sync(rfa_batch b) {
   if (!laid_out) return batch_build(b);
   if (same) return RFA_OK;
   b->built = false;  // half described if the call fails
-  const rfa_status s = batch_describe(b);
+  const rfa_status s = batch_describe(b, false);
   b->built = s == RFA_OK;
   return s;
 }

@@ -55,6 +55,25 @@ PairShape pair_shape(Grid3 g, int waves, int v, int xc);
 size_t pair_code_bytes(Grid3 g, const PairShape& s);
 hipError_t launch_pair_codes(Grid3 g, const PairShape& s, const uint8_t* lab,
                              const ClassParams& cp, uint8_t* codes, hipStream_t st);
+// The same for many grids of one kind of work-group in one launch: a table of
+// jobs on the device (first: the work-groups of the jobs before it), n_wg
+// work-groups in all.
+struct AlikeClasses {
+  unsigned short held[kMaxClasses];  // of each class: those of the same conductivity
+  unsigned short open[kMaxClasses];  // and of the same heat capacity
+};
+struct PairCodeJob {
+  const uint8_t* lab;
+  uint8_t* codes;
+  int ny, nz, seg, segs;
+  unsigned n_codes, first;
+  AlikeClasses alike;
+};
+PairCodeJob pair_code_job(Grid3 g, const PairShape& s, const uint8_t* lab, const ClassParams& cp,
+                          uint8_t* codes);
+unsigned pair_code_wg(const PairCodeJob& job);
+hipError_t launch_pair_code_jobs(int waves, int v, const PairCodeJob* jobs, int n_jobs,
+                                 unsigned n_wg, hipStream_t st);
 // Two steps, with the step constants of b.tab.  b.codes: the shape's wave codes; hi_mid: the image between the
 // steps (kPairKeep, kPairTemp).
 hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,

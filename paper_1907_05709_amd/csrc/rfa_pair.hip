@@ -14,24 +14,19 @@ namespace rfa {
 // classes, so that a voxel's test is a bit of a mask rather than 12 reads of
 // their values, and a voxel's six neighbours are read at once (128^3 31.2 ->
 // 12.7 us; bound by the latency of two rounds of byte reads).
-struct AlikeClasses {
-  unsigned short held[kMaxClasses];  // of each class: those of the same conductivity
-  unsigned short open[kMaxClasses];  // and of the same heat capacity
-};
-
-__global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, AlikeClasses alike,
-                                                    int ny, int nz, int nt, int v, int seg,
-                                                    int segs, unsigned n_codes, uint8_t* codes) {
+__device__ __forceinline__ void pair_codes(const PairCodeJob& job, unsigned wg, int nt, int v) {
   __shared__ unsigned held_like[kMaxClasses], open_like[kMaxClasses];
   if (threadIdx.x < kMaxClasses) {
-    held_like[threadIdx.x] = alike.held[threadIdx.x];
-    open_like[threadIdx.x] = alike.open[threadIdx.x];
+    held_like[threadIdx.x] = job.alike.held[threadIdx.x];
+    open_like[threadIdx.x] = job.alike.open[threadIdx.x];
   }
   __syncthreads();
+  const uint8_t* lab = job.lab;
+  const int nz = job.nz, seg = job.seg, segs = job.segs;
   const int lane = threadIdx.x & 63;
-  const int nw = nt / 64, np = ny * nz;
-  const unsigned id = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (id >= n_codes) return;
+  const int nw = nt / 64, np = job.ny * nz;
+  const unsigned id = wg * 4 + (threadIdx.x >> 6);
+  if (id >= job.n_codes) return;
   const unsigned line = id / nw;
   const int wave = (int)(id % nw);
   const int sg = (int)(line % segs);
@@ -70,7 +65,26 @@ __global__ __launch_bounds__(256) void k_pair_codes(const uint8_t* lab, AlikeCla
   }
   regular = regular && (none || only_free || all);
   code |= none ? 0u : (only_free ? kPairTissueFree : kPairTissueAll);
-  if (lane == 0) codes[id] = (uint8_t)(regular ? code : kPairIrregular);
+  if (lane == 0) job.codes[id] = (uint8_t)(regular ? code : kPairIrregular);
+}
+
+__global__ __launch_bounds__(256) void k_pair_codes(PairCodeJob job, int nt, int v) {
+  pair_codes(job, blockIdx.x, nt, v);
+}
+
+// One launch for the grids of a batch (64 of 24^3 to 30^3: one kernel of 14 us
+// in place of 64 of 2.7, one after another).
+__global__ __launch_bounds__(256) void k_pair_code_jobs(const PairCodeJob* jobs, int n_jobs,
+                                                        int nt, int v) {
+  int j = 0;  // the last job that starts at or before this work-group
+  for (int above = n_jobs; above - j > 1;) {
+    const int mid = (j + above) / 2;
+    if (jobs[mid].first <= blockIdx.x)
+      j = mid;
+    else
+      above = mid;
+  }
+  pair_codes(jobs[j], blockIdx.x - jobs[j].first, nt, v);
 }
 
 namespace {
@@ -156,18 +170,31 @@ size_t pair_code_bytes(Grid3 g, const PairShape& s) {
   return (size_t)g.nx * s.segs * s.waves;
 }
 
+PairCodeJob pair_code_job(Grid3 g, const PairShape& s, const uint8_t* lab, const ClassParams& cp,
+                          uint8_t* codes) {
+  PairCodeJob job{lab, codes, g.ny, g.nz, s.seg, s.segs, (unsigned)pair_code_bytes(g, s), 0, {}};
+  for (int a = 0; a < cp.n; ++a)
+    for (int b = 0; b < cp.n; ++b) {
+      if (cp.k[a] != cp.k[b]) continue;
+      job.alike.held[a] |= 1u << b;
+      if (cp.rc[a] == cp.rc[b]) job.alike.open[a] |= 1u << b;
+    }
+  return job;
+}
+
+unsigned pair_code_wg(const PairCodeJob& job) { return (job.n_codes + 3) / 4; }
+
 hipError_t launch_pair_codes(Grid3 g, const PairShape& s, const uint8_t* lab,
                              const ClassParams& cp, uint8_t* codes, hipStream_t st) {
-  const size_t n = pair_code_bytes(g, s);
-  AlikeClasses alike{};
-  for (int a = 0; a < kMaxClasses; ++a)
-    for (int b = 0; b < kMaxClasses; ++b) {
-      if (cp.k[a] != cp.k[b]) continue;
-      alike.held[a] |= 1u << b;
-      if (cp.rc[a] == cp.rc[b]) alike.open[a] |= 1u << b;
-    }
-  hipLaunchKernelGGL(k_pair_codes, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, lab, alike,
-                     g.ny, g.nz, 64 * s.waves, s.v, s.seg, s.segs, (unsigned)n, codes);
+  const PairCodeJob job = pair_code_job(g, s, lab, cp, codes);
+  hipLaunchKernelGGL(k_pair_codes, dim3(pair_code_wg(job)), dim3(256), 0, st, job, 64 * s.waves,
+                     s.v);
+  return hipGetLastError();
+}
+
+hipError_t launch_pair_code_jobs(int waves, int v, const PairCodeJob* jobs, int n_jobs,
+                                 unsigned n_wg, hipStream_t st) {
+  hipLaunchKernelGGL(k_pair_code_jobs, dim3(n_wg), dim3(256), 0, st, jobs, n_jobs, 64 * waves, v);
   return hipGetLastError();
 }
 
