@@ -204,7 +204,7 @@ __global__ __launch_bounds__(NT, 4) void k_adjoint_pair(AdjointBuffers a, int nx
     uintptr_t tab = (uintptr_t)a.tab;
     asm volatile("" : "+s"(tab));  // constants are read here, not kept in registers
     ConstF* q = (ConstF*)tab + offsetof(Tables, K) / 4;
-    StepConst K;
+    PairConst K;
     K.dtka = q[0];
     K.c2 = q[1];
     K.tak = q[2];

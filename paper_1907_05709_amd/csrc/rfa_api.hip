@@ -303,6 +303,7 @@ void split(double v, float& hi, float& lo) {
 }
 
 StepConst step_const(rfa_grid g, double dt);
+float cold_bound(rfa_grid g);
 
 // Per-dt coefficient tables (FP64 -> float-float) and step constants.
 void build_tables(rfa_grid g, double dt) {
@@ -333,6 +334,7 @@ void build_tables(rfa_grid g, double dt) {
     T.adj[a] = make_float4(own(0), own(1), own(2), T.cls[a].x + T.cls[a].y);
   }
   T.K = step_const(g, dt);
+  T.cold = cold_bound(g);
 }
 
 StepConst step_const(rfa_grid g, double dt) {
@@ -345,12 +347,15 @@ StepConst step_const(rfa_grid g, double dt) {
   K.cap = (float)g->opt.omega_cap;
   K.thr = (float)(g->opt.t_death - 37.0);
   K.decay2 = g->perf_decay ? (float)M_LOG2E : 0.0f;
-  // |exponent| = c2 |theta| / (T_aK + theta) below 2^-29, where 2^x rounds
-  // to 1 whatever its sign, and |theta| below half an ulp of T_aK (1.5e-5), so
-  // that T_aK + theta rounds to T_aK
-  const double c2 = c * M_LOG2E;
-  K.cold = (float)(c2 > 0.0 ? std::min(1e-5, std::ldexp(0.5 * kTBodyK / c2, -29)) : 1e-5);
   return K;
+}
+
+// Bound of PairConst: |exponent| = c2 |theta| / (T_aK + theta) below 2^-29,
+// where 2^x rounds to 1 whatever its sign, and |theta| below half an ulp of
+// T_aK (1.5e-5), so that T_aK + theta rounds to T_aK.
+float cold_bound(rfa_grid g) {
+  const double c2 = g->opt.Ea / (g->opt.R * kTBodyK) * M_LOG2E;
+  return (float)(c2 > 0.0 ? std::min(1e-5, std::ldexp(0.5 * kTBodyK / c2, -29)) : 1e-5);
 }
 
 // A perfusion field of ones (allocated if missing), for damage-coupled

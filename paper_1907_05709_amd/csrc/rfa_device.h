@@ -52,6 +52,11 @@ struct StepConst {
   float cap;     // Omega cap
   float thr;     // t_death - 37
   float decay2;  // log2(e) with damage-coupled perfusion, else 0
+};
+// Those of the two-step kernels (an eighth constant in StepConst changes how
+// the compiler schedules the one-step kernels: with a perfusion field they
+// then took 5 to 6 % longer, 60x70x299 11.1 -> 11.8 us a step).
+struct PairConst : StepConst {
   float cold;    // |theta| below which 2^x of the damage exponent x and T_aK + theta
                  // round to 1 and T_aK
 };
@@ -64,6 +69,7 @@ struct Tables {
   // constants, and per class the adjoint's coefficients {C(a,a) along x, y, z,
   // B}, each float-float value rounded to float
   StepConst K;
+  float cold;  // of PairConst, after K
   float4 adj[kMaxClasses];
 };
 

@@ -104,11 +104,11 @@ __device__ __forceinline__ ClassCoef class_coef(const Tables* tab, unsigned c) {
 
 // The step constants, read where they are used: as kernel arguments they
 // would occupy eight scalar registers through the plane loop, which spills.
-__device__ __forceinline__ StepConst step_constants(const Tables* tab) {
+__device__ __forceinline__ PairConst step_constants(const Tables* tab) {
   uintptr_t p = (uintptr_t)tab;
   asm volatile("" : "+s"(p));  // keeps the loads here
   ConstF* q = (ConstF*)p + offsetof(Tables, K) / 4;
-  StepConst K;
+  PairConst K;
   K.dtka = q[0];
   K.c2 = q[1];
   K.tak = q[2];
@@ -298,7 +298,7 @@ __device__ __forceinline__ void pair_march(PairSmem<NT, V, MAXNZ>& sm, const Ste
                   PairPlane<V>& q, const float (&dn)[V], const float (&dp)[V],
                   const unsigned (&bn)[V], const unsigned long long (&heldm)[V],
                   unsigned long long own) {
-    const StepConst K = step_constants(b.tab);
+    const PairConst K = step_constants(b.tab);
     auto cntm = [&](int v) { return ownm[v] & ~heldm[v]; };
     float f[V];
 #pragma unroll

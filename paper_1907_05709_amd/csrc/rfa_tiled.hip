@@ -320,10 +320,19 @@ __device__ __forceinline__ void march(float2* ts, uint8_t* bs, int cells, float*
 
 }  // namespace
 
-template <int TY, bool PERF, int AUX>
-__global__ __launch_bounds__(64 * TY) void k_step_tiled(StepBuffers b, StepConst K, int nx,
-                                                        int ny, int nz, int xc, int tiles_z,
-                                                        int tiles_y, int nwg) {
+// With a perfusion field the compiler's choice is 108 registers, four waves a
+// SIMD, on which kFourWaves of them are resident.  A launch of more would run
+// a second round for the rest: it takes the six waves of 78 registers (us a
+// step: 129x150x141, 1026 work-groups of four waves, 26.0 -> 23.4,
+// 100x100x321, 1050, 28.5 -> 26.6), a smaller one not (60x70x299, 720, 11.1
+// against 11.4; 100x90x75, 598, 10.7 against 11.1).
+constexpr int kFourWaves = 256 * 4 * 4;
+
+template <int TY, bool PERF, int AUX, bool MANY>
+__global__ __launch_bounds__(64 * TY) __attribute__((
+    amdgpu_waves_per_eu(MANY ? 6 : 1, MANY ? 6 : 8))) void
+k_step_tiled(StepBuffers b, StepConst K, int nx, int ny, int nz, int xc, int tiles_z, int tiles_y,
+             int nwg) {
   __shared__ TileSmem<TY> sm;
   stage_tables(sm.cf, sm.cls, b.tab, b.n_classes, 64 * TY);
   const int wg = remap_xcd(blockIdx.x, nwg);
@@ -337,16 +346,22 @@ __global__ __launch_bounds__(64 * TY) void k_step_tiled(StepBuffers b, StepConst
 
 // Batched step over the work list of all instances (items grouped by
 // instance).  LOOP: a persistent grid walks the list round-robin; otherwise
-// one work-group per item, in XCD-aware order, at eight waves per SIMD (64
-// registers with a ring two planes deep, no spills).  FLAT: items are flat plane
+// one work-group per item, in XCD-aware order (without a perfusion field eight
+// waves per SIMD: 64 registers with a ring two planes deep, no spills).  FLAT: items are flat plane
 // segments of 64 TY voxels (item tz = segment), else 2.5-D tiles.  Each
 // item stages its instance's tables before its march.  parity selects the
 // ping-pong image.
+// Waves a SIMD: eight without a perfusion field, six on flat segments with
+// one (16 damage-coupled grids of 64^3, 21 steps: 639 us with the compiler's
+// seven, 607 with six, 632 with five), else the compiler's choice.
+constexpr int batch_waves(bool perf, bool loop, bool flat, int any) {
+  return loop ? any : !perf ? 8 : flat ? 6 : any;
+}
 template <int TY, bool PERF, bool LOOP, bool FLAT>
-__global__ __launch_bounds__(64 * TY, PERF || LOOP ? 1 : 8) void k_step_batch(const BatchInstance* inst,
-                                                        const BatchItem* items, int first_item,
-                                                        int n_items, int parity,
-                                                        float* partials) {
+__global__ __launch_bounds__(64 * TY) __attribute__((
+    amdgpu_waves_per_eu(batch_waves(PERF, LOOP, FLAT, 1), batch_waves(PERF, LOOP, FLAT, 8)))) void
+k_step_batch(const BatchInstance* inst, const BatchItem* items, int first_item, int n_items,
+             int parity, float* partials) {
   using Smem = typename std::conditional<FLAT, FlatSmem<TY>, TileSmem<TY>>::type;
   __shared__ Smem sm;
   // Work item and instance fields are the same for the whole work-group;
@@ -463,13 +478,14 @@ template <int TY, int AUX>
 static hipError_t launch_ty(const TiledShape& s, Grid3 g, const StepBuffers& b,
                             const StepConst& K, hipStream_t st) {
   dim3 grid(s.nwg), block(64 * TY);
-  if (b.perf)
-    hipLaunchKernelGGL((k_step_tiled<TY, true, AUX>), grid, block, 0, st, b, K, g.nx, g.ny,
-                       g.nz, s.xc, s.tiles_z, s.tiles_y, s.nwg);
-  else
-    hipLaunchKernelGGL((k_step_tiled<TY, false, AUX>), grid, block, 0, st, b, K, g.nx, g.ny,
-                       g.nz, s.xc, s.tiles_z, s.tiles_y, s.nwg);
-  return hipGetLastError();
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, b, K, g.nx, g.ny, g.nz, s.xc, s.tiles_z,
+                       s.tiles_y, s.nwg);
+    return hipGetLastError();
+  };
+  if (!b.perf) return go(k_step_tiled<TY, false, AUX, false>);
+  return (long long)s.nwg * TY > kFourWaves ? go(k_step_tiled<TY, true, AUX, true>)
+                                            : go(k_step_tiled<TY, true, AUX, false>);
 }
 
 template <int TY>
