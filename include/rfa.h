@@ -368,10 +368,10 @@ rfa_status rfa_set_tine_powers(rfa_grid g, const double* power);
 /* n_steps forward steps (as rfa_step) keeping, for rfa_adjoint, the
  * temperature (hi word) of every step when ckpt_every = 0 (the launches, of
  * two steps by default, write it straight into the kept trajectory;
- * RFA_ERR_OOM if it does not fit: use checkpoints), else the state at steps 0, ckpt_every,
- * 2 ckpt_every, ... plus the hi word of every step of the last segment,
- * written into the adjoint's segment buffer (2 (ckpt_every + 1) images,
- * allocated here), so the first rfa_adjoint after it recomputes every
+ * RFA_ERR_OOM if it does not fit: use checkpoints), else the state at steps
+ * 0, ckpt_every, 2 ckpt_every, ... plus the hi word of every step of the last
+ * segment, written into the adjoint's segment buffer (2 (ckpt_every + 1)
+ * images, allocated here), so the first rfa_adjoint after it recomputes every
  * segment but the last. */
 rfa_status rfa_forward_checkpointed(rfa_grid g, int n_steps, double dt, int ckpt_every);
 

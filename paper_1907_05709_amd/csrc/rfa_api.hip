@@ -2125,7 +2125,7 @@ struct rfa_batch_s {
   int* pfirst_dev = nullptr;
   int n_pitems = 0;
   std::vector<Group> groups;
-  bool built = false;               // the tables below are those of inst (a build may fail half way)
+  bool built = false;               // the tables are those of inst (a build may fail half way)
   int parity = 0;
   long long voxels = 0;
   hipStream_t st = nullptr;
@@ -2510,7 +2510,8 @@ int batch_pairs(rfa_batch b, int n_steps) {
 rfa_status batch_graph(rfa_batch b, int n_steps, bool diag, hipGraphExec_t* out) {
   const int n_pair = batch_pairs(b, n_steps);
   for (auto& c : b->graphs)
-    if (c.n_steps == n_steps && c.n_pair == n_pair && c.parity == b->parity && c.diag == (int)diag) {
+    if (c.n_steps == n_steps && c.n_pair == n_pair && c.parity == b->parity &&
+        c.diag == (int)diag) {
       *out = c.exec;
       return RFA_OK;
     }

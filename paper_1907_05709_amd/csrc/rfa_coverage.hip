@@ -108,7 +108,8 @@ __global__ __launch_bounds__(192) void k_coverage_finish(const double* __restric
   const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double v[kCoverageBlocks / 64];
 #pragma unroll
-  for (int i = 0; i < kCoverageBlocks / 64; ++i) v[i] = partial[k * kCoverageBlocks + 64 * i + lane];
+  for (int i = 0; i < kCoverageBlocks / 64; ++i)
+    v[i] = partial[k * kCoverageBlocks + 64 * i + lane];
   double t = 0.0;
 #pragma unroll
   for (int i = 0; i < kCoverageBlocks / 64; ++i) t += v[i];

@@ -74,8 +74,8 @@ PairCodeJob pair_code_job(Grid3 g, const PairShape& s, const uint8_t* lab, const
 unsigned pair_code_wg(const PairCodeJob& job);
 hipError_t launch_pair_code_jobs(int waves, int v, const PairCodeJob* jobs, int n_jobs,
                                  unsigned n_wg, hipStream_t st);
-// Two steps, with the step constants of b.tab.  b.codes: the shape's wave codes; hi_mid: the image between the
-// steps (kPairKeep, kPairTemp).
+// Two steps, with the step constants of b.tab.  b.codes: the shape's wave
+// codes; hi_mid: the image between the steps (kPairKeep, kPairTemp).
 hipError_t launch_step_pair(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,
                             float* hi_mid, int store, hipStream_t st);
 

@@ -143,7 +143,8 @@ double pair_estimate_uneven(int waves, int v, int nwg, long long planes, int lon
 bool pair_fits(Grid3 g, int waves, int v, int xc) {
   for (const PairKind& k : kPairKinds)
     if (k.waves == waves && k.v == v)
-      return g.nz <= k.max_nz && 2 * g.nz <= 64 * waves && 64 * waves * v - pair_lead(g.nz, v) - g.nz >= 64 &&
+      return g.nz <= k.max_nz && 2 * g.nz <= 64 * waves &&
+             64 * waves * v - pair_lead(g.nz, v) - g.nz >= 64 &&
              (double)(xc + 6) * g.ny * g.nz * 4.0 < 2147483647.0;
   return false;
 }

@@ -33,14 +33,15 @@
 // 4.0 TB/s; vector instructions issue in 0.80 of a busy compute unit's cycles,
 // 224 a wave and plane for two steps of two voxels), on small ones the planes
 // computed twice and the latency of a plane (128^3: 0.71 of the cycles, 2.1
-// waves a SIMD, 44 % of their time spent waiting; 63 MB a launch, 1.19 times).  A vector memory instruction costs as much as 16 arithmetic ones, so
-// a lane's two voxels are consecutive and move as one access (11 a wave and
-// plane; 22 with single ones); uniform branches cost as much as the few
-// instructions they skip, so there are few.  The first step on halo rows and
-// planes is computed twice, so the footprint is trimmed to what the second
-// step reads: held rows at a plane's ends belong to nobody's segment, and
-// halo voxels pass on a temperature but no damage, latch or sum.  Against one
-// step a pass (us a step, with sums): 32^3 6.0 -> 3.3, 48^3 6.4 -> 3.9, 64^3
+// waves a SIMD, 44 % of their time spent waiting; 63 MB a launch, 1.19 times).
+// A vector memory instruction costs as much as 16 arithmetic ones, so a lane's
+// two voxels are consecutive and move as one access (11 a wave and plane; 22
+// with single ones); uniform branches cost as much as the few instructions
+// they skip, so there are few.  The first step on halo rows and planes is
+// computed twice, so the footprint is trimmed to what the second step reads:
+// held rows at a plane's ends belong to nobody's segment, and halo voxels pass
+// on a temperature but no damage, latch or sum.  Against one step a pass (us a
+// step, with sums): 32^3 6.0 -> 3.3, 48^3 6.4 -> 3.9, 64^3
 // 6.4 -> 4.9, 96^3 12.0 -> 7.1, 128^3 13.3 -> 10.8, 161x149x117 without sums
 // 20.6 -> 12.5, 160x152x144 coupled 35.7 -> 16.6, 256x256x234 91 -> 52.4,
 // 256^3 80 -> 57.0.
@@ -69,7 +70,7 @@ struct PairSmem {
   float4 cls[kMaxClasses];
   uint8_t lab[kPairRing][CELLS];
   alignas(16) float2 in[2][CELLS];    // input planes: footprint q at pair_lead + q
-  alignas(16) float2 mid[2][CELLS];   // first-step planes, footprint q at pair_lead + q (halo cells unused)
+  alignas(16) float2 mid[2][CELLS];   // first-step planes, likewise (halo cells unused)
   float red[3 * NT / 64];
 };
 
@@ -628,7 +629,8 @@ hipError_t launch_mode(const PairShape& s, Grid3 g, const StepBuffers& b, PairMo
 }
 
 template <int NT, int V, int MAXNZ, int AUX>
-hipError_t launch_kind(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode, float* hi_mid, hipStream_t st) {
+hipError_t launch_kind(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,
+                       float* hi_mid, hipStream_t st) {
   if (b.perf)
     return b.partials
                ? launch_mode<NT, V, MAXNZ, true, true, AUX>(s, g, b, mode, hi_mid, st)
@@ -638,7 +640,8 @@ hipError_t launch_kind(const PairShape& s, Grid3 g, const StepBuffers& b, PairMo
 }
 
 template <int NT, int V, int MAXNZ>
-hipError_t launch_store(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode, float* hi_mid, int store, hipStream_t st) {
+hipError_t launch_store(const PairShape& s, Grid3 g, const StepBuffers& b, PairMode mode,
+                        float* hi_mid, int store, hipStream_t st) {
   switch (store) {
     case kPolicyThrough:
       return launch_kind<NT, V, MAXNZ, kStoreThrough>(s, g, b, mode, hi_mid, st);

@@ -70,7 +70,8 @@ struct StepState {
   // reads *om and writes *om_alt, then the two are swapped (the caller's state
   // is the image *om ends at)
   float** om_alt = nullptr;
-  bool even = false;  // launches of two steps in even numbers: n steps swap the images n times mod 2
+  // launches of two steps in even numbers: n steps swap the images n times mod 2
+  bool even = false;
 };
 
 // One launch of the plan (plan.depth steps) from b's input to its output image.
@@ -84,8 +85,9 @@ hipError_t launch_plan_temperature(Grid3 g, const StepPlan& plan, const StepBuff
                                    float* hi_mid, const StepConst& K, hipStream_t st);
 
 // Advance n_steps: n_steps / depth launches of the plan (one fewer if s.even
-// asks for it), then the rest with its one-step plan.  partials (nullable) has room for `slots` launches and
-// is folded into dacc[3] every `slots` launches and at the end.  If events
+// asks for it), then the rest with its one-step plan.  partials (nullable) has
+// room for `slots` launches and is folded into dacc[3] every `slots` launches
+// and at the end.  If events
 // is not null, each block of `period` consecutive launches of the plan (the
 // last one may be shorter) is bracketed by the event pair events[2j],
 // events[2j+1] (j = 0, 1, ...; *n_timed receives the number of blocks,
